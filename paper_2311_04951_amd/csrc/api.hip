@@ -586,8 +586,10 @@ static int check_pair(const ss_model *m, const ss_kv_cache *kv, int batch, int M
     return SS_OK;
 }
 
-// all layers over the R = batch*M rows in m->h
-static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream_t st) {
+// All layers over the R = batch*M rows in h.  normed: whether act_a already holds the first layer's normalised rows (the
+// embedding writes them).  final_gain: the norm that follows the last layer when it covers all rows in order (NULL: none, or
+// the head gathers rows).  Returns what the last projection did about that norm (launch_gemm).
+static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const float *final_gain, int batch, int M, hipStream_t st) {
     const ss_model_cfg &c = m->cfg;
     const int R = batch * M, d = c.d_model, W = m->W, F = c.d_ff;
     const size_t pl = (size_t)m->R16;
@@ -608,7 +610,6 @@ static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream
     // anyway (split K, more than 16 rows) writes the normalised planes there (1); the kernels of at most 16 rows write
     // h * gain as planes and per-tile sums of squares, and the GEMM that consumes the planes multiplies its sums by the
     // row scale (2: the norm is deferred; no launch of its own either way).  0: the norm is still to be launched.
-    int normed = 0;
     const int T = d / 16;
     const bool defer_ok = R <= 16 && m->nsq_ws != nullptr;
     auto with_norm = [&](GemmArgs &g, const float *gain) {
@@ -624,7 +625,7 @@ static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream
         char *vc = (char *)kv->v + kv->layer_elems * l * kv->esz;
         if (!normed) {
             ProfScope ps(m, PT_NORM, st);
-            launch_rmsnorm_pack(c.dtype, m->h, L.g1, R, d, c.rms_eps, m->act_a, pl * d, d, st);
+            launch_rmsnorm_pack(c.dtype, h, L.g1, R, d, c.rms_eps, m->act_a, pl * d, d, st);
         }
         GemmArgs g{};
         g.splitk_ws = m->splitk_ws; g.splitk_ws_bytes = m->splitk_ws_bytes;
@@ -656,7 +657,7 @@ static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream
         o.splitk_ws = m->splitk_ws; o.splitk_ws_bytes = m->splitk_ws_bytes;
         o.W = L.wo; o.N = d; o.K = W; o.wscale = c.weight_quant ? L.so : nullptr; o.wbits = wbits;
         o.act = m->act_o; o.act_plane = pl * W; o.ld_act = W; o.R = R;
-        o.out = m->h; o.resid = m->h; o.ldo = d;
+        o.out = h; o.resid = h; o.ldo = d;
         with_norm(o, L.g2);
         {
             ProfScope ps(m, PT_OPROJ, st);
@@ -664,7 +665,7 @@ static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream
         }
         if (!normed) {
             ProfScope ps(m, PT_NORM, st);
-            launch_rmsnorm_pack(c.dtype, m->h, L.g2, R, d, c.rms_eps, m->act_a, pl * d, d, st);
+            launch_rmsnorm_pack(c.dtype, h, L.g2, R, d, c.rms_eps, m->act_a, pl * d, d, st);
         }
         GemmArgs u{};
         u.splitk_ws = m->splitk_ws; u.splitk_ws_bytes = m->splitk_ws_bytes;
@@ -681,22 +682,34 @@ static void run_layers(ss_model *m, ss_kv_cache *kv, int batch, int M, hipStream
         dn.splitk_ws = m->splitk_ws; dn.splitk_ws_bytes = m->splitk_ws_bytes;
         dn.W = L.wd; dn.N = d; dn.K = F; dn.wscale = c.weight_quant ? L.sd : nullptr; dn.wbits = wbits;
         dn.act = m->act_z; dn.act_plane = pl * F; dn.ld_act = F; dn.R = R;
-        dn.out = m->h; dn.resid = m->h; dn.ldo = d;
-        if (l + 1 < c.n_layers) with_norm(dn, m->layers[l + 1].g1); // (the final norm belongs to the head: it may gather rows)
+        dn.out = h; dn.resid = h; dn.ldo = d;
+        const float *next = l + 1 < c.n_layers ? m->layers[l + 1].g1 : final_gain;
+        if (next) with_norm(dn, next);
+        if (l + 1 == c.n_layers) { dn.len_add = kv->len_dev; dn.len_batch = batch; dn.len_delta = M; }
         {
             ProfScope ps(m, PT_DOWN, st);
             normed = launch_gemm(c.dtype, EPI_RESID, dn, st);
         }
     }
-    launch_len_add(kv->len_dev, batch, M, st);
+    if (c.n_layers == 0) launch_len_add(kv->len_dev, batch, M, st);
     for (int b = 0; b < batch; ++b) kv->len_ub[b] += M;
+    return c.n_layers ? normed : 0;
 }
 
-// logits[r][:] = RMSNorm(h[row0 + r*stride], gf) . W_lm^T for r < nrows
-static void run_head(ss_model *m, int nrows, int row0, int stride, float *logits, hipStream_t st) {
+// The embedding of the rows in m->h, with the first layer's norm of them in act_a.  Returns whether the norm was written.
+static int run_embed(ss_model *m, const int32_t *tokens, int R, hipStream_t st) {
+    const ss_model_cfg &c = m->cfg;
+    ProfScope ps(m, PT_NORM, st);
+    launch_embed_norm(c.dtype, m->embed, tokens, R, c.d_model, c.vocab, m->h, m->status, c.n_layers ? m->layers[0].g1 : nullptr, c.rms_eps, m->act_a,
+                      (size_t)m->R16 * c.d_model, c.d_model, st);
+    return c.n_layers ? 1 : 0;
+}
+
+// logits[r][:] = RMSNorm(h[row0 + r*stride], gf) . W_lm^T for r < nrows.  normed: what the last projection did about the norm
+static void run_head(ss_model *m, int normed, int nrows, int row0, int stride, float *logits, hipStream_t st) {
     const ss_model_cfg &c = m->cfg;
     const size_t pl = (size_t)m->R16;
-    {
+    if (!normed) {
         ProfScope ps(m, PT_NORM, st);
         launch_rmsnorm_pack_rows(c.dtype, m->h, m->gf, nrows, row0, stride, c.d_model, c.rms_eps, m->act_a, pl * c.d_model, c.d_model, st);
     }
@@ -705,6 +718,7 @@ static void run_head(ss_model *m, int nrows, int row0, int stride, float *logits
     g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.wscale = m->s_head; g.wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
     g.act = m->act_a; g.act_plane = pl * c.d_model; g.ld_act = c.d_model; g.R = nrows;
     g.out = logits; g.ldo = c.vocab;
+    if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_tiles = g.act_nsq_ld = c.d_model / 16; g.norm_eps = c.rms_eps; }
     launch_gemm(c.dtype, EPI_STORE, g, st);
 }
 
@@ -805,10 +819,7 @@ extern "C" int ss_decoder_layers_forward(ss_model *m, ss_kv_cache *kv, float *h_
         rc = run_persistent(m, kv, nullptr, h_dev, batch, M, nullptr, 0, 0, 1, st);
         return rc ? rc : check_launch();
     }
-    const size_t bytes = sizeof(float) * (size_t)batch * M * m->cfg.d_model;
-    HIP_TRY(hipMemcpyAsync(m->h, h_dev, bytes, hipMemcpyDeviceToDevice, st));
-    run_layers(m, kv, batch, M, st);
-    HIP_TRY(hipMemcpyAsync(h_dev, m->h, bytes, hipMemcpyDeviceToDevice, st));
+    run_layers(m, kv, h_dev, 0, nullptr, batch, M, st); // (in the caller's rows: copies to and from m->h are 3 - 4.5 us each)
     return check_launch();
 }
 
@@ -823,9 +834,9 @@ extern "C" int ss_verify_forward(ss_model *m, ss_kv_cache *kv, const int32_t *to
         rc = run_persistent(m, kv, tokens_dev, m->h, batch, M, logits_dev, batch * M, 0, 1, st);
         return rc ? rc : check_launch();
     }
-    launch_embed(m->cfg.dtype, m->embed, tokens_dev, batch * M, m->cfg.d_model, m->cfg.vocab, m->h, m->status, st);
-    run_layers(m, kv, batch, M, st);
-    if (logits_dev) run_head(m, batch * M, 0, 1, logits_dev, st);
+    int normed = run_embed(m, tokens_dev, batch * M, st);
+    normed = run_layers(m, kv, m->h, normed, logits_dev ? m->gf : nullptr, batch, M, st);
+    if (logits_dev) run_head(m, normed, batch * M, 0, 1, logits_dev, st);
     return check_launch();
 }
 
@@ -899,9 +910,9 @@ extern "C" int ss_draft_step(ss_model *m, ss_kv_cache *kv, const int32_t *tokens
         rc = run_persistent(m, kv, tokens_dev, m->h, batch, mrows, m->logits_ws, batch, mrows - 1, mrows, st);
         if (rc) return rc;
     } else {
-        launch_embed(m->cfg.dtype, m->embed, tokens_dev, batch * mrows, m->cfg.d_model, V, m->h, m->status, st);
-        run_layers(m, kv, batch, mrows, st);
-        run_head(m, batch, mrows - 1, mrows, m->logits_ws, st);
+        int normed = run_embed(m, tokens_dev, batch * mrows, st);
+        normed = run_layers(m, kv, m->h, normed, mrows == 1 ? m->gf : nullptr, batch, mrows, st);
+        run_head(m, normed, batch, mrows - 1, mrows, m->logits_ws, st);
     }
     if (temperature > 0.f) {
         const float inv_t = 1.0f / temperature;

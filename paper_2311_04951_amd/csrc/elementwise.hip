@@ -8,25 +8,6 @@
 
 namespace ss {
 
-// h[r][:] = E[token[r]][:]
-template <typename T>
-__global__ void embed_kernel(const T *embed, const int32_t *tokens, int d, int vocab, float *h, int32_t *status) {
-    const int r = blockIdx.x;
-    int tok = tokens[r];
-    if (tok < 0 || tok >= vocab) {
-        if (threadIdx.x == 0) atomicOr(status, 1);
-        tok = tok < 0 ? 0 : vocab - 1;
-    }
-    const T *src = embed + (size_t)tok * d;
-    for (int e = threadIdx.x; e < d; e += blockDim.x) h[(size_t)r * d + e] = to_f32(src[e]);
-}
-
-void launch_embed(int dtype, const void *embed, const int32_t *tokens, int R, int d, int vocab, float *h,
-                  int32_t *status, hipStream_t st) {
-    if (dtype) hipLaunchKernelGGL((embed_kernel<bf16_t>), dim3(R), dim3(256), 0, st, (const bf16_t *)embed, tokens, d, vocab, h, status);
-    else hipLaunchKernelGGL((embed_kernel<float>), dim3(R), dim3(256), 0, st, (const float *)embed, tokens, d, vocab, h, status);
-}
-
 // act[r][:] = h[src][:] * gain / sqrt(mean(h[src]^2) + eps) with src = row0 + r*row_stride.
 // One workgroup per row; a row of up to 8192 elements stays in registers between the two passes (16-byte
 // loads, 8-byte stores of four packed values per plane); longer or unaligned rows take the plain loops.
@@ -43,32 +24,70 @@ __device__ __forceinline__ void store_act4(const ActPlanes<bf16_t> &a, size_t of
 __device__ __forceinline__ void store_act4(const ActPlanes<float> &a, size_t off, const float (&x)[4]) {
     *reinterpret_cast<float4 *>(a.base + off) = make_float4(x[0], x[1], x[2], x[3]);
 }
-// SPLITK: the row is first completed, x = h[r] + (parts[0][r] + parts[1][r] + ...) with the splits added in order, and
-// stored back to h; without a gain that is all (the norm below is the same code either way, so a fused launch and
+// Where the row comes from.  ROW_PLAIN: from h.  ROW_SPLITK: x = h[r] + (parts[0][r] + parts[1][r] + ...) with the splits
+// added in order, stored back to h.  ROW_EMBED: the embedding of the row's token, stored to h (a launch of its own in front
+// of the norm costs 4 us).  Without a gain that is all (the norm below is the same code in every mode, so a fused launch and
 // the two separate ones give the same bits).
+enum RowMode { ROW_PLAIN, ROW_SPLITK, ROW_EMBED };
 constexpr int SPLITK_MAX = 4; // splits the fused form can sum (the wide GEMM never makes more)
-template <typename T, bool SPLITK>
+struct RowSource {
+    const float *parts; // ROW_SPLITK
+    int ksplit;
+    size_t part_stride;
+    const void *embed; // ROW_EMBED: [vocab][d], storage type
+    const int32_t *tokens;
+    int vocab;
+    int32_t *status;
+    float *h_out; // ROW_SPLITK, ROW_EMBED: where the row goes
+};
+__device__ __forceinline__ float4 load4(const bf16_t *p) {
+    const uint2 t = *reinterpret_cast<const uint2 *>(p);
+    return make_float4(u2f(t.x << 16), u2f(t.x & 0xffff0000u), u2f(t.y << 16), u2f(t.y & 0xffff0000u));
+}
+__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+template <typename T, int MODE>
 __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const float *gain, int row0, int row_stride,
-                                                           int d, float eps, ActPlanes<T> act, const float *parts,
-                                                           int ksplit, size_t part_stride, float *h_out) {
+                                                           int d, float eps, ActPlanes<T> act, RowSource src) {
     constexpr int MAXV = 8; // float4 per thread kept in registers
     const int r = blockIdx.x;
-    const float *x = h + (size_t)(row0 + r * row_stride) * d;
+    const float *x = MODE == ROW_EMBED ? src.h_out + (size_t)r * d : h + (size_t)(row0 + r * row_stride) * d;
+    const T *emb = nullptr;
+    if constexpr (MODE == ROW_EMBED) {
+        int tok = src.tokens[r];
+        if (tok < 0 || tok >= src.vocab) {
+            if (threadIdx.x == 0) atomicOr(src.status, 1);
+            tok = tok < 0 ? 0 : src.vocab - 1;
+        }
+        emb = reinterpret_cast<const T *>(src.embed) + (size_t)tok * d;
+    }
     const bool vec = d % 4 == 0 && d <= 256 * 4 * MAXV && act.ld % 4 == 0 && act.plane % 4 == 0 &&
-                     (reinterpret_cast<uintptr_t>(h) & 15) == 0 && (reinterpret_cast<uintptr_t>(gain) & 15) == 0 &&
+                     (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(gain) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(act.base) & 15) == 0 &&
-                     (!SPLITK || ((reinterpret_cast<uintptr_t>(parts) & 15) == 0 && part_stride % 4 == 0));
+                     (MODE != ROW_SPLITK || ((reinterpret_cast<uintptr_t>(src.parts) & 15) == 0 && src.part_stride % 4 == 0)) &&
+                     (MODE != ROW_EMBED || (reinterpret_cast<uintptr_t>(emb) & (4 * sizeof(T) - 1)) == 0);
     float4 v[MAXV], gn[MAXV];
     float ss = 0.f;
     if (vec) {
 #pragma unroll
         for (int j = 0; j < MAXV; ++j) {
             const int e4 = threadIdx.x + 256 * j;
-            v[j] = e4 * 4 < d ? reinterpret_cast<const float4 *>(x)[e4] : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (e4 * 4 < d) {
+                if constexpr (MODE == ROW_EMBED) v[j] = load4(emb + 4 * e4);
+                else v[j] = reinterpret_cast<const float4 *>(x)[e4];
+            }
             // the gains are requested with the row, not behind the reduction (one memory round trip less)
             gn[j] = (gain && e4 * 4 < d) ? reinterpret_cast<const float4 *>(gain)[e4] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        if constexpr (SPLITK) {
+        if constexpr (MODE == ROW_EMBED) {
+#pragma unroll
+            for (int j = 0; j < MAXV; ++j) {
+                const int e4 = threadIdx.x + 256 * j;
+                if (e4 * 4 < d) reinterpret_cast<float4 *>(src.h_out + (size_t)r * d)[e4] = v[j];
+            }
+            if (!gain) return;
+        }
+        if constexpr (MODE == ROW_SPLITK) {
             // every partial is requested before the first one is used (at most SPLITK_MAX splits)
             float4 p[MAXV][SPLITK_MAX];
 #pragma unroll
@@ -76,8 +95,8 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const
 #pragma unroll
                 for (int z = 0; z < SPLITK_MAX; ++z) {
                     const int e4 = threadIdx.x + 256 * j;
-                    p[j][z] = (e4 * 4 < d && z < ksplit) ? reinterpret_cast<const float4 *>(parts + z * part_stride + (size_t)r * d)[e4]
-                                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+                    p[j][z] = (e4 * 4 < d && z < src.ksplit) ? reinterpret_cast<const float4 *>(src.parts + z * src.part_stride + (size_t)r * d)[e4]
+                                                             : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
 #pragma unroll
             for (int j = 0; j < MAXV; ++j) {
@@ -86,11 +105,11 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const
                     float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                     for (int z = 0; z < SPLITK_MAX; ++z)
-                        if (z < ksplit) {
+                        if (z < src.ksplit) {
                             s4.x += p[j][z].x; s4.y += p[j][z].y; s4.z += p[j][z].z; s4.w += p[j][z].w;
                         }
                     v[j].x += s4.x; v[j].y += s4.y; v[j].z += s4.z; v[j].w += s4.w;
-                    reinterpret_cast<float4 *>(h_out + (size_t)r * d)[e4] = v[j];
+                    reinterpret_cast<float4 *>(src.h_out + (size_t)r * d)[e4] = v[j];
                 }
             }
             if (!gain) return;
@@ -98,12 +117,16 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const
 #pragma unroll
         for (int j = 0; j < MAXV; ++j) ss += (v[j].x * v[j].x + v[j].y * v[j].y) + (v[j].z * v[j].z + v[j].w * v[j].w);
     } else {
-        if constexpr (SPLITK) {
+        if constexpr (MODE == ROW_SPLITK) {
             for (int e = threadIdx.x; e < d; e += 256) {
                 float s1 = 0.f;
-                for (int z = 0; z < ksplit; ++z) s1 += parts[z * part_stride + (size_t)r * d + e];
-                h_out[(size_t)r * d + e] = x[e] + s1; // x is this row of h_out; the same thread reads it back below
+                for (int z = 0; z < src.ksplit; ++z) s1 += src.parts[z * src.part_stride + (size_t)r * d + e];
+                src.h_out[(size_t)r * d + e] = x[e] + s1; // x is this row of h_out; the same thread reads it back below
             }
+            if (!gain) return;
+        }
+        if constexpr (MODE == ROW_EMBED) {
+            for (int e = threadIdx.x; e < d; e += 256) src.h_out[(size_t)r * d + e] = to_f32(emb[e]); // read back by the same thread below
             if (!gain) return;
         }
         for (int e = threadIdx.x; e < d; e += 256) ss += x[e] * x[e];
@@ -129,15 +152,21 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const
     }
 }
 
-void launch_rmsnorm_pack_rows(int dtype, const float *h, const float *gain, int nrows, int row0, int row_stride,
-                              int d, float eps, void *act, size_t act_plane, int ld_act, hipStream_t st) {
+template <int MODE>
+static void launch_row_norm(int dtype, const float *h, const float *gain, int nrows, int row0, int row_stride, int d, float eps, void *act,
+                            size_t act_plane, int ld_act, const RowSource &src, hipStream_t st) {
     if (dtype) {
         ActPlanes<bf16_t> ap{(bf16_t *)act, act_plane, ld_act};
-        hipLaunchKernelGGL((rmsnorm_pack_kernel<bf16_t, false>), dim3(nrows), dim3(256), 0, st, h, gain, row0, row_stride, d, eps, ap, nullptr, 0, (size_t)0, nullptr);
+        hipLaunchKernelGGL((rmsnorm_pack_kernel<bf16_t, MODE>), dim3(nrows), dim3(256), 0, st, h, gain, row0, row_stride, d, eps, ap, src);
     } else {
         ActPlanes<float> ap{(float *)act, act_plane, ld_act};
-        hipLaunchKernelGGL((rmsnorm_pack_kernel<float, false>), dim3(nrows), dim3(256), 0, st, h, gain, row0, row_stride, d, eps, ap, nullptr, 0, (size_t)0, nullptr);
+        hipLaunchKernelGGL((rmsnorm_pack_kernel<float, MODE>), dim3(nrows), dim3(256), 0, st, h, gain, row0, row_stride, d, eps, ap, src);
     }
+}
+
+void launch_rmsnorm_pack_rows(int dtype, const float *h, const float *gain, int nrows, int row0, int row_stride,
+                              int d, float eps, void *act, size_t act_plane, int ld_act, hipStream_t st) {
+    launch_row_norm<ROW_PLAIN>(dtype, h, gain, nrows, row0, row_stride, d, eps, act, act_plane, ld_act, RowSource{}, st);
 }
 
 void launch_rmsnorm_pack(int dtype, const float *h, const float *gain, int R, int d, float eps, void *act,
@@ -145,17 +174,19 @@ void launch_rmsnorm_pack(int dtype, const float *h, const float *gain, int R, in
     launch_rmsnorm_pack_rows(dtype, h, gain, R, 0, 1, d, eps, act, act_plane, ld_act, st);
 }
 
+void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, int R, int d, int vocab, float *h, int32_t *status,
+                       const float *gain, float eps, void *act, size_t act_plane, int ld_act, hipStream_t st) {
+    RowSource src{};
+    src.embed = embed; src.tokens = tokens; src.vocab = vocab; src.status = status; src.h_out = h;
+    launch_row_norm<ROW_EMBED>(dtype, nullptr, gain, R, 0, 1, d, eps, act, act_plane, ld_act, src, st);
+}
+
 void launch_splitk_resid_norm(int dtype, float *h, const float *parts, int ksplit, const float *gain, int R, int d,
                               float eps, void *act, size_t act_plane, int ld_act, hipStream_t st) {
     if (ksplit > SPLITK_MAX) abort(); // the caller's split count is bounded by the same constant
-    const size_t stride = (size_t)R * d;
-    if (dtype) {
-        ActPlanes<bf16_t> ap{(bf16_t *)act, act_plane, ld_act};
-        hipLaunchKernelGGL((rmsnorm_pack_kernel<bf16_t, true>), dim3(R), dim3(256), 0, st, h, gain, 0, 1, d, eps, ap, parts, ksplit, stride, h);
-    } else {
-        ActPlanes<float> ap{(float *)act, act_plane, ld_act};
-        hipLaunchKernelGGL((rmsnorm_pack_kernel<float, true>), dim3(R), dim3(256), 0, st, h, gain, 0, 1, d, eps, ap, parts, ksplit, stride, h);
-    }
+    RowSource src{};
+    src.parts = parts; src.ksplit = ksplit; src.part_stride = (size_t)R * d; src.h_out = h;
+    launch_row_norm<ROW_SPLITK>(dtype, h, gain, R, 0, 1, d, eps, act, act_plane, ld_act, src, st);
 }
 
 __global__ void len_add_kernel(int32_t *len, int batch, int delta) {

@@ -82,6 +82,14 @@ __device__ __forceinline__ void epi_prefetch(const GemmArgs &a, const int (&n0)[
     }
 }
 
+// The lengths of the cache move with the last projection of a pass: by the first wave of the first workgroup.
+template <int EPI> __device__ __forceinline__ void move_lengths(const GemmArgs &a) {
+    if constexpr (EPI == EPI_RESID) {
+        if (a.len_add && (blockIdx.x | blockIdx.y | blockIdx.z) == 0 && threadIdx.x < 64)
+            for (int b = threadIdx.x; b < a.len_batch; b += 64) a.len_add[b] += a.len_delta;
+    }
+}
+
 // Epilogue of one output tile by one wave: lane (c, g) holds r[t][v] = the value of row m = rt*16 + c,
 // column n0[t] + 4g + v.  pre: operands fetched ahead by epi_prefetch for this tile and row tile (NULL: read here).
 template <typename T, int EPI>
@@ -408,6 +416,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
         for (int v = 0; v < 4; ++v) red[wave][t][v][lane] = acc[t][v];
     __syncthreads();
     if (wave == 0) tile_epilogue<T, EPI, NW>(a, red, n0, rt, PRE ? &pre : nullptr, rs);
+    move_lengths<EPI>(a);
 }
 
 // ---- weight-only int8 matrices (the quantised model Sections 2 and 3 assume; one fp32 scale per output row)
@@ -558,6 +567,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
             r[t][v] = sum * a.wscale[min(n0[t] + 4 * g + v, nrows_w - 1)] * rs;
         }
     apply_epilogue<T, EPI>(a, r, n0, 0, PRE ? &pre : nullptr);
+    move_lengths<EPI>(a);
 }
 
 // ---- weight-only int4 matrices with one scale per group of 128 K entries (the coarser reading of the same
@@ -731,6 +741,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     __syncthreads();
     if (wave != 0) return;
     tile_epilogue<T, EPI, NW>(a, red, n0, rt, PRE ? &pre : nullptr, rs);
+    move_lengths<EPI>(a);
 }
 
 // More than 16 rows (larger batches, prefill): the waves of a workgroup split the output columns instead
@@ -977,6 +988,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     if (s0 < nslab) step(s0, slab0, slab2, wring[0], wring[2], sring[0], sring[2]);
     if (s0 + 1 < nslab) step(s0 + 1, slab1, slab0, wring[1], wring[0], sring[1], sring[0]);
     wait_vmcnt_at_most<0>(); // nothing may still be landing in LDS when the workgroup ends
+    move_lengths<EPI>(a);
     if (!tile_live) return;
     const int row_tiles = (a.R + 15) / 16;
 #pragma unroll

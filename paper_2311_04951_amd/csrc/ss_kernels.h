@@ -55,6 +55,10 @@ struct GemmArgs {
     int nsq_ld;
     const float *act_nsq;
     int act_nsq_tiles, act_nsq_ld;
+    // EPI_RESID, optional: the launch also moves the sequences' lengths, len_add[b] += len_delta for b < len_batch (nothing in
+    // such a launch reads them; a launch of its own for this costs 4 - 5 us)
+    int32_t *len_add;
+    int len_batch, len_delta;
     // weight-only int8: W is int8 [N][K] and output column n is scaled by wscale[n] (NULL: W is in the storage type).
     // bf16 activation planes only; K a multiple of 16.
     const float *wscale;
@@ -83,8 +87,9 @@ struct AttnArgs {
 };
 void launch_attention(int dtype, const AttnArgs &a, hipStream_t st);
 
-void launch_embed(int dtype, const void *embed, const int32_t *tokens, int R, int d, int vocab, float *h,
-                  int32_t *status, hipStream_t st);
+// h[r] = E[token[r]] and, with a gain, the RMSNorm of the row exactly as launch_rmsnorm_pack computes it
+void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, int R, int d, int vocab, float *h, int32_t *status,
+                       const float *gain, float eps, void *act, size_t act_plane, int ld_act, hipStream_t st);
 void launch_rmsnorm_pack(int dtype, const float *h, const float *gain, int R, int d, float eps, void *act,
                          size_t act_plane, int ld_act, hipStream_t st);
 // second pass of a split-K residual projection: h[r][:] += sum over splits (in split order) of parts[z][r][:], then,
