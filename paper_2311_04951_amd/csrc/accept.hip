@@ -266,18 +266,17 @@ __device__ __forceinline__ unsigned long long inv_cdf_threshold(float u, unsigne
 
 constexpr int SAMPLE_THREADS = 1024, SAMPLE_WAVES = SAMPLE_THREADS / 64;
 
-// Integer inverse CDF over the range [r0, r1) of one row (r0 a multiple of 4) by a 1024-thread
-// workgroup.  Wave w owns a contiguous segment of the range; pass A sums every segment, pass B rescans
+// Integer inverse CDF over the range [r0, r1) of one row (r0 a multiple of 4) by a workgroup of NWAVES wavefronts.  Wave w owns a contiguous segment of the range; pass A sums every segment, pass B rescans
 // the one segment that holds the threshold.  have_T: the threshold T (relative to the weight in front
 // of r0, known to fall inside the range) is given; otherwise it is derived from u and the range's
 // total, and -1 is returned when that total is 0.  Returns the token to every thread.
-template <bool RESID>
+template <bool RESID, int NWAVES = SAMPLE_WAVES>
 __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, int r1, bool have_T, unsigned long long T,
                              float u, unsigned long long *sm_wave, int *sm_tok) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(P.row) & 15) == 0) &&
                      (!RESID || (reinterpret_cast<uintptr_t>(Q.row) & 15) == 0);
-    int seg = (r1 - r0 + SAMPLE_WAVES - 1) / SAMPLE_WAVES;
+    int seg = (r1 - r0 + NWAVES - 1) / NWAVES;
     seg = (seg + 255) & ~255;
     const int v_begin = min(r0 + wave * seg, r1), v_end = min(v_begin + seg, r1);
 
@@ -295,7 +294,7 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
     __syncthreads();
     if (!have_T) {
         unsigned long long S = 0;
-        for (int w = 0; w < SAMPLE_WAVES; ++w) S += sm_wave[w];
+        for (int w = 0; w < NWAVES; ++w) S += sm_wave[w];
         if (S == 0) return -1;
         T = inv_cdf_threshold(u, S);
     }
@@ -769,38 +768,161 @@ void launch_sample_rows(const float *probs, int64_t ld, int B, int V, const floa
     hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_THREADS), 0, st, probs, ld, V, u, token_out);
 }
 
-__global__ __launch_bounds__(SAMPLE_THREADS) void argmax_rows_kernel(const float *x, int64_t ld, int V, int32_t *out) {
-    __shared__ float sm_val[SAMPLE_WAVES];
-    __shared__ int sm_idx[SAMPLE_WAVES];
+// Softmax of a row and one token from it in one launch, for rows of one statistics segment (no workgroup waits for another):
+// the statistics, the probabilities and the token are those of the three launches it replaces, bit for bit (the first two by
+// the same operations in the same order, the token because the inverse CDF adds integers).  The row is read three times, twice
+// from the caches; at 1024 logits the three launches took 3 x 3.7 us back to back, this one one of them.
+__global__ __launch_bounds__(256) void softmax_sample_kernel(const float *logits, int V, float inv_t, float *probs, int64_t ld, const float *u,
+                                                             int32_t *token_out) {
+    __shared__ unsigned long long sm_wave[4];
+    __shared__ int sm_tok;
+    __shared__ float sm_val[4];
+    __shared__ int sm_idx[4];
+    __shared__ float2 sm_stats;
+    const int b = blockIdx.x;
+    const float *x = logits + (size_t)b * V;
+    float *p = probs + (size_t)b * ld;
+    const float2 r = segment_stats(x, V, inv_t, (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0));
+    if (threadIdx.x == 0) sm_stats = r;
+    __syncthreads();
     RowSrc P;
-    P.row = x + (size_t)blockIdx.x * ld;
-    P.from_logits = 0;
-    P.inv_t = 1.f;
-    P.mx = 0.f;
-    P.invZ = 1.f;
-    const int t = block_argmax(P, V, sm_val, sm_idx);
-    if (threadIdx.x == 0) out[blockIdx.x] = t;
+    P.row = x;
+    P.from_logits = 1;
+    P.inv_t = inv_t;
+    P.mx = sm_stats.x;
+    P.invZ = inv_norm(sm_stats.y);
+    for (int v = threadIdx.x; v < V; v += 256) p[v] = P.at(v);
+    int tok = block_inv_cdf<false, 4>(P, P, V, 0, V, false, 0, u[b], sm_wave, &sm_tok);
+    if (tok < 0) tok = block_argmax(P, V, sm_val, sm_idx);
+    if (threadIdx.x == 0) token_out[b] = tok;
+}
+bool launch_softmax_sample(const float *logits, int B, int V, float inv_t, float *probs, int64_t ld, const float *u, int32_t *token_out, hipStream_t st) {
+    if (V > STATS_SEG) return false;
+    if (B > 0) hipLaunchKernelGGL(softmax_sample_kernel, dim3(B), dim3(256), 0, st, logits, V, inv_t, probs, ld, u, token_out);
+    return true;
+}
+
+// (value, index) of the largest of x[0 .. n) plus `first`, the lowest index on ties; NaNs lose to everything (all NaN: index
+// `first`).  ARGMAX_UNROLL independent loads per thread are in flight: a row is read once and the kernel is bound by how many
+// loads a compute unit has outstanding.  Valid in thread 0.
+constexpr int ARGMAX_UNROLL = 8;
+template <int THREADS> __device__ __forceinline__ void block_argmax_range(const float *x, int n, int first, float &best, int &bi) {
+    best = -INFINITY;
+    bi = 0x7fffffff;
+    auto see = [&](float v, int i) {
+        if (v > best || (v == best && i < bi)) {
+            best = v;
+            bi = i;
+        }
+    };
+    if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
+        const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+        const int n4 = n / 4;
+        for (int i0 = threadIdx.x; i0 < n4; i0 += THREADS * ARGMAX_UNROLL) {
+            f32x4 t[ARGMAX_UNROLL];
+#pragma unroll
+            for (int j = 0; j < ARGMAX_UNROLL; ++j) t[j] = x4[min(i0 + THREADS * j, n4 - 1)]; // (past the end: the last unit again, with its own index)
+#pragma unroll
+            for (int j = 0; j < ARGMAX_UNROLL; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) see(t[j][e], 4 * min(i0 + THREADS * j, n4 - 1) + e);
+        }
+        if ((int)threadIdx.x < n - 4 * n4) see(x[4 * n4 + threadIdx.x], 4 * n4 + threadIdx.x);
+    } else {
+        for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * ARGMAX_UNROLL) {
+            float t[ARGMAX_UNROLL];
+#pragma unroll
+            for (int j = 0; j < ARGMAX_UNROLL; ++j) t[j] = x[min(i0 + THREADS * j, n - 1)];
+#pragma unroll
+            for (int j = 0; j < ARGMAX_UNROLL; ++j) see(t[j], min(i0 + THREADS * j, n - 1));
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float b2 = __shfl_xor(best, o);
+        const int i2 = __shfl_xor(bi, o);
+        see(b2, i2);
+    }
+    __shared__ float sm_val[THREADS / 64];
+    __shared__ int sm_idx[THREADS / 64];
+    if ((threadIdx.x & 63) == 0) {
+        sm_val[threadIdx.x >> 6] = best;
+        sm_idx[threadIdx.x >> 6] = bi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < THREADS / 64; ++w) see(sm_val[w], sm_idx[w]);
+        bi = first + (bi == 0x7fffffff ? 0 : bi);
+    }
+}
+
+// one workgroup per row (a draft's call has one to a few rows, and a second launch that merges segments costs 4.5 us:
+// 32000 logits 12.9 -> 6 us with the loads in flight together)
+__global__ __launch_bounds__(SAMPLE_THREADS) void argmax_rows_kernel(const float *x, int64_t ld, int V, int32_t *out) {
+    float best;
+    int bi;
+    block_argmax_range<SAMPLE_THREADS>(x + (size_t)blockIdx.x * ld, V, 0, best, bi);
+    if (threadIdx.x == 0) out[blockIdx.x] = bi;
 }
 void launch_argmax_rows(const float *logits, int64_t ld, int B, int V, int32_t *token_out, hipStream_t st) {
     if (B <= 0) return;
     hipLaunchKernelGGL(argmax_rows_kernel, dim3(B), dim3(SAMPLE_THREADS), 0, st, logits, ld, V, token_out);
 }
 
-// greedy: accept while the draft token is the target row's argmax; next = argmax at the first mismatch
-__global__ void greedy_scan_kernel(const int32_t *row_argmax, const int32_t *draft, int B, int K, int32_t *n_accepted,
-                                   int32_t *next_token) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    int n = 0;
-    while (n < K && draft[b * K + n] == row_argmax[b * (K + 1) + n]) ++n;
-    n_accepted[b] = n;
-    next_token[b] = row_argmax[b * (K + 1) + n];
+// Greedy: accept while the draft token is the target row's argmax; next = argmax at the first mismatch.  The rows are cut into
+// segments (grid: segments x rows) whose (value, index) pairs the second launch, which scans the positions anyway, merges in
+// index order: one workgroup per row left a row's stream to one compute unit (72 rows of 128256 logits: 45.6 us = 0.8 TB/s).
+__global__ __launch_bounds__(256) void argmax_segment_kernel(const float *x, int V, int seg_len, float2 *part) {
+    const int r0 = blockIdx.x * seg_len;
+    float best;
+    int bi;
+    block_argmax_range<256>(x + (size_t)blockIdx.y * V + r0, min(seg_len, V - r0), r0, best, bi);
+    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(best, __int_as_float(bi));
 }
-void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, int32_t *row_argmax,
+// one wavefront per sequence, lane i = position i (K + 1 <= 16 positions)
+// row_argmax: the rows' tokens where they were not cut (part NULL)
+__global__ __launch_bounds__(64) void greedy_finish_kernel(const float2 *part, int nseg, const int32_t *row_argmax, const int32_t *draft, int K,
+                                                           int32_t *n_accepted, int32_t *next_token) {
+    const int b = blockIdx.x, i = min((int)threadIdx.x, K);
+    const size_t row = (size_t)b * (K + 1) + i;
+    int tok;
+    if (part) {
+        float2 best = part[row * nseg];
+        for (int s = 1; s < nseg; ++s)
+            if (part[row * nseg + s].x > best.x) best = part[row * nseg + s]; // (equal values: the earlier segment holds the lower index)
+        tok = __float_as_int(best.y);
+    } else {
+        tok = row_argmax[row];
+    }
+    const bool mismatch = (int)threadIdx.x >= K || draft[(size_t)b * K + threadIdx.x] != tok;
+    const int n = min(__ffsll((long long)__ballot(mismatch)) - 1, K);
+    if ((int)threadIdx.x == n) {
+        n_accepted[b] = n;
+        next_token[b] = tok;
+    }
+}
+// segments per row: at most 16, of at least 4096 entries each while that fills the chip (2048 workgroups), and no more than the
+// workspace holds pairs for (avail: bytes)
+static int greedy_segments(int64_t rows, int V, size_t avail, int &seg_len) {
+    int64_t nseg = std::min<int64_t>(std::min<int64_t>(16, V / 4096), 2048 / rows);
+    nseg = std::max<int64_t>(1, std::min<int64_t>(nseg, (int64_t)(avail / (sizeof(float2) * (size_t)rows))));
+    seg_len = (int)((V + nseg - 1) / nseg);
+    seg_len = (seg_len + 3) & ~3; // keeps the 16-byte alignment of an aligned row
+    return (V + seg_len - 1) / seg_len;
+}
+void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, void *scratch, size_t scratch_bytes,
                           int32_t *n_accepted, int32_t *next_token, hipStream_t st) {
     if (B <= 0) return;
-    launch_argmax_rows(p_logits, V, B * (K + 1), V, row_argmax, st);
-    hipLaunchKernelGGL(greedy_scan_kernel, dim3((B + 63) / 64), dim3(64), 0, st, row_argmax, draft, B, K, n_accepted, next_token);
+    const int64_t rows = (int64_t)B * (K + 1);
+    int seg_len;
+    const int nseg = greedy_segments(rows, V, scratch_bytes, seg_len);
+    if (nseg == 1) { // (a row's one workgroup needs no pair)
+        launch_argmax_rows(p_logits, V, (int)rows, V, (int32_t *)scratch, st);
+        hipLaunchKernelGGL(greedy_finish_kernel, dim3(B), dim3(64), 0, st, (const float2 *)nullptr, 1, (const int32_t *)scratch, draft, K, n_accepted, next_token);
+        return;
+    }
+    hipLaunchKernelGGL(argmax_segment_kernel, dim3(nseg, (unsigned)rows), dim3(256), 0, st, p_logits, V, seg_len, (float2 *)scratch); // (rows <= 1024 here)
+    hipLaunchKernelGGL(greedy_finish_kernel, dim3(B), dim3(64), 0, st, (const float2 *)scratch, nseg, (const int32_t *)nullptr, draft, K, n_accepted, next_token);
 }
 
 } // namespace ss

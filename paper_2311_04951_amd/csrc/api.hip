@@ -916,6 +916,7 @@ extern "C" int ss_draft_step(ss_model *m, ss_kv_cache *kv, const int32_t *tokens
     }
     if (temperature > 0.f) {
         const float inv_t = 1.0f / temperature;
+        if (!kk && !P24 && launch_softmax_sample(m->logits_ws, batch, V, inv_t, q_rows_dev, ldq, u_dev, token_out_dev, st)) return check_launch();
         launch_row_stats(m->logits_ws, batch, V, inv_t, m->stats_ws, m->stats_cnt, m->stats_part, st);
         launch_softmax_write(m->logits_ws, batch, V, inv_t, m->stats_ws, q_rows_dev, ldq, st);
         if (kk) launch_top_k_filter(q_rows_dev, ldq, batch, V, kk, q_rows_dev, ldq, st); // top-k first, top-p on its output
@@ -1082,7 +1083,7 @@ extern "C" int ss_greedy_accept(const float *p_logits_dev, const int32_t *draft_
     if (!p_logits_dev || !n_accepted_dev || !next_token_dev || (K > 0 && !draft_tokens_dev)) return fail(SS_EINVAL, "ss_greedy_accept: NULL argument");
     int rc = check_ws(ws, ws_bytes, greedy_need(batch, K), "ss_greedy_accept");
     if (rc) return rc;
-    launch_greedy_accept(p_logits_dev, draft_tokens_dev, batch, K, vocab, (int32_t *)scr_data(ws), n_accepted_dev, next_token_dev, (hipStream_t)stream);
+    launch_greedy_accept(p_logits_dev, draft_tokens_dev, batch, K, vocab, scr_data(ws), ws_bytes - SCR_DATA, n_accepted_dev, next_token_dev, (hipStream_t)stream);
     return check_launch();
 }
 

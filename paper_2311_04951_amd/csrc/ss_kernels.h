@@ -145,8 +145,11 @@ void launch_row_stats_staged(const AcceptArgs &a, float2 *p_stats, float2 *q_sta
 // partial: device workspace of accept_workspace_bytes(B, V) bytes (per-segment weight sums)
 size_t accept_workspace_bytes(int B, int V);
 void launch_accept(const AcceptArgs &a, unsigned long long *partial, hipStream_t st);
-void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, int32_t *row_argmax,
+// scratch: device memory of at least 4 bytes per row (B * (K + 1) rows), 8-byte aligned; more (8 bytes per row and segment) lets a row be cut into segments
+void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, void *scratch, size_t scratch_bytes,
                           int32_t *n_accepted, int32_t *next_token, hipStream_t st);
+// softmax rows (probs, leading dimension ld) and one token of each; false (nothing launched) when a row is longer than one statistics segment
+bool launch_softmax_sample(const float *logits, int B, int V, float inv_t, float *probs, int64_t ld, const float *u, int32_t *token_out, hipStream_t st);
 // token ~ row by the integer inverse CDF (rows are probabilities), or argmax when greedy
 // rows of probabilities -> the rows restricted to their top-p nucleus and renormalised (P24 = top_p on a 2^-24 grid); out may alias probs
 void launch_top_p_filter(const float *probs, long long ld_in, int rows, int V, unsigned P24, float *out, long long ld_out, hipStream_t st);

@@ -50,3 +50,48 @@ def test_embedding_and_final_norm_on_other_launches_match_the_oracle(d, batch, r
     toks[0, 0] = shape.vocab - 1
     for b in range(batch):
         assert maxabs(got[b], om.forward(om.new_kv(64), toks[b].numpy())) < 1e-4
+
+
+@pytest.mark.parametrize("V", [1, 3, 1000, 4096, 8193, 32000, 50257, 128256])
+@pytest.mark.parametrize("B,K", [(1, 0), (2, 4), (9, 15), (200, 8)])
+def test_greedy_acceptance_by_segments(V, B, K):
+    """Rows cut into segments, one to many, aligned and not, with ties across segments, infinities and NaNs, and a workspace that
+    holds no pairs at all: the lowest index of the largest value, NaNs aside."""
+    if B * V > 4_000_000:
+        B = max(1, 4_000_000 // V)
+    x = torch.randint(-4, 5, (B, K + 1, V), generator=torch.Generator().manual_seed(V + B)).float()     # ties everywhere
+    x[0, 0] = -torch.inf
+    if V > 5:
+        x[-1, -1, 5] = torch.inf
+        x[-1, -1, 0] = torch.nan
+        x[0, K, V - 1] = 9.0
+    best = torch.where(x.isnan(), -torch.inf, x).argmax(-1).to(torch.int32)
+    first = torch.where(x.isnan(), -torch.inf, x) == torch.where(x.isnan(), -torch.inf, x).max(-1, keepdim=True).values
+    best = first.float().argmax(-1).to(torch.int32)                                 # the lowest index
+    d = best[:, :K].clone()
+    d[torch.rand(d.shape, generator=torch.Generator().manual_seed(1)) < 0.2] += 1
+    want_n = [next((i for i in range(K) if d[b, i] != best[b, i]), K) for b in range(B)]
+    tight = sv.ss_workspace_init(torch.empty(256 + 65536 + 4 * B * (K + 1) + 16, dtype=torch.uint8, device=dev()))
+    for ws in (None, tight):
+        na, nx = sv.ss_greedy_accept(x.to(dev()), d.contiguous().to(dev()), ws=ws)
+        assert na.tolist() == want_n
+        assert nx.tolist() == [int(best[b, n]) for b, n in enumerate(want_n)]
+
+
+@pytest.mark.parametrize("V", [64, 1000, 1027, 16384, 16388])      # one statistics segment (one launch), and the first that has two
+def test_a_draft_step_in_one_sampling_launch_gives_the_bits_of_the_separate_ones(V):
+    shape = si.DecoderShape(1, 256, 4, 64, 344, V, dtype="f32")
+    gm = sv.Model(shape, weights_to_device(si.decoder_weights(shape, seed=73)), max_rows=16, max_pos=64)
+    for batch, T in ((1, 1.0), (5, 0.3)):
+        toks = si.token_ids(73, "t", (batch, 1), V).to(dev())
+        u = si.uniforms(73, f"u{batch}", (batch,)).to(dev())
+        ld = V + 3
+        q = torch.full((batch, ld), -1.0, device=dev())
+        out = torch.empty(batch, dtype=torch.int32, device=dev())
+        sv.ss_draft_step(gm, sv.KVCache(gm, batch, 32), toks, 1, T, u, q, ld, out)
+        logits = sv.ss_verify_forward(gm, sv.KVCache(gm, batch, 32), toks, 1)
+        p = sv.ss_softmax(logits.reshape(batch, 1, V), T)
+        assert torch.equal(q[:, :V], p[:, 0]) and bool((q[:, V:] == -1).all())
+        none = torch.zeros(1, dtype=torch.int32, device=dev())
+        _, tok = sv.ss_speculative_accept(p, p, none, u.reshape(batch, 1).contiguous())      # K = 0: a plain sample
+        assert out.tolist() == tok.tolist()
