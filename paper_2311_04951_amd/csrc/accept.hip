@@ -16,6 +16,7 @@
 #include "ss_device.h"
 #include "ss_kernels.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace ss {
 
@@ -529,43 +530,48 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void accept_finish_kernel(AcceptArg
     if (threadIdx.x == 0) a.next_token[b] = tok;
 }
 
-// segments per sequence: enough workgroups to fill the chip, at least 8192 vocabulary entries each
-static int accept_segments(int B, int V, int &seg_len) {
-    int nseg = std::max(1, std::min(std::min(16, V / 8192), (1024 + B - 1) / std::max(B, 1)));
+// segments per sequence: enough workgroups to fill the chip, of at least `least` vocabulary entries each
+static int accept_segments(int B, int V, int least, int &seg_len) {
+    int nseg = std::max(1, std::min(std::min(16, V / least), (1024 + B - 1) / std::max(B, 1)));
     seg_len = (V + nseg - 1) / nseg;
     seg_len = (seg_len + 1023) & ~1023; // multiple of the 4-wide loads of a whole workgroup
     nseg = (V + seg_len - 1) / seg_len;
     return std::max(nseg, 1);
 }
+constexpr int ACCEPT_SEG = 8192;
 
 size_t accept_workspace_bytes(int B, int V) {
     int seg_len;
-    return sizeof(unsigned long long) * (size_t)B * accept_segments(B, V, seg_len);
+    return sizeof(unsigned long long) * (size_t)B * accept_segments(B, V, ACCEPT_SEG, seg_len);
 }
 
-void launch_accept(const AcceptArgs &a, unsigned long long *partial, hipStream_t st) {
+// avail: bytes at `partial` (at least accept_workspace_bytes).  Where they hold more pairs than that minimum, segments go down to
+// 2048 entries (two loads per thread; one sequence of 32000 entries: 9.2 -> 5.0 us with 11 segments instead of 3)
+void launch_accept(const AcceptArgs &a, unsigned long long *partial, size_t avail, hipStream_t st) {
     if (a.B <= 0) return;
     int seg_len;
-    const int nseg = accept_segments(a.B, a.V, seg_len);
+    int nseg = accept_segments(a.B, a.V, 2048, seg_len);
+    if (sizeof(unsigned long long) * (size_t)a.B * nseg > avail) nseg = accept_segments(a.B, a.V, ACCEPT_SEG, seg_len);
     hipLaunchKernelGGL(accept_partial_kernel, dim3(nseg, a.B), dim3(PART_THREADS), 0, st, a, seg_len, partial);
     hipLaunchKernelGGL(accept_finish_kernel, dim3(a.B), dim3(SAMPLE_THREADS), 0, st, a, seg_len, nseg, partial);
 }
 
 // ------------------------------------------------------------------ top-p filter
 //
-// Top-p ("nucleus") selection of probability rows (Section 3 names it beside argmax; the arithmetic is fixed
+// Top-p ("nucleus") and top-k selection of probability rows (Section 3 names both beside argmax; the arithmetic is fixed
 // in the header of the C ABI): 32-bit integer weights, kept set = shortest prefix in (weight descending, index
-// ascending) order whose weights reach the target, renormalised by one fp32 division per element.  One
-// workgroup per row finds the threshold weight by a three-digit radix selection (11 + 11 + 10 bits) over
-// histograms of weight sums in LDS: all sums are integers, so the result does not depend on the order in
-// which threads add.  Four reads of the row (three digits, one write pass; L2-resident), a fifth only when
-// equal weights straddle the boundary.
-constexpr int TP_THREADS = 1024, TP_WAVES = TP_THREADS / 64, TP_BINS = 2048, TP_UNROLL = 8;
-
-__device__ __forceinline__ uint32_t fx_weight32(float r) {
-    const unsigned long long w = fx_weight(r);
-    return w > 0xffffffffull ? 0xffffffffu : (uint32_t)w;
-}
+// ascending) order whose weights reach the target (top-p) or the first k of that order (top-k), renormalised by one fp32
+// division per element.  One workgroup per row looks for the weight of the last kept token:
+//   1. a histogram over 2048 logarithmic bins (position of the leading bit, the six bits behind it), which spreads the weights of
+//      a softmax over hundreds of bins (the top eleven bits of the weight put all but a few tokens into one);
+//   2. the tokens of the bin that holds the boundary go to a list in LDS, usually some hundred, and the remaining bits are
+//      found by digits of eleven bits over that list - or over the row when they do not fit (a row of equal weights);
+//   3. one pass writes the row.
+// All sums are integers, so the result does not depend on the order in which threads add.  A row of up to 32768 entries stays in
+// LDS between the passes; a longer one is read again from the caches in each (16-byte loads where the rows allow).  Bound by the one compute unit that a row has; a split over several would need launches between the passes at
+// 4 - 5 us each.  Measured at 5 rows of 32000 logits N(0, 2): top-k 35 -> 16 us (three digits over the row, five reads
+// of it, before), top-p of what top-200 left 29 -> 9, of whole rows 18.
+constexpr int TP_THREADS = 1024, TP_WAVES = TP_THREADS / 64, TP_BINS = 2048;
 
 // Workgroup-wide exclusive prefix sum of one value per thread in thread order; also returns the total.
 __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long mine, unsigned long long *sm_wave, unsigned long long &total) {
@@ -590,111 +596,243 @@ __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long
     return before + incl - mine;
 }
 
+constexpr int TP_FITS = 32768; // longest row that stays in LDS
+constexpr int TP_LIST = 2048, TP_RANK = 512; // entries of the boundary bin that fit LDS; up to which they are ranked one against all
+
+// An entry's weight as the bits of a float, f = trunc(min(max(p * 2^32, 0), 2^32)): whole numbers of at most 24 significant bits, so
+// f orders like the integer weight min(trunc(p * 2^32), 2^32 - 1) and is equal where that is (2^32 stands for 2^32 - 1).  Four
+// instructions; a conversion to 64 bits takes some twenty, and a row has one compute unit to do them on.
+__device__ __forceinline__ uint32_t tp_key(float p) { return f2u(truncf(fminf(fmaxf(__fmul_rn(p, 4294967296.0f), 0.f), 4294967296.0f))); }
+__device__ __forceinline__ uint32_t tp_weight(uint32_t key) { return key >= 0x4f800000u ? 0xffffffffu : (uint32_t)u2f(key); }
+// monotone bin of a key >= 1.0: exponent and the six bits behind it.  2^0 .. 2^32 would be 2049 bins; 1.0 is alone in the 64 of its
+// exponent, so everything above moves down by one
+__device__ __forceinline__ int tp_bin(uint32_t key) { return max((int)(key >> 17) - 8129, 0); }
+__device__ __forceinline__ uint32_t tp_bin_prefix(int bin) { return bin ? (uint32_t)bin + 8129u : 8128u; } // key >> 17 of the bin's keys
+// x / Z rounded to nearest, for 2^-32 <= x < 1 and 2^-32 <= Z < 2^18, from rZ = 1 / Z rounded to nearest: two remainder steps, the
+// first of which makes the quotient faithful and the second rounds it correctly (Markstein, "Computation of elementary functions
+// on the IBM RISC System/6000 processor", 1990); nothing under- or overflows in that range.  Five instructions; the general
+// division takes three times as many and changes the rounding mode twice, which made the writing pass the longest of the kernel.
+__device__ __forceinline__ float tp_divide(float x, float Z, float rZ) {
+    float q = __fmul_rn(x, rZ);
+    q = __fmaf_rn(__fmaf_rn(-q, Z, x), rZ, q);
+    return __fmaf_rn(__fmaf_rn(-q, Z, x), rZ, q);
+}
+// Four entries from v on (absent ones read as 0)
+template <bool VEC> __device__ __forceinline__ f32x4 tp_load4(const float *p, int v, int V) {
+    if (VEC && v + 3 < V) return *reinterpret_cast<const f32x4 *>(p + v);
+    f32x4 q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = v + e < V ? p[v + e] : 0.f;
+    return q;
+}
+
 // BY_COUNT = false: top-p, the histograms hold sums of weights and the selection looks for the weight at which the running
-// sum reaches ceil(P24 * S / 2^24).  BY_COUNT = true: top-k (`P24` carries k, 1 <= k < V), the histograms hold counts (tokens
-// without a weight count too: they are the tail of the order) and the selection looks for the weight of the k-th token;
-// the kept weight is then summed in one more pass over the row.
-template <bool BY_COUNT>
+// sum reaches ceil(P24 * S / 2^24).  BY_COUNT = true: top-k (`P24` carries k, 1 <= k < V), the histograms hold counts and the
+// selection looks for the weight of the k-th token (tokens without a weight are the tail of the order).
+template <bool BY_COUNT, bool VEC, bool FITS>
 __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *probs, long long ld_in, int V, unsigned P24, float *out, long long ld_out) {
-    __shared__ unsigned long long hist[TP_BINS];
+    typedef typename std::conditional<BY_COUNT, unsigned, unsigned long long>::type Bin;
+    __shared__ Bin hist[TP_BINS];
     __shared__ unsigned long long sm_wave[TP_WAVES];
     __shared__ unsigned long long sm_above, sm_binw;
-    __shared__ int sm_bin, sm_cut;
+    __shared__ uint32_t list[TP_LIST];
+    __shared__ int sm_bin, sm_cut, sm_n;
+    __shared__ f32x4 row[FITS ? TP_FITS / 4 : 1];
     const float *p = probs + (size_t)blockIdx.x * (size_t)ld_in;
     float *o = out + (size_t)blockIdx.x * (size_t)ld_out;
-    const int t = threadIdx.x;
-
-    uint32_t prefix = 0;          // the digits of the threshold weight chosen so far
-    unsigned long long need = 0;  // what the keys inside the chosen range still have to contribute
-    unsigned long long S = 0, tie_weight = 0, target = 0;
-    const int shifts[3] = {21, 10, 0}, nbits[3] = {11, 11, 10};
+    const int t = threadIdx.x, n4 = (V + 3) / 4;
+    // f(key) for every entry of the row.  Short loop bodies: 32 entries of a thread unrolled in registers were bound by the
+    // fetch of instructions that a wavefront runs once (top-k 21 us against 16).
+    auto each = [&](auto f) {
+        constexpr int U = FITS ? 2 : 4; // 16-byte loads in flight
+        for (int i0 = t; i0 < n4; i0 += TP_THREADS * U) {
+            f32x4 x[U];
 #pragma unroll
-    for (int pass = 0; pass < 3; ++pass) {
-        const int sh = shifts[pass], nb = nbits[pass];
-        for (int b = t; b < TP_BINS; b += TP_THREADS) hist[b] = 0;
-        __syncthreads();
-        // A thread adds up runs of elements that fall into one bin before it touches the histogram: in the first
-        // digit the weights of a whole vocabulary usually share their leading zeros (one bin), and per-element
-        // atomics on one address would serialise.
-        uint32_t run_bin = 0xffffffffu;
-        unsigned long long run_sum = 0;
-        for (int v0 = 0; v0 < V; v0 += TP_UNROLL * TP_THREADS) {
-            float x[TP_UNROLL]; // the loads of a batch go out together
-#pragma unroll
-            for (int e = 0; e < TP_UNROLL; ++e) {
-                const int v = v0 + e * TP_THREADS + t;
-                x[e] = v < V ? p[v] : 0.f;
+            for (int j = 0; j < U; ++j) {
+                const int i = i0 + TP_THREADS * j;
+                x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, 4 * i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
-            for (int e = 0; e < TP_UNROLL; ++e) {
-                const uint32_t w = fx_weight32(x[e]);
-                // keys inside the range chosen so far (pass 0: every key with a weight)
-                if ((BY_COUNT ? v0 + e * TP_THREADS + t < V : w != 0) && (pass == 0 || (w >> (sh + nb)) == prefix)) {
-                    const uint32_t bin = (w >> sh) & ((1u << nb) - 1);
-                    if (bin != run_bin) {
-                        if (run_bin != 0xffffffffu) atomicAdd(&hist[run_bin], run_sum);
-                        run_bin = bin;
-                        run_sum = 0;
-                    }
-                    run_sum += BY_COUNT ? 1u : w;
-                }
-            }
+            for (int j = 0; j < U; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f(tp_key(x[j][e]));
         }
-        if (run_bin != 0xffffffffu) atomicAdd(&hist[run_bin], run_sum);
+    };
+    if constexpr (FITS) { // the row is fetched once
+        for (int i0 = t; i0 < n4; i0 += TP_THREADS * 8) {
+            f32x4 x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = tp_load4<VEC>(p, 4 * min(i0 + TP_THREADS * j, n4 - 1), V);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (i0 + TP_THREADS * j < n4) row[i0 + TP_THREADS * j] = x[j]; // (read back by the same thread; clear() below has the barrier for others)
+        }
+    }
+    auto unchanged = [&]() {
+        for (int v = t; v < V; v += TP_THREADS) o[v] = p[v];
+    };
+    auto count = [&](int bin, uint32_t key) { atomicAdd(&hist[bin], BY_COUNT ? (Bin)1 : (Bin)tp_weight(key)); };
+    auto clear = [&]() {
+        hist[t] = 0;
+        hist[t + TP_THREADS] = 0;
+        __syncthreads();
+    };
+    // the bin, from the top, in which the running sum reaches `need`; `need` becomes what it has to contribute, binw what it holds.
+    // first: `need` comes from the total
+    unsigned long long need = 0, target = 0, binw = 0, S = 0;
+    auto choose = [&](bool first) -> int {
         __syncthreads();
         // thread t owns bins 2047 - 2t and 2046 - 2t, so thread order is descending weight order
         const unsigned long long a = hist[TP_BINS - 1 - 2 * t], b = hist[TP_BINS - 2 - 2 * t];
         unsigned long long total;
-        const unsigned long long above = block_excl_scan(a + b, sm_wave, total);
-        if (BY_COUNT && pass == 0) {
-            need = P24; // the k-th token of the order
-            target = need;
-        }
-        if (!BY_COUNT && pass == 0) {
+        const unsigned long long before = block_excl_scan(a + b, sm_wave, total);
+        if (first) {
             S = total;
-            if (S == 0) { // nothing has a weight: the row is returned as it is
-                for (int v = t; v < V; v += TP_THREADS) o[v] = p[v];
-                return;
+            if (BY_COUNT) {
+                need = P24; // the k-th token of the order
+            } else {
+                // target = ceil(P24 * S / 2^24) from the 128-bit product, at least 1
+                const unsigned long long lo = (unsigned long long)P24 * S, hi = __umul64hi((unsigned long long)P24, S);
+                const unsigned long long lo2 = lo + 16777215ull, hi2 = hi + (lo2 < lo ? 1ull : 0ull);
+                need = (hi2 << 40) | (lo2 >> 24);
+                if (need < 1) need = 1;
             }
-            // target = ceil(P24 * S / 2^24) from the 128-bit product, at least 1
-            const unsigned long long lo = (unsigned long long)P24 * S, hi = __umul64hi((unsigned long long)P24, S);
-            const unsigned long long lo2 = lo + 16777215ull, hi2 = hi + (lo2 < lo ? 1ull : 0ull);
-            need = (hi2 << 40) | (lo2 >> 24);
-            if (need < 1) need = 1;
             target = need;
+            if (S == 0 || need > S) return -1; // nothing has a weight; top-k: k reaches into the tokens without one
         }
-        if (above < need && need <= above + a) {
+        if (before < need && need <= before + a) {
             sm_bin = TP_BINS - 1 - 2 * t;
-            sm_above = above;
+            sm_above = before;
             sm_binw = a;
-        } else if (above + a < need && need <= above + a + b) {
+        } else if (before + a < need && need <= before + a + b) {
             sm_bin = TP_BINS - 2 - 2 * t;
-            sm_above = above + a;
+            sm_above = before + a;
             sm_binw = b;
         }
         __syncthreads();
-        prefix = (prefix << nb) | (uint32_t)sm_bin;
         need -= sm_above;
-        tie_weight = sm_binw;
-        __syncthreads(); // everyone has read the choice before the next pass overwrites it
+        binw = sm_binw;
+        const int bin = sm_bin;
+        __syncthreads(); // everyone has read the choice before the next one overwrites it
+        return bin;
+    };
+
+    if (t == 0) sm_n = 0;
+    clear();
+    each([&](uint32_t key) {
+        if (key) count(tp_bin(key), key);
+    });
+    const int bin0 = choose(true);
+    if (S == 0) { // nothing has a weight: the row is returned as it is
+        unchanged();
+        return;
     }
-    // prefix = threshold weight tau (>= 1); need = what tokens of weight tau must contribute; tie_weight = their total
-    const unsigned long long tau = prefix;
-    // (top-k: counts already; tau may be 0 there, when k reaches into the tokens without a weight)
-    const unsigned long long n_ties = BY_COUNT ? tie_weight : tie_weight / tau, n_keep = BY_COUNT ? need : (need + tau - 1) / tau;
+    uint32_t tau = 0;                  // key of the last kept token (0: top-k keeps every token with a weight and some without)
+    unsigned long long n_ties, n_keep; // tokens of that weight, and how many of them are kept
+    unsigned long long kept;           // weight of the kept set
+    if (bin0 >= 0) {
+        // the boundary bin's tokens to the list; top-k: the weight above the bin on the way
+        uint32_t prefix = tp_bin_prefix(bin0);
+        unsigned long long mine = 0;
+        each([&](uint32_t key) {
+            const uint32_t k17 = key >> 17;
+            if (k17 >= prefix) {
+                if (k17 == prefix) {
+                    const int at = atomicAdd(&sm_n, 1);
+                    if (at < TP_LIST) list[at] = key;
+                } else if (BY_COUNT) {
+                    mine += tp_weight(key);
+                }
+            }
+        });
+        unsigned long long above_w = 0;
+        if (BY_COUNT) block_excl_scan(mine, sm_wave, above_w);
+        __syncthreads();
+        const int n = sm_n;
+        if (n <= TP_RANK) { // few: the token in whose turn the sum is reached finds itself
+            if (t < n) {
+                const uint32_t key = list[t];
+                unsigned long long above = 0, equal = 0;
+                for (int i = 0; i < n; ++i) {
+                    const uint32_t other = list[i];
+                    const unsigned long long add = BY_COUNT ? 1ull : tp_weight(other);
+                    above += other > key ? add : 0ull;
+                    equal += other == key ? add : 0ull;
+                }
+                if (above < need && need <= above + equal) { // (equal tokens write the same)
+                    sm_bin = (int)key;
+                    sm_above = above;
+                    sm_binw = equal;
+                }
+            }
+            __syncthreads();
+            tau = (uint32_t)sm_bin;
+            need -= sm_above;
+            binw = sm_binw;
+            __syncthreads();
+        } else { // the 17 bits behind the bin's, by digits
+            for (int low = 17; low > 0;) {
+                const int nb = low < 11 ? low : 11;
+                clear();
+                auto digit = [&](uint32_t key) {
+                    if ((key >> low) == prefix) count((int)((key >> (low - nb)) & ((1u << nb) - 1)), key);
+                };
+                if (n <= TP_LIST) {
+                    for (int i = t; i < n; i += TP_THREADS) digit(list[i]);
+                } else {
+                    each(digit);
+                }
+                prefix = (prefix << nb) | (uint32_t)choose(false);
+                low -= nb;
+            }
+            tau = prefix;
+        }
+        const unsigned long long w = tp_weight(tau);
+        if (BY_COUNT) {
+            n_ties = binw;
+            n_keep = need;
+        } else if (binw == w) { // one token of that weight, the usual case (two 64-bit divisions by 1024 threads take 2 us)
+            n_ties = n_keep = 1;
+        } else {
+            n_ties = binw / w;
+            n_keep = (need + w - 1) / w;
+        }
+        if (BY_COUNT) {
+            // above the boundary inside the bin: summed over the list (or the row)
+            unsigned long long in_bin = 0, more;
+            const uint32_t first = tp_bin_prefix(bin0);
+            if (n <= TP_LIST) {
+                for (int i = t; i < n; i += TP_THREADS) in_bin += list[i] > tau ? tp_weight(list[i]) : 0u;
+            } else {
+                each([&](uint32_t key) {
+                    if (key > tau && (key >> 17) == first) in_bin += tp_weight(key);
+                });
+            }
+            block_excl_scan(in_bin, sm_wave, more);
+            kept = above_w + more + n_keep * w;
+        } else {
+            kept = target - need + n_keep * w; // everything above tau (target - need) plus the kept tokens of weight tau
+        }
+    } else { // top-k past the tokens with a weight (S of them): all of those, and the first k - S of the others
+        unsigned long long mine = 0;
+        each([&](uint32_t key) { mine += tp_weight(key); });
+        block_excl_scan(mine, sm_wave, kept);
+        n_ties = (unsigned long long)V - S;
+        n_keep = P24 - S;
+    }
     int cut = V; // ties are kept up to and including this index
     if (n_keep < n_ties) {
         // the n_keep-th token of weight tau in index order: contiguous chunks per thread, counts scanned over threads
         const int chunk = (V + TP_THREADS - 1) / TP_THREADS;
         const int v0 = min(t * chunk, V), v1 = min(v0 + chunk, V);
         unsigned long long cnt = 0;
-        for (int v = v0; v < v1; ++v) cnt += fx_weight32(p[v]) == prefix;
+        for (int v = v0; v < v1; ++v) cnt += tp_key(p[v]) == tau;
         unsigned long long total;
         const unsigned long long before = block_excl_scan(cnt, sm_wave, total);
         if (before < n_keep && n_keep <= before + cnt) {
             unsigned long long seen = before;
             for (int v = v0; v < v1; ++v)
-                if (fx_weight32(p[v]) == prefix && ++seen == n_keep) {
+                if (tp_key(p[v]) == tau && ++seen == n_keep) {
                     sm_cut = v;
                     break;
                 }
@@ -702,45 +840,55 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         __syncthreads();
         cut = sm_cut;
     }
-    // weight of the kept set: everything above tau (target - need) plus the kept tokens of weight tau
-    unsigned long long kept = target - need + n_keep * tau;
-    if (BY_COUNT) { // the weight above tau is not known from counts: one more pass over the row
-        unsigned long long mine = 0;
-        for (int v = t; v < V; v += TP_THREADS) {
-            const uint32_t w = fx_weight32(p[v]);
-            mine += w > prefix ? w : 0u;
+    const float Z = __fmul_rn(__ull2float_rn(kept), 2.3283064365386963e-10f), rZ = __fdiv_rn(1.0f, Z);
+    constexpr int U = FITS ? 2 : 4;
+    for (int i0 = t; i0 < n4; i0 += TP_THREADS * U) {
+        f32x4 x[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) { // (a thread reads what it writes: in place is fine)
+            const int i = i0 + TP_THREADS * j;
+            x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, 4 * i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        unsigned long long total;
-        block_excl_scan(mine, sm_wave, total);
-        kept = total + n_keep * tau;
-        if (kept == 0) { // nothing kept has a weight (then nothing has): the row is returned as it is
-            for (int v = t; v < V; v += TP_THREADS) o[v] = p[v];
-            return;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int v = 4 * (i0 + TP_THREADS * j);
+            f32x4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t key = tp_key(x[j][e]);
+                const bool keep = key > tau || (key == tau && v + e <= cut);
+                float q = tp_divide(x[j][e], Z, rZ);
+                if (keep && (key < 0x3f800000u || key >= 0x4f800000u)) q = __fdiv_rn(x[j][e], Z); // outside its range (a kept token without a weight, or of 1 and more)
+                y[e] = keep ? q : 0.f;
+            }
+            if (VEC && v + 3 < V) {
+                *reinterpret_cast<f32x4 *>(o + v) = y;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (v + e < V) o[v + e] = y[e];
+            }
         }
     }
-    const float Z = __fmul_rn(__ull2float_rn(kept), 2.3283064365386963e-10f);
-    for (int v0 = 0; v0 < V; v0 += TP_UNROLL * TP_THREADS) {
-        float x[TP_UNROLL];
-#pragma unroll
-        for (int e = 0; e < TP_UNROLL; ++e) {
-            const int v = v0 + e * TP_THREADS + t;
-            x[e] = v < V ? p[v] : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < TP_UNROLL; ++e) {
-            const int v = v0 + e * TP_THREADS + t;
-            const uint32_t w = fx_weight32(x[e]);
-            if (v < V) o[v] = (w > prefix || (w == prefix && v <= cut)) ? __fdiv_rn(x[e], Z) : 0.f;
-        }
+}
+template <bool BY_COUNT>
+static void launch_filter(const float *probs, long long ld_in, int rows, int V, unsigned arg, float *out, long long ld_out, hipStream_t st) {
+    if (rows <= 0) return;
+    const bool vec = ((reinterpret_cast<uintptr_t>(probs) | reinterpret_cast<uintptr_t>(out)) & 15) == 0 && (rows == 1 || (ld_in % 4 == 0 && ld_out % 4 == 0));
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(rows), dim3(TP_THREADS), 0, st, probs, ld_in, V, arg, out, ld_out); };
+    if (V <= TP_FITS) {
+        if (vec) go(top_p_filter_kernel<BY_COUNT, true, true>);
+        else go(top_p_filter_kernel<BY_COUNT, false, true>);
+    } else {
+        if (vec) go(top_p_filter_kernel<BY_COUNT, true, false>);
+        else go(top_p_filter_kernel<BY_COUNT, false, false>);
     }
 }
 void launch_top_p_filter(const float *probs, long long ld_in, int rows, int V, unsigned P24, float *out, long long ld_out, hipStream_t st) {
-    if (rows <= 0) return;
-    hipLaunchKernelGGL(top_p_filter_kernel<false>, dim3(rows), dim3(TP_THREADS), 0, st, probs, ld_in, V, P24, out, ld_out);
+    launch_filter<false>(probs, ld_in, rows, V, P24, out, ld_out, st);
 }
 void launch_top_k_filter(const float *probs, long long ld_in, int rows, int V, int k, float *out, long long ld_out, hipStream_t st) {
-    if (rows <= 0) return;
-    hipLaunchKernelGGL(top_p_filter_kernel<true>, dim3(rows), dim3(TP_THREADS), 0, st, probs, ld_in, V, (unsigned)k, out, ld_out);
+    launch_filter<true>(probs, ld_in, rows, V, (unsigned)k, out, ld_out, st);
 }
 
 // ------------------------------------------------------------------ sampling / argmax of plain rows

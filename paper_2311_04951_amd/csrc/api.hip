@@ -1017,14 +1017,14 @@ static int check_accept(const void *p, const void *q, const void *d, const void 
     return SS_OK;
 }
 
-// the rejection step on materialised probabilities; status: device status word, partial: accept_workspace_bytes(B, V) bytes
+// the rejection step on materialised probabilities; status: device status word, partial: `avail` bytes (at least accept_workspace_bytes(B, V))
 static void accept_probs(const float *p, const float *q, const int32_t *d, const float *u, int B, int K, int V, int32_t *na, int32_t *nx,
-                         int32_t *status, unsigned long long *partial, hipStream_t st) {
+                         int32_t *status, unsigned long long *partial, size_t avail, hipStream_t st) {
     AcceptArgs a{};
     a.p = p; a.q = q; a.from_logits = 0; a.inv_t = 1.f;
     a.draft = d; a.u = u; a.B = B; a.K = K; a.V = V;
     a.n_accepted = na; a.next_token = nx; a.status = status;
-    launch_accept(a, partial, st);
+    launch_accept(a, partial, avail, st);
 }
 
 extern "C" int ss_speculative_accept(const float *p_dev, const float *q_dev, const int32_t *draft_tokens_dev,
@@ -1035,7 +1035,7 @@ extern "C" int ss_speculative_accept(const float *p_dev, const float *q_dev, con
     rc = check_ws(ws, ws_bytes, accept_need(batch, vocab), "ss_speculative_accept");
     if (rc) return rc;
     accept_probs(p_dev, q_dev, draft_tokens_dev, uniforms_dev, batch, K, vocab, n_accepted_dev, next_token_dev, (int32_t *)ws,
-                 (unsigned long long *)scr_data(ws), (hipStream_t)stream);
+                 (unsigned long long *)scr_data(ws), ws_bytes - SCR_DATA, (hipStream_t)stream);
     return check_launch();
 }
 
@@ -1071,7 +1071,7 @@ extern "C" int ss_speculative_accept_logits(const float *p_logits_dev, const flo
         stats_rows(p_logits_dev, np, vocab, inv_t, ps, ws, part, st);
         stats_rows(q_logits_dev, nq, vocab, inv_t, qs, ws, part, st);
     }
-    launch_accept(a, partial, st);
+    launch_accept(a, partial, accept_workspace_bytes(batch, vocab), st);
     if (p_out_dev) launch_softmax_write(p_logits_dev, (int)np, vocab, inv_t, ps, p_out_dev, vocab, st);
     if (q_out_dev) launch_softmax_write(q_logits_dev, (int)nq, vocab, inv_t, qs, q_out_dev, vocab, st);
     return check_launch();
@@ -1142,7 +1142,7 @@ extern "C" int ss_speculative_accept_noalloc(const float *p_dev, const float *q_
     // nothing here has to start at zero: every per-segment sum the finish kernel reads is written by this call's first
     // kernel, and the status word only ever accumulates flags
     accept_probs(p_dev, q_dev, draft_tokens_dev, uniforms_dev, batch, K, vocab, n_accepted_dev, next_token_dev,
-                 status_dev ? status_dev : (int32_t *)scratch, (unsigned long long *)((char *)scratch + 256), (hipStream_t)stream);
+                 status_dev ? status_dev : (int32_t *)scratch, (unsigned long long *)((char *)scratch + 256), NOALLOC_SCRATCH_BYTES - 256, (hipStream_t)stream);
     return check_launch();
 }
 

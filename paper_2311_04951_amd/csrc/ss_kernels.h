@@ -142,9 +142,9 @@ struct AcceptArgs {
 // row statistics of the logits entry in stages that skip the positions behind a sequence's first rejection
 // (a.p / a.q are logits, a.p_stats / a.q_stats the arrays written)
 void launch_row_stats_staged(const AcceptArgs &a, float2 *p_stats, float2 *q_stats, unsigned *cnt, float2 *part, hipStream_t st);
-// partial: device workspace of accept_workspace_bytes(B, V) bytes (per-segment weight sums)
+// partial: device workspace of at least accept_workspace_bytes(B, V) bytes (per-segment weight sums), avail: what it has
 size_t accept_workspace_bytes(int B, int V);
-void launch_accept(const AcceptArgs &a, unsigned long long *partial, hipStream_t st);
+void launch_accept(const AcceptArgs &a, unsigned long long *partial, size_t avail, hipStream_t st);
 // scratch: device memory of at least 4 bytes per row (B * (K + 1) rows), 8-byte aligned; more (8 bytes per row and segment) lets a row be cut into segments
 void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, void *scratch, size_t scratch_bytes,
                           int32_t *n_accepted, int32_t *next_token, hipStream_t st);

@@ -98,3 +98,27 @@ def test_speculative_loop_with_top_p(K, top_p):
     assert all(a == K for a in st["accepted"])
     u_ar = np.concatenate([np.concatenate([ud[s], ua[s, K:]]) for s in range(steps)])
     assert same == gen.autoregressive_generate(gt, prompt, steps * (K + 1), 1.0, u_ar, top_p=top_p)
+
+
+@pytest.mark.parametrize("V", [1, 2, 32768, 32769, 70001])      # the longest row that stays on chip, and longer ones
+def test_both_filters_where_the_route_changes_equal_oracle_bit_for_bit(V):
+    """Rows that fit the on-chip copy and rows that don't, aligned and not (a leading dimension of V on an odd offset), with the
+    boundary among a few tokens, among more than are ranked one by one, and among more than the list of candidates holds; with
+    weights of 2^32 (probability 1 and more), of zero, and values that are no probabilities."""
+    rows = oracle.softmax(si.normal(8, f"r{V}", (6, V), 2.0).numpy(), 1.0)
+    rows[1] = np.float32(1.0 / V)                                                # all in one bin, equal
+    rows[2] = (1.0 + np.arange(V, dtype=np.float32) / (64.0 * V)) / V            # all in one or two bins, different
+    rows[3, V // 2:] = 0.0                                                       # half without a weight
+    rows[4, 0] = 1.0
+    rows[4, V // 2] = 3.0                                                        # more than 1
+    rows[5] = -rows[5]
+    rows[5, V - 1] = 0.25
+    arena = torch.zeros(6 * V + 8, device=dev())
+    for at in (0, 1):
+        g = arena[at:at + 6 * V].view(6, V)
+        g.copy_(torch.from_numpy(rows))
+        out = torch.empty_like(arena)[at:at + 6 * V].view(6, V)
+        for top_p in (0.003, 0.5, 0.97):
+            assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p, out).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p, at)
+        for k in sorted({1, max(1, V // 100), max(1, (2 * V) // 3), max(1, V - 1)} - {V}):
+            assert np.array_equal(_bits(sv.ss_top_k_filter(g, k, out).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k, at)
