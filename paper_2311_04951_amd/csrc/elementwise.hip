@@ -29,7 +29,6 @@ __device__ __forceinline__ void store_act4(const ActPlanes<float> &a, size_t off
 // of the norm costs 4 us).  Without a gain that is all (the norm below is the same code in every mode, so a fused launch and
 // the two separate ones give the same bits).
 enum RowMode { ROW_PLAIN, ROW_SPLITK, ROW_EMBED };
-constexpr int SPLITK_MAX = 4; // splits the fused form can sum (the wide GEMM never makes more)
 struct RowSource {
     const float *parts; // ROW_SPLITK
     int ksplit;
@@ -88,27 +87,33 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *h, const
             if (!gain) return;
         }
         if constexpr (MODE == ROW_SPLITK) {
-            // every partial is requested before the first one is used (at most SPLITK_MAX splits)
-            float4 p[MAXV][SPLITK_MAX];
+            // the partials of four splits are requested before the first one is used
+            float4 s4[MAXV];
 #pragma unroll
-            for (int j = 0; j < MAXV; ++j)
+            for (int j = 0; j < MAXV; ++j) s4[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int z0 = 0; z0 < src.ksplit; z0 += 4) {
+                float4 p[MAXV][4];
 #pragma unroll
-                for (int z = 0; z < SPLITK_MAX; ++z) {
-                    const int e4 = threadIdx.x + 256 * j;
-                    p[j][z] = (e4 * 4 < d && z < src.ksplit) ? reinterpret_cast<const float4 *>(src.parts + z * src.part_stride + (size_t)r * d)[e4]
-                                                             : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                for (int j = 0; j < MAXV; ++j)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const int e4 = threadIdx.x + 256 * j;
+                        p[j][z] = (e4 * 4 < d && z0 + z < src.ksplit) ? reinterpret_cast<const float4 *>(src.parts + (z0 + z) * src.part_stride + (size_t)r * d)[e4]
+                                                                      : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+#pragma unroll
+                for (int j = 0; j < MAXV; ++j)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z)
+                        if (z0 + z < src.ksplit) {
+                            s4[j].x += p[j][z].x; s4[j].y += p[j][z].y; s4[j].z += p[j][z].z; s4[j].w += p[j][z].w;
+                        }
+            }
 #pragma unroll
             for (int j = 0; j < MAXV; ++j) {
                 const int e4 = threadIdx.x + 256 * j;
                 if (e4 * 4 < d) {
-                    float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int z = 0; z < SPLITK_MAX; ++z)
-                        if (z < src.ksplit) {
-                            s4.x += p[j][z].x; s4.y += p[j][z].y; s4.z += p[j][z].z; s4.w += p[j][z].w;
-                        }
-                    v[j].x += s4.x; v[j].y += s4.y; v[j].z += s4.z; v[j].w += s4.w;
+                    v[j].x += s4[j].x; v[j].y += s4[j].y; v[j].z += s4[j].z; v[j].w += s4[j].w;
                     reinterpret_cast<float4 *>(src.h_out + (size_t)r * d)[e4] = v[j];
                 }
             }
@@ -183,7 +188,6 @@ void launch_embed_norm(int dtype, const void *embed, const int32_t *tokens, int 
 
 void launch_splitk_resid_norm(int dtype, float *h, const float *parts, int ksplit, const float *gain, int R, int d,
                               float eps, void *act, size_t act_plane, int ld_act, hipStream_t st) {
-    if (ksplit > SPLITK_MAX) abort(); // the caller's split count is bounded by the same constant
     RowSource src{};
     src.parts = parts; src.ksplit = ksplit; src.part_stride = (size_t)R * d; src.h_out = h;
     launch_row_norm<ROW_SPLITK>(dtype, h, gain, R, 0, 1, d, eps, act, act_plane, ld_act, src, st);

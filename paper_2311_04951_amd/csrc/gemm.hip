@@ -90,6 +90,52 @@ template <int EPI> __device__ __forceinline__ void move_lengths(const GemmArgs &
     }
 }
 
+// Rotary embedding and stores of four column pairs (j0 + v, j0 + hd/2 + v) of row m, head h of region 0 q, 1 k, 2 v.
+template <typename T>
+__device__ __forceinline__ void qkv_store(const GemmArgs &a, int m, int region, int h, int j0, float (&x0)[4], float (&x1)[4], int pos, const float2 (&rope)[4]) {
+    const int b = m / a.M;
+    if (region < 2) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float2 cs = rope[v];
+            const float p0 = x0[v] * cs.x - x1[v] * cs.y;
+            const float p1 = x0[v] * cs.y + x1[v] * cs.x;
+            x0[v] = p0;
+            x1[v] = p1;
+        }
+    }
+    if (region == 0) {
+        ActPlanes<T> q{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_act_out};
+        const size_t o = (size_t)m * a.ld_act_out + h * a.hd + j0;
+        store_act_quad(q, o, x0, 4);
+        store_act_quad(q, o + a.hd / 2, x1, 4);
+    } else if (region == 1) {
+        T *kc = reinterpret_cast<T *>(a.kcache) + (((size_t)b * a.H + h) * a.S + pos) * a.hd + j0;
+        store_quad(kc, x0); // (the cache is 16-byte aligned, j0 a multiple of 4)
+        store_quad(kc + a.hd / 2, x1);
+    } else {
+        // values are kept transposed inside blocks of 64 positions: [pos/64][hd][64]
+        T *vc = reinterpret_cast<T *>(a.vcache) + ((size_t)b * a.H + h) * a.S * a.hd + ((size_t)(pos >> 6) * a.hd) * 64 + (pos & 63);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            vc[(size_t)(j0 + v) * 64] = to_storage<T>(x0[v]);
+            vc[(size_t)(j0 + a.hd / 2 + v) * 64] = to_storage<T>(x1[v]);
+        }
+    }
+}
+// ... with the position and the rotary factors read here
+template <typename T>
+__device__ __forceinline__ void qkv_finish_quad(const GemmArgs &a, int m, int region, int h, int j0, float (&x0)[4], float (&x1)[4]) {
+    const int b = m / a.M;
+    int pos = a.len[b] + m - b * a.M;
+    if (pos > a.max_pos - 1) pos = a.max_pos - 1; // host validation keeps these from happening
+    if (pos > a.S - 1) pos = a.S - 1;
+    float2 rope[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) rope[v] = region < 2 ? a.rope[(size_t)pos * (a.hd / 2) + j0 + v] : make_float2(1.f, 0.f);
+    qkv_store<T>(a, m, region, h, j0, x0, x1, pos, rope);
+}
+
 // Epilogue of one output tile by one wave: lane (c, g) holds r[t][v] = the value of row m = rt*16 + c,
 // column n0[t] + 4g + v.  pre: operands fetched ahead by epi_prefetch for this tile and row tile (NULL: read here).
 template <typename T, int EPI>
@@ -101,23 +147,31 @@ __device__ __forceinline__ void apply_epilogue(const GemmArgs &a, const float (&
 
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESID) {
         float hn[4];
+        const size_t o0 = (size_t)m * a.ldo + n0[0] + 4 * g;
+        if (n0[0] + 4 * g + 3 < a.N && a.ldo % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.out) | reinterpret_cast<uintptr_t>(a.resid)) & 15) == 0) {
+            float4 old = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (EPI == EPI_RESID) old = pre ? make_float4(pre->resid[0], pre->resid[1], pre->resid[2], pre->resid[3]) : *reinterpret_cast<const float4 *>(a.resid + o0);
+            hn[0] = EPI == EPI_RESID ? old.x + r[0][0] : r[0][0];
+            hn[1] = EPI == EPI_RESID ? old.y + r[0][1] : r[0][1];
+            hn[2] = EPI == EPI_RESID ? old.z + r[0][2] : r[0][2];
+            hn[3] = EPI == EPI_RESID ? old.w + r[0][3] : r[0][3];
+            *reinterpret_cast<float4 *>(a.out + o0) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int n = n0[0] + 4 * g + v;
-            hn[v] = 0.f;
-            if (n < a.N) {
-                const size_t o = (size_t)m * a.ldo + n;
-                hn[v] = (EPI == EPI_RESID) ? (pre ? pre->resid[v] : a.resid[o]) + r[0][v] : r[0][v];
-                a.out[o] = hn[v];
+            for (int v = 0; v < 4; ++v) {
+                hn[v] = 0.f;
+                if (n0[0] + 4 * g + v < a.N) {
+                    hn[v] = (EPI == EPI_RESID) ? (pre ? pre->resid[v] : a.resid[o0 + v]) + r[0][v] : r[0][v];
+                    a.out[o0 + v] = hn[v];
+                }
             }
         }
         if (EPI == EPI_RESID && a.nsq_out && pre) { // deferred norm: h * gain as planes, the tile's sum of squares per row
             ActPlanes<T> np{reinterpret_cast<T *>(a.norm_act), a.norm_act_plane, a.norm_ld};
+            float y[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int n = n0[0] + 4 * g + v;
-                if (n < a.N) store_act(np, (size_t)m * a.norm_ld + n, hn[v] * pre->gain[v]);
-            }
+            for (int v = 0; v < 4; ++v) y[v] = hn[v] * pre->gain[v];
+            store_act_quad(np, (size_t)m * a.norm_ld + n0[0] + 4 * g, y, a.N - (n0[0] + 4 * g));
             float sq = (hn[0] * hn[0] + hn[1] * hn[1]) + (hn[2] * hn[2] + hn[3] * hn[3]);
             const float s1 = __shfl_xor(sq, 16);
             const float lo = (lane & 16) ? s1 : sq, hi = (lane & 16) ? sq : s1;
@@ -128,71 +182,27 @@ __device__ __forceinline__ void apply_epilogue(const GemmArgs &a, const float (&
         }
     } else if constexpr (EPI == EPI_SWIGLU) {
         ActPlanes<T> z{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_act_out};
+        float y[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int n = n0[0] + 4 * g + v;
-            if (n < a.N) {
-                const float gt = r[0][v], up = r[1][v];
-                const float s = gt / (1.0f + expf(-gt));
-                store_act(z, (size_t)m * a.ld_act_out + n, s * up);
-            }
+            const float gt = r[0][v], up = r[1][v];
+            y[v] = gt / (1.0f + expf(-gt)) * up;
         }
+        store_act_quad(z, (size_t)m * a.ld_act_out + n0[0] + 4 * g, y, a.N - (n0[0] + 4 * g));
     } else { // EPI_QKV
         const int d_all = a.H * a.hd;
         const int region = n0[0] / d_all; // 0 q, 1 k, 2 v
         const int within = n0[0] - region * d_all;
         const int h = within / a.hd;
         const int j0 = within - h * a.hd + 4 * g; // column inside the head (first half)
-        const int b = m / a.M, i = m - b * a.M;
-        int pos;
-        if (pre) {
-            pos = pre->pos;
-        } else {
-            pos = a.len[b] + i;
-            if (pos > a.max_pos - 1) pos = a.max_pos - 1; // host validation keeps these from happening
-            if (pos > a.S - 1) pos = a.S - 1;
-        }
         float x0[4], x1[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             x0[v] = r[0][v];
             x1[v] = r[1][v];
         }
-        if (region < 2) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float2 cs = pre ? pre->rope[v] : a.rope[(size_t)pos * (a.hd / 2) + j0 + v];
-                const float p0 = x0[v] * cs.x - x1[v] * cs.y;
-                const float p1 = x0[v] * cs.y + x1[v] * cs.x;
-                x0[v] = p0;
-                x1[v] = p1;
-            }
-        }
-        if (region == 0) {
-            ActPlanes<T> q{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_act_out};
-            const size_t o = (size_t)m * a.ld_act_out + h * a.hd + j0;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                store_act(q, o + v, x0[v]);
-                store_act(q, o + a.hd / 2 + v, x1[v]);
-            }
-        } else if (region == 1) {
-            T *kc = reinterpret_cast<T *>(a.kcache) + (((size_t)b * a.H + h) * a.S + pos) * a.hd + j0;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                kc[v] = to_storage<T>(x0[v]);
-                kc[a.hd / 2 + v] = to_storage<T>(x1[v]);
-            }
-        } else {
-            // values are kept transposed inside blocks of 64 positions: [pos/64][hd][64]
-            T *vc = reinterpret_cast<T *>(a.vcache) + ((size_t)b * a.H + h) * a.S * a.hd +
-                    ((size_t)(pos >> 6) * a.hd) * 64 + (pos & 63);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                vc[(size_t)(j0 + v) * 64] = to_storage<T>(x0[v]);
-                vc[(size_t)(j0 + a.hd / 2 + v) * 64] = to_storage<T>(x1[v]);
-            }
-        }
+        if (pre) qkv_store<T>(a, m, region, h, j0, x0, x1, pre->pos, pre->rope);
+        else qkv_finish_quad<T>(a, m, region, h, j0, x0, x1);
     }
 }
 
@@ -1075,6 +1085,337 @@ template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wid
     return 0;
 }
 
+// More than 16 rows, bf16 matrices.  A workgroup multiplies BM = 16 * RTW * WR rows (two planes of activations) with 16 * CT columns;
+// both operands of a stage (KBS k-blocks of 32 K entries) come by load-to-LDS instructions, whole 128- or 256-byte pieces of a
+// row, and are read back as operands (16-byte units of a row at position unit xor row: no bank conflicts).  The wavefronts split
+// the rows WR ways, the columns WC ways and the k-blocks of a stage WK ways (their sums meet in LDS at the end), each keeps
+// RTW x CTW tiles in registers: with one column tile per wavefront, as in the kernel below, every 10 - 20 MFMAs cost 10 KB of LDS reads.
+//   What bounds it: a compute unit has about 32 KB of loads in flight whatever the ring in LDS holds (a loads-only build
+// takes 85 - 95 % of the time, deeper rings change nothing), so a launch costs about 16 us per MB of activations and 40 us per MB of
+// weights that one workgroup fetches - 32 KB per round trip to the L2 and to memory.  Hence tiles that are as square as LDS and
+// registers allow, and the choice of tile and split by exactly that sum (launch_tile).
+//   Measured against the column-per-wavefront kernel (7B shape, us): 256 rows gate/up 180 -> 103, QKV 112 -> 71, O 40 -> 21,
+// down 115 -> 48; 72 rows 61 -> 52, 49 -> 45, 22 -> 12 (+ 6 for the second launch), 41 -> 30 (+ 6).
+template <int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int NBUF_> struct TileCfg {
+    static constexpr int RTW = RTW_, CTW = CTW_, WR = WR_, WC = WC_, WK = WK_, KBS = KBS_, NBUF = NBUF_;
+    static constexpr int NW = WR * WC * WK;         // wavefronts
+    static constexpr int BM = 16 * RTW * WR;        // rows
+    static constexpr int CT = CTW * WC;             // 16-column tiles
+    static constexpr int ROWB = 64 * KBS;           // bytes of a row in a stage (KBS k-blocks of 32 entries)
+    static constexpr int UPR = 4 * KBS;             // ... in 16-byte units
+    static constexpr int RPI = 64 / UPR;            // rows per load instruction
+    static constexpr int LROWS = 2 * BM + 16 * CT;  // rows of a stage: two activation planes, then the matrix
+    static constexpr int STAGE = LROWS * ROWB;
+    static constexpr int GROUPS = LROWS / RPI;      // load instructions per stage
+    static constexpr int GMAX = (GROUPS + NW - 1) / NW, GMIN = GROUPS / NW;
+    static_assert(NBUF * STAGE <= 160 * 1024, "LDS");
+};
+
+// A load-to-LDS instruction (16 bytes per lane, from base + off to lds + 16 * lane) that the compiler does not see as one: it
+// would wait for every such load in flight in front of the next LDS read.  It has no register result; whoever reads the data
+// waits for it with wait_vm.
+__device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+__device__ __forceinline__ void stage_barrier() { // ... which no LDS access may cross
+    asm volatile("" ::: "memory");
+    wide_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <int EPI, class C>
+__global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
+    typedef bf16_t T;
+    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
+    constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, NBUF = C::NBUF, NW = C::NW;
+    static_assert(CTW % NT == 0 && KBS % WK == 0 && NBUF <= 3, "");
+    __shared__ __align__(16) unsigned char lds[NBUF * C::STAGE];
+    typedef const unsigned char __attribute__((address_space(3))) *lptr;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr)lds;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int wk = wave % WK, wc = (wave / WK) % C::WC, wr = wave / (WK * C::WC);
+    const int K = a.K;
+    const int row0 = blockIdx.y * C::BM;
+    // first column of output tile `ct` of the workgroup (fused epilogues: tiles 2p and 2p + 1 are the two halves of pair p)
+    const int npairs = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
+    const int nrows_w = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
+    auto tile_col = [&](int ct) {
+        const int p = min((int)blockIdx.x * (C::CT / NT) + ct / NT, npairs - 1), half = ct % NT;
+        if constexpr (EPI == EPI_QKV) {
+            const int per_head = a.hd / 32, hh = p / per_head;
+            return hh * a.hd + (p % per_head) * 16 + half * (a.hd / 2);
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            return p * 16 + half * a.N;
+        } else {
+            return p * 16;
+        }
+    };
+    const int nst_all = (K + 32 * KBS - 1) / (32 * KBS);
+    const int s_lo = a.ksplit > 1 ? blockIdx.z * a.kslabs : 0;
+    const int nst = (a.ksplit > 1 ? min(s_lo + a.kslabs, nst_all) : nst_all) - s_lo;
+    const int rot = a.rotate ? k_rotation(nst) : 0; // (see the launcher)
+    auto stage_at = [&](int s) { return s_lo + rotated(s, rot, nst); };
+
+    // this wave's load instructions of a stage: group wave + i * NW; lane l brings unit (l % UPR) xor row of row l / UPR
+    const char *base[C::GMAX];
+    uint32_t voff[C::GMAX];
+    const int lr = lane / C::UPR, lu = lane % C::UPR;
+#pragma unroll
+    for (int i = 0; i < C::GMAX; ++i) {
+        const int grp = min(wave + i * NW, C::GROUPS - 1);
+        const int r0 = grp * C::RPI, row = r0 + lr;
+        if (r0 < 2 * C::BM) {
+            const int pl = r0 / C::BM, r = row - pl * C::BM;
+            base[i] = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + pl * a.act_plane + (size_t)min(row0, a.R - 1) * a.ld_act);
+            voff[i] = (uint32_t)(min(row0 + r, a.R - 1) - min(row0, a.R - 1)) * (uint32_t)a.ld_act * 2u;
+        } else {
+            const int wrow0 = r0 - 2 * C::BM, ct = wrow0 / 16, n0 = tile_col(ct);
+            const int n = min(n0 + (wrow0 & 15) + lr, nrows_w - 1);
+            base[i] = reinterpret_cast<const char *>(a.W) + (size_t)n0 * K * 2;
+            voff[i] = (uint32_t)(n - n0) * (uint32_t)K * 2u;
+        }
+        voff[i] += (uint32_t)(lu ^ (row & (C::UPR - 1))) * 16u;
+    }
+    const bool ragged = K % (32 * KBS) != 0;
+    auto issue = [&](int s, int buf) {
+        const int st = stage_at(s);
+        const uint32_t to = lds0 + buf * C::STAGE + wave * 1024;
+        const size_t kb = (size_t)st * C::ROWB;
+        if (ragged && st == nst_all - 1) { // units past K repeat the row's last one (their weights are zeroed when used)
+#pragma unroll
+            for (int i = 0; i < C::GMAX; ++i)
+                if (i < C::GMIN || wave + i * NW < C::GROUPS) {
+                    const int row = (wave + i * NW) * C::RPI + lr, u = lu ^ (row & (C::UPR - 1));
+                    dma16(base[i] + kb, voff[i] - 2u * (uint32_t)max(st * 32 * KBS + u * 8 - (K - 8), 0), to + i * NW * 1024);
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < C::GMAX; ++i)
+                if (i < C::GMIN || wave + i * NW < C::GROUPS) {
+                    dma16(base[i] + kb, voff[i], to + i * NW * 1024);
+                }
+        }
+    };
+    f32x4 acc[RTW][CTW];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+        for (int t = 0; t < CTW; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // operand offsets in a stage (the xor only touches the low bits of the row, which is c's for every tile)
+    auto step = [&](int s, int bcur, int bfill) {
+        const unsigned char *cur = lds + bcur * C::STAGE;
+        // stages s + 1 .. of what was issued may still be in flight
+        const int ahead = min(NBUF - 2, nst - 1 - s);
+        if (C::GMAX == C::GMIN || wave < C::GROUPS % NW) {
+            if (NBUF > 2 && ahead) wait_vmcnt_at_most<C::GMAX>();
+            else wait_vmcnt_at_most<0>();
+        } else {
+            if (NBUF > 2 && ahead) wait_vmcnt_at_most<C::GMIN>();
+            else wait_vmcnt_at_most<0>();
+        }
+        stage_barrier(); // everybody's part of the stage has landed, and everybody is done reading the one that is filled next
+        if (s + NBUF - 1 < nst) issue(s + NBUF - 1, bfill);
+        const int st = stage_at(s);
+#pragma unroll
+        for (int kk = 0; kk < KBS / WK; ++kk) {
+            const int kb = wk * (KBS / WK) + kk;
+            const int un = ((4 * kb + g) ^ (c & (C::UPR - 1))) * 16;
+            u32x4 w[CTW], b[RTW][2];
+#pragma unroll
+            for (int t = 0; t < CTW; ++t) w[t] = *reinterpret_cast<const u32x4 *>(cur + (2 * C::BM + (wc * CTW + t) * 16 + c) * C::ROWB + un);
+#pragma unroll
+            for (int r = 0; r < RTW; ++r)
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl) b[r][pl] = *reinterpret_cast<const u32x4 *>(cur + (pl * C::BM + (wr * RTW + r) * 16 + c) * C::ROWB + un);
+            if (ragged && st == nst_all - 1 && st * 32 * KBS + kb * 32 + g * 8 >= K) {
+#pragma unroll
+                for (int t = 0; t < CTW; ++t) w[t] = zero16();
+            }
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int r = 0; r < RTW; ++r)
+#pragma unroll
+                    for (int t = 0; t < CTW; ++t)
+                        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, b[r][pl]), acc[r][t], 0, 0, 0);
+        }
+    };
+    issue(0, 0);
+    if (NBUF > 2 && nst > 1) issue(1, 1);
+    for (int s = 0, bc = 0; s < nst; ++s) {
+        step(s, bc, bc == 0 ? NBUF - 1 : bc - 1);
+        bc = bc == NBUF - 1 ? 0 : bc + 1;
+    }
+
+    auto finish = [&](const float (&out)[NT][4], int r, int p) { // row tile r and column tile (pair) p of the workgroup
+        const int ct = p * NT;
+        if ((int)blockIdx.x * (C::CT / NT) + p >= npairs) return;
+        int n0[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) n0[t] = tile_col(ct + t);
+        const int m = row0 + r * 16 + c;
+        if ((EPI == EPI_RESID || EPI == EPI_QKV) && a.ksplit > 1) { // plain rows [split][R][N]: the launch that follows works row by row
+            if (m < a.R) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    *reinterpret_cast<float4 *>(a.splitk_ws + ((size_t)blockIdx.z * a.R + m) * a.N + n0[t] + 4 * g) = make_float4(out[t][0], out[t][1], out[t][2], out[t][3]);
+            }
+        } else {
+            apply_epilogue<T, EPI>(a, out, n0, row0 / 16 + r);
+        }
+    };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int r = 0; r < RTW; ++r)
+#pragma unroll
+            for (int p = 0; p < CTW / NT; ++p) {
+                float out[NT][4];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) out[t][v] = acc[r][p * NT + t][v];
+                finish(out, wr * RTW + r, wc * (CTW / NT) + p);
+            }
+    } else {
+        // the K shares of a tile are summed in order through LDS, a row tile at a time in alternating buffers
+        static_assert(NW * CTW * 1024 <= C::STAGE, "");
+#pragma unroll
+        for (int r = 0; r < RTW; ++r) {
+            float *red = reinterpret_cast<float *>(lds + (r & 1) * C::STAGE);
+            if (r == 0) stage_barrier(); // nobody reads the stages any more
+#pragma unroll
+            for (int t = 0; t < CTW; ++t) *reinterpret_cast<f32x4 *>(red + ((size_t)(wave * CTW + t) * 64 + lane) * 4) = acc[r][t];
+            stage_barrier();
+#pragma unroll
+            for (int p = 0; p < CTW / NT; ++p)
+                if (p % WK == wk) {
+                    float out[NT][4];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int k2 = 0; k2 < WK; ++k2)
+                            sum += *reinterpret_cast<const f32x4 *>(red + ((size_t)((wave - wk + k2) * CTW + p * NT + t) * 64 + lane) * 4);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) out[t][v] = sum[v];
+                    }
+                    finish(out, wr * RTW + r, wc * (CTW / NT) + p);
+                }
+        }
+    }
+    move_lengths<EPI>(a);
+}
+
+// Second launch of a split QKV projection: four column pairs of a row per thread, the splits added in order.  A workgroup takes 16
+// rows x 16 quads, neighbouring lanes neighbouring rows: a value column of the cache has its positions side by side, two bytes
+// each (a row per workgroup wrote every one of them to a line of its own: 72 rows 10.6 -> 8.1 us, 256 rows 19 -> 15).
+// grid (rows / 16, quads / 16)
+__global__ __launch_bounds__(256) void qkv_finish_kernel(GemmArgs a) {
+    const int m = blockIdx.x * 16 + (threadIdx.x & 15), half = a.hd / 2, quads = half / 4; // quads of pairs per head
+    const int i = blockIdx.y * 16 + (threadIdx.x >> 4), hh = i / quads;
+    if (hh >= 3 * a.H || m >= a.R) return;
+    const int j0 = 4 * (i - hh * quads);
+    const float *p = a.splitk_ws + (size_t)m * a.N + hh * a.hd + j0;
+    float4 lo[4], hi[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) { // (all requested before the first is used; at most four splits)
+        const size_t at = (size_t)min(z, a.ksplit - 1) * a.R * a.N;
+        lo[z] = *reinterpret_cast<const float4 *>(p + at);
+        hi[z] = *reinterpret_cast<const float4 *>(p + at + half);
+    }
+    float x0[4] = {lo[0].x, lo[0].y, lo[0].z, lo[0].w}, x1[4] = {hi[0].x, hi[0].y, hi[0].z, hi[0].w};
+#pragma unroll
+    for (int z = 1; z < 4; ++z)
+        if (z < a.ksplit) {
+            x0[0] += lo[z].x; x0[1] += lo[z].y; x0[2] += lo[z].z; x0[3] += lo[z].w;
+            x1[0] += hi[z].x; x1[1] += hi[z].y; x1[2] += hi[z].z; x1[3] += hi[z].w;
+        }
+    qkv_finish_quad<bf16_t>(a, m, hh / a.H, hh % a.H, j0, x0, x1);
+}
+
+// Which tile and which split of K: the least of  rounds * K share * (16 us/MB * activations + 40 us/MB * weights)  over the
+// shapes there are (see gemm_tile_kernel; within 15 % of what every 7B-shaped matrix takes at 72 and 256 rows), where a second
+// row block on the chip reads the same weights from the L2 (34 on average).  A split adds its partial rows, written and read
+// once (8 MB/us), and for QKV a launch (4.5 us; a residual projection's is the RMSNorm that follows anyway).
+struct TileChoice {
+    int cols, ksplit;
+    double us;
+};
+static TileChoice tile_cost(int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
+    const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols;
+    const int rounds = (gx * gy * ksplit + 255) / 256;
+    const double per = bm * 4 * 16e-6 + cols * 2 * (gy > 1 ? 34e-6 : 40e-6);
+    return TileChoice{cols, ksplit, rounds * (double)((K + ksplit - 1) / ksplit) * per + (ksplit > 1 ? launch_us + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
+}
+
+template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int columns, int ksplit, hipStream_t st) {
+    GemmArgs a = a0;
+    const int nst = (a.K + 32 * C::KBS - 1) / (32 * C::KBS);
+    a.kslabs = (nst + ksplit - 1) / ksplit;
+    a.ksplit = (nst + a.kslabs - 1) / a.kslabs; // no empty split
+    // Workgroups that start at different places of K (k_rotation) do not meet in one memory channel where the rows of the matrix
+    // lie a multiple of 4 KB apart (72 rows, gate/up 54 us against 59), but share no activations in the L2 at a time: not where
+    // those of a pass over K are too many to stay there (256 rows of K 11008: 69 us with, 48 without), and for nothing where the
+    // rows lie otherwise (72 rows of K 11008: 33 with, 31 without)
+    a.rotate = a.K % 2048 == 0 && (size_t)a.R * a.K * 4 / a.ksplit <= (size_t)3 << 19;
+    hipLaunchKernelGGL((gemm_tile_kernel<EPI, C>), dim3((columns + 16 * C::CT - 1) / (16 * C::CT), (a.R + C::BM - 1) / C::BM, a.ksplit), dim3(C::NW * 64), 0, st, a);
+    if (a.ksplit == 1) return 0;
+    if constexpr (EPI == EPI_QKV) {
+        hipLaunchKernelGGL(qkv_finish_kernel, dim3((a.R + 15) / 16, (3 * a.H * (a.hd / 8) + 15) / 16), dim3(256), 0, st, a);
+        return 0;
+    }
+    launch_splitk_resid_norm(1, a.out, a.splitk_ws, a.ksplit, a.norm_gain, a.R, a.N, a.norm_eps, a.norm_act, a.norm_act_plane, a.norm_ld, st);
+    return a.norm_gain != nullptr ? 1 : 0;
+}
+
+template <int EPI, int RT> static int launch_tile_rows(const GemmArgs &a, int columns, const TileChoice &c, hipStream_t st) {
+    if constexpr (RT == 8) {
+        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+            if (c.cols == 192) return launch_tile_as<EPI, TileCfg<4, 6, 2, 2, 2, 2, 2>>(a, columns, c.ksplit, st);
+            return launch_tile_as<EPI, TileCfg<4, 6, 2, 1, 2, 2, 3>>(a, columns, c.ksplit, st);
+        } else {
+            if (c.cols == 128) return launch_tile_as<EPI, TileCfg<4, 4, 2, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
+            return launch_tile_as<EPI, TileCfg<4, 4, 2, 1, 2, 2, 3>>(a, columns, c.ksplit, st);
+        }
+    } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+        if (c.cols == 192) return launch_tile_as<EPI, TileCfg<RT, 6, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
+        if (c.cols == 96) return launch_tile_as<EPI, TileCfg<RT, 6, 1, 1, 4, 4, 2>>(a, columns, c.ksplit, st);
+        return launch_tile_as<EPI, TileCfg<RT, 4, 1, 1, 4, 4, 2>>(a, columns, c.ksplit, st);
+    } else {
+        if (c.cols == 128) return launch_tile_as<EPI, TileCfg<RT, 4, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
+        return launch_tile_as<EPI, TileCfg<RT, 2, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
+    }
+}
+
+// tiles: 16-column tiles (pairs of them for the fused epilogues)
+template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStream_t st) {
+    constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV;
+    const int columns = 16 * tiles * (FUSED ? 2 : 1);
+    // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80, where that pads less
+    const int p80 = (a.R + 79) / 80 * 80, p128 = (a.R + 127) / 128 * 128;
+    const int bm = a.R <= 32 ? 32 : a.R <= 48 ? 48 : (a.R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
+    // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
+    const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
+    const int narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
+    TileChoice best{0, 1, 1e30};
+    for (int i = 0; i < (FUSED ? 3 : 2); ++i) {
+        const int cols = FUSED ? narrow[i] : plain[i];
+        if (bm == 128 && cols == 64 && FUSED) continue;
+        for (int ks = 1; ks <= (split_ok ? (EPI == EPI_QKV ? 4 : 8) : 1); ++ks) {
+            if (ks > 1 && sizeof(float) * (size_t)ks * a.R * a.N > a.splitk_ws_bytes) break;
+            const TileChoice c = tile_cost(bm, cols, columns, a.R, a.K, ks, EPI == EPI_QKV ? 4.5 : 0.0);
+            if (c.us < best.us) best = c;
+        }
+    }
+    if (bm == 32) return launch_tile_rows<EPI, 2>(a, columns, best, st);
+    if (bm == 48) return launch_tile_rows<EPI, 3>(a, columns, best, st);
+    if (bm == 80) return launch_tile_rows<EPI, 5>(a, columns, best, st);
+    return launch_tile_rows<EPI, 8>(a, columns, best, st);
+}
+
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);
 
 template <typename T, int EPI, int NW, int U> static void launch_narrow(const GemmArgs &a, int tiles, hipStream_t st) {
@@ -1096,7 +1437,8 @@ template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipSt
         else launch_narrow<T, EPI, 8, 2>(a, tiles, st);
         return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
     }
-    return launch_wide_any<T, EPI, 0>(a, tiles, row_tiles, st);
+    if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI>(a, tiles, st);
+    else return launch_wide_any<T, EPI, 0>(a, tiles, row_tiles, st);
 }
 
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {

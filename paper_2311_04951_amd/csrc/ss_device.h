@@ -109,6 +109,35 @@ __device__ __forceinline__ void store_act(const ActPlanes<bf16_t> &a, size_t off
 }
 __device__ __forceinline__ void store_act(const ActPlanes<float> &a, size_t off, float x) { a.base[off] = x; }
 
+// four consecutive elements as one store (8 bytes of bf16, 16 of fp32; p aligned accordingly)
+__device__ __forceinline__ void store_quad(bf16_t *p, const float (&x)[4]) {
+    *reinterpret_cast<uint2 *>(p) = make_uint2(bf16_rne(x[0]) | (bf16_rne(x[1]) << 16), bf16_rne(x[2]) | (bf16_rne(x[3]) << 16));
+}
+__device__ __forceinline__ void store_quad(float *p, const float (&x)[4]) { *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]); }
+// activation values of four consecutive columns, the first `live` of which exist; one store per plane where the planes allow
+__device__ __forceinline__ void store_act_quad(const ActPlanes<bf16_t> &a, size_t off, const float (&x)[4], int live) {
+    if (live >= 4 && a.ld % 4 == 0 && a.plane % 4 == 0 && (reinterpret_cast<uintptr_t>(a.base) & 7) == 0 && off % 4 == 0) {
+        float lo[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lo[v] = x[v] - bf16_bits_to_f32(bf16_rne(x[v]));
+        store_quad(a.base + off, x);
+        store_quad(a.base + a.plane + off, lo);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v < live) store_act(a, off + v, x[v]);
+    }
+}
+__device__ __forceinline__ void store_act_quad(const ActPlanes<float> &a, size_t off, const float (&x)[4], int live) {
+    if (live >= 4 && a.ld % 4 == 0 && (reinterpret_cast<uintptr_t>(a.base) & 15) == 0 && off % 4 == 0) {
+        store_quad(a.base + off, x);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v < live) store_act(a, off + v, x[v]);
+    }
+}
+
 // pack E fp32 values held by one lane into the activation operand of a k-block
 __device__ __forceinline__ Act<bf16_t> pack_act(const float (&x)[8], bf16_t) {
     Act<bf16_t> r;
