@@ -215,6 +215,52 @@ __device__ __forceinline__ int rotated(int i, int rot, int nst) {
     return i >= nst ? i - nst : i;
 }
 
+typedef const unsigned char __attribute__((address_space(3))) *lds_ptr;
+__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(lds_ptr)p; }
+// A load-to-LDS instruction (16 bytes per lane, from base + off to lds + 16 * lane) that the compiler does not see as one: it
+// would wait for every such load in flight in front of the next LDS read.  It has no register result; whoever reads the data
+// waits for it with counted waits (such loads return in order with the wavefront's other loads).
+// STREAM: the non-temporal bit, for weight lines, which are used once (the activation lines by every workgroup): 7B-shaped bf16 pass
+// 3.04 -> 2.85 ms at 5 rows, 2.97 -> 2.75 at 1 row (int8 -3.6 %, int4 -2.5 %); the scope bits on top of it change nothing.
+template <bool STREAM = false> __device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+__device__ __forceinline__ void dma4(const void *base, uint32_t off, uint32_t lds) { // the same, a word per lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_waitcnt vmcnt(N), N < 64
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+template <int N> __device__ __forceinline__ void wait_per(int per) { // N steps of `per` loads (of more than 12: waits for some of them as well)
+    switch (per) {
+    case 2: wait_vmcnt_at_most<2 * N>(); break;
+    case 3: wait_vmcnt_at_most<3 * N>(); break;
+    case 4: wait_vmcnt_at_most<4 * N>(); break;
+    case 5: wait_vmcnt_at_most<5 * N>(); break;
+    case 6: wait_vmcnt_at_most<6 * N>(); break;
+    case 7: wait_vmcnt_at_most<7 * N>(); break;
+    case 8: wait_vmcnt_at_most<8 * N>(); break;
+    case 9: wait_vmcnt_at_most<9 * N>(); break;
+    case 10: wait_vmcnt_at_most<10 * N>(); break;
+    case 11: wait_vmcnt_at_most<11 * N>(); break;
+    default: wait_vmcnt_at_most<12 * N>(); break;
+    }
+}
+// Waits until at most `ahead` steps of `per` loads each (per >= 2) are in flight; AHEAD: the most steps asked for.
+template <int AHEAD> __device__ __forceinline__ void wait_steps(int ahead, int per) {
+    if (ahead <= 0) {
+        wait_vmcnt_at_most<0>();
+    } else {
+        if (AHEAD >= 3 && ahead >= 3) { wait_per<3>(per); }
+        else if (AHEAD >= 2 && ahead >= 2) { wait_per<2>(per); }
+        else { wait_per<1>(per); }
+    }
+    asm volatile("" ::: "memory");
+}
+
 // Activations of the kernels for at most 16 rows, through a wave-private piece of LDS.  A step of a wave is UPS units
 // of 16 bytes of K for every row and plane: PL * R * UPS pieces.  Loaded per lane into MFMA operand layout that is
 // 2 * PL * UPS / 8 load instructions with R / 16 of their lanes active; instead ceil(PL * R * UPS / 64) full-width
@@ -227,10 +273,9 @@ template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most ro
     static constexpr int NDMA = (PL * RCAP * UPS + 63) / 64; // instructions that bring a step at RCAP rows
     static constexpr int SLOTS = NDMA * 64;                   // ... and the slots they fill
     static constexpr int BYTES = (SLOTS + 1) * 16; // LDS of one step of one wave (the last slot holds zeros)
-    typedef const void __attribute__((address_space(1))) *gptr;
-    typedef void __attribute__((address_space(3))) *lptr;
-    const T *src[NDMA]; // the row (and plane) of this lane's piece of instruction i
-    int ucol[NDMA];     // ... and its first K element inside the step
+    uint32_t off[NDMA]; // byte offset in the planes of this lane's piece of instruction i in the step at K = 0
+    int ucol[NDMA];     // its first K element inside the step
+    const char *base;
     int rows, npiece, kmax;
 
     // row0: first row of the tile; K: reduction length (a multiple of EPU)
@@ -238,37 +283,55 @@ template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most ro
         rows = min(a.R - row0, RCAP);
         npiece = PL * rows * UPS;
         kmax = K - EPU;
+        base = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + (size_t)row0 * a.ld_act);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
             const int p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
             const int plane = p / (rows * UPS), rem = p - plane * rows * UPS, row = rem / UPS, pos = rem % UPS;
-            src[i] = reinterpret_cast<const T *>(a.act) + (size_t)plane * a.act_plane + (size_t)(row0 + row) * a.ld_act;
             ucol[i] = (pos ^ (row & (UPS - 1))) * EPU;
+            off[i] = (uint32_t)((plane * a.act_plane + (size_t)row * a.ld_act + ucol[i]) * sizeof(T));
         }
     }
     __device__ __forceinline__ static void clear(unsigned char *region, int lane) {
         if (lane == 0) *reinterpret_cast<u32x4 *>(region + SLOTS * 16) = zero16();
     }
-    // asks for the step that starts at K element k0 (columns past the end are clamped to the row's last unit: the
-    // weights there are zero, so any finite value does)
-    __device__ __forceinline__ void request(unsigned char *region, int k0) const {
+    __device__ __forceinline__ int loads() const { return (npiece + 63) / 64; } // instructions of a step
+    // asks for the step that starts at K element k0, to LDS address `to`.  tail: the step ends inside its units: columns past the end
+    // are clamped to the row's last unit (the weights there are zero, so any finite value does)
+    __device__ __forceinline__ void request(uint32_t to, int k0, bool tail) const {
+        const char *b = base + (size_t)k0 * sizeof(T);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i)
-            if (i * 64 < npiece) __builtin_amdgcn_global_load_lds((gptr)(src[i] + min(k0 + ucol[i], kmax)), (lptr)(region + i * 1024), 16, 0, 0);
+            if (i * 64 < npiece) dma16(b, tail ? off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)) : off[i], to + i * 1024);
     }
     // byte offset in a step's region of row c's unit `unit` of plane pl
     __device__ __forceinline__ int operand_offset(int c, int unit, int pl) const {
         return c < rows ? ((pl * rows + c) * UPS + (unit ^ (c & (UPS - 1)))) * 16 : SLOTS * 16;
     }
 };
-// cache policy of the weight loads (the non-temporal bit of a load-to-LDS instruction): a weight line is used once,
-// the activation lines by every workgroup.  Measured on the 7B-shaped bf16 pass: 3.04 -> 2.85 ms at 5 rows,
-// 2.97 -> 2.75 at 1 row (int8 -3.6 %, int4 -2.5 %); the scope bits on top of it change nothing.
-constexpr int WEIGHT_STREAM = 2;
-// every load of the wave has landed (in registers or in LDS); the compiler may not move LDS reads above
-__device__ __forceinline__ void act_stage_wait() {
-    __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0)
-    asm volatile("" ::: "memory");
+// A wavefront's steps of K: every NW-th of nst, through a ring of NB buffers of its own.  request(i, buffer) asks for its i-th step,
+// use(i, buffer) multiplies it; between them the step's loads are waited for, the NB - 1 younger steps stay in flight.  `per`: loads
+// of a step.  prologue() runs behind the first requests.
+template <int NB, class Request, class Use, class Prologue>
+__device__ __forceinline__ void ring_walk(int n, int per, Request request, Use use, Prologue prologue) {
+    constexpr int AHEAD = NB > 1 ? NB - 1 : 1; // steps requested in front of the first
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+        if (i < n) request(i, i);
+    prologue();
+    for (int i = 0, buf = 0; i < n; ++i) {
+        if (NB > 1 && i + NB - 1 < n) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // what was read from the buffer that is filled now has arrived
+            request(i + NB - 1, buf == 0 ? NB - 1 : buf - 1);
+        }
+        wait_steps<NB - 1>(NB > 1 ? min(NB - 1, n - 1 - i) : 0, per);
+        use(i, buf);
+        if (NB == 1 && i + 1 < n) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            request(i + 1, 0);
+        }
+        buf = buf == NB - 1 ? 0 : buf + 1;
+    }
 }
 
 // Sum of the waves' partial tiles of row tile rt (fixed order) and the epilogue, by one wave.
@@ -291,8 +354,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, const float (&r
     apply_epilogue<T, EPI>(a, r, n0, rt, pre);
 }
 
-// The kernel for at most 16 rows: NW = wavefronts per workgroup (interleaved over K), U = 128-byte steps in flight per
-// wave, RCAP = most rows (8 or 16: sizes the LDS); blockIdx.x = column tile (pair), blockIdx.y = row tile.
+// The kernel for at most 16 rows: NW = wavefronts per workgroup (interleaved over K), NB = buffers of a wavefront's ring of 128-byte
+// steps, RCAP = most rows (8 or 16: sizes the LDS); blockIdx.x = column tile (pair), blockIdx.y = row tile.
 // The weights go through LDS like the activations: loaded straight into MFMA operand layout, a load instruction takes
 // 64 bytes of each of 16 weight rows (four lanes per row), i.e. half a cache line per row; a load-to-LDS instruction
 // whose lane l brings unit l & 7 of row l >> 3 takes whole 128-byte lines of 8 rows, and two of them bring a step's
@@ -300,11 +363,11 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, const float (&r
 // on the 7B-shaped layer: 5-row pass 3.28 -> 3.05 ms, 1 row 3.09 -> 2.99 (requests of whole lines are what counts:
 // timing-only variants with a tile-major weight order gained 6 % with a contiguous kilobyte per instruction and
 // nothing with half lines).
-template <typename T, int EPI, int NW, int U, int RCAP>
+template <typename T, int EPI, int NW, int NB, int RCAP>
 __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     constexpr int E = Traits<T>::E, KB = 4 * E, EPU = 16 / (int)sizeof(T);
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int rt = blockIdx.y;
     const int K = a.K;
@@ -325,14 +388,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
 
     // this lane's pieces of a weight step: instruction i brings rows 8i .. 8i + 7 of the tile, lane l unit
     // (l & 7) xor (row & 7) of row 8i + (l >> 3), into slot 64 i + l = row * 8 + (l & 7)
-    const T *W = reinterpret_cast<const T *>(a.W);
-    const T *wsrc[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) wsrc[t][i] = W + (size_t)min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) * K; // ragged last tile: a valid row, masked at the store
     const int wucol = ((lane & 7) ^ (lane >> 3)) * EPU;
-    const int kmax = K - EPU;
+    const char *wbase[NT];
+    uint32_t woff[NT][2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        wbase[t] = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.W) + (size_t)n0[t] * K);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) // ragged last tile: a valid row, masked at the store
+            woff[t][i] = ((uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)K + wucol) * (uint32_t)sizeof(T);
+    }
 
     f32x4 acc[NT];
 #pragma unroll
@@ -340,16 +405,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
     EpiPre pre;
     if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, rt, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave up front
+    // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave from sums that are
+    // asked for in front of the first steps and used behind their request (one memory round trip less than ahead of them)
     float rs = 1.0f;
-    if (a.act_nsq && wave == 0) {
-        float4 nsq[NSQ4];
-        nsq_prefetch(a, rt, nsq);
-        rs = deferred_row_scale(a, nsq);
-    }
+    float4 nsq[NSQ4];
+    const bool scaled = a.act_nsq && wave == 0;
+    if (scaled) nsq_prefetch(a, rt, nsq);
 
-    // Each wave takes 128-byte steps (two k-blocks) of every row, interleaved with the other waves, U steps per
-    // iteration: all their loads are in flight before the first MFMA.
+    // Each wave takes 128-byte steps (two k-blocks) of every row, interleaved with the other waves.
     // Every workgroup starts at another place of K and wraps around (k_rotation): with all of them walking K in step,
     // the loads of a moment differ by multiples of the row stride and meet in the same memory channels, and all ask
     // for the same activation lines (measured on the 7B-shaped layer: 6 % of the 5-row pass, QKV 33.3 -> 29.7 us).
@@ -358,10 +421,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     const int rot = k_rotation(nst);
     const bool ragged = (K % (2 * KB)) != 0; // the last step ends inside its 128 bytes
     typedef ActStage<T, 8, RCAP> Stage;
-    constexpr int WBYTES = NT * 2048;
-    __shared__ __align__(16) unsigned char lds[NW][U][WBYTES + Stage::BYTES];
-    typedef const void __attribute__((address_space(1))) *gptr;
-    typedef void __attribute__((address_space(3))) *lptr;
+    constexpr int WBYTES = NT * 2048, SBYTES = WBYTES + Stage::BYTES;
+    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     Stage stage;
     stage.init(a, rt * 16, K, lane);
     int rdw[2], rda[2][Stage::PL];
@@ -372,36 +433,36 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
         for (int pl = 0; pl < Stage::PL; ++pl) rda[j][pl] = WBYTES + stage.operand_offset(c, 4 * j + g, pl);
     }
 #pragma unroll
-    for (int s = 0; s < U; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    for (int kp = wave; kp < nst; kp += U * NW) {
+    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
+    const uint32_t lds0 = lds_address(lds[wave][0]);
+    const int n = wave < nst ? (nst - wave + NW - 1) / NW : 0;
+    ring_walk<NB>(
+        n, 2 * NT + stage.loads(),
+        [&](int i, int buf) {
+            const int st = rotated(wave + i * NW, rot, nst), k0 = 2 * st * KB;
+            const bool tail = ragged && st == nst - 1;
+            const uint32_t to = lds0 + buf * SBYTES;
+            const uint32_t over = tail ? (uint32_t)(max(k0 + wucol - (K - EPU), 0) * (int)sizeof(T)) : 0u; // past a ragged end: the row's last unit, zeroed after the read
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (kp + s * NW < nst) { // (the same for the whole wave)
-                const int k0 = 2 * rotated(kp + s * NW, rot, nst) * KB;
-                const int kw = min(k0 + wucol, kmax); // past a ragged end: the row's last unit, zeroed after the read
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + (size_t)k0 * sizeof(T), woff[t][j] - over, to + t * 2048 + j * 1024);
+            stage.request(to + WBYTES, k0, tail);
+        },
+        [&](int i, int buf) {
+            const unsigned char *cur = lds[wave][buf];
+            u32x4 w[NT][2];
+            Act<T> av[2];
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        __builtin_amdgcn_global_load_lds((gptr)(wsrc[t][i] + kw), (lptr)(lds[wave][s] + t * 2048 + i * 1024), 16, 0, WEIGHT_STREAM);
-                stage.request(lds[wave][s] + WBYTES, k0);
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) w[t][j] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[j]);
+#pragma unroll
+                for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + rda[j][pl]);
             }
-        }
-        act_stage_wait();
-#pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (kp + s * NW < nst) {
-                const int st = rotated(kp + s * NW, rot, nst);
-                u32x4 w[NT][2];
-                Act<T> av[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) w[t][j] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + t * 2048 + rdw[j]);
-#pragma unroll
-                    for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + rda[j][pl]);
-                }
-                if (ragged && st == nst - 1) {
+            if (ragged) {
+                const int st = rotated(wave + i * NW, rot, nst);
+                if (st == nst - 1) {
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
                         if ((2 * st + j) * KB + g * E >= K) {
@@ -409,14 +470,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
                             for (int t = 0; t < NT; ++t) w[t][j] = zero16();
                         }
                 }
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w[t][j], av[j]);
             }
-        }
-        asm volatile("" ::: "memory"); // the reads stay above the next requests
-    }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w[t][j], av[j]);
+        },
+        [&] {
+            if (scaled) rs = deferred_row_scale(a, nsq);
+        });
 
     // fixed-order sum of the waves' partial tiles; wave 0 applies the epilogue
     __shared__ float red[NW][NT][4][64];
@@ -445,11 +507,11 @@ __device__ __forceinline__ u32x4 w8_to_bf16x8(uint32_t a, uint32_t b) {
     return u32x4{w8_pair_to_bf16x2(a, 0), w8_pair_to_bf16x2(a, 2), w8_pair_to_bf16x2(b, 0), w8_pair_to_bf16x2(b, 2)};
 }
 
-template <int EPI, int NW, int U, int RCAP>
+template <int EPI, int NW, int NB, int RCAP>
 __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int K = a.K;
 
@@ -469,14 +531,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
 
     // a step is 128 entries of K, a whole 128-byte line of every weight row; as in gemm_kernel the tile's 16 x 128 bytes
     // come through LDS by two load-to-LDS instructions (lane l: unit (l & 7) xor (row & 7) of row 8i + (l >> 3))
-    const int8_t *W = reinterpret_cast<const int8_t *>(a.W);
-    const int8_t *wsrc[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) wsrc[t][i] = W + (size_t)min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) * K; // ragged last tile: a valid row, masked at the store
     const int wucol = ((lane & 7) ^ (lane >> 3)) * 16;
-    const int kmax = K - 16; // K is a multiple of 16
+    const char *wbase[NT];
+    uint32_t woff[NT][2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        wbase[t] = reinterpret_cast<const char *>(a.W) + (size_t)n0[t] * K;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) woff[t][i] = (uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)K + wucol; // ragged last tile: a valid row, masked at the store
+    }
 
     f32x4 acc[NT];
 #pragma unroll
@@ -484,13 +547,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
     constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
     EpiPre pre;
     if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, 0, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave up front
+    // the row scale of a deferred norm on the activations (1 otherwise): see gemm_kernel
     float rs = 1.0f;
-    if (a.act_nsq && wave == 0) {
-        float4 nsq[NSQ4];
-        nsq_prefetch(a, 0, nsq);
-        rs = deferred_row_scale(a, nsq);
-    }
+    float4 nsq[NSQ4];
+    const bool scaled = a.act_nsq && wave == 0;
+    if (scaled) nsq_prefetch(a, 0, nsq);
 
     const int nsteps = (K + 127) / 128;
     const int rot = k_rotation(nsteps); // (see gemm_kernel)
@@ -498,10 +559,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
     // lane (c, g) reads units g and 4 + g of its weight row: entries 64h + 16g .. + 15, i.e. two k-blocks (j = 0, 1) of 8
     // entries each, whose activations are unit 8h + 2g + j of the row's 16
     typedef ActStage<T, 16, RCAP> Stage;
-    constexpr int WBYTES = NT * 2048;
-    __shared__ __align__(16) unsigned char lds[NW][U][WBYTES + Stage::BYTES];
-    typedef const void __attribute__((address_space(1))) *gptr;
-    typedef void __attribute__((address_space(3))) *lptr;
+    constexpr int WBYTES = NT * 2048, SBYTES = WBYTES + Stage::BYTES;
+    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     Stage stage;
     stage.init(a, 0, K, lane);
     int rdw[2], rda[2][2][Stage::PL];
@@ -514,49 +573,48 @@ __global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
             for (int pl = 0; pl < Stage::PL; ++pl) rda[h][j][pl] = WBYTES + stage.operand_offset(c, 8 * h + 2 * g + j, pl);
     }
 #pragma unroll
-    for (int s = 0; s < U; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    for (int ks = wave; ks < nsteps; ks += U * NW) {
+    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
+    const uint32_t lds0 = lds_address(lds[wave][0]);
+    const int n = wave < nsteps ? (nsteps - wave + NW - 1) / NW : 0;
+    ring_walk<NB>(
+        n, 2 * NT + stage.loads(),
+        [&](int i, int buf) {
+            const int k0 = rotated(wave + i * NW, rot, nsteps) * 128;
+            const bool tail = ragged && k0 + 128 > K;
+            const uint32_t to = lds0 + buf * SBYTES;
+            const uint32_t over = tail ? (uint32_t)max(k0 + wucol - (K - 16), 0) : 0u; // past a ragged end: the row's last unit, zeroed after the read (K is a multiple of 16)
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (ks + s * NW < nsteps) { // (the same for the whole wave)
-                const int k0 = rotated(ks + s * NW, rot, nsteps) * 128;
-                const int kw = min(k0 + wucol, kmax); // past a ragged end: the row's last unit, zeroed after the read
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + k0, woff[t][j] - over, to + t * 2048 + j * 1024);
+            stage.request(to + WBYTES, k0, tail);
+        },
+        [&](int i, int buf) {
+            const unsigned char *cur = lds[wave][buf];
+            const int k0 = ragged ? rotated(wave + i * NW, rot, nsteps) * 128 : 0;
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        __builtin_amdgcn_global_load_lds((gptr)(wsrc[t][i] + kw), (lptr)(lds[wave][s] + t * 2048 + i * 1024), 16, 0, WEIGHT_STREAM);
-                stage.request(lds[wave][s] + WBYTES, k0);
-            }
-        }
-        act_stage_wait();
+            for (int h = 0; h < 2; ++h) {
+                u32x4 w[NT];
+                Act<T> av[2];
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (ks + s * NW < nsteps) {
-                const int k0 = rotated(ks + s * NW, rot, nsteps) * 128;
+                for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[h]);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    u32x4 w[NT];
-                    Act<T> av[2];
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + t * 2048 + rdw[h]);
+                    for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + rda[h][j][pl]);
+                if (ragged && k0 + 64 * h + 16 * g >= K) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + rda[h][j][pl]);
-                    if (ragged && k0 + 64 * h + 16 * g >= K) {
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) w[t] = zero16();
-                    }
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w8_to_bf16x8(w[t][2 * j], w[t][2 * j + 1]), av[j]);
+                    for (int t = 0; t < NT; ++t) w[t] = zero16();
                 }
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w8_to_bf16x8(w[t][2 * j], w[t][2 * j + 1]), av[j]);
             }
-        }
-        asm volatile("" ::: "memory"); // the reads stay above the next requests
-    }
+        },
+        [&] {
+            if (scaled) rs = deferred_row_scale(a, nsq);
+        });
 
     // fixed-order sum of the waves' partial tiles; wave 0 scales the columns and applies the epilogue
     __shared__ float red[NW][NT][4][64];
@@ -614,11 +672,11 @@ __device__ __forceinline__ u32x4 w4_to_bf16x8_plus136(uint32_t x) {
 }
 constexpr float W4_BIAS = 136.0f;
 
-template <int EPI, int NW, int U, int RCAP>
+template <int EPI, int NW, int NB, int RCAP>
 __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int K = a.K;
 
@@ -638,18 +696,20 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
 
     // the tile's 16 x 128 bytes of a step come through LDS by two load-to-LDS instructions, as in gemm_kernel
     // (lane l: unit (l & 7) xor (row & 7) of row 8i + (l >> 3))
-    const unsigned char *W = reinterpret_cast<const unsigned char *>(a.W);
-    const unsigned char *wsrc[NT][2];
-    int ncol[NT][4]; // the lane's four output columns (weight rows 4g + v of the tile), clamped into the matrix
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) wsrc[t][i] = W + (size_t)min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) * (K / 2); // ragged last tile: a valid row, masked at the store
-#pragma unroll
-        for (int v = 0; v < 4; ++v) ncol[t][v] = min(n0[t] + 4 * g + v, nrows_w - 1);
-    }
     const int wucol = ((lane & 7) ^ (lane >> 3)) * 16; // bytes
     const int bmax = K / 2 - 16;
+    const char *wbase[NT];
+    uint32_t woff[NT][2], soff = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        wbase[t] = reinterpret_cast<const char *>(a.W) + (size_t)n0[t] * (K / 2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) woff[t][i] = (uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)(K / 2) + wucol; // ragged last tile: a valid row, masked at the store
+        // the step's scales, one load instruction of a word per lane: lane (h * NT + t) * 16 + column has group h, tile t (with one tile
+        // the upper half of the wavefront repeats the lower)
+        if ((lane >> 4) % NT == t) soff = (uint32_t)min(n0[t] + c, nrows_w - 1) * 4u;
+    }
+    const int sh = (lane >> 4) / NT & 1;
     // calls of more than 16 rows: one workgroup per (column tile, row tile); every row tile streams the (quarter-size)
     // weights again
     const int rt = blockIdx.y;
@@ -660,13 +720,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
     EpiPre pre;
     if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, rt, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave up front
+    // the row scale of a deferred norm on the activations (1 otherwise): see gemm_kernel
     float rs = 1.0f;
-    if (a.act_nsq && wave == 0) {
-        float4 nsq[NSQ4];
-        nsq_prefetch(a, rt, nsq);
-        rs = deferred_row_scale(a, nsq);
-    }
+    float4 nsq[NSQ4];
+    const bool scaled = a.act_nsq && wave == 0;
+    if (scaled) nsq_prefetch(a, rt, nsq);
 
     // lane (c, g) reads units g and 4 + g of its weight row: unit 4h + g is entries 128h + 32g .. + 31 of the step, all in
     // scale group h, i.e. four k-blocks (j = 0..3) of 8 entries whose activations are unit 16h + 4g + j of the row's 32
@@ -674,73 +732,69 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     const int nsteps = (ngroups + 1) / 2; // two scale groups (a 128-byte line of a weight row) per step
     const int rot = k_rotation(nsteps);   // (see gemm_kernel)
     typedef ActStage<T, 32, RCAP> Stage;
-    constexpr int WBYTES = NT * 2048;
-    __shared__ __align__(16) unsigned char lds[NW][U][WBYTES + Stage::BYTES];
-    typedef const void __attribute__((address_space(1))) *gptr;
-    typedef void __attribute__((address_space(3))) *lptr;
+    constexpr int SBASE = NT * 2048, WBYTES = SBASE + 256, SBYTES = WBYTES + Stage::BYTES;
+    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     Stage stage;
     stage.init(a, rt * 16, K, lane);
     int rdw[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) rdw[h] = (c * 8 + ((4 * h + g) ^ (c & 7))) * 16;
 #pragma unroll
-    for (int s = 0; s < U; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    for (int ks = wave; ks < nsteps; ks += U * NW) {
-        float sc[U][2][NT][4];
+    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
+    const uint32_t lds0 = lds_address(lds[wave][0]);
+    const int n = wave < nsteps ? (nsteps - wave + NW - 1) / NW : 0;
+    ring_walk<NB>(
+        n, 2 * NT + 1 + stage.loads(),
+        [&](int i, int buf) {
+            const int st = rotated(wave + i * NW, rot, nsteps);
+            const bool tail = 2 * st + 1 >= ngroups; // a last step of one group: valid units and scales, not used
+            const uint32_t to = lds0 + buf * SBYTES;
+            const uint32_t over = tail ? (uint32_t)max(st * 128 + wucol - bmax, 0) : 0u;
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (ks + s * NW < nsteps) { // (the same for the whole wave)
-                const int st = rotated(ks + s * NW, rot, nsteps);
-                const int kw = min(st * 128 + wucol, bmax); // past the end (a last step of one group): a valid unit, not used
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
+                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + (size_t)st * 128, woff[t][j] - over, to + t * 2048 + j * 1024);
+            dma4(a.wscale + (size_t)(2 * st) * nrows_w, soff + (sh && !tail ? (uint32_t)nrows_w * 4u : 0u), to + SBASE);
+            stage.request(to + WBYTES, st * 256, tail);
+        },
+        [&](int i, int buf) {
+            const unsigned char *cur = lds[wave][buf];
+            const int st = rotated(wave + i * NW, rot, nsteps);
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        __builtin_amdgcn_global_load_lds((gptr)(wsrc[t][i] + kw), (lptr)(lds[wave][s] + t * 2048 + i * 1024), 16, 0, WEIGHT_STREAM);
+            for (int h = 0; h < 2; ++h) {
+                if (2 * st + h < ngroups) { // (the same for the whole wave)
+                    u32x4 w[NT];
+                    f32x4 sc[NT];
+                    Act<T> av[4];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
+                    for (int t = 0; t < NT; ++t) {
+                        w[t] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[h]);
+                        sc[t] = *reinterpret_cast<const f32x4 *>(cur + SBASE + (h * NT + t) * 64 + g * 16);
+                    }
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) sc[s][h][t][v] = a.wscale[(size_t)min(2 * st + h, ngroups - 1) * nrows_w + ncol[t][v]];
-                }
-                stage.request(lds[wave][s] + WBYTES, st * 256);
-            }
-        }
-        act_stage_wait();
+                    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            if (ks + s * NW < nsteps) {
-                const int st = rotated(ks + s * NW, rot, nsteps);
+                        for (int pl = 0; pl < Stage::PL; ++pl)
+                            av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + WBYTES + stage.operand_offset(c, 16 * h + 4 * g + j, pl));
+                    // the group's activation sums per row (an all-ones weight tile: every output column gets the sum)
+                    f32x4 asum = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (2 * st + h < ngroups) { // (the same for the whole wave)
-                        u32x4 w[NT];
-                        Act<T> av[4];
+                    for (int j = 0; j < 4; ++j) asum = mma(asum, ones, av[j]);
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + t * 2048 + rdw[h]);
+                    for (int t = 0; t < NT; ++t) {
+                        f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
+                        for (int j = 0; j < 4; ++j) part = mma(part, w4_to_bf16x8_plus136(w[t][j]), av[j]);
 #pragma unroll
-                            for (int pl = 0; pl < Stage::PL; ++pl)
-                                av[j].p[pl] = *reinterpret_cast<const u32x4 *>(lds[wave][s] + WBYTES + stage.operand_offset(c, 16 * h + 4 * g + j, pl));
-                        // the group's activation sums per row (an all-ones weight tile: every output column gets the sum)
-                        f32x4 asum = f32x4{0.f, 0.f, 0.f, 0.f};
-                        const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) asum = mma(asum, ones, av[j]);
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) part = mma(part, w4_to_bf16x8_plus136(w[t][j]), av[j]);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) acc[t][v] += sc[s][h][t][v] * (part[v] - W4_BIAS * asum[v]);
-                        }
+                        for (int v = 0; v < 4; ++v) acc[t][v] += sc[t][v] * (part[v] - W4_BIAS * asum[v]);
                     }
                 }
             }
-        }
-        asm volatile("" ::: "memory"); // the reads stay above the next requests
-    }
+        },
+        [&] {
+            if (scaled) rs = deferred_row_scale(a, nsq);
+        });
 
     // fixed-order sum of the waves' partial tiles; wave 0 applies the epilogue
     __shared__ float red[NW][NT][4][64];
@@ -784,10 +838,6 @@ __device__ __forceinline__ void wide_barrier() { // workgroup barrier that order
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();
 }
-template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_waitcnt vmcnt(N), N < 64
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
 // columns of wave tile `tile`: n0[t] = first column of its t-th 16-column output tile; returns the number of wave tiles
 template <int EPI>
 __device__ __forceinline__ int wide_tile_cols(const GemmArgs &a, int tile, int (&n0)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1]) {
@@ -1111,13 +1161,6 @@ template <int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int NBUF_> st
     static_assert(NBUF * STAGE <= 160 * 1024, "LDS");
 };
 
-// A load-to-LDS instruction (16 bytes per lane, from base + off to lds + 16 * lane) that the compiler does not see as one: it
-// would wait for every such load in flight in front of the next LDS read.  It has no register result; whoever reads the data
-// waits for it with wait_vm.
-__device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
-}
-
 __device__ __forceinline__ void stage_barrier() { // ... which no LDS access may cross
     asm volatile("" ::: "memory");
     wide_barrier();
@@ -1131,8 +1174,7 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, NBUF = C::NBUF, NW = C::NW;
     static_assert(CTW % NT == 0 && KBS % WK == 0 && NBUF <= 3, "");
     __shared__ __align__(16) unsigned char lds[NBUF * C::STAGE];
-    typedef const unsigned char __attribute__((address_space(3))) *lptr;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr)lds;
+    const uint32_t lds0 = lds_address(lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int wk = wave % WK, wc = (wave / WK) % C::WC, wr = wave / (WK * C::WC);
@@ -1418,9 +1460,10 @@ template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStrea
 
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);
 
-template <typename T, int EPI, int NW, int U> static void launch_narrow(const GemmArgs &a, int tiles, hipStream_t st) {
-    if (a.R <= 8) hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, U, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, U, 16>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
+// NW wavefronts per workgroup and NB buffers each, for calls of at most 8 rows and of 9 to 16
+template <typename T, int EPI, int NW, int NB, int NW16 = NW, int NB16 = NB> static void launch_narrow(const GemmArgs &a, int tiles, hipStream_t st) {
+    if (a.R <= 8) hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, NB, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((gemm_kernel<T, EPI, NW16, NB16, 16>), dim3(tiles, 1), dim3(NW16 * 64), 0, st, a);
 }
 
 template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipStream_t st) {
@@ -1428,13 +1471,25 @@ template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipSt
     if (EPI == EPI_QKV) tiles = 3 * a.H * (a.hd / 32);
     else tiles = (a.N + 15) / 16;
     const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles <= 1) { // the verify pass proper: the waves of a workgroup split K, two steps in flight each
-        // fused epilogues (688 gate/up pairs, 384 rotary pairs at the 7B shape: several workgroups per compute unit anyway)
-        // run 2 (gate/up) and 4 (QKV) waves per workgroup, the projections with 256 tiles 8: measured over
-        // (2 | 3 | 4 | 5 | 6 | 8 | 16 waves) x (1 - 5 steps in flight) per kind of epilogue on the 7B-shaped layer
-        if (EPI == EPI_QKV) launch_narrow<T, EPI, 4, 2>(a, tiles, st);
-        else if (EPI == EPI_SWIGLU) launch_narrow<T, EPI, 2, 2>(a, tiles, st);
-        else launch_narrow<T, EPI, 8, 2>(a, tiles, st);
+    if (row_tiles <= 1) { // the verify pass proper: the waves of a workgroup split K
+        // Measured over (1 - 8 | 10 | 12 | 16 waves) x (1 - 4 buffers) per kind of epilogue on the 7B- and 3B-shaped layers at 5 and 1
+        // rows.  A wave that asks for one step while it multiplies the other (two buffers) is the best where the launch has one or two
+        // workgroups per compute unit; a third buffer makes every launch slower (94 -> 103 us a layer: with more asked for than a
+        // compute unit can have in flight, what is needed first comes later).  Gate/up has several workgroups per compute unit
+        // anyway: up to three, twice the waves with one buffer each are ahead (512 pairs 20.6 -> 18.9 us, 688 31.2 -> 30.0), beyond
+        // (864 pairs, K 5120) two waves with two (49 against 52).
+        constexpr bool BF16 = std::is_same<T, bf16_t>::value;
+        if constexpr (EPI == EPI_QKV) {
+            launch_narrow<T, EPI, 4, 2>(a, tiles, st);
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            if (BF16 && tiles <= 3 * 256) launch_narrow<T, EPI, 4, 1, 2, 2>(a, tiles, st);
+            else launch_narrow<T, EPI, 2, 2>(a, tiles, st);
+        } else if constexpr (EPI == EPI_RESID) {
+            launch_narrow<T, EPI, 8, 2>(a, tiles, st);
+        } else {
+            if (BF16) launch_narrow<T, EPI, 4, 1, 8, 2>(a, tiles, st); // (2000 tiles of 32000 logits: 33.3 -> 32.2 us at K 3072)
+            else launch_narrow<T, EPI, 8, 2>(a, tiles, st);
+        }
         return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
     }
     if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI>(a, tiles, st);
@@ -1466,53 +1521,32 @@ template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs
     }
 }
 
-// (a shape whose LDS does not fit at this row count runs with 8 waves and one step in flight)
-template <int EPI, int NW, int U> static void launch_w8(const GemmArgs &a, int tiles, hipStream_t st) {
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    constexpr int red = NW * NT * 4 * 64 * 4;
-    constexpr bool fit8 = NW * U * (NT * 2048 + ActStage<bf16_t, 16, 8>::BYTES) + red <= 160 * 1024;
-    constexpr bool fit16 = NW * U * (NT * 2048 + ActStage<bf16_t, 16, 16>::BYTES) + red <= 160 * 1024;
-    if (a.R <= 8) {
-        if constexpr (fit8) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, U, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((gemm_w8_kernel<EPI, 8, 1, 8>), dim3(tiles, 1), dim3(8 * 64), 0, st, a);
-    } else {
-        if constexpr (fit16) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, U, 16>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((gemm_w8_kernel<EPI, 8, 1, 16>), dim3(tiles, 1), dim3(8 * 64), 0, st, a);
-    }
+// waves and buffers per kind of epilogue, measured like those of launch_gemm_t; fewer waves at 9 to 16 rows, whose activations
+// take twice the LDS (O and down on average: 8 waves x 2 buffers 12.1, 16 x 1 11.5, 12 x 1 11.0 us)
+template <int EPI, int NW, int NB, int NW16 = NW> static void launch_w8(const GemmArgs &a, int tiles, hipStream_t st) {
+    if (a.R <= 8) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, NB, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW16, NB, 16>), dim3(tiles, 1), dim3(NW16 * 64), 0, st, a);
 }
 
-// 8 waves per workgroup for the projections with few tiles, 4 for the fused epilogues; one or two steps in flight per
-// wave (measured per kind of epilogue on the 7B-shaped layer among (2 | 3 | 4 | 5 | 6 | 7 | 8 | 16 waves) x (1..3 steps))
 template <int EPI> static int launch_gemm_w8(const GemmArgs &a, hipStream_t st) {
     const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     const int row_tiles = (a.R + 15) / 16;
     if (row_tiles > 1) return launch_wide_any<bf16_t, EPI, 8>(a, tiles, row_tiles, st);
-    if (EPI == EPI_QKV) launch_w8<EPI, 4, 2>(a, tiles, st);
-    else if (EPI == EPI_SWIGLU) launch_w8<EPI, 4, 1>(a, tiles, st);
-    else if (EPI == EPI_RESID) launch_w8<EPI, 8, 2>(a, tiles, st);
+    if constexpr (EPI == EPI_QKV) launch_w8<EPI, 4, 2>(a, tiles, st);
+    else if constexpr (EPI == EPI_SWIGLU) launch_w8<EPI, 4, 1>(a, tiles, st);
+    else if constexpr (EPI == EPI_RESID) launch_w8<EPI, 12, 1, 8>(a, tiles, st);
     else launch_w8<EPI, 8, 1>(a, tiles, st);
     return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
 }
 
-// One step in flight; 8 waves for the residual projections, 4 for the fused epilogues and the LM head: measured best of
-// (2 | 3 | 4 | 5 | 6 | 8 waves) x (1 | 2 | 3 steps) on the 7B-shaped layer
-// (a shape whose LDS does not fit at this row count runs with 4 waves and one step in flight)
-template <int EPI, int NW, int U> static void launch_w4(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    constexpr int red = NW * NT * 4 * 64 * 4;
-    constexpr bool fit5 = NW * U * (NT * 2048 + ActStage<bf16_t, 32, 5>::BYTES) + red <= 160 * 1024;
-    constexpr bool fit8 = NW * U * (NT * 2048 + ActStage<bf16_t, 32, 8>::BYTES) + red <= 160 * 1024;
-    constexpr bool fit16 = NW * U * (NT * 2048 + ActStage<bf16_t, 32, 16>::BYTES) + red <= 160 * 1024;
-    if (a.R <= 5) { // the K + 1 = 5 rows of the usual verify pass: the smaller staging area lets a compute unit hold a workgroup more
-        if constexpr (fit5) hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, U, 5>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((gemm_w4_kernel<EPI, 4, 1, 5>), dim3(tiles, row_tiles), dim3(4 * 64), 0, st, a);
-    } else if (a.R <= 8) {
-        if constexpr (fit8) hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, U, 8>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((gemm_w4_kernel<EPI, 4, 1, 8>), dim3(tiles, row_tiles), dim3(4 * 64), 0, st, a);
-    } else {
-        if constexpr (fit16) hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, U, 16>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((gemm_w4_kernel<EPI, 4, 1, 16>), dim3(tiles, row_tiles), dim3(4 * 64), 0, st, a);
-    }
+// one buffer per wave: 8 or 12 waves for the residual projections (12 with the small staging area of at most 5 rows), 4 otherwise
+template <int EPI, int NW, int NW5 = NW> static void launch_w4(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
+    if (a.R <= 5) // the K + 1 = 5 rows of the usual verify pass: the smaller staging area lets a compute unit hold more workgroups
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW5, 1, 5>), dim3(tiles, row_tiles), dim3(NW5 * 64), 0, st, a);
+    else if (a.R <= 8)
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 8>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
+    else
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
 }
 
 template <int EPI> static int launch_gemm_w4(const GemmArgs &a, hipStream_t st) {
@@ -1522,8 +1556,8 @@ template <int EPI> static int launch_gemm_w4(const GemmArgs &a, hipStream_t st) 
     // more than 16 rows: the wide kernel (it reads a lane's four scales as one 16-byte load); otherwise, or with a
     // row count that is not a multiple of 4, one workgroup per (column tile, row tile)
     if (row_tiles > 1 && nrows_w % 4 == 0 && (reinterpret_cast<uintptr_t>(a.wscale) & 15) == 0) return launch_wide_any<bf16_t, EPI, 4>(a, tiles, row_tiles, st);
-    if (EPI == EPI_RESID) launch_w4<EPI, 8, 1>(a, tiles, row_tiles, st);
-    else launch_w4<EPI, 4, 1>(a, tiles, row_tiles, st);
+    if constexpr (EPI == EPI_RESID) launch_w4<EPI, 8, 12>(a, tiles, row_tiles, st);
+    else launch_w4<EPI, 4>(a, tiles, row_tiles, st);
     return (EPI == EPI_RESID && a.nsq_out && row_tiles == 1) ? 2 : 0;
 }
 
