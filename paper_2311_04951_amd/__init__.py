@@ -7,7 +7,9 @@ no CPU fallback - importing works without a GPU, calling does not.
 """
 from __future__ import annotations
 
+import array
 import atexit
+import functools
 import weakref
 import ctypes as C
 import os
@@ -144,27 +146,37 @@ def _check(rc):
         raise SpecVerifyError(rc, lib().ss_last_error().decode())
 
 
+# The calls of a decode loop are short (two launches, some 10 us on the device), so the marshalling below is kept to a few
+# attribute reads per argument: plain integers instead of ctypes objects, the raw stream handle instead of a Stream object.
+
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if torch.cuda.is_initialized() else torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t, dtype=None):
-    """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
+    """Device address of a contiguous CUDA tensor (None -> NULL)."""
     if t is None:
-        return C.c_void_p(0)
+        return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _host_i32(seq):
+    """(owner, address) of a host int32 array with the numbers of `seq`."""
+    try:
+        a = array.array("i", seq if isinstance(seq, (list, tuple)) else [])
+        if isinstance(seq, (list, tuple)):
+            return a, a.buffer_info()[0]
+    except TypeError:       # not all integers: as numpy converts them
+        pass
     import numpy as np
     a = np.ascontiguousarray(seq, dtype=np.int32)
-    return a, a.ctypes.data_as(C.c_void_p)
+    return a, a.ctypes.data
 
 
 # ---------------------------------------------------------------------------------- handles
@@ -221,9 +233,9 @@ class Model:
         arr = (_LayerW * max(1, len(packed_layers)))()
         for i, pl in enumerate(packed_layers):
             for n in ("wqkv", "wo", "wgu", "wd"):
-                setattr(arr[i], n, _dev(pl[n], wt).value)
+                setattr(arr[i], n, _dev(pl[n], wt))
             for n in ("g1", "g2") + (("sqkv", "so", "sgu", "sd") if self.int8_weights else ()):
-                setattr(arr[i], n, _dev(pl[n], torch.float32).value)
+                setattr(arr[i], n, _dev(pl[n], torch.float32))
         w = _Weights(_dev(self.embed, st if self.embed is not None else None), arr,
                      _dev(self.gf, torch.float32 if self.gf is not None else None),
                      _dev(self.lm_head, wt if self.lm_head is not None else None),
@@ -279,6 +291,7 @@ class KVCache:
 _workspaces = {}
 
 
+@functools.lru_cache(maxsize=256)
 def ss_workspace_bytes(rows: int, vocab: int) -> int:
     return lib().ss_workspace_bytes(int(rows), int(vocab))
 
@@ -298,7 +311,7 @@ def workspace(device, rows: int, vocab: int):
     """A device workspace for the calls without a handle: one per (device, stream), kept between calls and
     replaced by a larger one when a call needs more (memory plumbing: the C calls never allocate)."""
     need = ss_workspace_bytes(rows, vocab)
-    key = (str(device), torch.cuda.current_stream().cuda_stream)
+    key = (getattr(device, "index", device), _stream(None))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < need:
         ws = torch.empty(max(need, 1 << 20), dtype=torch.uint8, device=device)
@@ -334,14 +347,14 @@ def ss_kv_cache_append(kv: KVCache, layer: int, seq: int, pos0: int, k, v, strea
 
 def ss_kv_cache_set_len(kv: KVCache, lens, stream=None):
     a, p = _host_i32(lens)
-    if a.size != kv.batch:
+    if (a.size if hasattr(a, "size") else len(a)) != kv.batch:
         raise ValueError("one length per sequence")
     _check(lib().ss_kv_cache_set_len(kv.handle, p, _stream(stream)))
 
 
 def ss_kv_cache_truncate(kv: KVCache, new_len, new_len_host=None, status=None, stream=None):
     """Device-side truncation: len[b] = min(len[b], new_len[b]) (new_len: device int32 [batch])."""
-    hp = C.c_void_p(0)
+    hp = None
     if new_len_host is not None:
         keep, hp = _host_i32(new_len_host)
     _check(lib().ss_kv_cache_truncate(kv.handle, _dev(new_len, torch.int32), hp, _dev(status, torch.int32 if status is not None else None),
@@ -356,7 +369,7 @@ def ss_kv_cache_get_len(kv: KVCache, stream=None):
 
 
 def ss_kv_cache_rollback(kv: KVCache, n_accepted, M: int, n_accepted_host=None, stream=None):
-    hp = C.c_void_p(0)
+    hp = None
     if n_accepted_host is not None:
         keep, hp = _host_i32(n_accepted_host)
     _check(lib().ss_kv_cache_rollback(kv.handle, _dev(n_accepted, torch.int32), hp, M, _stream(stream)))
@@ -382,7 +395,7 @@ def ss_decoder_layers_forward(model: Model, kv: KVCache, h, batch: int, M: int, 
 def ss_draft_step(draft: Model, kv: KVCache, tokens, m: int, temperature: float, u, q_rows, ldq: int,
                   token_out, stream=None, top_p: float = 1.0, top_k: int = 0):
     batch = tokens.numel() // m
-    qp = C.c_void_p(0) if q_rows is None else C.c_void_p(q_rows.data_ptr())
+    qp = None if q_rows is None else q_rows.data_ptr()
     _check(lib().ss_draft_step(draft.handle, kv.handle, _dev(tokens, torch.int32), batch, m, float(temperature), float(top_p), int(top_k),
                                _dev(u, torch.float32 if u is not None else None), qp, int(ldq),
                                _dev(token_out, torch.int32), _stream(stream)))
@@ -430,8 +443,8 @@ def _accept_out(batch, device, n_accepted, next_token):
 def ss_speculative_accept(p, q, draft_tokens, uniforms, n_accepted=None, next_token=None, stream=None, ws=None):
     B, K1, V = p.shape
     n_accepted, next_token = _accept_out(B, p.device, n_accepted, next_token)
-    _check(lib().ss_speculative_accept(_dev(p, torch.float32), _dev(q, torch.float32) if K1 > 1 else C.c_void_p(0),
-                                       _dev(draft_tokens, torch.int32) if K1 > 1 else C.c_void_p(0),
+    _check(lib().ss_speculative_accept(_dev(p, torch.float32), _dev(q, torch.float32) if K1 > 1 else None,
+                                       _dev(draft_tokens, torch.int32) if K1 > 1 else None,
                                        _dev(uniforms, torch.float32), B, K1 - 1, V, _dev(n_accepted), _dev(next_token),
                                        *_ws_args(ws, p.device, B * (2 * K1 - 1), V), _stream(stream)))
     return n_accepted, next_token
@@ -440,8 +453,8 @@ def ss_speculative_accept(p, q, draft_tokens, uniforms, n_accepted=None, next_to
 def ss_speculative_accept_noalloc(p, q, draft_tokens, uniforms, n_accepted, next_token, status=None, stream=None):
     """The rejection step with the library's built-in scratch array: every tensor, outputs included, is the caller's."""
     B, K1, V = p.shape
-    _check(lib().ss_speculative_accept_noalloc(_dev(p, torch.float32), _dev(q, torch.float32) if K1 > 1 else C.c_void_p(0),
-                                               _dev(draft_tokens, torch.int32) if K1 > 1 else C.c_void_p(0),
+    _check(lib().ss_speculative_accept_noalloc(_dev(p, torch.float32), _dev(q, torch.float32) if K1 > 1 else None,
+                                               _dev(draft_tokens, torch.int32) if K1 > 1 else None,
                                                _dev(uniforms, torch.float32), B, K1 - 1, V, _dev(n_accepted, torch.int32),
                                                _dev(next_token, torch.int32), _dev(status, torch.int32 if status is not None else None),
                                                _stream(stream)))
@@ -453,8 +466,8 @@ def ss_speculative_accept_logits(p_logits, q_logits, temperature, draft_tokens, 
     B, K1, V = p_logits.shape
     n_accepted, next_token = _accept_out(B, p_logits.device, n_accepted, next_token)
     _check(lib().ss_speculative_accept_logits(
-        _dev(p_logits, torch.float32), _dev(q_logits, torch.float32) if K1 > 1 else C.c_void_p(0), float(temperature),
-        _dev(draft_tokens, torch.int32) if K1 > 1 else C.c_void_p(0), _dev(uniforms, torch.float32), B, K1 - 1, V,
+        _dev(p_logits, torch.float32), _dev(q_logits, torch.float32) if K1 > 1 else None, float(temperature),
+        _dev(draft_tokens, torch.int32) if K1 > 1 else None, _dev(uniforms, torch.float32), B, K1 - 1, V,
         _dev(n_accepted), _dev(next_token), _dev(p_out), _dev(q_out), *_ws_args(ws, p_logits.device, B * (2 * K1 - 1), V),
         _stream(stream)))
     return n_accepted, next_token
@@ -464,7 +477,7 @@ def ss_greedy_accept(p_logits, draft_tokens, n_accepted=None, next_token=None, s
     B, K1, V = p_logits.shape
     n_accepted, next_token = _accept_out(B, p_logits.device, n_accepted, next_token)
     _check(lib().ss_greedy_accept(_dev(p_logits, torch.float32),
-                                  _dev(draft_tokens, torch.int32) if K1 > 1 else C.c_void_p(0), B, K1 - 1, V,
+                                  _dev(draft_tokens, torch.int32) if K1 > 1 else None, B, K1 - 1, V,
                                   _dev(n_accepted), _dev(next_token), *_ws_args(ws, p_logits.device, B * K1, V), _stream(stream)))
     return n_accepted, next_token
 
@@ -575,7 +588,7 @@ def ss_model_set_persistent_options(model: Model, workgroups: int = 0, data_sync
 def ss_model_set_timeline(model: Model, buf):
     """Development aid: device clock samples of the persistent kernel into `buf` (int64 device tensor, zero-filled)."""
     if buf is None:
-        _check(lib().ss_model_set_timeline(model.handle, C.c_void_p(0), 0))
+        _check(lib().ss_model_set_timeline(model.handle, None, 0))
     else:
         _check(lib().ss_model_set_timeline(model.handle, _dev(buf, torch.int64), buf.numel()))
 

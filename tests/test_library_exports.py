@@ -4,6 +4,8 @@ import ctypes
 import os
 import re
 
+import pytest
+
 import paper_2311_04951_amd as sv
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -90,3 +92,17 @@ def test_calls_without_a_handle_refuse_a_workspace_that_is_too_small_on_the_host
     out = vp()
     assert L.ss_kv_cache_create(None, 1, 64, fake[0], 1 << 20, None, ctypes.byref(out)) == sv.SS_EINVAL
     assert L.ss_shutdown() == 0 and L.ss_shutdown() == 0      # nothing alive: a no-op, twice
+
+
+def test_host_lengths_are_marshalled_as_numpy_would():
+    """Lists of integers take a short way into the call, everything else goes through numpy: the same numbers and the same refusals."""
+    import numpy as np
+    import paper_2311_04951_amd as sv
+
+    for seq in ([3, 0, 2 ** 31 - 1, -7], (5,), [], [True, 2], [np.int32(4), np.int64(9)], [1.0, 2.0], np.array([7, 8]), np.arange(6)[::2]):
+        owner, address = sv._host_i32(seq)
+        want = np.ascontiguousarray(seq, dtype=np.int32)
+        assert (ctypes.c_int32 * len(want)).from_address(address)[:] == want.tolist() if len(want) else True
+    for bad in ([2 ** 31], [2 ** 40, 1]):
+        with pytest.raises(OverflowError):
+            sv._host_i32(bad)
