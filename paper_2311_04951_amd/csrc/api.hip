@@ -586,13 +586,17 @@ static int check_pair(const ss_model *m, const ss_kv_cache *kv, int batch, int M
     return SS_OK;
 }
 
+// Rows of an activation plane in a call of R rows: the buffers hold max_rows of them, but calls of at most 16 rows pack their two
+// planes together (their GEMMs reach both with 32-bit offsets).
+static size_t plane_rows(const ss_model *m, int R) { return R <= 16 ? 16 : (size_t)m->R16; }
+
 // All layers over the R = batch*M rows in h.  normed: whether act_a already holds the first layer's normalised rows (the
 // embedding writes them).  final_gain: the norm that follows the last layer when it covers all rows in order (NULL: none, or
 // the head gathers rows).  Returns what the last projection did about that norm (launch_gemm).
 static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const float *final_gain, int batch, int M, hipStream_t st) {
     const ss_model_cfg &c = m->cfg;
     const int R = batch * M, d = c.d_model, W = m->W, F = c.d_ff;
-    const size_t pl = (size_t)m->R16;
+    const size_t pl = plane_rows(m, R);
     int Lmax = 0;
     for (int b = 0; b < batch; ++b) Lmax = std::max(Lmax, kv->len_ub[b] + M);
     // KV splits per (sequence, head): about 512 workgroups in all, but a single split (no partials, no merge launch)
@@ -701,14 +705,14 @@ static int run_embed(ss_model *m, const int32_t *tokens, int R, hipStream_t st) 
     const ss_model_cfg &c = m->cfg;
     ProfScope ps(m, PT_NORM, st);
     launch_embed_norm(c.dtype, m->embed, tokens, R, c.d_model, c.vocab, m->h, m->status, c.n_layers ? m->layers[0].g1 : nullptr, c.rms_eps, m->act_a,
-                      (size_t)m->R16 * c.d_model, c.d_model, st);
+                      plane_rows(m, R) * c.d_model, c.d_model, st);
     return c.n_layers ? 1 : 0;
 }
 
 // logits[r][:] = RMSNorm(h[row0 + r*stride], gf) . W_lm^T for r < nrows.  normed: what the last projection did about the norm
 static void run_head(ss_model *m, int normed, int nrows, int row0, int stride, float *logits, hipStream_t st) {
     const ss_model_cfg &c = m->cfg;
-    const size_t pl = (size_t)m->R16;
+    const size_t pl = plane_rows(m, nrows); // (normed: nrows are the rows of the pass)
     if (!normed) {
         ProfScope ps(m, PT_NORM, st);
         launch_rmsnorm_pack_rows(c.dtype, m->h, m->gf, nrows, row0, stride, c.d_model, c.rms_eps, m->act_a, pl * c.d_model, c.d_model, st);

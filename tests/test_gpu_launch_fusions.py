@@ -95,3 +95,21 @@ def test_a_draft_step_in_one_sampling_launch_gives_the_bits_of_the_separate_ones
         none = torch.zeros(1, dtype=torch.int32, device=dev())
         _, tok = sv.ss_speculative_accept(p, p, none, u.reshape(batch, 1).contiguous())      # K = 0: a plain sample
         assert out.tolist() == tok.tolist()
+
+
+@pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.mem_get_info()[0] < 120 << 30, reason="the model's buffers take 80 GB")
+def test_few_rows_of_a_model_whose_activation_planes_pass_4_gib():
+    """A model sized for so many rows that one activation plane of max_rows x d_ff holds more than 2^32 bytes: calls of a few rows
+    give the bits that the same weights give in a small model (their GEMMs address the planes with 32 bits)."""
+    shape = si.DecoderShape(1, 256, 4, 64, 32768, 64, dtype="bf16")
+    w = weights_to_device(si.decoder_weights(shape, seed=74))
+    toks = si.token_ids(74, "t", (1, 5), shape.vocab).to(dev())
+    outs = []
+    for max_rows in (16, 65552):
+        assert max_rows == 16 or max_rows * shape.d_ff * 2 > 1 << 32
+        gm = sv.Model(shape, w, max_rows=max_rows, max_pos=32)
+        kv = sv.KVCache(gm, 1, 16)
+        outs.append(sv.ss_verify_forward(gm, kv, toks, 5).clone())
+        torch.cuda.synchronize()
+        del kv, gm
+    assert torch.equal(outs[0], outs[1])
