@@ -5,12 +5,10 @@
 //   workgroup multiplies every weight chunk it streams with up to RT row tiles (weights are read once for
 //   up to 16*RT rows).
 //
-// One workgroup (8 wavefronts for at most 16 rows) owns 16 output columns (or a pair of 16-column tiles for the fused
-// epilogues).  Each lane streams 16-byte chunks of 16 weight rows straight from HBM into registers -
-// weights are used exactly once, so they never pass through LDS - and feeds them to MFMA as the A
-// operand; the activation rows are the B operand, read as packed planes through L1/L2.  The
-// waves interleave over K in 128-byte steps per row, their partial tiles are summed in a fixed
-// order through LDS (deterministic), and wave 0 applies the epilogue:
+// At most 16 rows: one workgroup owns 16 output columns (or a pair of 16-column tiles for the fused epilogues).  Weights and
+// activation rows (packed planes) come through LDS by load-to-LDS instructions that take whole 128-byte lines, into a ring of the
+// wavefront's own, and are read back as the A and B operands of the MFMAs.  The waves interleave over K in 128-byte steps, their
+// partial tiles are summed in a fixed order through LDS (deterministic), and wave 0 applies the epilogue:
 //   STORE   plain fp32 store (LM head)
 //   RESID   h += ...            (O projection, down projection)
 //   SWIGLU  silu(gate) * up     (gate tile + up tile in one workgroup) -> activation planes
@@ -808,7 +806,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     move_lengths<EPI>(a);
 }
 
-// More than 16 rows (larger batches, prefill): the waves of a workgroup split the output columns instead
+// More than 16 rows of fp32 or quantised models (bf16 matrices: gemm_tile_kernel): the waves of a workgroup split the output columns instead
 // of K, so that all of them walk K together and share the activation rows through LDS - with R rows
 // the activations a wave needs are R*4/32 times its weight bytes, too much to fetch per wave from L2.
 //   * wave w owns the 16 (or, fused epilogues, 2 x 16) weight rows of tile blockIdx.x*NW + w and the
