@@ -455,7 +455,9 @@ constexpr int PART_THREADS = 256, PART_UNROLL = 4;
 // grid (nseg, B): the accepted count of sequence b, and the total weight of segment blockIdx.x of the
 // row the next token is drawn from (residual at the first rejection, else the bonus row).  The
 // vocabulary is cut into nseg segments so that a few sequences still fill the chip; integer partial
-// sums make the split invisible in the result.
+// sums make the split invisible in the result.  Bound by the two rows' bytes behind the chain draft -> probabilities -> row: a
+// thread asks for all eight 16-byte pieces of a round before it uses the first (with the loads inside the bounds test of each
+// piece, two were in flight; 64 sequences x K 8 x 128256, the whole call 106.8 -> 102.9 us).
 __global__ __launch_bounds__(PART_THREADS) void accept_partial_kernel(AcceptArgs a, int seg_len, unsigned long long *partial) {
     __shared__ int sm_rej;
     __shared__ unsigned long long sm_part[PART_THREADS / 64];
@@ -468,20 +470,32 @@ __global__ __launch_bounds__(PART_THREADS) void accept_partial_kernel(AcceptArgs
     const bool vec = (a.V % 4 == 0) && ((reinterpret_cast<uintptr_t>(P.row) & 15) == 0) && ((reinterpret_cast<uintptr_t>(Q.row) & 15) == 0);
     const int r0 = min(seg * seg_len, a.V), r1 = min(r0 + seg_len, a.V);
     unsigned long long sum = 0;
-    for (int v0 = r0 + 4 * threadIdx.x; v0 < r1; v0 += 4 * PART_THREADS * PART_UNROLL) {
-        unsigned long long w[PART_UNROLL][4];
+    if (vec) { // (r0 and r1 are multiples of 4)
+        for (int v0 = r0 + 4 * threadIdx.x; v0 < r1; v0 += 4 * PART_THREADS * PART_UNROLL) {
+            float4 p4[PART_UNROLL], q4[PART_UNROLL];
 #pragma unroll
-        for (int j = 0; j < PART_UNROLL; ++j) {
-            const int v = v0 + 4 * PART_THREADS * j;
-            if (v < r1) {
-                if (resid) weights4<true>(P, Q, v, a.V, vec, w[j]);
-                else weights4<false>(P, P, v, a.V, vec, w[j]);
-            } else {
-                w[j][0] = w[j][1] = w[j][2] = w[j][3] = 0;
+            for (int j = 0; j < PART_UNROLL; ++j) p4[j] = *reinterpret_cast<const float4 *>(P.row + min(v0 + 4 * PART_THREADS * j, r1 - 4));
+#pragma unroll
+            for (int j = 0; j < PART_UNROLL; ++j) q4[j] = p4[j];
+            if (resid) {
+#pragma unroll
+                for (int j = 0; j < PART_UNROLL; ++j) q4[j] = *reinterpret_cast<const float4 *>(Q.row + min(v0 + 4 * PART_THREADS * j, r1 - 4));
             }
-        }
 #pragma unroll
-        for (int j = 0; j < PART_UNROLL; ++j) sum += (w[j][0] + w[j][1]) + (w[j][2] + w[j][3]);
+            for (int j = 0; j < PART_UNROLL; ++j)
+                if (v0 + 4 * PART_THREADS * j < r1) {
+                    const float p[4] = {p4[j].x, p4[j].y, p4[j].z, p4[j].w}, q[4] = {q4[j].x, q4[j].y, q4[j].z, q4[j].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum += fx_weight(resid ? fmaxf(__fsub_rn(P.conv(p[e]), Q.conv(q[e])), 0.f) : P.conv(p[e]));
+                }
+        }
+    } else {
+        for (int v = r0 + 4 * threadIdx.x; v < r1; v += 4 * PART_THREADS) {
+            unsigned long long w[4];
+            if (resid) weights4<true>(P, Q, v, a.V, false, w);
+            else weights4<false>(P, P, v, a.V, false, w);
+            sum += (w[0] + w[1]) + (w[2] + w[3]);
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += shfl_xor_u64(sum, o);
