@@ -266,7 +266,10 @@ template <int AHEAD> __device__ __forceinline__ void wait_steps(int ahead, int p
 // 16 bytes each) and the operands are read back from LDS.  Piece (plane * R + row) * UPS + (unit xor row) holds unit
 // `unit` of the row, so that the 16 rows a wave reads together fall into different banks.  Lanes of rows that do not
 // exist read a slot that holds zeros.  Measured on the 7B-shaped layer: 5-row pass 3.62 -> 3.37 ms, 1 row 3.29 -> 3.18.
-template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most rows (5, 8 or 16)
+// FAR: the planes may lie more than 2^32 bytes apart (calls of more than 16 rows: max_rows apart).  A step then always brings RCAP
+// rows of each plane, the last one again past the end, so that an instruction's pieces are of one plane, whose base is uniform and
+// has 64 bits; without it the plane is part of a piece's 32-bit offset (calls of at most 16 rows pack their planes 16 rows apart).
+template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage { // RCAP: most rows (5, 8 or 16)
     static constexpr int PL = Traits<T>::PLANES, EPU = 16 / (int)sizeof(T);
     static constexpr int NDMA = (PL * RCAP * UPS + 63) / 64; // instructions that bring a step at RCAP rows
     static constexpr int SLOTS = NDMA * 64;                   // ... and the slots they fill
@@ -274,20 +277,24 @@ template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most ro
     uint32_t off[NDMA]; // byte offset in the planes of this lane's piece of instruction i in the step at K = 0
     int ucol[NDMA];     // its first K element inside the step
     const char *base;
+    size_t plane_bytes;
     int rows, npiece, kmax;
+    static_assert(!FAR || RCAP * UPS % 64 == 0, "an instruction's pieces are of one plane");
 
     // row0: first row of the tile; K: reduction length (a multiple of EPU)
     __device__ __forceinline__ void init(const GemmArgs &a, int row0, int K, int lane) {
-        rows = min(a.R - row0, RCAP);
+        const int live = min(a.R - row0, RCAP);
+        rows = FAR ? RCAP : live;
         npiece = PL * rows * UPS;
         kmax = K - EPU;
+        plane_bytes = a.act_plane * sizeof(T);
         base = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + (size_t)row0 * a.ld_act);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
             const int p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
             const int plane = p / (rows * UPS), rem = p - plane * rows * UPS, row = rem / UPS, pos = rem % UPS;
             ucol[i] = (pos ^ (row & (UPS - 1))) * EPU;
-            off[i] = (uint32_t)((plane * a.act_plane + (size_t)row * a.ld_act + ucol[i]) * sizeof(T));
+            off[i] = (uint32_t)(((FAR ? 0 : plane * a.act_plane) + (size_t)min(row, live - 1) * a.ld_act + ucol[i]) * sizeof(T));
         }
     }
     __device__ __forceinline__ static void clear(unsigned char *region, int lane) {
@@ -300,7 +307,7 @@ template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most ro
         const char *b = base + (size_t)k0 * sizeof(T);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i)
-            if (i * 64 < npiece) dma16(b, tail ? off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)) : off[i], to + i * 1024);
+            if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, tail ? off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)) : off[i], to + i * 1024);
     }
     // byte offset in a step's region of row c's unit `unit` of plane pl
     __device__ __forceinline__ int operand_offset(int c, int unit, int pl) const {
@@ -670,7 +677,7 @@ __device__ __forceinline__ u32x4 w4_to_bf16x8_plus136(uint32_t x) {
 }
 constexpr float W4_BIAS = 136.0f;
 
-template <int EPI, int NW, int NB, int RCAP>
+template <int EPI, int NW, int NB, int RCAP, bool FAR = false>
 __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
@@ -729,7 +736,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
     const int ngroups = K / 128;
     const int nsteps = (ngroups + 1) / 2; // two scale groups (a 128-byte line of a weight row) per step
     const int rot = k_rotation(nsteps);   // (see gemm_kernel)
-    typedef ActStage<T, 32, RCAP> Stage;
+    typedef ActStage<T, 32, RCAP, FAR> Stage;
     constexpr int SBASE = NT * 2048, WBYTES = SBASE + 256, SBYTES = WBYTES + Stage::BYTES;
     __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     Stage stage;
@@ -1540,11 +1547,13 @@ template <int EPI> static int launch_gemm_w8(const GemmArgs &a, hipStream_t st) 
 // one buffer per wave: 8 or 12 waves for the residual projections (12 with the small staging area of at most 5 rows), 4 otherwise
 template <int EPI, int NW, int NW5 = NW> static void launch_w4(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
     if (a.R <= 5) // the K + 1 = 5 rows of the usual verify pass: the smaller staging area lets a compute unit hold more workgroups
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW5, 1, 5>), dim3(tiles, row_tiles), dim3(NW5 * 64), 0, st, a);
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW5, 1, 5>), dim3(tiles), dim3(NW5 * 64), 0, st, a);
     else if (a.R <= 8)
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 8>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
+    else if (row_tiles <= 1)
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16>), dim3(tiles), dim3(NW * 64), 0, st, a);
     else
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
+        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16, true>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
 }
 
 template <int EPI> static int launch_gemm_w4(const GemmArgs &a, hipStream_t st) {

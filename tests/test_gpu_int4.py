@@ -121,3 +121,45 @@ def test_int4_configurations_that_are_refused():
     gm = sv.Model(shape, w, max_rows=16, max_pos=64, int4_weights=True)
     with pytest.raises(sv.SpecVerifyError):
         sv.ss_model_set_persistent(gm, True)
+
+
+@pytest.mark.parametrize("B,M", [(1, 16), (17, 1), (3, 8), (8, 9)])      # a full row tile; one row, half a tile and half a tile behind full ones
+def test_int4_head_whose_columns_are_no_multiple_of_four(B, M):
+    """1001 columns: the kernel of larger calls reads a lane's four scales at once and cannot take them, so every row tile streams
+    the head again."""
+    shape = si.DecoderShape(1, 256, 4, 64, 384, 1001, dtype="bf16")
+    w = si.decoder_weights(shape, 54)
+    om = oracle.Model(shape, w, int4_weights=True)
+    gm = sv.Model(shape, weights_to_device(w), max_rows=80, max_pos=64, int4_weights=True)
+    toks = si.token_ids(54, f"t{B}x{M}", (B, M), shape.vocab).numpy().astype(np.int32)
+    got = sv.ss_verify_forward(gm, sv.KVCache(gm, B, 64), torch.from_numpy(toks).to(dev()), M).cpu().numpy()
+    for b in range(B):
+        assert maxabs(got[b], om.forward(om.new_kv(64), toks[b])) < 2e-2, b
+
+
+@pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.mem_get_info()[0] < 100 << 30, reason="the model's buffers take 60 GB")
+def test_more_than_16_rows_of_a_model_whose_activation_planes_pass_4_gib():
+    """Scales that the kernel of larger calls cannot read four at a time (a head of 66 columns, a scale array that is only 4-byte
+    aligned) in a model sized for so many rows that one activation plane of max_rows x d_model holds more than 2^32 bytes: the bits that
+    the same weights give in a small model."""
+    shape = si.DecoderShape(1, 32768, 4, 64, 256, 66, dtype="bf16")
+    g = torch.Generator(device=dev()).manual_seed(53)
+    n = lambda *s: (torch.randn(s, generator=g, device=dev()) * 0.02).to(torch.bfloat16)
+    L = {"g1": torch.ones(32768, device=dev()), "g2": torch.ones(32768, device=dev())}
+    for name, sname, s in (("wqkv", "sqkv", (768, 32768)), ("wo", "so", (32768, 256)), ("wgu", "sgu", (512, 32768)), ("wd", "sd", (32768, 256))):
+        L[name], L[sname] = sv.ss_quantize_rows_int4(n(*s))
+    arena = torch.zeros(L["sqkv"].numel() + 1, device=dev())
+    arena[1:] = L["sqkv"].flatten()
+    L["sqkv"] = arena[1:].view_as(L["sqkv"])
+    ends = {"embed": n(66, 32768), "gf": torch.ones(32768, device=dev()), "lm_head": n(66, 32768)}
+    toks = si.token_ids(53, "t", (2, 10), shape.vocab).to(dev())
+    outs = []
+    for max_rows in (32, 65552):
+        assert max_rows == 32 or max_rows * shape.d_model * 2 > 1 << 32
+        gm = sv.Model(shape, dict(ends), max_rows=max_rows, max_pos=32, packed_layers=[L], int4_weights=True)
+        kv = sv.KVCache(gm, 2, 16)
+        outs.append((sv.ss_verify_forward(gm, kv, toks, 10).clone(), kv.buf.clone()))
+        torch.cuda.synchronize()
+        del kv, gm
+    assert bool(torch.isfinite(outs[0][0]).all())
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
