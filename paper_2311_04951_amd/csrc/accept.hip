@@ -964,19 +964,25 @@ bool launch_softmax_sample(const float *logits, int B, int V, float inv_t, float
     return true;
 }
 
-// (value, index) of the largest of x[0 .. n) plus `first`, the lowest index on ties; NaNs lose to everything (all NaN: index
-// `first`).  ARGMAX_UNROLL independent loads per thread are in flight: a row is read once and the kernel is bound by how many
-// loads a compute unit has outstanding.  Valid in thread 0.
-constexpr int ARGMAX_UNROLL = 8;
-template <int THREADS> __device__ __forceinline__ void block_argmax_range(const float *x, int n, int first, float &best, int &bi) {
-    best = -INFINITY;
-    bi = 0x7fffffff;
-    auto see = [&](float v, int i) {
-        if (v > best || (v == best && i < bi)) {
+// Running argmax: the lowest index on ties; NaNs lose to everything, -inf included (nothing but NaNs: NO_INDEX, which loses in turn
+// when pieces of a row meet)
+constexpr int NO_INDEX = 0x7fffffff;
+struct Argmax {
+    float best = -INFINITY;
+    int index = NO_INDEX;
+    __device__ __forceinline__ void see(float v, int i) {
+        if (v > best || (v == best && i < index)) {
             best = v;
-            bi = i;
+            index = i;
         }
-    };
+    }
+    __device__ __forceinline__ int token() const { return index == NO_INDEX ? 0 : index; }
+};
+// (value, index) of the largest of x[0 .. n), indices from `first`.  ARGMAX_UNROLL independent loads per thread are in flight: a row
+// is read once and the kernel is bound by how many loads a compute unit has outstanding.  Valid in thread 0.
+constexpr int ARGMAX_UNROLL = 8;
+template <int THREADS> __device__ __forceinline__ Argmax block_argmax_range(const float *x, int n, int first) {
+    Argmax a;
     if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
         const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
         const int n4 = n / 4;
@@ -987,44 +993,43 @@ template <int THREADS> __device__ __forceinline__ void block_argmax_range(const 
 #pragma unroll
             for (int j = 0; j < ARGMAX_UNROLL; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) see(t[j][e], 4 * min(i0 + THREADS * j, n4 - 1) + e);
+                for (int e = 0; e < 4; ++e) a.see(t[j][e], 4 * min(i0 + THREADS * j, n4 - 1) + e);
         }
-        if ((int)threadIdx.x < n - 4 * n4) see(x[4 * n4 + threadIdx.x], 4 * n4 + threadIdx.x);
+        if ((int)threadIdx.x < n - 4 * n4) a.see(x[4 * n4 + threadIdx.x], 4 * n4 + threadIdx.x);
     } else {
         for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * ARGMAX_UNROLL) {
             float t[ARGMAX_UNROLL];
 #pragma unroll
             for (int j = 0; j < ARGMAX_UNROLL; ++j) t[j] = x[min(i0 + THREADS * j, n - 1)];
 #pragma unroll
-            for (int j = 0; j < ARGMAX_UNROLL; ++j) see(t[j], min(i0 + THREADS * j, n - 1));
+            for (int j = 0; j < ARGMAX_UNROLL; ++j) a.see(t[j], min(i0 + THREADS * j, n - 1));
         }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-        const float b2 = __shfl_xor(best, o);
-        const int i2 = __shfl_xor(bi, o);
-        see(b2, i2);
+        const float b2 = __shfl_xor(a.best, o);
+        const int i2 = __shfl_xor(a.index, o);
+        a.see(b2, i2);
     }
     __shared__ float sm_val[THREADS / 64];
     __shared__ int sm_idx[THREADS / 64];
     if ((threadIdx.x & 63) == 0) {
-        sm_val[threadIdx.x >> 6] = best;
-        sm_idx[threadIdx.x >> 6] = bi;
+        sm_val[threadIdx.x >> 6] = a.best;
+        sm_idx[threadIdx.x >> 6] = a.index;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < THREADS / 64; ++w) see(sm_val[w], sm_idx[w]);
-        bi = first + (bi == 0x7fffffff ? 0 : bi);
+        for (int w = 1; w < THREADS / 64; ++w) a.see(sm_val[w], sm_idx[w]);
+        if (a.index != NO_INDEX) a.index += first;
     }
+    return a;
 }
 
 // one workgroup per row (a draft's call has one to a few rows, and a second launch that merges segments costs 4.5 us:
 // 32000 logits 12.9 -> 6 us with the loads in flight together)
 __global__ __launch_bounds__(SAMPLE_THREADS) void argmax_rows_kernel(const float *x, int64_t ld, int V, int32_t *out) {
-    float best;
-    int bi;
-    block_argmax_range<SAMPLE_THREADS>(x + (size_t)blockIdx.x * ld, V, 0, best, bi);
-    if (threadIdx.x == 0) out[blockIdx.x] = bi;
+    const Argmax a = block_argmax_range<SAMPLE_THREADS>(x + (size_t)blockIdx.x * ld, V, 0);
+    if (threadIdx.x == 0) out[blockIdx.x] = a.token();
 }
 void launch_argmax_rows(const float *logits, int64_t ld, int B, int V, int32_t *token_out, hipStream_t st) {
     if (B <= 0) return;
@@ -1036,10 +1041,8 @@ void launch_argmax_rows(const float *logits, int64_t ld, int B, int V, int32_t *
 // index order: one workgroup per row left a row's stream to one compute unit (72 rows of 128256 logits: 45.6 us = 0.8 TB/s).
 __global__ __launch_bounds__(256) void argmax_segment_kernel(const float *x, int V, int seg_len, float2 *part) {
     const int r0 = blockIdx.x * seg_len;
-    float best;
-    int bi;
-    block_argmax_range<256>(x + (size_t)blockIdx.y * V + r0, min(seg_len, V - r0), r0, best, bi);
-    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(best, __int_as_float(bi));
+    const Argmax a = block_argmax_range<256>(x + (size_t)blockIdx.y * V + r0, min(seg_len, V - r0), r0);
+    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(a.best, __int_as_float(a.index));
 }
 // one wavefront per sequence, lane i = position i (K + 1 <= 16 positions)
 // row_argmax: the rows' tokens where they were not cut (part NULL)
@@ -1049,10 +1052,12 @@ __global__ __launch_bounds__(64) void greedy_finish_kernel(const float2 *part, i
     const size_t row = (size_t)b * (K + 1) + i;
     int tok;
     if (part) {
-        float2 best = part[row * nseg];
-        for (int s = 1; s < nseg; ++s)
-            if (part[row * nseg + s].x > best.x) best = part[row * nseg + s]; // (equal values: the earlier segment holds the lower index)
-        tok = __float_as_int(best.y);
+        Argmax a;
+        for (int s = 0; s < nseg; ++s) {
+            const float2 p = part[row * nseg + s];
+            a.see(p.x, __float_as_int(p.y));
+        }
+        tok = a.token();
     } else {
         tok = row_argmax[row];
     }

@@ -113,3 +113,25 @@ def test_few_rows_of_a_model_whose_activation_planes_pass_4_gib():
         torch.cuda.synchronize()
         del kv, gm
     assert torch.equal(outs[0], outs[1])
+
+
+def test_greedy_acceptance_of_rows_that_hold_nothing_but_nan_and_minus_infinity():
+    """NaNs lose to everything, minus infinity included, wherever the cuts between segments fall; a row of NaNs alone gives index 0."""
+    V = 20000                                                       # four segments of 5000 in a workspace that holds their pairs
+    x = torch.full((1, 4, V), -torch.inf)
+    x[0, 0, :5000] = torch.nan                                      # the whole first segment
+    x[0, 1, :12345] = torch.nan                                     # two segments and part of the third
+    x[0, 2] = torch.nan
+    x[0, 2, V - 1] = -torch.inf                                     # one number, the last
+    x[0, 3] = torch.nan
+    want = [5000, 12345, V - 1, 0]
+    for K in range(4):
+        rows = x[:, 3 - K:].contiguous().to(dev())                  # every row is a position's and, in its turn, the first mismatch
+        best = want[3 - K:]
+        for n in range(K + 1):
+            d = torch.tensor([best[:K]], dtype=torch.int32)
+            if n < K:
+                d[0, n] += 1
+            for ws in (None, sv.ss_workspace_init(torch.empty(256 + 65536 + 4 * (K + 1) + 16, dtype=torch.uint8, device=dev()))):
+                na, nx = sv.ss_greedy_accept(rows, d.to(dev()), ws=ws)
+                assert (na.tolist(), nx.tolist()) == ([n], [best[n]]), (K, n, ws is None)
