@@ -615,8 +615,10 @@ constexpr int TP_LIST = 2048, TP_RANK = 512; // entries of the boundary bin that
 
 // An entry's weight as the bits of a float, f = trunc(min(max(p * 2^32, 0), 2^32)): whole numbers of at most 24 significant bits, so
 // f orders like the integer weight min(trunc(p * 2^32), 2^32 - 1) and is equal where that is (2^32 stands for 2^32 - 1).  Four
-// instructions; a conversion to 64 bits takes some twenty, and a row has one compute unit to do them on.
-__device__ __forceinline__ uint32_t tp_key(float p) { return f2u(truncf(fminf(fmaxf(__fmul_rn(p, 4294967296.0f), 0.f), 4294967296.0f))); }
+// instructions; a conversion to 64 bits takes some twenty, and a row has one compute unit to do them on.  The product is a
+// fused multiply-add with +0, which makes +0 of a -0: a maximum of -0 and +0 may be either, and the bits of -0 would be the largest
+// key of all (a comparison and a selection for that cost 3 - 9 % of the kernel, the multiply-add nothing).
+__device__ __forceinline__ uint32_t tp_key(float p) { return f2u(truncf(fminf(fmaxf(__fmaf_rn(p, 4294967296.0f, 0.0f), 0.f), 4294967296.0f))); }
 __device__ __forceinline__ uint32_t tp_weight(uint32_t key) { return key >= 0x4f800000u ? 0xffffffffu : (uint32_t)u2f(key); }
 // monotone bin of a key >= 1.0: exponent and the six bits behind it.  2^0 .. 2^32 would be 2049 bins; 1.0 is alone in the 64 of its
 // exponent, so everything above moves down by one

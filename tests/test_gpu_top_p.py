@@ -122,3 +122,17 @@ def test_both_filters_where_the_route_changes_equal_oracle_bit_for_bit(V):
             assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p, out).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p, at)
         for k in sorted({1, max(1, V // 100), max(1, (2 * V) // 3), max(1, V - 1)} - {V}):
             assert np.array_equal(_bits(sv.ss_top_k_filter(g, k, out).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k, at)
+
+
+@pytest.mark.parametrize("V", [1, 5, 4096, 32770])
+def test_negative_zeros_have_no_weight(V):
+    """-0.0 among the entries (what a masked product leaves): no weight, whatever a maximum of -0 and +0 is."""
+    rows = oracle.softmax(si.normal(9, f"z{V}", (3, V), 2.0).numpy(), 1.0)
+    rows[0, ::3] = -0.0
+    rows[1, : V // 2 + 1] = -0.0
+    rows[2] = -0.0                                                               # nothing has a weight: returned unchanged
+    g = torch.from_numpy(rows).to(dev())
+    for top_p in (0.01, 0.5, 0.99):
+        assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p)
+    for k in sorted({1, V // 2, V - 1} - {0, V}):                                # (beyond half of V: into the tokens without a weight)
+        assert np.array_equal(_bits(sv.ss_top_k_filter(g, k).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k)
