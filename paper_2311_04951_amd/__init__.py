@@ -311,7 +311,9 @@ def workspace(device, rows: int, vocab: int):
     """A device workspace for the calls without a handle: one per (device, stream), kept between calls and
     replaced by a larger one when a call needs more (memory plumbing: the C calls never allocate)."""
     need = ss_workspace_bytes(rows, vocab)
-    key = (getattr(device, "index", device), _stream(None))
+    if not isinstance(device, torch.device):
+        device = torch.device(device)
+    key = (device.type, torch.cuda.current_device() if device.index is None else device.index, _stream(None))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < need:
         ws = torch.empty(max(need, 1 << 20), dtype=torch.uint8, device=device)

@@ -191,3 +191,10 @@ def test_shutdown_releases_live_handles_and_later_releases_are_no_ops():
     kv = sv.KVCache(gm, 1, 32)
     out = sv.ss_verify_forward(gm, kv, torch.zeros((1, 4), dtype=torch.int32, device=dev()), 4)
     assert bool(torch.isfinite(out).all())
+
+
+def test_one_workspace_per_device_however_the_device_is_named():
+    ws = sv.workspace(dev(), 4, 1000)
+    at = torch.zeros(1, device=dev()).device                         # the device as a tensor carries it
+    names = [torch.device("cuda", 0), at, "".join(["cuda", ":0"]), "".join(["cuda", ":0"]), "cuda", torch.device("cuda"), 0]
+    assert all(sv.workspace(d, 4, 1000) is ws for d in names)
