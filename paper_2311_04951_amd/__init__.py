@@ -292,8 +292,12 @@ _workspaces = {}
 
 
 @functools.lru_cache(maxsize=256)
+def _workspace_bytes(rows: int, vocab: int) -> int:
+    return lib().ss_workspace_bytes(rows, vocab)
+
+
 def ss_workspace_bytes(rows: int, vocab: int) -> int:
-    return lib().ss_workspace_bytes(int(rows), int(vocab))
+    return _workspace_bytes(int(rows), int(vocab))      # (the numbers are remembered, not the objects that they came in)
 
 
 def ss_workspace_init(ws, stream=None):

@@ -106,3 +106,16 @@ def test_host_lengths_are_marshalled_as_numpy_would():
     for bad in ([2 ** 31], [2 ** 40, 1]):
         with pytest.raises(OverflowError):
             sv._host_i32(bad)
+
+
+def test_workspace_bytes_are_those_of_the_numbers_passed_now():
+    """Anything that converts to an integer is a row count, also an array or a tensor that changes between two calls."""
+    import numpy as np
+    import torch
+    want = sv.ss_workspace_bytes(5, 1000), sv.ss_workspace_bytes(500, 1000)
+    assert want[0] != want[1]
+    for rows in (torch.tensor(5), np.array(5)):
+        assert sv.ss_workspace_bytes(rows, 1000) == want[0]
+        rows += 495
+        assert sv.ss_workspace_bytes(rows, 1000) == want[1]
+    assert sv.ss_workspace_bytes(np.int64(5), vocab=np.int32(1000)) == want[0]
