@@ -221,12 +221,12 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_
 // STREAM: the non-temporal bit, for weight lines, which are used once (the activation lines by every workgroup): 7B-shaped bf16 pass
 // 3.04 -> 2.85 ms at 5 rows, 2.97 -> 2.75 at 1 row (int8 -3.6 %, int4 -2.5 %); the scope bits on top of it change nothing.
 template <bool STREAM = false> __device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
-    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 
 __device__ __forceinline__ void dma4(const void *base, uint32_t off, uint32_t lds) { // the same, a word per lane
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_waitcnt vmcnt(N), N < 64
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
