@@ -578,8 +578,9 @@ void launch_accept(const AcceptArgs &a, unsigned long long *partial, size_t avai
 // division per element.  One workgroup per row looks for the weight of the last kept token:
 //   1. a histogram over 2048 logarithmic bins (position of the leading bit, the six bits behind it), which spreads the weights of
 //      a softmax over hundreds of bins (the top eleven bits of the weight put all but a few tokens into one);
-//   2. the tokens of the bin that holds the boundary go to a list in LDS, usually some hundred, and the remaining bits are
-//      found by digits of eleven bits over that list - or over the row when they do not fit (a row of equal weights);
+//   2. the tokens of the bin that holds the boundary go to a list in LDS, usually some hundred, and the last kept one is found by
+//      ranking them; where they are many, by digits of eleven of the remaining bits over that list - or over the row when they do not
+//      fit (a row of equal weights);
 //   3. one pass writes the row.
 // All sums are integers, so the result does not depend on the order in which threads add.  A row of up to 32768 entries stays in
 // LDS between the passes; a longer one is read again from the caches in each (16-byte loads where the rows allow).  Bound by the one compute unit that a row has; a split over several would need launches between the passes at
@@ -611,7 +612,8 @@ __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long
 }
 
 constexpr int TP_FITS = 32768; // longest row that stays in LDS
-constexpr int TP_LIST = 2048, TP_RANK = 512; // entries of the boundary bin that fit LDS; up to which they are ranked one against all
+// entries of the boundary bin that fit LDS; up to which they are ranked one against all (512 take 10 us, the digits 3 whatever their number)
+constexpr int TP_LIST = 2048, TP_RANK = 128;
 
 // An entry's weight as the bits of a float, f = trunc(min(max(p * 2^32, 0), 2^32)): whole numbers of at most 24 significant bits, so
 // f orders like the integer weight min(trunc(p * 2^32), 2^32 - 1) and is equal where that is (2^32 stands for 2^32 - 1).  Four
@@ -633,12 +635,16 @@ __device__ __forceinline__ float tp_divide(float x, float Z, float rZ) {
     q = __fmaf_rn(__fmaf_rn(-q, Z, x), rZ, q);
     return __fmaf_rn(__fmaf_rn(-q, Z, x), rZ, q);
 }
-// Four entries from v on (absent ones read as 0)
-template <bool VEC> __device__ __forceinline__ f32x4 tp_load4(const float *p, int v, int V) {
-    if (VEC && v + 3 < V) return *reinterpret_cast<const f32x4 *>(p + v);
+// A row in units of four entries, unit i to thread i % TP_THREADS: neighbouring entries where 16-byte accesses are possible, else
+// entries TP_THREADS apart (a wavefront's word loads then cover whole lines; four neighbouring words per lane took four times the
+// requests: top-k of 5 rows of 50257 entries 49 -> 29 us).  Entry e of unit i:
+template <bool VEC> __device__ __forceinline__ int tp_entry(int i, int e) { return VEC ? 4 * i + e : (i & ~(TP_THREADS - 1)) * 4 + e * TP_THREADS + (i & (TP_THREADS - 1)); }
+template <bool VEC> __device__ __forceinline__ int tp_units(int V) { return VEC ? (V + 3) / 4 : (V + 4 * TP_THREADS - 1) / (4 * TP_THREADS) * TP_THREADS; }
+template <bool VEC> __device__ __forceinline__ f32x4 tp_load4(const float *p, int i, int V) { // absent entries read as 0
+    if (VEC && 4 * i + 3 < V) return *reinterpret_cast<const f32x4 *>(p + 4 * i);
     f32x4 q;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) q[e] = v + e < V ? p[v + e] : 0.f;
+    for (int e = 0; e < 4; ++e) q[e] = tp_entry<VEC>(i, e) < V ? p[tp_entry<VEC>(i, e)] : 0.f;
     return q;
 }
 
@@ -651,22 +657,22 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     __shared__ Bin hist[TP_BINS];
     __shared__ unsigned long long sm_wave[TP_WAVES];
     __shared__ unsigned long long sm_above, sm_binw;
-    __shared__ uint32_t list[TP_LIST];
+    __shared__ __align__(16) uint32_t list[TP_LIST];
     __shared__ int sm_bin, sm_cut, sm_n;
     __shared__ f32x4 row[FITS ? TP_FITS / 4 : 1];
     const float *p = probs + (size_t)blockIdx.x * (size_t)ld_in;
     float *o = out + (size_t)blockIdx.x * (size_t)ld_out;
-    const int t = threadIdx.x, n4 = (V + 3) / 4;
+    const int t = threadIdx.x, n4 = tp_units<VEC>(V);
     // f(key) for every entry of the row.  Short loop bodies: 32 entries of a thread unrolled in registers were bound by the
     // fetch of instructions that a wavefront runs once (top-k 21 us against 16).
     auto each = [&](auto f) {
-        constexpr int U = FITS ? 2 : 4; // 16-byte loads in flight
+        constexpr int U = FITS || !VEC ? 2 : 4; // units in flight (of words: 2 x 4 loads)
         for (int i0 = t; i0 < n4; i0 += TP_THREADS * U) {
             f32x4 x[U];
 #pragma unroll
             for (int j = 0; j < U; ++j) {
                 const int i = i0 + TP_THREADS * j;
-                x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, 4 * i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
+                x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
             for (int j = 0; j < U; ++j)
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         for (int i0 = t; i0 < n4; i0 += TP_THREADS * 8) {
             f32x4 x[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = tp_load4<VEC>(p, 4 * min(i0 + TP_THREADS * j, n4 - 1), V);
+            for (int j = 0; j < 8; ++j) x[j] = tp_load4<VEC>(p, min(i0 + TP_THREADS * j, n4 - 1), V);
 #pragma unroll
             for (int j = 0; j < 8; ++j)
                 if (i0 + TP_THREADS * j < n4) row[i0 + TP_THREADS * j] = x[j]; // (read back by the same thread; clear() below has the barrier for others)
@@ -687,7 +693,39 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     auto unchanged = [&]() {
         for (int v = t; v < V; v += TP_THREADS) o[v] = p[v];
     };
-    auto count = [&](int bin, uint32_t key) { atomicAdd(&hist[bin], BY_COUNT ? (Bin)1 : (Bin)tp_weight(key)); };
+    auto add_of = [](uint32_t key) { return BY_COUNT ? (Bin)1 : (Bin)tp_weight(key); };
+    // The histogram of the row's entries with live(key), by bin(key).  Additions to one address are carried out one after another, and
+    // the weights of a flat row are all in one bin (32000 equal ones: 116 us for the row, 16 for one of a softmax): each wavefront looks
+    // at an entry per lane from all over the row, and where a quarter of those are in one bin it adds that bin's up in registers (43 us;
+    // the look takes 0.3 us, a vote at every entry took 20 - 40 % of the kernel).
+    uint32_t sample; // the key of one entry, the lanes' spread over the row
+    auto histogram = [&](auto live, auto bin) {
+        int hot = -1;
+        const bool l = live(sample);
+        const unsigned long long lanes = __ballot(l);
+        if (lanes) {
+            const int b = bin(sample);
+            const int first = __builtin_amdgcn_readlane(b, __ffsll((long long)lanes) - 1), last = __builtin_amdgcn_readlane(b, 63 - __clzll((long long)lanes));
+            const int n1 = __popcll(__ballot(l && b == first)), n2 = __popcll(__ballot(l && b == last));
+            if (max(n1, n2) >= 16) hot = n1 >= n2 ? first : last;
+        }
+        if (hot < 0) {
+            each([&](uint32_t key) {
+                if (live(key)) atomicAdd(&hist[bin(key)], add_of(key));
+            });
+        } else {
+            unsigned long long sum = 0;
+            each([&](uint32_t key) {
+                if (live(key)) {
+                    if (bin(key) == hot) sum += add_of(key);
+                    else atomicAdd(&hist[bin(key)], add_of(key));
+                }
+            });
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sum += shfl_xor_u64(sum, o);
+            if ((t & 63) == 0) atomicAdd(&hist[hot], (Bin)sum);
+        }
+    };
     auto clear = [&]() {
         hist[t] = 0;
         hist[t + TP_THREADS] = 0;
@@ -734,10 +772,16 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     };
 
     if (t == 0) sm_n = 0;
-    clear();
-    each([&](uint32_t key) {
-        if (key) count(tp_bin(key), key);
-    });
+    {
+        // the sample: the first entry of one of the thread's own units, the lanes' spread over the row
+        const int own = t + TP_THREADS * (int)((long long)(t & 63) * ((n4 - t + TP_THREADS - 1) / TP_THREADS) >> 6);
+        float x0 = 0.f;
+        if (own < n4 && tp_entry<VEC>(own, 0) < V) x0 = FITS ? row[own].x : p[tp_entry<VEC>(own, 0)];
+        list[t] = list[t + TP_THREADS] = 0;
+        clear();
+        sample = tp_key(x0);
+    }
+    histogram([](uint32_t key) { return key != 0; }, [](uint32_t key) { return tp_bin(key); });
     const int bin0 = choose(true);
     if (S == 0) { // nothing has a weight: the row is returned as it is
         unchanged();
@@ -749,31 +793,43 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     if (bin0 >= 0) {
         // the boundary bin's tokens to the list; top-k: the weight above the bin on the way
         uint32_t prefix = tp_bin_prefix(bin0);
-        unsigned long long mine = 0;
-        each([&](uint32_t key) {
-            const uint32_t k17 = key >> 17;
-            if (k17 >= prefix) {
-                if (k17 == prefix) {
-                    const int at = atomicAdd(&sm_n, 1);
-                    if (at < TP_LIST) list[at] = key;
-                } else if (BY_COUNT) {
-                    mine += tp_weight(key);
-                }
-            }
-        });
+        // more of them than the list holds, by what the bin holds and the largest weight in it (a flat row): no list
+        const bool crowded = binw > (unsigned long long)TP_LIST * (BY_COUNT ? 1u : tp_weight((prefix << 17) | 0x1ffffu));
         unsigned long long above_w = 0;
-        if (BY_COUNT) block_excl_scan(mine, sm_wave, above_w);
+        if (crowded) {
+            if (BY_COUNT) {
+                unsigned long long mine = 0;
+                each([&](uint32_t key) { mine += (key >> 17) > prefix ? tp_weight(key) : 0u; });
+                block_excl_scan(mine, sm_wave, above_w);
+            }
+        } else {
+            unsigned long long mine = 0;
+            each([&](uint32_t key) {
+                const uint32_t k17 = key >> 17;
+                if (k17 >= prefix) {
+                    if (k17 == prefix) {
+                        const int at = atomicAdd(&sm_n, 1);
+                        if (at < TP_LIST) list[at] = key;
+                    } else if (BY_COUNT) {
+                        mine += tp_weight(key);
+                    }
+                }
+            });
+            if (BY_COUNT) block_excl_scan(mine, sm_wave, above_w);
+        }
         __syncthreads();
-        const int n = sm_n;
+        const int n = crowded ? TP_LIST + 1 : sm_n;
         if (n <= TP_RANK) { // few: the token in whose turn the sum is reached finds itself
             if (t < n) {
                 const uint32_t key = list[t];
-                unsigned long long above = 0, equal = 0;
-                for (int i = 0; i < n; ++i) {
-                    const uint32_t other = list[i];
-                    const unsigned long long add = BY_COUNT ? 1ull : tp_weight(other);
-                    above += other > key ? add : 0ull;
-                    equal += other == key ? add : 0ull;
+                Bin above = 0, equal = 0;
+                for (int i = 0; i < n; i += 4) { // (the list is filled up with zeros)
+                    const u32x4 other = *reinterpret_cast<const u32x4 *>(list + i);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        above += other[e] > key ? add_of(other[e]) : (Bin)0;
+                        equal += other[e] == key ? add_of(other[e]) : (Bin)0;
+                    }
                 }
                 if (above < need && need <= above + equal) { // (equal tokens write the same)
                     sm_bin = (int)key;
@@ -786,17 +842,19 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
             need -= sm_above;
             binw = sm_binw;
             __syncthreads();
+        } else if (n <= TP_LIST && __syncthreads_and(list[t] == list[0] || t >= n) && __syncthreads_and(list[t + TP_THREADS] == list[0] || t + TP_THREADS >= n)) {
+            tau = list[0]; // all of them equal
         } else { // the 17 bits behind the bin's, by digits
             for (int low = 17; low > 0;) {
                 const int nb = low < 11 ? low : 11;
                 clear();
-                auto digit = [&](uint32_t key) {
-                    if ((key >> low) == prefix) count((int)((key >> (low - nb)) & ((1u << nb) - 1)), key);
-                };
+                const auto live = [&](uint32_t key) { return (key >> low) == prefix; };
+                const auto digit = [&](uint32_t key) { return (int)((key >> (low - nb)) & ((1u << nb) - 1)); };
                 if (n <= TP_LIST) {
-                    for (int i = t; i < n; i += TP_THREADS) digit(list[i]);
+                    for (int i = t; i < n; i += TP_THREADS)
+                        if (live(list[i])) atomicAdd(&hist[digit(list[i])], add_of(list[i]));
                 } else {
-                    each(digit);
+                    histogram(live, digit);
                 }
                 prefix = (prefix << nb) | (uint32_t)choose(false);
                 low -= nb;
@@ -857,32 +915,32 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         cut = sm_cut;
     }
     const float Z = __fmul_rn(__ull2float_rn(kept), 2.3283064365386963e-10f), rZ = __fdiv_rn(1.0f, Z);
-    constexpr int U = FITS ? 2 : 4;
+    constexpr int U = FITS || !VEC ? 2 : 4;
     for (int i0 = t; i0 < n4; i0 += TP_THREADS * U) {
         f32x4 x[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) { // (a thread reads what it writes: in place is fine)
             const int i = i0 + TP_THREADS * j;
-            x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, 4 * i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
+            x[j] = i < n4 ? (FITS ? row[i] : tp_load4<VEC>(p, i, V)) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const int v = 4 * (i0 + TP_THREADS * j);
+            const int i = i0 + TP_THREADS * j;
             f32x4 y;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t key = tp_key(x[j][e]);
-                const bool keep = key > tau || (key == tau && v + e <= cut);
+                const bool keep = key > tau || (key == tau && tp_entry<VEC>(i, e) <= cut);
                 float q = tp_divide(x[j][e], Z, rZ);
                 if (keep && (key < 0x3f800000u || key >= 0x4f800000u)) q = __fdiv_rn(x[j][e], Z); // outside its range (a kept token without a weight, or of 1 and more)
                 y[e] = keep ? q : 0.f;
             }
-            if (VEC && v + 3 < V) {
-                *reinterpret_cast<f32x4 *>(o + v) = y;
-            } else {
+            if (VEC && 4 * i + 3 < V) {
+                *reinterpret_cast<f32x4 *>(o + 4 * i) = y;
+            } else if (i < n4) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (v + e < V) o[v + e] = y[e];
+                    if (tp_entry<VEC>(i, e) < V) o[tp_entry<VEC>(i, e)] = y[e];
             }
         }
     }

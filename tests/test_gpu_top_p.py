@@ -136,3 +136,50 @@ def test_negative_zeros_have_no_weight(V):
         assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p)
     for k in sorted({1, V // 2, V - 1} - {0, V}):                                # (beyond half of V: into the tokens without a weight)
         assert np.array_equal(_bits(sv.ss_top_k_filter(g, k).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k)
+
+
+@pytest.mark.parametrize("V", [127, 1025, 4097, 32767, 36865])
+def test_crowded_bins_and_unaligned_rows_equal_oracle_bit_for_bit(V):
+    """Bins that hold a few tokens, some hundred (the bounds of what is ranked and listed) and most of the row, alone and between other
+    tokens, in rows whose entries are read word by word: equal weights, weights within one bin, every second entry equal, a flat tail."""
+    n = si.normal(11, f"c{V}", (8, V), 1.0).numpy()
+    n[0] *= 0.001                                                        # all within one bin or two
+    n[1] *= 0.01
+    n[2, ::2] = n[2, 0]
+    n[3, V // 8:] = -3.0
+    n[4] *= 4.0
+    n[5, :128] = 9.0 + 1e-4 * n[5, :128]                                 # 127 to 129 tokens in the top bin
+    n[6, :129] = 9.0 + 1e-4 * n[6, :129]
+    n[7, :2049] = 9.0 + 1e-4 * n[7, :2049]
+    rows = oracle.softmax(n, 1.0)
+    g = torch.from_numpy(rows).to(dev())
+    for top_p in (0.02, 0.5, 0.95):
+        assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p)
+    for k in sorted({1, 64, 100, 128, 200, V // 2, V - 2} - {V}):
+        if k < V:
+            assert np.array_equal(_bits(sv.ss_top_k_filter(g, k).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k)
+
+
+@pytest.mark.parametrize("V", [32000, 128256])
+def test_rows_of_equal_weights_take_no_multiple_of_the_time_of_others(V):
+    """Equal weights meet in one bin: were every entry an atomic addition of its own, the row would take seven to eleven times as long
+    as one of a softmax; with the additions of a wavefront put together it takes about three."""
+    def us(x, f):
+        out = torch.empty_like(x)
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                f(x, out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    usual = torch.softmax(2 * si.normal(10, f"u{V}", (1, V), 1.0).to(dev()), -1)
+    flat = torch.full_like(usual, 1.0 / V)
+    mixed = torch.where(torch.arange(V, device=dev()) % 2 == 0, flat, usual)     # ... and where they lie between others
+    for f in (lambda x, o: sv.ss_top_k_filter(x, 200, o), lambda x, o: sv.ss_top_p_filter(x, 0.9, o)):
+        times = [us(x, f) for x in (usual, flat, mixed)]
+        assert max(times) < 4.5 * times[0], times
