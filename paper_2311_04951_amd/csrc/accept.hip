@@ -990,10 +990,14 @@ void launch_sample_rows(const float *probs, int64_t ld, int B, int V, const floa
     hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_THREADS), 0, st, probs, ld, V, u, token_out);
 }
 
-// Softmax of a row and one token from it in one launch, for rows of one statistics segment (no workgroup waits for another):
+// Softmax of a row and one token from it in one launch, for short rows of one statistics segment (no workgroup waits for another):
 // the statistics, the probabilities and the token are those of the three launches it replaces, bit for bit (the first two by
 // the same operations in the same order, the token because the inverse CDF adds integers).  The row is read three times, twice
-// from the caches; at 1024 logits the three launches took 3 x 3.7 us back to back, this one one of them.
+// from the caches, by one workgroup, so the launches saved pay up to some length only.  A draft's call of one fp32 layer, 1 | 16
+// sequences, us, three launches -> this one: 1024 logits 38.1 -> 35.5 | 41.4 -> 37.8, 4096 42.8 -> 38.7 | 45.4 -> 42.0, 6000 44.5 -> 41.2 |
+// 47.4 -> 45.6, 8192 44.4 -> 43.7 | 47.3 -> 48.1, 12288 48.7 -> 51.6 | 52.1 -> 57.4, 16384 49.0 -> 55.5 | 54.0 -> 63.3.
+constexpr int SOFTMAX_SAMPLE_MAX = 6144;
+static_assert(SOFTMAX_SAMPLE_MAX <= STATS_SEG, "one statistics segment");
 __global__ __launch_bounds__(256) void softmax_sample_kernel(const float *logits, int V, float inv_t, float *probs, int64_t ld, const float *u,
                                                              int32_t *token_out) {
     __shared__ unsigned long long sm_wave[4];
@@ -1019,7 +1023,7 @@ __global__ __launch_bounds__(256) void softmax_sample_kernel(const float *logits
     if (threadIdx.x == 0) token_out[b] = tok;
 }
 bool launch_softmax_sample(const float *logits, int B, int V, float inv_t, float *probs, int64_t ld, const float *u, int32_t *token_out, hipStream_t st) {
-    if (V > STATS_SEG) return false;
+    if (V > SOFTMAX_SAMPLE_MAX) return false;
     if (B > 0) hipLaunchKernelGGL(softmax_sample_kernel, dim3(B), dim3(256), 0, st, logits, V, inv_t, probs, ld, u, token_out);
     return true;
 }

@@ -149,7 +149,7 @@ void launch_accept(const AcceptArgs &a, unsigned long long *partial, size_t avai
 // scratch: device memory of at least 4 bytes per row (B * (K + 1) rows), 8-byte aligned; more (8 bytes per row and segment) lets a row be cut into segments
 void launch_greedy_accept(const float *p_logits, const int32_t *draft, int B, int K, int V, void *scratch, size_t scratch_bytes,
                           int32_t *n_accepted, int32_t *next_token, hipStream_t st);
-// softmax rows (probs, leading dimension ld) and one token of each; false (nothing launched) when a row is longer than one statistics segment
+// softmax rows (probs, leading dimension ld) and one token of each; false (nothing launched) when a row is too long for one workgroup to pay
 bool launch_softmax_sample(const float *logits, int B, int V, float inv_t, float *probs, int64_t ld, const float *u, int32_t *token_out, hipStream_t st);
 // token ~ row by the integer inverse CDF (rows are probabilities), or argmax when greedy
 // rows of probabilities -> the rows restricted to their top-p nucleus and renormalised (P24 = top_p on a 2^-24 grid); out may alias probs

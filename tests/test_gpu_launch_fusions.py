@@ -78,7 +78,7 @@ def test_greedy_acceptance_by_segments(V, B, K):
         assert nx.tolist() == [int(best[b, n]) for b, n in enumerate(want_n)]
 
 
-@pytest.mark.parametrize("V", [64, 1000, 1027, 16384, 16388])      # one statistics segment (one launch), and the first that has two
+@pytest.mark.parametrize("V", [64, 1000, 1027, 6144, 6145, 16384, 16388])      # one launch up to 6144; one statistics segment up to 16384
 def test_a_draft_step_in_one_sampling_launch_gives_the_bits_of_the_separate_ones(V):
     shape = si.DecoderShape(1, 256, 4, 64, 344, V, dtype="f32")
     gm = sv.Model(shape, weights_to_device(si.decoder_weights(shape, seed=73)), max_rows=16, max_pos=64)
