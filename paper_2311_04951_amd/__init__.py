@@ -297,6 +297,8 @@ def _workspace_bytes(rows: int, vocab: int) -> int:
 
 
 def ss_workspace_bytes(rows: int, vocab: int) -> int:
+    if type(rows) is int and type(vocab) is int:
+        return _workspace_bytes(rows, vocab)
     return _workspace_bytes(int(rows), int(vocab))      # (the numbers are remembered, not the objects that they came in)
 
 
@@ -315,14 +317,17 @@ def workspace(device, rows: int, vocab: int):
     """A device workspace for the calls without a handle: one per (device, stream), kept between calls and
     replaced by a larger one when a call needs more (memory plumbing: the C calls never allocate)."""
     need = ss_workspace_bytes(rows, vocab)
-    if not isinstance(device, torch.device):
+    stream = _stream(None)
+    ws = _workspaces.get((device, stream))      # (kept under devices with an index only)
+    if ws is None:
         device = torch.device(device)
-    key = (device.type, torch.cuda.current_device() if device.index is None else device.index, _stream(None))
-    ws = _workspaces.get(key)
+        if device.index is None:
+            device = torch.device(device.type, torch.cuda.current_device())
+        ws = _workspaces.get((device, stream))
     if ws is None or ws.numel() < need:
         ws = torch.empty(max(need, 1 << 20), dtype=torch.uint8, device=device)
         ss_workspace_init(ws)
-        _workspaces[key] = ws
+        _workspaces[device, stream] = ws
     return ws
 
 
