@@ -456,8 +456,9 @@ constexpr int PART_THREADS = 256, PART_UNROLL = 4;
 // row the next token is drawn from (residual at the first rejection, else the bonus row).  The
 // vocabulary is cut into nseg segments so that a few sequences still fill the chip; integer partial
 // sums make the split invisible in the result.  Bound by the two rows' bytes behind the chain draft -> probabilities -> row: a
-// thread asks for all eight 16-byte pieces of a round before it uses the first (with the loads inside the bounds test of each
-// piece, two were in flight; 64 sequences x K 8 x 128256, the whole call 106.8 -> 102.9 us).
+// thread asks for the target's four 16-byte pieces of a round, then for the draft's four, none inside the bounds test of a piece (there,
+// two were in flight; the logits call of 8 sequences x K 4 x 32000 25.5 -> 22.7 us, of 64 x K 8 x 128256 101.3 -> 99.4).  All eight
+// asked for before the first is used measure the same.
 __global__ __launch_bounds__(PART_THREADS) void accept_partial_kernel(AcceptArgs a, int seg_len, unsigned long long *partial) {
     __shared__ int sm_rej;
     __shared__ unsigned long long sm_part[PART_THREADS / 64];
