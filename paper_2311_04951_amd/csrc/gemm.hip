@@ -1443,18 +1443,29 @@ template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStrea
     const int columns = 16 * tiles * (FUSED ? 2 : 1);
     // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80, where that pads less
     const int p80 = (a.R + 79) / 80 * 80, p128 = (a.R + 127) / 128 * 128;
-    const int bm = a.R <= 32 ? 32 : a.R <= 48 ? 48 : (a.R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
+    const int bm0 = a.R <= 32 ? 32 : a.R <= 48 ? 48 : (a.R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
+    // Many rows of a short K: few such blocks leave most of the chip idle and splitting K cannot fill it (a share of less than 256 entries
+    // is over before the ring is full, and the partial rows come on top), so the cost chooses the block as well.  1024 rows, a pass of
+    // 2 layers, us: d_model 128 133 -> 81, 256 161 -> 115, 512 205 -> 188, 1024 428 both (the column-per-wavefront kernel 127, 147, 250, 603)
+    const bool short_k = a.R > 512 && a.K <= 1024;
     // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
     const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
-    const int narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
+    const int rows[4] = {32, 48, 80, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
     TileChoice best{0, 1, 1e30};
-    for (int i = 0; i < (FUSED ? 3 : 2); ++i) {
-        const int cols = FUSED ? narrow[i] : plain[i];
-        if (bm == 128 && cols == 64 && FUSED) continue;
-        for (int ks = 1; ks <= (split_ok ? (EPI == EPI_QKV ? 4 : 8) : 1); ++ks) {
-            if (ks > 1 && sizeof(float) * (size_t)ks * a.R * a.N > a.splitk_ws_bytes) break;
-            const TileChoice c = tile_cost(bm, cols, columns, a.R, a.K, ks, EPI == EPI_QKV ? 4.5 : 0.0);
-            if (c.us < best.us) best = c;
+    int bm = bm0;
+    for (int b : rows) {
+        if (b != bm0 && !(short_k && b < bm0)) continue;
+        for (int i = 0; i < (FUSED ? 3 : 2); ++i) {
+            const int cols = FUSED ? narrow[i] : plain[i];
+            if (b == 128 && cols == 64 && FUSED) continue;
+            for (int ks = 1; ks <= (split_ok ? (EPI == EPI_QKV ? 4 : 8) : 1); ++ks) {
+                if (ks > 1 && (sizeof(float) * (size_t)ks * a.R * a.N > a.splitk_ws_bytes || (short_k && a.K < 256 * ks))) break;
+                const TileChoice c = tile_cost(b, cols, columns, a.R, a.K, ks, EPI == EPI_QKV ? 4.5 : 0.0);
+                if (c.us < best.us) {
+                    best = c;
+                    bm = b;
+                }
+            }
         }
     }
     if (bm == 32) return launch_tile_rows<EPI, 2>(a, columns, best, st);

@@ -59,3 +59,16 @@ def test_one_layer_against_64_bits(R, d, heads, ff):
     x = x + (gate * torch.sigmoid(gate) * up) @ L["wd"].double().t()
     assert float((out.double() - x).norm() / x.norm()) < 1e-5
     assert float((out.double() - x).abs().max()) < 1e-3
+
+
+@pytest.mark.parametrize("d,ff", [(128, 344), (256, 688), (768, 1032)])
+@pytest.mark.parametrize("batch,rows", [(32, 16), (33, 16), (57, 9), (64, 16)])      # 512 rows: the blocks of any call; 513 and more: those of the cost
+def test_many_rows_of_a_short_k_match_the_oracle(batch, rows, d, ff):
+    shape = si.DecoderShape(1, d, d // 64, 64, ff, 333, dtype="bf16")
+    w = si.decoder_weights(shape, seed=82)
+    gm = sv.Model(shape, weights_to_device(w), max_rows=batch * rows, max_pos=64)
+    om = oracle.Model(shape, w)
+    toks = si.token_ids(82, "t", (batch, rows), shape.vocab)
+    got = sv.ss_verify_forward(gm, sv.KVCache(gm, batch, 64), toks.to(dev()), rows)
+    for b in {0, batch // 2, batch - 1}:
+        assert maxabs(got[b], om.forward(om.new_kv(64), toks[b].numpy())) < 2e-2
