@@ -1388,14 +1388,14 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(GemmArgs a) {
 // row block on the chip reads the same weights from the L2 (34 on average).  A split adds its partial rows, written and read
 // once (8 MB/us), and for QKV a launch (4.5 us; a residual projection's is the RMSNorm that follows anyway).
 struct TileChoice {
-    int cols, ksplit;
+    int rows, cols, ksplit;
     double us;
 };
 static TileChoice tile_cost(int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
     const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols;
     const int rounds = (gx * gy * ksplit + 255) / 256;
     const double per = bm * 4 * 16e-6 + cols * 2 * (gy > 1 ? 34e-6 : 40e-6);
-    return TileChoice{cols, ksplit, rounds * (double)((K + ksplit - 1) / ksplit) * per + (ksplit > 1 ? launch_us + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
+    return TileChoice{bm, cols, ksplit, rounds * (double)((K + ksplit - 1) / ksplit) * per + (ksplit > 1 ? launch_us + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
 }
 
 template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int columns, int ksplit, hipStream_t st) {
@@ -1437,41 +1437,49 @@ template <int EPI, int RT> static int launch_tile_rows(const GemmArgs &a, int co
     }
 }
 
-// tiles: 16-column tiles (pairs of them for the fused epilogues)
-template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStream_t st) {
-    constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV;
-    const int columns = 16 * tiles * (FUSED ? 2 : 1);
+// tiles: 16-column tiles (pairs of them for the fused epilogues); ws_bytes: room for partial rows (0: K is not split)
+static TileChoice choose_tile(int epi, int tiles, int R, int N, int K, size_t ws_bytes) {
+    const bool fused = epi == EPI_SWIGLU || epi == EPI_QKV;
+    const int columns = 16 * tiles * (fused ? 2 : 1);
     // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80, where that pads less
-    const int p80 = (a.R + 79) / 80 * 80, p128 = (a.R + 127) / 128 * 128;
-    const int bm0 = a.R <= 32 ? 32 : a.R <= 48 ? 48 : (a.R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
+    const int p80 = (R + 79) / 80 * 80, p128 = (R + 127) / 128 * 128;
+    const int bm0 = R <= 32 ? 32 : R <= 48 ? 48 : (R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
     // Many rows of a short K: few such blocks leave most of the chip idle and splitting K cannot fill it (a share of less than 256 entries
     // is over before the ring is full, and the partial rows come on top), so the cost chooses the block as well.  1024 rows, a pass of
     // 2 layers, us: d_model 128 133 -> 81, 256 161 -> 115, 512 205 -> 188, 1024 428 both (the column-per-wavefront kernel 127, 147, 250, 603)
-    const bool short_k = a.R > 512 && a.K <= 1024;
-    // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
-    const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
+    const bool short_k = R > 512 && K <= 1024;
     const int rows[4] = {32, 48, 80, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
-    TileChoice best{0, 1, 1e30};
-    int bm = bm0;
-    for (int b : rows) {
-        if (b != bm0 && !(short_k && b < bm0)) continue;
-        for (int i = 0; i < (FUSED ? 3 : 2); ++i) {
-            const int cols = FUSED ? narrow[i] : plain[i];
-            if (b == 128 && cols == 64 && FUSED) continue;
-            for (int ks = 1; ks <= (split_ok ? (EPI == EPI_QKV ? 4 : 8) : 1); ++ks) {
-                if (ks > 1 && (sizeof(float) * (size_t)ks * a.R * a.N > a.splitk_ws_bytes || (short_k && a.K < 256 * ks))) break;
-                const TileChoice c = tile_cost(b, cols, columns, a.R, a.K, ks, EPI == EPI_QKV ? 4.5 : 0.0);
-                if (c.us < best.us) {
-                    best = c;
-                    bm = b;
-                }
+    const int splits = epi == EPI_QKV ? 4 : epi == EPI_RESID ? 8 : 1;
+    TileChoice best{0, 0, 1, 1e30};
+    for (int bm : rows) {
+        if (bm != bm0 && !(short_k && bm < bm0)) continue;
+        for (int i = 0; i < (fused ? 3 : 2); ++i) {
+            const int cols = fused ? narrow[i] : plain[i];
+            if (bm == 128 && cols == 64 && fused) continue;
+            for (int ks = 1; ks <= splits; ++ks) {
+                if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
+                const TileChoice c = tile_cost(bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
+                if (c.us < best.us) best = c;
             }
         }
     }
-    if (bm == 32) return launch_tile_rows<EPI, 2>(a, columns, best, st);
-    if (bm == 48) return launch_tile_rows<EPI, 3>(a, columns, best, st);
-    if (bm == 80) return launch_tile_rows<EPI, 5>(a, columns, best, st);
+    return best;
+}
+template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStream_t st) {
+    const int columns = 16 * tiles * (EPI == EPI_SWIGLU || EPI == EPI_QKV ? 2 : 1);
+    // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
+    const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
+    const TileChoice best = choose_tile(EPI, tiles, a.R, a.N, a.K, split_ok ? a.splitk_ws_bytes : 0);
+    if (best.rows == 32) return launch_tile_rows<EPI, 2>(a, columns, best, st);
+    if (best.rows == 48) return launch_tile_rows<EPI, 3>(a, columns, best, st);
+    if (best.rows == 80) return launch_tile_rows<EPI, 5>(a, columns, best, st);
     return launch_tile_rows<EPI, 8>(a, columns, best, st);
+}
+// For the tests, which have to meet every tile (not part of the library's interface): what a launch of R rows, N columns (3 * heads *
+// head_dim for EPI_QKV) and K entries takes: rows and columns of a workgroup, splits of K.
+extern "C" void ss_dev_gemm_tile(int epi, int R, int N, int K, size_t ws_bytes, int *out3) {
+    const TileChoice c = choose_tile(epi, epi == EPI_QKV ? N / 32 : (N + 15) / 16, R, N, K, N % 16 == 0 ? ws_bytes : 0);
+    out3[0] = c.rows; out3[1] = c.cols; out3[2] = c.ksplit;
 }
 
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);

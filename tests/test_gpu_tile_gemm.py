@@ -1,5 +1,5 @@
-"""Calls of more than 16 rows with bf16 matrices: every tile of the GEMM (32, 48, 80 and 128 rows per workgroup, both column counts,
-K split and not), ragged rows, columns and K."""
+"""Calls of more than 16 rows with bf16 matrices: every tile of the GEMM (32, 48, 80 and 128 rows per workgroup with every column count
+that there is, K split and not: test_tile_coverage.py asks the library which tile each shape below takes), ragged rows, columns and K."""
 import pytest
 import torch
 
@@ -34,8 +34,14 @@ def test_ragged_batches_match_the_oracle(batch, rows):
             assert maxabs(got[b], ref) < 2e-2 and maxabs(got[b], ref) < 2e-2 * abs(ref).max()
 
 
-@pytest.mark.parametrize("R", [17, 33, 49, 72, 81, 128, 160, 256])
-@pytest.mark.parametrize("d,heads,ff", [(4096, 32, 1032), (1536, 12, 4104)])      # K split four ways and less; columns and K that end inside a tile
+LAYERS = [(R, d, heads, ff) for d, heads, ff in ((4096, 32, 1032), (1536, 12, 4104)) for R in (17, 33, 49, 72, 81, 128, 160, 256)]
+# what those leave out: short K (few rows, many columns: wide tiles, no split), 7B- and 13B-shaped gate/up, the widest there is
+LAYERS += [(17, 136, 8, 11008), (33, 136, 8, 11008), (81, 136, 8, 13824), (129, 136, 8, 11008), (17, 136, 64, 65536), (33, 136, 64, 65536), (49, 136, 64, 344),
+           (17, 1096, 16, 344), (33, 1096, 16, 344), (129, 136, 40, 344), (1024, 2056, 16, 344), (144, 4096, 32, 11008), (256, 4096, 32, 11008)]
+HEADS = [(R, V, 72) for R in (17, 40, 72, 200) for V in (333, 32000, 50257)]      # rows, columns, K
+
+
+@pytest.mark.parametrize("R,d,heads,ff", LAYERS)      # K split four ways and less; columns and K that end inside a tile
 def test_one_layer_against_64_bits(R, d, heads, ff):
     """A whole layer without cached positions, one row per sequence: the attention of a row is its own value, so the layer is four
     products.  bf16 matrices are exact, activations carry 16 bits (two planes), sums 32: 1e-5 relative."""
@@ -59,6 +65,20 @@ def test_one_layer_against_64_bits(R, d, heads, ff):
     x = x + (gate * torch.sigmoid(gate) * up) @ L["wd"].double().t()
     assert float((out.double() - x).norm() / x.norm()) < 1e-5
     assert float((out.double() - x).abs().max()) < 1e-3
+
+
+@pytest.mark.parametrize("R,V,d", HEADS)
+def test_a_head_against_64_bits(R, V, d):
+    """No layers: the norm of the embedded row times the head.  Activations of 16 bits, sums of 72 products in 32: 1e-5 relative."""
+    g = torch.Generator(device=dev()).manual_seed(R + V)
+    n = lambda *s: (torch.randn(s, generator=g, device=dev()) * 0.02).to(torch.bfloat16)
+    ends = {"embed": n(V, d), "gf": torch.ones(d, device=dev()), "lm_head": n(V, d)}
+    gm = sv.Model(si.DecoderShape(0, d, 2, 32, 64, V, dtype="bf16"), ends, max_rows=R, max_pos=64, packed_layers=[])
+    toks = torch.randint(0, V, (R, 1), generator=g, device=dev(), dtype=torch.int32)
+    got = sv.ss_verify_forward(gm, sv.KVCache(gm, R, 16), toks, 1)[:, 0].double()
+    want = _rms(ends["embed"][toks[:, 0].long()].float(), ends["gf"], 1e-5) @ ends["lm_head"].double().t()
+    assert float((got - want).norm() / want.norm()) < 1e-5
+    assert float((got - want).abs().max()) < 1e-4
 
 
 @pytest.mark.parametrize("d,ff", [(128, 344), (256, 688), (768, 1032)])
