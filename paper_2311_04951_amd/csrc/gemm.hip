@@ -232,31 +232,20 @@ template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_wai
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-template <int N> __device__ __forceinline__ void wait_per(int per) { // N steps of `per` loads (of more than 12: waits for some of them as well)
+// Waits until at most one step of `per` loads (3 and more) is in flight (of more than 12: waits for some of it as well).
+__device__ __forceinline__ void wait_for_step(int per) {
     switch (per) {
-    case 2: wait_vmcnt_at_most<2 * N>(); break;
-    case 3: wait_vmcnt_at_most<3 * N>(); break;
-    case 4: wait_vmcnt_at_most<4 * N>(); break;
-    case 5: wait_vmcnt_at_most<5 * N>(); break;
-    case 6: wait_vmcnt_at_most<6 * N>(); break;
-    case 7: wait_vmcnt_at_most<7 * N>(); break;
-    case 8: wait_vmcnt_at_most<8 * N>(); break;
-    case 9: wait_vmcnt_at_most<9 * N>(); break;
-    case 10: wait_vmcnt_at_most<10 * N>(); break;
-    case 11: wait_vmcnt_at_most<11 * N>(); break;
-    default: wait_vmcnt_at_most<12 * N>(); break;
+    case 3: wait_vmcnt_at_most<3>(); break;
+    case 4: wait_vmcnt_at_most<4>(); break;
+    case 5: wait_vmcnt_at_most<5>(); break;
+    case 6: wait_vmcnt_at_most<6>(); break;
+    case 7: wait_vmcnt_at_most<7>(); break;
+    case 8: wait_vmcnt_at_most<8>(); break;
+    case 9: wait_vmcnt_at_most<9>(); break;
+    case 10: wait_vmcnt_at_most<10>(); break;
+    case 11: wait_vmcnt_at_most<11>(); break;
+    default: wait_vmcnt_at_most<12>(); break;
     }
-}
-// Waits until at most `ahead` steps of `per` loads each (per >= 2) are in flight; AHEAD: the most steps asked for.
-template <int AHEAD> __device__ __forceinline__ void wait_steps(int ahead, int per) {
-    if (ahead <= 0) {
-        wait_vmcnt_at_most<0>();
-    } else {
-        if (AHEAD >= 3 && ahead >= 3) { wait_per<3>(per); }
-        else if (AHEAD >= 2 && ahead >= 2) { wait_per<2>(per); }
-        else { wait_per<1>(per); }
-    }
-    asm volatile("" ::: "memory");
 }
 
 // Activations of the kernels for at most 16 rows, through a wave-private piece of LDS.  A step of a wave is UPS units
@@ -314,28 +303,30 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
         return c < rows ? ((pl * rows + c) * UPS + (unit ^ (c & (UPS - 1)))) * 16 : SLOTS * 16;
     }
 };
-// A wavefront's steps of K: every NW-th of nst, through a ring of NB buffers of its own.  request(i, buffer) asks for its i-th step,
-// use(i, buffer) multiplies it; between them the step's loads are waited for, the NB - 1 younger steps stay in flight.  `per`: loads
-// of a step.  prologue() runs behind the first requests.
+// A wavefront's n steps of K through a ring of NB (one or two) buffers of its own.  request(i, buffer) asks for its i-th step, use(i, buffer)
+// multiplies it; between them the step's loads are waited for, with two buffers the next step's stay in flight.  `per`: loads of a step.
+// prologue() runs behind the first request.
 template <int NB, class Request, class Use, class Prologue>
 __device__ __forceinline__ void ring_walk(int n, int per, Request request, Use use, Prologue prologue) {
-    constexpr int AHEAD = NB > 1 ? NB - 1 : 1; // steps requested in front of the first
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i)
-        if (i < n) request(i, i);
+    static_assert(NB == 1 || NB == 2, "a third buffer made every launch slower: no counted wait for two steps");
+    if (n > 0) request(0, 0);
     prologue();
     for (int i = 0, buf = 0; i < n; ++i) {
-        if (NB > 1 && i + NB - 1 < n) {
+        const bool ahead = NB == 2 && i + 1 < n;
+        if (ahead) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // what was read from the buffer that is filled now has arrived
-            request(i + NB - 1, buf == 0 ? NB - 1 : buf - 1);
+            request(i + 1, buf ^ 1);
+            wait_for_step(per);
+        } else {
+            wait_vmcnt_at_most<0>();
         }
-        wait_steps<NB - 1>(NB > 1 ? min(NB - 1, n - 1 - i) : 0, per);
+        asm volatile("" ::: "memory");
         use(i, buf);
         if (NB == 1 && i + 1 < n) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             request(i + 1, 0);
         }
-        buf = buf == NB - 1 ? 0 : buf + 1;
+        if (NB == 2) buf ^= 1;
     }
 }
 
@@ -360,7 +351,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, const float (&r
 }
 
 // The kernel for at most 16 rows: NW = wavefronts per workgroup (interleaved over K), NB = buffers of a wavefront's ring of 128-byte
-// steps, RCAP = most rows (8 or 16: sizes the LDS); blockIdx.x = column tile (pair), blockIdx.y = row tile.
+// steps, RCAP = most rows (8 or 16: sizes the LDS); blockIdx.x = column tile (pair).
 // The weights go through LDS like the activations: loaded straight into MFMA operand layout, a load instruction takes
 // 64 bytes of each of 16 weight rows (four lanes per row), i.e. half a cache line per row; a load-to-LDS instruction
 // whose lane l brings unit l & 7 of row l >> 3 takes whole 128-byte lines of 8 rows, and two of them bring a step's
@@ -374,7 +365,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int rt = blockIdx.y;
     const int K = a.K;
 
     int n0[NT];
@@ -409,13 +399,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
     EpiPre pre;
-    if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, rt, pre);
+    if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, 0, pre);
     // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave from sums that are
     // asked for in front of the first steps and used behind their request (one memory round trip less than ahead of them)
     float rs = 1.0f;
     float4 nsq[NSQ4];
     const bool scaled = a.act_nsq && wave == 0;
-    if (scaled) nsq_prefetch(a, rt, nsq);
+    if (scaled) nsq_prefetch(a, 0, nsq);
 
     // Each wave takes 128-byte steps (two k-blocks) of every row, interleaved with the other waves.
     // Every workgroup starts at another place of K and wraps around (k_rotation): with all of them walking K in step,
@@ -429,7 +419,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
     constexpr int WBYTES = NT * 2048, SBYTES = WBYTES + Stage::BYTES;
     __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     Stage stage;
-    stage.init(a, rt * 16, K, lane);
+    stage.init(a, 0, K, lane);
     int rdw[2], rda[2][Stage::PL];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -492,7 +482,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[wave][t][v][lane] = acc[t][v];
     __syncthreads();
-    if (wave == 0) tile_epilogue<T, EPI, NW>(a, red, n0, rt, PRE ? &pre : nullptr, rs);
+    if (wave == 0) tile_epilogue<T, EPI, NW>(a, red, n0, 0, PRE ? &pre : nullptr, rs);
     move_lengths<EPI>(a);
 }
 
@@ -1486,8 +1476,8 @@ template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs
 
 // NW wavefronts per workgroup and NB buffers each, for calls of at most 8 rows and of 9 to 16
 template <typename T, int EPI, int NW, int NB, int NW16 = NW, int NB16 = NB> static void launch_narrow(const GemmArgs &a, int tiles, hipStream_t st) {
-    if (a.R <= 8) hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, NB, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_kernel<T, EPI, NW16, NB16, 16>), dim3(tiles, 1), dim3(NW16 * 64), 0, st, a);
+    if (a.R <= 8) hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, NB, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((gemm_kernel<T, EPI, NW16, NB16, 16>), dim3(tiles), dim3(NW16 * 64), 0, st, a);
 }
 
 template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipStream_t st) {
@@ -1539,17 +1529,19 @@ template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs
             const int ks = std::max(1, std::min(256 / std::max(wgs, 1), 4));
             return (double)(wgs * ks) / (double)((wgs * ks + 255) / 256 * 256);
         };
-        if ((small || FUSED) && fill(3) > fill(4) + 0.1) return launch_wide<T, EPI, 3, 5, QB>(a, tiles, row_tiles, st);
-        if (small || FUSED) return launch_wide<T, EPI, 4, 5, QB>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 8, 5, QB>(a, tiles, row_tiles, st);
+        if constexpr (!FUSED) {
+            if (!small) return launch_wide<T, EPI, 8, 5, QB>(a, tiles, row_tiles, st);
+        }
+        if (fill(3) > fill(4) + 0.1) return launch_wide<T, EPI, 3, 5, QB>(a, tiles, row_tiles, st);
+        return launch_wide<T, EPI, 4, 5, QB>(a, tiles, row_tiles, st);
     }
 }
 
 // waves and buffers per kind of epilogue, measured like those of launch_gemm_t; fewer waves at 9 to 16 rows, whose activations
 // take twice the LDS (O and down on average: 8 waves x 2 buffers 12.1, 16 x 1 11.5, 12 x 1 11.0 us)
 template <int EPI, int NW, int NB, int NW16 = NW> static void launch_w8(const GemmArgs &a, int tiles, hipStream_t st) {
-    if (a.R <= 8) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, NB, 8>), dim3(tiles, 1), dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW16, NB, 16>), dim3(tiles, 1), dim3(NW16 * 64), 0, st, a);
+    if (a.R <= 8) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, NB, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW16, NB, 16>), dim3(tiles), dim3(NW16 * 64), 0, st, a);
 }
 
 template <int EPI> static int launch_gemm_w8(const GemmArgs &a, hipStream_t st) {

@@ -54,14 +54,6 @@ template <> __device__ __forceinline__ bf16_t to_storage<bf16_t>(float x) { retu
 template <> __device__ __forceinline__ float to_storage<float>(float x) { return x; }
 
 __device__ __forceinline__ u32x4 ld16(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }
-// non-temporal load.  Measured on the 7B-shaped layer: where a wave-level load covers half of each 128-byte line
-// it touches (16 rows x 64 bytes: the MFMA operand layout of bf16 and int8 matrices and of the cache) the plain
-// load is the faster one (the other half of the line, asked for by the next instruction or by a neighbouring wave,
-// then hits; the counters showed 20 to 40 % more bytes fetched with the non-temporal form), so only the int4
-// kernel, whose loads cover whole lines, still uses this.
-__device__ __forceinline__ u32x4 ld16_stream(const void *p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-}
 // 16-byte load through a pointer that is known to be global memory although the compiler cannot see
 // it (pointers read from a descriptor in memory are generic): keeps it a global_load, not a flat_load,
 // which matters for wait counting (flat loads can return out of order and force vmcnt(0))
@@ -91,12 +83,6 @@ template <typename T> __device__ __forceinline__ Act<T> load_act(const ActPlanes
     Act<T> r;
 #pragma unroll
     for (int pl = 0; pl < Traits<T>::PLANES; ++pl) r.p[pl] = ld16(a.base + pl * a.plane + off);
-    return r;
-}
-template <typename T> __device__ __forceinline__ Act<T> zero_act() {
-    Act<T> r;
-#pragma unroll
-    for (int pl = 0; pl < Traits<T>::PLANES; ++pl) r.p[pl] = zero16();
     return r;
 }
 
@@ -183,11 +169,6 @@ __device__ __forceinline__ void st_coh(bf16_t *p, bf16_t v) {
 __device__ __forceinline__ unsigned long long ld_coh64(const void *p) {
     return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16-byte chunk as two coherent 8-byte loads
-__device__ __forceinline__ u32x4 ld16_coh(const void *p) {
-    const unsigned long long a = ld_coh64(p), b = ld_coh64(reinterpret_cast<const char *>(p) + 8);
-    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
-}
 // 16-byte agent-coherent load (sc0 sc1: performed at the memory side, like the relaxed agent-scope
 // atomics above, but four dwords per lane) through a raw buffer resource over `base`; `byte_off` < 4 GiB
 __device__ __forceinline__ u32x4 ld16_coh_buf(const void *base, uint32_t byte_off) {
@@ -214,11 +195,6 @@ __device__ __forceinline__ void store_act_coh(const ActPlanes<float> &a, size_t 
     st_coh(a.base + off, f2u(x) == 0xffffffffu ? u2f(0xffc00000u) : x);
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
