@@ -613,8 +613,8 @@ __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long
 }
 
 constexpr int TP_FITS = 32768; // longest row that stays in LDS
-// entries of the boundary bin that fit LDS; up to which they are ranked one against all (512 take 10 us, the digits 3 whatever their number)
-constexpr int TP_LIST = 2048, TP_RANK = 128;
+// entries of the boundary bin that fit LDS; up to which they are ranked one against all (200 take as long as the digits, 3.5 us)
+constexpr int TP_LIST = 2048, TP_RANK = 192;
 
 // An entry's weight as the bits of a float, f = trunc(min(max(p * 2^32, 0), 2^32)): whole numbers of at most 24 significant bits, so
 // f orders like the integer weight min(trunc(p * 2^32), 2^32 - 1) and is equal where that is (2^32 stands for 2^32 - 1).  Four
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     __shared__ Bin hist[TP_BINS];
     __shared__ unsigned long long sm_wave[TP_WAVES];
     __shared__ unsigned long long sm_above, sm_binw;
-    __shared__ __align__(16) uint32_t list[TP_LIST];
+    __shared__ uint32_t list[TP_LIST];
     __shared__ int sm_bin, sm_cut, sm_n;
     __shared__ f32x4 row[FITS ? TP_FITS / 4 : 1];
     const float *p = probs + (size_t)blockIdx.x * (size_t)ld_in;
@@ -698,19 +698,19 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     // The histogram of the row's entries with live(key), by bin(key).  Additions to one address are carried out one after another, and
     // the weights of a flat row are all in one bin (32000 equal ones: 116 us for the row, 16 for one of a softmax): each wavefront looks
     // at an entry per lane from all over the row, and where a quarter of those are in one bin it adds that bin's up in registers (43 us;
-    // the look takes 0.3 us, a vote at every entry took 20 - 40 % of the kernel).
-    uint32_t sample; // the key of one entry, the lanes' spread over the row
-    auto histogram = [&](auto live, auto bin) {
-        int hot = -1;
+    // a vote at every entry took 20 - 40 % of the kernel).
+    uint32_t sample = 0; // the key of one entry, the lanes' spread over the row
+    auto crowded_bin = [&](auto live, auto bin) { // (in front of clear(): most wavefronts wait at its barrier anyway)
         const bool l = live(sample);
         const unsigned long long lanes = __ballot(l);
-        if (lanes) {
-            const int b = bin(sample);
-            const int first = __builtin_amdgcn_readlane(b, __ffsll((long long)lanes) - 1), last = __builtin_amdgcn_readlane(b, 63 - __clzll((long long)lanes));
-            const int n1 = __popcll(__ballot(l && b == first)), n2 = __popcll(__ballot(l && b == last));
-            if (max(n1, n2) >= 16) hot = n1 >= n2 ? first : last;
-        }
-        if (hot < 0) {
+        if (!lanes) return -1;
+        const int b = bin(sample);
+        const int first = __builtin_amdgcn_readlane(b, __ffsll((long long)lanes) - 1), last = __builtin_amdgcn_readlane(b, 63 - __clzll((long long)lanes));
+        const int n1 = __popcll(__ballot(l && b == first)), n2 = __popcll(__ballot(l && b == last));
+        return max(n1, n2) < 16 ? -1 : n1 >= n2 ? first : last;
+    };
+    auto histogram = [&](int hot, auto live, auto bin) {
+        if (__builtin_expect(hot < 0, 1)) {
             each([&](uint32_t key) {
                 if (live(key)) atomicAdd(&hist[bin(key)], add_of(key));
             });
@@ -775,14 +775,14 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     if (t == 0) sm_n = 0;
     {
         // the sample: the first entry of one of the thread's own units, the lanes' spread over the row
-        const int own = t + TP_THREADS * (int)((long long)(t & 63) * ((n4 - t + TP_THREADS - 1) / TP_THREADS) >> 6);
-        float x0 = 0.f;
-        if (own < n4 && tp_entry<VEC>(own, 0) < V) x0 = FITS ? row[own].x : p[tp_entry<VEC>(own, 0)];
-        list[t] = list[t + TP_THREADS] = 0;
+        const int own = t + TP_THREADS * ((t & 63) * ((n4 - t + TP_THREADS - 1) / TP_THREADS) >> 6);
+        if (own < n4 && tp_entry<VEC>(own, 0) < V) sample = tp_key(FITS ? row[own].x : p[tp_entry<VEC>(own, 0)]);
+        const auto live = [](uint32_t key) { return key != 0; };
+        const auto bin = [](uint32_t key) { return tp_bin(key); };
+        const int hot = crowded_bin(live, bin);
         clear();
-        sample = tp_key(x0);
+        histogram(hot, live, bin);
     }
-    histogram([](uint32_t key) { return key != 0; }, [](uint32_t key) { return tp_bin(key); });
     const int bin0 = choose(true);
     if (S == 0) { // nothing has a weight: the row is returned as it is
         unchanged();
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         // more of them than the list holds, by what the bin holds and the largest weight in it (a flat row): no list
         const bool crowded = binw > (unsigned long long)TP_LIST * (BY_COUNT ? 1u : tp_weight((prefix << 17) | 0x1ffffu));
         unsigned long long above_w = 0;
-        if (crowded) {
+        if (__builtin_expect(crowded, 0)) {
             if (BY_COUNT) {
                 unsigned long long mine = 0;
                 each([&](uint32_t key) { mine += (key >> 17) > prefix ? tp_weight(key) : 0u; });
@@ -823,14 +823,12 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         if (n <= TP_RANK) { // few: the token in whose turn the sum is reached finds itself
             if (t < n) {
                 const uint32_t key = list[t];
-                Bin above = 0, equal = 0;
-                for (int i = 0; i < n; i += 4) { // (the list is filled up with zeros)
-                    const u32x4 other = *reinterpret_cast<const u32x4 *>(list + i);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        above += other[e] > key ? add_of(other[e]) : (Bin)0;
-                        equal += other[e] == key ? add_of(other[e]) : (Bin)0;
-                    }
+                unsigned long long above = 0, equal = 0;
+                for (int i = 0; i < n; ++i) {
+                    const uint32_t other = list[i];
+                    const unsigned long long add = add_of(other);
+                    above += other > key ? add : 0ull;
+                    equal += other == key ? add : 0ull;
                 }
                 if (above < need && need <= above + equal) { // (equal tokens write the same)
                     sm_bin = (int)key;
@@ -848,14 +846,15 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         } else { // the 17 bits behind the bin's, by digits
             for (int low = 17; low > 0;) {
                 const int nb = low < 11 ? low : 11;
-                clear();
                 const auto live = [&](uint32_t key) { return (key >> low) == prefix; };
                 const auto digit = [&](uint32_t key) { return (int)((key >> (low - nb)) & ((1u << nb) - 1)); };
+                const int hot = n <= TP_LIST ? -1 : crowded_bin(live, digit);
+                clear();
                 if (n <= TP_LIST) {
                     for (int i = t; i < n; i += TP_THREADS)
                         if (live(list[i])) atomicAdd(&hist[digit(list[i])], add_of(list[i]));
                 } else {
-                    histogram(live, digit);
+                    histogram(hot, live, digit);
                 }
                 prefix = (prefix << nb) | (uint32_t)choose(false);
                 low -= nb;
@@ -1109,6 +1108,7 @@ __global__ __launch_bounds__(256) void argmax_segment_kernel(const float *x, int
     const Argmax a = block_argmax_range<256>(x + (size_t)blockIdx.y * V + r0, min(seg_len, V - r0), r0);
     if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(a.best, __int_as_float(a.index));
 }
+constexpr int GREEDY_SEGS = 16; // most segments of a row
 // one wavefront per sequence, lane i = position i (K + 1 <= 16 positions)
 // row_argmax: the rows' tokens where they were not cut (part NULL)
 __global__ __launch_bounds__(64) void greedy_finish_kernel(const float2 *part, int nseg, const int32_t *row_argmax, const int32_t *draft, int K,
@@ -1118,10 +1118,11 @@ __global__ __launch_bounds__(64) void greedy_finish_kernel(const float2 *part, i
     int tok;
     if (part) {
         Argmax a;
-        for (int s = 0; s < nseg; ++s) {
-            const float2 p = part[row * nseg + s];
-            a.see(p.x, __float_as_int(p.y));
-        }
+        float2 p[GREEDY_SEGS];
+#pragma unroll
+        for (int s = 0; s < GREEDY_SEGS; ++s) p[s] = part[row * nseg + min(s, nseg - 1)]; // (all asked for together; the last one again past the end)
+#pragma unroll
+        for (int s = 0; s < GREEDY_SEGS; ++s) a.see(p[s].x, __float_as_int(p[s].y));
         tok = a.token();
     } else {
         tok = row_argmax[row];
@@ -1133,10 +1134,10 @@ __global__ __launch_bounds__(64) void greedy_finish_kernel(const float2 *part, i
         next_token[b] = tok;
     }
 }
-// segments per row: at most 16, of at least 4096 entries each while that fills the chip (2048 workgroups), and no more than the
+// segments per row: at most GREEDY_SEGS, of at least 4096 entries each while that fills the chip (2048 workgroups), and no more than the
 // workspace holds pairs for (avail: bytes)
 static int greedy_segments(int64_t rows, int V, size_t avail, int &seg_len) {
-    int64_t nseg = std::min<int64_t>(std::min<int64_t>(16, V / 4096), 2048 / rows);
+    int64_t nseg = std::min<int64_t>(std::min<int64_t>(GREEDY_SEGS, V / 4096), 2048 / rows);
     nseg = std::max<int64_t>(1, std::min<int64_t>(nseg, (int64_t)(avail / (sizeof(float2) * (size_t)rows))));
     seg_len = (int)((V + nseg - 1) / nseg);
     seg_len = (seg_len + 3) & ~3; // keeps the 16-byte alignment of an aligned row
