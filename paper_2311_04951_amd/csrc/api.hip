@@ -586,8 +586,9 @@ static int check_pair(const ss_model *m, const ss_kv_cache *kv, int batch, int M
     return SS_OK;
 }
 
-// Rows of an activation plane in a call of R rows: the buffers hold max_rows of them, but calls of at most 16 rows pack their two
-// planes together (their GEMMs reach both with 32-bit offsets).
+// Rows of an activation plane in a call of R rows: the buffers hold max_rows of them, but calls of at most 16 rows (all that the
+// persistent kernel takes) pack their two planes together: their GEMMs reach both with 32-bit offsets, the persistent kernel through
+// a buffer descriptor of 2 GiB.
 static size_t plane_rows(const ss_model *m, int R) { return R <= 16 ? 16 : (size_t)m->R16; }
 
 // All layers over the R = batch*M rows in h.  normed: whether act_a already holds the first layer's normalised rows (the
@@ -763,7 +764,7 @@ extern "C" int ss_model_set_wait_limit(ss_model *m, uint32_t polls) {
 static int run_persistent(ss_model *m, ss_kv_cache *kv, const int32_t *tokens, float *h, int batch, int M, float *logits,
                           int head_rows, int head_row0, int head_stride, hipStream_t st) {
     const ss_model_cfg &c = m->cfg;
-    const size_t pl = (size_t)m->R16;
+    const size_t pl = plane_rows(m, batch * M);
     MegaCall P{};
     const bool with_head = logits != nullptr;
     P.phases = with_head ? m->prog_full : m->prog_nohead;

@@ -115,6 +115,27 @@ def test_few_rows_of_a_model_whose_activation_planes_pass_4_gib():
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.mem_get_info()[0] < 120 << 30, reason="the model's buffers take 40 to 80 GB")
+@pytest.mark.parametrize("max_rows", [32800, 65552])      # planes 2 and 4 GiB apart
+@pytest.mark.parametrize("grid8", [False, True])
+def test_the_persistent_kernel_on_a_model_whose_activation_planes_lie_far_apart(grid8, max_rows):
+    """Both planes are read through one buffer descriptor with 32-bit offsets: the bits of a small model with the same weights."""
+    shape = si.DecoderShape(1, 256, 4, 64, 32768, 64, dtype="bf16")
+    w = weights_to_device(si.decoder_weights(shape, seed=75))
+    toks = si.token_ids(75, "t", (1, 5), shape.vocab).to(dev())
+    outs = []
+    for rows in (16, max_rows):
+        gm = sv.Model(shape, w, max_rows=rows, max_pos=32)
+        sv.ss_model_set_persistent(gm, True)
+        if grid8:
+            sv.ss_model_set_persistent_options(gm, 8, True)
+        kv = sv.KVCache(gm, 1, 16)
+        outs.append(sv.ss_verify_forward(gm, kv, toks, 5).clone())
+        assert sv.ss_device_status(gm) == 0
+        del kv, gm
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
+
+
 def test_greedy_acceptance_of_rows_that_hold_nothing_but_nan_and_minus_infinity():
     """NaNs lose to everything, minus infinity included, wherever the cuts between segments fall; a row of NaNs alone gives index 0."""
     V = 20000                                                       # four segments of 5000 in a workspace that holds their pairs
