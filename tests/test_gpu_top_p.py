@@ -142,20 +142,19 @@ def test_negative_zeros_have_no_weight(V):
 def test_crowded_bins_and_unaligned_rows_equal_oracle_bit_for_bit(V):
     """Bins that hold a few tokens, some hundred (the bounds of what is ranked and listed) and most of the row, alone and between other
     tokens, in rows whose entries are read word by word: equal weights, weights within one bin, every second entry equal, a flat tail."""
-    n = si.normal(11, f"c{V}", (8, V), 1.0).numpy()
+    n = si.normal(11, f"c{V}", (9, V), 1.0).numpy()
     n[0] *= 0.001                                                        # all within one bin or two
     n[1] *= 0.01
     n[2, ::2] = n[2, 0]
     n[3, V // 8:] = -3.0
     n[4] *= 4.0
-    n[5, :128] = 9.0 + 1e-4 * n[5, :128]                                 # 127 to 129 tokens in the top bin
-    n[6, :129] = 9.0 + 1e-4 * n[6, :129]
-    n[7, :2049] = 9.0 + 1e-4 * n[7, :2049]
+    for r, top in ((5, 192), (6, 193), (7, 2048), (8, 2049)):            # as many tokens in the top bin
+        n[r, :top] = 9.0 + 1e-4 * n[r, :top]
     rows = oracle.softmax(n, 1.0)
     g = torch.from_numpy(rows).to(dev())
     for top_p in (0.02, 0.5, 0.95):
         assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p).cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p)
-    for k in sorted({1, 64, 100, 128, 200, V // 2, V - 2} - {V}):
+    for k in sorted({1, 64, 100, 192, 193, V // 2, V - 2} - {V}):
         if k < V:
             assert np.array_equal(_bits(sv.ss_top_k_filter(g, k).cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k)
 
