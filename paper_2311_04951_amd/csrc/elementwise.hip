@@ -12,14 +12,11 @@ namespace ss {
 // One workgroup per row; a row of up to 8192 elements stays in registers between the two passes (16-byte
 // loads, 8-byte stores of four packed values per plane); longer or unaligned rows take the plain loops.
 __device__ __forceinline__ void store_act4(const ActPlanes<bf16_t> &a, size_t off, const float (&x)[4]) {
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        hi[j] = bf16_rne(x[j]);
-        lo[j] = bf16_rne(x[j] - bf16_bits_to_f32(hi[j]));
-    }
-    *reinterpret_cast<uint2 *>(a.base + off) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-    *reinterpret_cast<uint2 *>(a.base + a.plane + off) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+    uint2 hi, lo;
+    bf16_split(x[0], x[1], hi.x, lo.x);
+    bf16_split(x[2], x[3], hi.y, lo.y);
+    *reinterpret_cast<uint2 *>(a.base + off) = hi;
+    *reinterpret_cast<uint2 *>(a.base + a.plane + off) = lo;
 }
 __device__ __forceinline__ void store_act4(const ActPlanes<float> &a, size_t off, const float (&x)[4]) {
     *reinterpret_cast<float4 *>(a.base + off) = make_float4(x[0], x[1], x[2], x[3]);

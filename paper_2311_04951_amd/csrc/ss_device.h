@@ -38,13 +38,23 @@ template <> struct Traits<float> {
 __device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uint32_t, x); }
 __device__ __forceinline__ float u2f(uint32_t x) { return __builtin_bit_cast(float, x); }
 
-// fp32 -> bf16, round to nearest even (finite inputs; NaN/Inf pass through the high half).
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-    uint32_t u = f2u(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return u >> 16;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// fp32 -> bf16, round to nearest even, two values in one conversion instruction (a in the low half).  Compared with integer
+// rounding (u + 0x7fff + bit 16) for all 2^32 inputs: the same bits for every number and infinity; a NaN stays a NaN.  Epilogues and
+// the softmax weights of the attention spend most of their instructions here (seven and a branch per value with integers): 7B-shaped
+// layer of 5 rows 93.5 -> 92.5 us, 72 rows 254.0 -> 251.5, 8 int4 layers 450 -> 441.
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
+__device__ __forceinline__ uint32_t bf16_rne(float x) { return bf16_pair(x, 0.f); }
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return u2f(b << 16); }
+
+// a pair's high parts and what is left of it: x = hi + lo to about 16 mantissa bits
+__device__ __forceinline__ void bf16_split(float a, float b, uint32_t &hi, uint32_t &lo) {
+    hi = bf16_pair(a, b);
+    lo = bf16_pair(a - u2f(hi << 16), b - u2f(hi & 0xffff0000u));
+}
 
 __device__ __forceinline__ float to_f32(bf16_t x) { return bf16_bits_to_f32(x.bits); }
 __device__ __forceinline__ float to_f32(float x) { return x; }
@@ -97,17 +107,17 @@ __device__ __forceinline__ void store_act(const ActPlanes<float> &a, size_t off,
 
 // four consecutive elements as one store (8 bytes of bf16, 16 of fp32; p aligned accordingly)
 __device__ __forceinline__ void store_quad(bf16_t *p, const float (&x)[4]) {
-    *reinterpret_cast<uint2 *>(p) = make_uint2(bf16_rne(x[0]) | (bf16_rne(x[1]) << 16), bf16_rne(x[2]) | (bf16_rne(x[3]) << 16));
+    *reinterpret_cast<uint2 *>(p) = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
 }
 __device__ __forceinline__ void store_quad(float *p, const float (&x)[4]) { *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]); }
 // activation values of four consecutive columns, the first `live` of which exist; one store per plane where the planes allow
 __device__ __forceinline__ void store_act_quad(const ActPlanes<bf16_t> &a, size_t off, const float (&x)[4], int live) {
     if (live >= 4 && a.ld % 4 == 0 && a.plane % 4 == 0 && (reinterpret_cast<uintptr_t>(a.base) & 7) == 0 && off % 4 == 0) {
-        float lo[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) lo[v] = x[v] - bf16_bits_to_f32(bf16_rne(x[v]));
-        store_quad(a.base + off, x);
-        store_quad(a.base + a.plane + off, lo);
+        uint2 hi, lo;
+        bf16_split(x[0], x[1], hi.x, lo.x);
+        bf16_split(x[2], x[3], hi.y, lo.y);
+        *reinterpret_cast<uint2 *>(a.base + off) = hi;
+        *reinterpret_cast<uint2 *>(a.base + a.plane + off) = lo;
     } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -129,11 +139,10 @@ __device__ __forceinline__ Act<bf16_t> pack_act(const float (&x)[8], bf16_t) {
     Act<bf16_t> r;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        uint32_t h0 = bf16_rne(x[2 * j]), h1 = bf16_rne(x[2 * j + 1]);
-        uint32_t l0 = bf16_rne(x[2 * j] - bf16_bits_to_f32(h0));
-        uint32_t l1 = bf16_rne(x[2 * j + 1] - bf16_bits_to_f32(h1));
-        r.p[0][j] = h0 | (h1 << 16);
-        r.p[1][j] = l0 | (l1 << 16);
+        uint32_t hi, lo;
+        bf16_split(x[2 * j], x[2 * j + 1], hi, lo);
+        r.p[0][j] = hi;
+        r.p[1][j] = lo;
     }
     return r;
 }
