@@ -62,7 +62,7 @@ struct ss_model {
     float *part_o, *part_m, *part_l;
     float *logits_ws; // [max_rows][vocab] (draft step)
     float2 *stats_ws; // [max_rows]
-    float *nsq_ws = nullptr;       // per-tile sums of squares of a deferred RMSNorm (calls of at most 16 rows): [16][d_model / 16]
+    float *nsq_ws = nullptr;       // partial sums of squares of a deferred RMSNorm (calls of at most 16 rows): [16][deferred_norm_parts(d_model)]
     float *splitk_ws = nullptr;    // partial tiles of split-K GEMM launches (models that take more than 16 rows per call)
     size_t splitk_ws_bytes = 0;
     unsigned *stats_cnt = nullptr; // [max_rows] arrival counters of the segmented row statistics (zero between launches)
@@ -235,7 +235,7 @@ extern "C" int ss_model_create(const ss_model_cfg *cfg, const ss_weights *w, ss_
         A((void **)&m->splitk_ws, m->splitk_ws_bytes, false);
     }
     A((void **)&m->stats_cnt, sizeof(unsigned) * (size_t)c.max_rows, true);
-    if (c.d_model % 256 == 0 && c.d_model / 16 <= NSQ_MAX_TILES) A((void **)&m->nsq_ws, sizeof(float) * 16 * (size_t)(c.d_model / 16), true);
+    if (deferred_norm_parts(c.d_model)) A((void **)&m->nsq_ws, sizeof(float) * 16 * (size_t)deferred_norm_parts(c.d_model), true);
     A((void **)&m->stats_part, row_stats_partial_bytes(c.max_rows, c.vocab) + 16, true);
     m->ws_bytes = ss_workspace_bytes(2 * (int64_t)c.max_rows, c.vocab); // target rows + draft rows of a step
     A(&m->ws, m->ws_bytes, true);
@@ -613,16 +613,15 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
     const int wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
     // The two residual projections name the RMSNorm that follows them.  A launcher that has a row-wise last launch
     // anyway (split K, more than 16 rows) writes the normalised planes there (1); the kernels of at most 16 rows write
-    // h * gain as planes and per-tile sums of squares, and the GEMM that consumes the planes multiplies its sums by the
+    // h * gain as planes and partial sums of squares, and the GEMM that consumes the planes multiplies its sums by the
     // row scale (2: the norm is deferred; no launch of its own either way).  0: the norm is still to be launched.
-    const int T = d / 16;
     const bool defer_ok = R <= 16 && m->nsq_ws != nullptr;
     auto with_norm = [&](GemmArgs &g, const float *gain) {
         g.norm_gain = gain; g.norm_act = m->act_a; g.norm_act_plane = pl * d; g.norm_ld = d; g.norm_eps = c.rms_eps;
-        if (defer_ok) { g.nsq_out = m->nsq_ws; g.nsq_ld = T; }
+        if (defer_ok) g.nsq_out = m->nsq_ws;
     };
     auto consumes_norm = [&](GemmArgs &g) { // the GEMM reads act_a: tell it when the row scale is still missing
-        if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_tiles = T; g.act_nsq_ld = T; g.norm_eps = c.rms_eps; }
+        if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_parts = deferred_norm_parts(d); g.norm_eps = c.rms_eps; }
     };
     for (int l = 0; l < c.n_layers; ++l) {
         const ss_layer_weights &L = m->layers[l];
@@ -723,7 +722,7 @@ static void run_head(ss_model *m, int normed, int nrows, int row0, int stride, f
     g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.wscale = m->s_head; g.wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
     g.act = m->act_a; g.act_plane = pl * c.d_model; g.ld_act = c.d_model; g.R = nrows;
     g.out = logits; g.ldo = c.vocab;
-    if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_tiles = g.act_nsq_ld = c.d_model / 16; g.norm_eps = c.rms_eps; }
+    if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_parts = deferred_norm_parts(c.d_model); g.norm_eps = c.rms_eps; }
     launch_gemm(c.dtype, EPI_STORE, g, st);
 }
 

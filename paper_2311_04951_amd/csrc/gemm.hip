@@ -5,14 +5,14 @@
 //   workgroup multiplies every weight chunk it streams with up to RT row tiles (weights are read once for
 //   up to 16*RT rows).
 //
-// At most 16 rows: one workgroup owns 16 output columns (or a pair of 16-column tiles for the fused epilogues).  Weights and
-// activation rows (packed planes) come through LDS by load-to-LDS instructions that take whole 128-byte lines, into a ring of the
-// wavefront's own, and are read back as the A and B operands of the MFMAs.  The waves interleave over K in 128-byte steps, their
-// partial tiles are summed in a fixed order through LDS (deterministic), and wave 0 applies the epilogue:
+// At most 16 rows (gemm_cols_kernel): the output columns (pairs of them for the fused epilogues) are dealt out evenly over the compute
+// units.  Weights and activation rows (packed planes) come through LDS by load-to-LDS instructions that take whole 128-byte lines, into a
+// ring of the wavefront's own, and are read back as the A and B operands of the MFMAs.  The waves interleave over K in 128-byte steps,
+// their partial tiles are summed in a fixed order through LDS (deterministic), two columns of a row per thread, and finished:
 //   STORE   plain fp32 store (LM head)
 //   RESID   h += ...            (O projection, down projection)
-//   SWIGLU  silu(gate) * up     (gate tile + up tile in one workgroup) -> activation planes
-//   QKV     rotary embedding of q and k (pairs j, j + hd/2 sit in the two tiles), q -> activation
+//   SWIGLU  silu(gate) * up     (gate and up columns in one workgroup) -> activation planes
+//   QKV     rotary embedding of q and k (pairs j, j + hd/2 in one workgroup), q -> activation
 //           planes, k and v -> KV cache at positions len[b] + i
 #include <type_traits>
 #include "ss_device.h"
@@ -20,62 +20,56 @@
 
 namespace ss {
 
-// What an epilogue reads besides the sums (the residual, the sequence's length and the rotary factors): a kernel whose
-// K loop takes many memory round trips asks for them in front of it, so that the epilogue does not add two more.
-struct EpiPre {
-    float resid[4];
-    float2 rope[4];
-    int pos;
-    float gain[4]; // deferred norm, producer: the next norm's gains of the lane's four columns
+// What an epilogue reads besides the sums (the residual, the sequence's length and the rotary factors), for V columns of a row: a
+// kernel whose K loop takes many memory round trips asks for them behind its first request, so that the epilogue adds none.
+template <int V> struct EpiPre {
+    float resid[V];
+    float2 rope[V];
+    int len;       // of the row's sequence
+    float gain[V]; // deferred norm, producer: the next norm's gains of these columns
 };
-// Deferred norm, consumer: a lane's quarter of its activation row's per-tile sums of squares (lane group g holds tiles
-// [g * T/4, (g + 1) * T/4) of row c), requested ahead of the K loop like the rest ...
-constexpr int NSQ4 = NSQ_MAX_TILES / 16;
-__device__ __forceinline__ void nsq_prefetch(const GemmArgs &a, int rt, float4 (&nsq)[NSQ4]) {
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-    const int m = min(rt * 16 + c, a.R - 1);
-    const float4 *p = reinterpret_cast<const float4 *>(a.act_nsq + (size_t)m * a.act_nsq_ld + g * (a.act_nsq_tiles / 4));
-    const int n4 = a.act_nsq_tiles / 16;
-#pragma unroll
-    for (int i = 0; i < NSQ4; ++i) nsq[i] = p[min(i, n4 - 1)]; // (surplus slots repeat the last one and are not added)
+
+// Where columns sit.  `col`: the first of them, for EPI_QKV the weight row of the first one in the first half of its head
+// ((head over [q heads | k heads | v heads]) * head_dim + column in the head).
+struct QkvPlace {
+    int region, h, j0; // 0 q, 1 k, 2 v; head; column in the head
+};
+__device__ __forceinline__ QkvPlace qkv_place(const GemmArgs &a, int col) {
+    const int hh = col >> (31 - __clz(a.hd)); // head_dim is 32, 64 or 128
+    const int region = (hh >= a.H) + (hh >= 2 * a.H);
+    return QkvPlace{region, hh - region * a.H, col & (a.hd - 1)};
 }
-// ... and 1 / rms of the row from them: fixed order inside a lane, then over the four lane groups
-__device__ __forceinline__ float deferred_row_scale(const GemmArgs &a, const float4 (&nsq)[NSQ_MAX_TILES / 16]) {
-    const int n4 = a.act_nsq_tiles / 16;
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < NSQ_MAX_TILES / 16; ++i) s += i < n4 ? (nsq[i].x + nsq[i].y) + (nsq[i].z + nsq[i].w) : 0.f;
-    const float s1 = __shfl_xor(s, 16);
-    const float lo = (threadIdx.x & 16) ? s1 : s, hi = (threadIdx.x & 16) ? s : s1; // (g even, g odd) of the pair, in that order
-    const float pair = lo + hi;
-    const float p2 = __shfl_xor(pair, 32);
-    const float tot = (threadIdx.x & 32) ? p2 + pair : pair + p2;                   // (groups 0,1) + (groups 2,3)
-    return 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
-}
-template <typename T, int EPI>
-__device__ __forceinline__ void epi_prefetch(const GemmArgs &a, const int (&n0)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1], int rt, EpiPre &pre) {
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-    const int m = min(rt * 16 + c, a.R - 1); // a row past the end asks for the last row's operands and never uses them
+// cache position of row m whose sequence holds `len` (host validation keeps it inside; the bounds are a second one)
+__device__ __forceinline__ int qkv_position(const GemmArgs &a, int m, int len) { return min(len + m - m / a.M * a.M, min(a.max_pos, a.S) - 1); }
+template <int EPI, int V> __device__ __forceinline__ void epi_prefetch(const GemmArgs &a, int m, int col, EpiPre<V> &pre) {
+    m = min(m, a.R - 1); // a row past the end asks for the last row's operands and never uses them
     if constexpr (EPI == EPI_RESID) {
+        const size_t o0 = (size_t)m * a.ldo + col;
+        if (col + V <= a.N && a.ldo % V == 0 && (reinterpret_cast<uintptr_t>(a.resid) & (4 * V - 1)) == 0) {
+            typedef float vec __attribute__((ext_vector_type(V)));
+            const vec r = *reinterpret_cast<const vec *>(a.resid + o0);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) pre.resid[v] = a.resid[(size_t)m * a.ldo + min(n0[0] + 4 * g + v, a.N - 1)];
+            for (int v = 0; v < V; ++v) pre.resid[v] = r[v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) pre.resid[v] = a.resid[(size_t)m * a.ldo + min(col + v, a.N - 1)];
+        }
         if (a.nsq_out) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) pre.gain[v] = a.norm_gain[min(n0[0] + 4 * g + v, a.N - 1)];
+            for (int v = 0; v < V; ++v) pre.gain[v] = a.norm_gain[min(col + v, a.N - 1)];
         }
     } else if constexpr (EPI == EPI_QKV) {
-        const int d_all = a.H * a.hd;
-        const int region = n0[0] / d_all;
-        const int within = n0[0] - region * d_all;
-        const int j0 = within - (within / a.hd) * a.hd + 4 * g;
-        const int b = m / a.M, i = m - b * a.M;
-        int pos = a.len[b] + i;
-        if (pos > a.max_pos - 1) pos = a.max_pos - 1;
-        if (pos > a.S - 1) pos = a.S - 1;
-        pre.pos = pos;
-        if (region < 2) {
+        pre.len = a.len[m / a.M];
+    }
+}
+// ... what depends on the first: the rotary factors of the row's position
+template <int EPI, int V> __device__ __forceinline__ void epi_prefetch_rope(const GemmArgs &a, int m, int col, EpiPre<V> &pre) {
+    if constexpr (EPI == EPI_QKV) {
+        const QkvPlace at = qkv_place(a, col);
+        if (at.region < 2) {
+            const float2 *p = a.rope + (size_t)qkv_position(a, min(m, a.R - 1), pre.len) * (a.hd / 2) + at.j0;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) pre.rope[v] = a.rope[(size_t)pos * (a.hd / 2) + j0 + v];
+            for (int v = 0; v < V; ++v) pre.rope[v] = p[v];
         }
     }
 }
@@ -88,13 +82,13 @@ template <int EPI> __device__ __forceinline__ void move_lengths(const GemmArgs &
     }
 }
 
-// Rotary embedding and stores of four column pairs (j0 + v, j0 + hd/2 + v) of row m, head h of region 0 q, 1 k, 2 v.
-template <typename T>
-__device__ __forceinline__ void qkv_store(const GemmArgs &a, int m, int region, int h, int j0, float (&x0)[4], float (&x1)[4], int pos, const float2 (&rope)[4]) {
-    const int b = m / a.M;
-    if (region < 2) {
+// Rotary embedding and stores of V column pairs (j0 + v, j0 + hd/2 + v) of row m.
+template <typename T, int V>
+__device__ __forceinline__ void qkv_store(const GemmArgs &a, int m, const QkvPlace &at, float (&x0)[V], float (&x1)[V], int pos, const float2 (&rope)[V]) {
+    const int b = m / a.M, h = at.h, j0 = at.j0;
+    if (at.region < 2) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < V; ++v) {
             const float2 cs = rope[v];
             const float p0 = x0[v] * cs.x - x1[v] * cs.y;
             const float p1 = x0[v] * cs.y + x1[v] * cs.x;
@@ -102,111 +96,89 @@ __device__ __forceinline__ void qkv_store(const GemmArgs &a, int m, int region, 
             x1[v] = p1;
         }
     }
-    if (region == 0) {
+    if (at.region == 0) {
         ActPlanes<T> q{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_act_out};
         const size_t o = (size_t)m * a.ld_act_out + h * a.hd + j0;
-        store_act_quad(q, o, x0, 4);
-        store_act_quad(q, o + a.hd / 2, x1, 4);
-    } else if (region == 1) {
+        store_act_cols(q, o, x0, V);
+        store_act_cols(q, o + a.hd / 2, x1, V);
+    } else if (at.region == 1) {
         T *kc = reinterpret_cast<T *>(a.kcache) + (((size_t)b * a.H + h) * a.S + pos) * a.hd + j0;
-        store_quad(kc, x0); // (the cache is 16-byte aligned, j0 a multiple of 4)
-        store_quad(kc + a.hd / 2, x1);
+        store_cols(kc, x0); // (the cache is 16-byte aligned, j0 a multiple of V)
+        store_cols(kc + a.hd / 2, x1);
     } else {
         // values are kept transposed inside blocks of 64 positions: [pos/64][hd][64]
         T *vc = reinterpret_cast<T *>(a.vcache) + ((size_t)b * a.H + h) * a.S * a.hd + ((size_t)(pos >> 6) * a.hd) * 64 + (pos & 63);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < V; ++v) {
             vc[(size_t)(j0 + v) * 64] = to_storage<T>(x0[v]);
             vc[(size_t)(j0 + a.hd / 2 + v) * 64] = to_storage<T>(x1[v]);
         }
     }
 }
-// ... with the position and the rotary factors read here
-template <typename T>
-__device__ __forceinline__ void qkv_finish_quad(const GemmArgs &a, int m, int region, int h, int j0, float (&x0)[4], float (&x1)[4]) {
-    const int b = m / a.M;
-    int pos = a.len[b] + m - b * a.M;
-    if (pos > a.max_pos - 1) pos = a.max_pos - 1; // host validation keeps these from happening
-    if (pos > a.S - 1) pos = a.S - 1;
-    float2 rope[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) rope[v] = region < 2 ? a.rope[(size_t)pos * (a.hd / 2) + j0 + v] : make_float2(1.f, 0.f);
-    qkv_store<T>(a, m, region, h, j0, x0, x1, pos, rope);
-}
 
-// Epilogue of one output tile by one wave: lane (c, g) holds r[t][v] = the value of row m = rt*16 + c,
-// column n0[t] + 4g + v.  pre: operands fetched ahead by epi_prefetch for this tile and row tile (NULL: read here).
-template <typename T, int EPI>
-__device__ __forceinline__ void apply_epilogue(const GemmArgs &a, const float (&r)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1][4],
-                                               const int (&n0)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1], int rt, const EpiPre *pre = nullptr) {
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-    const int m = rt * 16 + c;
-    if (m >= a.R) return;
-
+// Epilogue of V columns from `col` (see qkv_place) of row m < R: x0, and x1 the second half of a fused pair; pre: operands
+// fetched ahead by epi_prefetch for this row and these columns.  Returns, where a deferred norm is asked for, the sum of squares of
+// the row's new values.
+template <typename T, int EPI, int V>
+__device__ __forceinline__ float epilogue_cols(const GemmArgs &a, int m, int col, float (&x0)[V], float (&x1)[V], const EpiPre<V> &pre) {
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESID) {
-        float hn[4];
-        const size_t o0 = (size_t)m * a.ldo + n0[0] + 4 * g;
-        if (n0[0] + 4 * g + 3 < a.N && a.ldo % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.out) | reinterpret_cast<uintptr_t>(a.resid)) & 15) == 0) {
-            float4 old = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (EPI == EPI_RESID) old = pre ? make_float4(pre->resid[0], pre->resid[1], pre->resid[2], pre->resid[3]) : *reinterpret_cast<const float4 *>(a.resid + o0);
-            hn[0] = EPI == EPI_RESID ? old.x + r[0][0] : r[0][0];
-            hn[1] = EPI == EPI_RESID ? old.y + r[0][1] : r[0][1];
-            hn[2] = EPI == EPI_RESID ? old.z + r[0][2] : r[0][2];
-            hn[3] = EPI == EPI_RESID ? old.w + r[0][3] : r[0][3];
-            *reinterpret_cast<float4 *>(a.out + o0) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+        if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) x0[v] = pre.resid[v] + x0[v];
+        }
+        const size_t o0 = (size_t)m * a.ldo + col;
+        if (col + V <= a.N && a.ldo % V == 0 && (reinterpret_cast<uintptr_t>(a.out) & (4 * V - 1)) == 0) {
+            store_cols(a.out + o0, x0);
         } else {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                hn[v] = 0.f;
-                if (n0[0] + 4 * g + v < a.N) {
-                    hn[v] = (EPI == EPI_RESID) ? (pre ? pre->resid[v] : a.resid[o0 + v]) + r[0][v] : r[0][v];
-                    a.out[o0 + v] = hn[v];
-                }
+            for (int v = 0; v < V; ++v) {
+                if (col + v < a.N) a.out[o0 + v] = x0[v];
+                else x0[v] = 0.f;
             }
         }
-        if (EPI == EPI_RESID && a.nsq_out && pre) { // deferred norm: h * gain as planes, the tile's sum of squares per row
+        if (EPI == EPI_RESID && a.nsq_out) { // deferred norm: h * gain as planes
             ActPlanes<T> np{reinterpret_cast<T *>(a.norm_act), a.norm_act_plane, a.norm_ld};
-            float y[4];
+            float y[V], sq = 0.f;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) y[v] = hn[v] * pre->gain[v];
-            store_act_quad(np, (size_t)m * a.norm_ld + n0[0] + 4 * g, y, a.N - (n0[0] + 4 * g));
-            float sq = (hn[0] * hn[0] + hn[1] * hn[1]) + (hn[2] * hn[2] + hn[3] * hn[3]);
-            const float s1 = __shfl_xor(sq, 16);
-            const float lo = (lane & 16) ? s1 : sq, hi = (lane & 16) ? sq : s1;
-            const float pair = lo + hi;
-            const float p2 = __shfl_xor(pair, 32);
-            const float tot = (lane & 32) ? p2 + pair : pair + p2;
-            if (g == 0) a.nsq_out[(size_t)m * a.nsq_ld + n0[0] / 16] = tot;
+            for (int v = 0; v < V; ++v) {
+                y[v] = x0[v] * pre.gain[v];
+                sq += x0[v] * x0[v];
+            }
+            store_act_cols(np, (size_t)m * a.norm_ld + col, y, a.N - col);
+            return sq;
         }
     } else if constexpr (EPI == EPI_SWIGLU) {
         ActPlanes<T> z{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_act_out};
-        float y[4];
+        float y[V];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float gt = r[0][v], up = r[1][v];
-            y[v] = gt / (1.0f + expf(-gt)) * up;
-        }
-        store_act_quad(z, (size_t)m * a.ld_act_out + n0[0] + 4 * g, y, a.N - (n0[0] + 4 * g));
+        for (int v = 0; v < V; ++v) y[v] = x0[v] / (1.0f + expf(-x0[v])) * x1[v];
+        store_act_cols(z, (size_t)m * a.ld_act_out + col, y, a.N - col);
     } else { // EPI_QKV
-        const int d_all = a.H * a.hd;
-        const int region = n0[0] / d_all; // 0 q, 1 k, 2 v
-        const int within = n0[0] - region * d_all;
-        const int h = within / a.hd;
-        const int j0 = within - h * a.hd + 4 * g; // column inside the head (first half)
-        float x0[4], x1[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            x0[v] = r[0][v];
-            x1[v] = r[1][v];
-        }
-        if (pre) qkv_store<T>(a, m, region, h, j0, x0, x1, pre->pos, pre->rope);
-        else qkv_finish_quad<T>(a, m, region, h, j0, x0, x1);
+        qkv_store<T, V>(a, m, qkv_place(a, col), x0, x1, qkv_position(a, m, pre.len), pre.rope);
     }
+    return 0.f;
+}
+// ... with the operands read here
+template <typename T, int EPI, int V>
+__device__ __forceinline__ void epilogue_cols(const GemmArgs &a, int m, int col, float (&x0)[V], float (&x1)[V]) {
+    EpiPre<V> pre;
+    epi_prefetch<EPI, V>(a, m, col, pre);
+    epi_prefetch_rope<EPI, V>(a, m, col, pre);
+    epilogue_cols<T, EPI, V>(a, m, col, x0, x1, pre);
+}
+// Epilogue of one output tile by one wave: lane (c, g) holds r[t][v] = the value of row m = rt*16 + c, column n0[t] + 4g + v.
+template <typename T, int EPI>
+__device__ __forceinline__ void apply_epilogue(const GemmArgs &a, float (&r)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1][4],
+                                               const int (&n0)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1], int rt) {
+    const int lane = threadIdx.x & 63, m = rt * 16 + (lane & 15);
+    constexpr int LAST = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 1 : 0;
+    if (m < a.R) epilogue_cols<T, EPI, 4>(a, m, n0[0] + 4 * (lane >> 4), r[0], r[LAST]);
 }
 
 // The K steps of a workgroup in rotated order: step i of nst becomes (i + rot) mod nst; steps past the end stay there
 // (they are masked).  The offset depends on the workgroup alone, so a tile's sum is always formed in the same order.
-__device__ __forceinline__ int k_rotation(int nst) { return (int)((blockIdx.x * 13u) % (unsigned)nst); }
+// (The golden ratio's multiples spread neighbours over K; a remainder would cost a division in front of the first load.)
+__device__ __forceinline__ int k_rotation(int nst) { return (int)__umulhi(blockIdx.x * 0x9E3779B9u, (unsigned)nst); }
 __device__ __forceinline__ int rotated(int i, int rot, int nst) {
     if (i >= nst) return i;
     i += rot;
@@ -232,20 +204,12 @@ template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_wai
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// Waits until at most one step of `per` loads (3 and more) is in flight (of more than 12: waits for some of it as well).
-__device__ __forceinline__ void wait_for_step(int per) {
-    switch (per) {
-    case 3: wait_vmcnt_at_most<3>(); break;
-    case 4: wait_vmcnt_at_most<4>(); break;
-    case 5: wait_vmcnt_at_most<5>(); break;
-    case 6: wait_vmcnt_at_most<6>(); break;
-    case 7: wait_vmcnt_at_most<7>(); break;
-    case 8: wait_vmcnt_at_most<8>(); break;
-    case 9: wait_vmcnt_at_most<9>(); break;
-    case 10: wait_vmcnt_at_most<10>(); break;
-    case 11: wait_vmcnt_at_most<11>(); break;
-    default: wait_vmcnt_at_most<12>(); break;
+// Waits until at most `loads` + FIXED loads are in flight (1 <= loads <= MOST).
+template <int FIXED, int MOST> __device__ __forceinline__ void wait_for_step(int loads) {
+    if constexpr (MOST > 1) {
+        if (loads < MOST) return wait_for_step<FIXED, MOST - 1>(loads);
     }
+    wait_vmcnt_at_most<FIXED + MOST>();
 }
 
 // Activations of the kernels for at most 16 rows, through a wave-private piece of LDS.  A step of a wave is UPS units
@@ -281,7 +245,7 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
             const int p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
-            const int plane = p / (rows * UPS), rem = p - plane * rows * UPS, row = rem / UPS, pos = rem % UPS;
+            const int plane = PL == 2 && p >= rows * UPS, rem = p - plane * rows * UPS, row = rem / UPS, pos = rem % UPS; // (UPS is a power of two)
             ucol[i] = (pos ^ (row & (UPS - 1))) * EPU;
             off[i] = (uint32_t)(((FAR ? 0 : plane * a.act_plane) + (size_t)min(row, live - 1) * a.ld_act + ucol[i]) * sizeof(T));
         }
@@ -304,195 +268,45 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
     }
 };
 // A wavefront's n steps of K through a ring of NB (one or two) buffers of its own.  request(i, buffer) asks for its i-th step, use(i, buffer)
-// multiplies it; between them the step's loads are waited for, with two buffers the next step's stay in flight.  `per`: loads of a step.
-// prologue() runs behind the first request.
-template <int NB, class Request, class Use, class Prologue>
-__device__ __forceinline__ void ring_walk(int n, int per, Request request, Use use, Prologue prologue) {
+// multiplies it; between them the step's loads are waited for - with two buffers by wait_ahead(), which leaves the next step's in
+// flight.  behind_first() runs behind the first request, what it asks for has arrived when the first step has; with_first() runs then.
+template <int NB, class Request, class Use, class Wait, class Behind, class With>
+__device__ __forceinline__ void ring_walk(int n, Request request, Use use, Wait wait_ahead, Behind behind_first, With with_first) {
     static_assert(NB == 1 || NB == 2, "a third buffer made every launch slower: no counted wait for two steps");
     if (n > 0) request(0, 0);
-    prologue();
+    behind_first();
     for (int i = 0, buf = 0; i < n; ++i) {
         const bool ahead = NB == 2 && i + 1 < n;
         if (ahead) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // what was read from the buffer that is filled now has arrived
             request(i + 1, buf ^ 1);
-            wait_for_step(per);
+            wait_ahead();
         } else {
             wait_vmcnt_at_most<0>();
         }
         asm volatile("" ::: "memory");
         use(i, buf);
+        if (i == 0) with_first();
         if (NB == 1 && i + 1 < n) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             request(i + 1, 0);
         }
         if (NB == 2) buf ^= 1;
     }
+    if (n <= 0) with_first();
 }
 
-// Sum of the waves' partial tiles of row tile rt (fixed order) and the epilogue, by one wave.
-template <typename T, int EPI, int NW>
-__device__ __forceinline__ void tile_epilogue(const GemmArgs &a, const float (&red)[NW][(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1][4][64],
-                                              const int (&n0)[(EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1], int rt, const EpiPre *pre = nullptr,
-                                              float rs = 1.0f) {
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63;
-    float r[NT][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float sum = red[0][t][v][lane];
-#pragma unroll 4
-            for (int w2 = 1; w2 < NW; ++w2) sum += red[w2][t][v][lane];
-            r[t][v] = sum * rs; // rs: the row scale of a deferred norm (1 otherwise: exact)
-        }
-    apply_epilogue<T, EPI>(a, r, n0, rt, pre);
+// Sum over the PS (4, 8 or 16) neighbouring lanes that share a row; every one of them gets it.
+template <int PS> __device__ __forceinline__ float row_sum(float x) {
+    auto add = [](float v, auto ctrl) { return v + u2f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)f2u(v), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    x = add(x, std::integral_constant<int, 0xB1>{});  // quad_perm: lane xor 1
+    x = add(x, std::integral_constant<int, 0x4E>{});  // quad_perm: lane xor 2
+    if constexpr (PS >= 8) x = add(x, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other four of eight
+    if constexpr (PS >= 16) x = add(x, std::integral_constant<int, 0x140>{}); // row_mirror: the other eight of sixteen
+    return x;
 }
 
-// The kernel for at most 16 rows: NW = wavefronts per workgroup (interleaved over K), NB = buffers of a wavefront's ring of 128-byte
-// steps, RCAP = most rows (8 or 16: sizes the LDS); blockIdx.x = column tile (pair).
-// The weights go through LDS like the activations: loaded straight into MFMA operand layout, a load instruction takes
-// 64 bytes of each of 16 weight rows (four lanes per row), i.e. half a cache line per row; a load-to-LDS instruction
-// whose lane l brings unit l & 7 of row l >> 3 takes whole 128-byte lines of 8 rows, and two of them bring a step's
-// 16 x 128 bytes, which the lanes then read from LDS as operands (same xor placement as the activations).  Measured
-// on the 7B-shaped layer: 5-row pass 3.28 -> 3.05 ms, 1 row 3.09 -> 2.99 (requests of whole lines are what counts:
-// timing-only variants with a tile-major weight order gained 6 % with a contiguous kilobyte per instruction and
-// nothing with half lines).
-template <typename T, int EPI, int NW, int NB, int RCAP>
-__global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
-    constexpr int E = Traits<T>::E, KB = 4 * E, EPU = 16 / (int)sizeof(T);
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = lane & 15, g = lane >> 4;
-    const int K = a.K;
-
-    int n0[NT];
-    if constexpr (EPI == EPI_QKV) {
-        const int per_head = a.hd / 32;
-        const int hh = blockIdx.x / per_head; // head index over [q heads | k heads | v heads]
-        n0[0] = hh * a.hd + (blockIdx.x % per_head) * 16;
-        n0[1] = n0[0] + a.hd / 2;
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        n0[0] = blockIdx.x * 16;
-        n0[1] = a.N + n0[0];
-    } else {
-        n0[0] = blockIdx.x * 16;
-    }
-    const int nrows_w = (EPI == EPI_SWIGLU) ? 2 * a.N : a.N;
-
-    // this lane's pieces of a weight step: instruction i brings rows 8i .. 8i + 7 of the tile, lane l unit
-    // (l & 7) xor (row & 7) of row 8i + (l >> 3), into slot 64 i + l = row * 8 + (l & 7)
-    const int wucol = ((lane & 7) ^ (lane >> 3)) * EPU;
-    const char *wbase[NT];
-    uint32_t woff[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        wbase[t] = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.W) + (size_t)n0[t] * K);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) // ragged last tile: a valid row, masked at the store
-            woff[t][i] = ((uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)K + wucol) * (uint32_t)sizeof(T);
-    }
-
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
-    EpiPre pre;
-    if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, 0, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise), worked out by the epilogue's wave from sums that are
-    // asked for in front of the first steps and used behind their request (one memory round trip less than ahead of them)
-    float rs = 1.0f;
-    float4 nsq[NSQ4];
-    const bool scaled = a.act_nsq && wave == 0;
-    if (scaled) nsq_prefetch(a, 0, nsq);
-
-    // Each wave takes 128-byte steps (two k-blocks) of every row, interleaved with the other waves.
-    // Every workgroup starts at another place of K and wraps around (k_rotation): with all of them walking K in step,
-    // the loads of a moment differ by multiples of the row stride and meet in the same memory channels, and all ask
-    // for the same activation lines (measured on the 7B-shaped layer: 6 % of the 5-row pass, QKV 33.3 -> 29.7 us).
-    const int nkb = (K + KB - 1) / KB;
-    const int nst = (nkb + 1) / 2;
-    const int rot = k_rotation(nst);
-    const bool ragged = (K % (2 * KB)) != 0; // the last step ends inside its 128 bytes
-    typedef ActStage<T, 8, RCAP> Stage;
-    constexpr int WBYTES = NT * 2048, SBYTES = WBYTES + Stage::BYTES;
-    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
-    Stage stage;
-    stage.init(a, 0, K, lane);
-    int rdw[2], rda[2][Stage::PL];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        rdw[j] = (c * 8 + ((4 * j + g) ^ (c & 7))) * 16;
-#pragma unroll
-        for (int pl = 0; pl < Stage::PL; ++pl) rda[j][pl] = WBYTES + stage.operand_offset(c, 4 * j + g, pl);
-    }
-#pragma unroll
-    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    const uint32_t lds0 = lds_address(lds[wave][0]);
-    const int n = wave < nst ? (nst - wave + NW - 1) / NW : 0;
-    ring_walk<NB>(
-        n, 2 * NT + stage.loads(),
-        [&](int i, int buf) {
-            const int st = rotated(wave + i * NW, rot, nst), k0 = 2 * st * KB;
-            const bool tail = ragged && st == nst - 1;
-            const uint32_t to = lds0 + buf * SBYTES;
-            const uint32_t over = tail ? (uint32_t)(max(k0 + wucol - (K - EPU), 0) * (int)sizeof(T)) : 0u; // past a ragged end: the row's last unit, zeroed after the read
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + (size_t)k0 * sizeof(T), woff[t][j] - over, to + t * 2048 + j * 1024);
-            stage.request(to + WBYTES, k0, tail);
-        },
-        [&](int i, int buf) {
-            const unsigned char *cur = lds[wave][buf];
-            u32x4 w[NT][2];
-            Act<T> av[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) w[t][j] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[j]);
-#pragma unroll
-                for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + rda[j][pl]);
-            }
-            if (ragged) {
-                const int st = rotated(wave + i * NW, rot, nst);
-                if (st == nst - 1) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        if ((2 * st + j) * KB + g * E >= K) {
-#pragma unroll
-                            for (int t = 0; t < NT; ++t) w[t][j] = zero16();
-                        }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w[t][j], av[j]);
-        },
-        [&] {
-            if (scaled) rs = deferred_row_scale(a, nsq);
-        });
-
-    // fixed-order sum of the waves' partial tiles; wave 0 applies the epilogue
-    __shared__ float red[NW][NT][4][64];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][t][v][lane] = acc[t][v];
-    __syncthreads();
-    if (wave == 0) tile_epilogue<T, EPI, NW>(a, red, n0, 0, PRE ? &pre : nullptr, rs);
-    move_lengths<EPI>(a);
-}
-
-// ---- weight-only int8 matrices (the quantised model Sections 2 and 3 assume; one fp32 scale per output row)
-//
-// Same decomposition as gemm_kernel for at most 16 rows, a step being 128 entries of K (a 128-byte line of a weight
-// row).  A lane's 16-byte unit holds 16 consecutive K entries of its weight row, i.e. two MFMA k-blocks: lane (c, g)
-// supplies k = 128*step + 64*h + 16*g + 8*j .. +7 to block (h, j), and reads the activations of exactly those k.  An
-// int8 value is exact in bf16, the sum runs in fp32, and the row scale multiplies the finished sum, so the only
-// roundings are those of the sum.
+// int8 entries as bf16 (exact)
 __device__ __forceinline__ uint32_t w8_pair_to_bf16x2(uint32_t x, int first_byte) {
     const float f0 = (float)((int)(x << (24 - 8 * first_byte)) >> 24); // sign-extended bytes
     const float f1 = (float)((int)(x << (16 - 8 * first_byte)) >> 24);
@@ -502,143 +316,7 @@ __device__ __forceinline__ u32x4 w8_to_bf16x8(uint32_t a, uint32_t b) {
     return u32x4{w8_pair_to_bf16x2(a, 0), w8_pair_to_bf16x2(a, 2), w8_pair_to_bf16x2(b, 0), w8_pair_to_bf16x2(b, 2)};
 }
 
-template <int EPI, int NW, int NB, int RCAP>
-__global__ __launch_bounds__(NW * 64) void gemm_w8_kernel(GemmArgs a) {
-    typedef bf16_t T;
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = lane & 15, g = lane >> 4;
-    const int K = a.K;
-
-    int n0[NT];
-    if constexpr (EPI == EPI_QKV) {
-        const int per_head = a.hd / 32;
-        const int hh = blockIdx.x / per_head;
-        n0[0] = hh * a.hd + (blockIdx.x % per_head) * 16;
-        n0[1] = n0[0] + a.hd / 2;
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        n0[0] = blockIdx.x * 16;
-        n0[1] = a.N + n0[0];
-    } else {
-        n0[0] = blockIdx.x * 16;
-    }
-    const int nrows_w = (EPI == EPI_SWIGLU) ? 2 * a.N : a.N;
-
-    // a step is 128 entries of K, a whole 128-byte line of every weight row; as in gemm_kernel the tile's 16 x 128 bytes
-    // come through LDS by two load-to-LDS instructions (lane l: unit (l & 7) xor (row & 7) of row 8i + (l >> 3))
-    const int wucol = ((lane & 7) ^ (lane >> 3)) * 16;
-    const char *wbase[NT];
-    uint32_t woff[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        wbase[t] = reinterpret_cast<const char *>(a.W) + (size_t)n0[t] * K;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) woff[t][i] = (uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)K + wucol; // ragged last tile: a valid row, masked at the store
-    }
-
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
-    EpiPre pre;
-    if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, 0, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise): see gemm_kernel
-    float rs = 1.0f;
-    float4 nsq[NSQ4];
-    const bool scaled = a.act_nsq && wave == 0;
-    if (scaled) nsq_prefetch(a, 0, nsq);
-
-    const int nsteps = (K + 127) / 128;
-    const int rot = k_rotation(nsteps); // (see gemm_kernel)
-    const bool ragged = (K % 128) != 0;
-    // lane (c, g) reads units g and 4 + g of its weight row: entries 64h + 16g .. + 15, i.e. two k-blocks (j = 0, 1) of 8
-    // entries each, whose activations are unit 8h + 2g + j of the row's 16
-    typedef ActStage<T, 16, RCAP> Stage;
-    constexpr int WBYTES = NT * 2048, SBYTES = WBYTES + Stage::BYTES;
-    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
-    Stage stage;
-    stage.init(a, 0, K, lane);
-    int rdw[2], rda[2][2][Stage::PL];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        rdw[h] = (c * 8 + ((4 * h + g) ^ (c & 7))) * 16;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int pl = 0; pl < Stage::PL; ++pl) rda[h][j][pl] = WBYTES + stage.operand_offset(c, 8 * h + 2 * g + j, pl);
-    }
-#pragma unroll
-    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    const uint32_t lds0 = lds_address(lds[wave][0]);
-    const int n = wave < nsteps ? (nsteps - wave + NW - 1) / NW : 0;
-    ring_walk<NB>(
-        n, 2 * NT + stage.loads(),
-        [&](int i, int buf) {
-            const int k0 = rotated(wave + i * NW, rot, nsteps) * 128;
-            const bool tail = ragged && k0 + 128 > K;
-            const uint32_t to = lds0 + buf * SBYTES;
-            const uint32_t over = tail ? (uint32_t)max(k0 + wucol - (K - 16), 0) : 0u; // past a ragged end: the row's last unit, zeroed after the read (K is a multiple of 16)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + k0, woff[t][j] - over, to + t * 2048 + j * 1024);
-            stage.request(to + WBYTES, k0, tail);
-        },
-        [&](int i, int buf) {
-            const unsigned char *cur = lds[wave][buf];
-            const int k0 = ragged ? rotated(wave + i * NW, rot, nsteps) * 128 : 0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                u32x4 w[NT];
-                Act<T> av[2];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[h]);
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int pl = 0; pl < Stage::PL; ++pl) av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + rda[h][j][pl]);
-                if (ragged && k0 + 64 * h + 16 * g >= K) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) w[t] = zero16();
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) acc[t] = mma(acc[t], w8_to_bf16x8(w[t][2 * j], w[t][2 * j + 1]), av[j]);
-            }
-        },
-        [&] {
-            if (scaled) rs = deferred_row_scale(a, nsq);
-        });
-
-    // fixed-order sum of the waves' partial tiles; wave 0 scales the columns and applies the epilogue
-    __shared__ float red[NW][NT][4][64];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][t][v][lane] = acc[t][v];
-    __syncthreads();
-    if (wave != 0) return;
-    float r[NT][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float sum = red[0][t][v][lane];
-#pragma unroll 4
-            for (int w2 = 1; w2 < NW; ++w2) sum += red[w2][t][v][lane];
-            r[t][v] = sum * a.wscale[min(n0[t] + 4 * g + v, nrows_w - 1)] * rs;
-        }
-    apply_epilogue<T, EPI>(a, r, n0, 0, PRE ? &pre : nullptr);
-    move_lengths<EPI>(a);
-}
-
-// ---- weight-only int4 matrices with one scale per group of 128 K entries (the coarser reading of the same
-// quantised model).  A lane's 16-byte unit holds 32 consecutive K entries of its weight row, i.e. four MFMA
-// k-blocks (dword j = entries 8j..8j+7, entry e in bits 4e..4e+3, two's complement).  A step is a 128-byte line of
-// every weight row = 256 entries of K = two scale groups, the lane's two units being one of each: a group accumulates
-// into a fresh tile and the tile is added to the running sum times the group's scales of the lane's four output
-// columns (scales are stored group-major, scale[group][column]).  K is a multiple of 128.
+// int4 entries as bf16: dword j of a unit holds entries 8j .. 8j + 7, entry e in bits 4e .. 4e + 3, two's complement
 __device__ __forceinline__ u32x4 w4_to_bf16x8(uint32_t x) {
     uint32_t r[4];
 #pragma unroll
@@ -667,140 +345,256 @@ __device__ __forceinline__ u32x4 w4_to_bf16x8_plus136(uint32_t x) {
 }
 constexpr float W4_BIAS = 136.0f;
 
-template <int EPI, int NW, int NB, int RCAP, bool FAR = false>
-__global__ __launch_bounds__(NW * 64) void gemm_w4_kernel(GemmArgs a) {
-    typedef bf16_t T;
-    constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
+// The kernel for at most 16 rows, for every kind of matrix (QB: 0 storage type, 8 int8 with one scale per weight row, 4 int4 with one
+// scale per 128 K entries).  blockIdx.x owns a share of the output columns, in quads of four (a quad of pairs for the fused epilogues:
+// its first and its second half): the launcher deals them out evenly, so that every compute unit has the same number of bytes to
+// fetch - with 16 columns to a workgroup the compute units with one workgroup more than the others were what a launch took (a 13B-shaped
+// down projection, 320 workgroups on 256 units: 21 us the median workgroup, 37 the launch) - and stages the activations once for all
+// its columns.  The NW wavefronts interleave over K in steps of 128 bytes of every row, each through a ring of NB buffers of its own;
+// EI load instructions of eight weight rows (per half) make a step, in CT 16-column tiles.
+//   Up to 8 rows (RCAP), two planes: operand columns 0 .. 7 hold the rows' high parts and 8 .. 15 the low ones, one MFMA and one LDS read
+// per k-block instead of two; the two halves of the sums are added in front of the epilogue.
+//   int8: a lane's 16-byte unit holds 16 entries of its weight row, two k-blocks: lane (c, g) supplies k = 64h + 16g + 8j .. + 7 of the
+// step to block (h, j) and reads the activations of exactly those; the row scale multiplies the finished sum.  int4: a unit holds 32
+// entries, four k-blocks, all in scale group h of the step's two; a group accumulates into a fresh tile, which is added to the
+// running sum times the group's scales of the lane's four columns (stored group-major, scale[group][column]).
+//   Weights through LDS: a load-to-LDS instruction takes whole 128-byte lines of 8 rows (lane l: unit (l & 7) xor (row & 7) of row
+// l >> 3), loads in operand layout would take half lines of 16.
+//   In front of the first request stands only what it needs, and a lane finishes two columns of a row: a launch spent 0.6 - 1.3 us ahead
+// of its first load and as much behind its last one.
+//   Measured against 16 columns to a workgroup (us a launch, back to back, 5 rows; QKV, O, gate/up, down): 7B shape bf16 20.0, 9.0, 29.4, 18.2 ->
+// 17.7, 7.9, 28.8, 16.5 (6.2 TB/s in gate/up); 13B 28.8, 16.0, 49.0, 35.4 -> 26.9, 11.3, 45.7, 24.3; 3B 15.6, 7.2, 17.9, 12.1 -> 11.8, 6.3, 17.7, 10.9;
+// 7B int8 15.7, 7.8, 20.0, 14.3 -> 12.0, 6.3, 18.5, 11.7; int4 13.0, 7.2, 16.3, 11.2 -> 10.7, 5.9, 14.5, 9.7.  Heads of 32000 columns, K 4096: bf16
+// 42.0 -> 40.6, int8 35.3 -> 24.0, int4 24.6 -> 17.2; 12 rows: gate/up 32.6 -> 31.2, 13B 59.0 -> 49.0, bf16 head 65.4 -> 43.3.
+template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP, bool FAR = false>
+__global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
+    constexpr int E = Traits<T>::E, KB = 4 * E, CT = (EI + 1) / 2;
+    constexpr int NH = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1, NT = NH * CT; // halves; 16-column tiles
+    constexpr bool HL = Traits<T>::PLANES == 2 && RCAP <= 8; // high and low rows side by side in one operand
+    constexpr int SK = QB == 4 ? 256 : QB == 8 ? 128 : 128 / (int)sizeof(T); // K entries of a step
+    constexpr int PV = HL ? 1 : Traits<T>::PLANES;
+    constexpr int SW = QB == 4 ? (2 * NT * 16 + 63) / 64 : 0; // int4: load instructions for a step's scales
+    typedef ActStage<T, SK * (int)sizeof(T) / 16, RCAP, FAR> Stage;
+    constexpr int SBASE = NH * EI * 1024, WBYTES = SBASE + SW * 256, SBYTES = WBYTES + Stage::BYTES; // (the rows that an odd EI's last tile does not have read what follows)
+    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int K = a.K;
+    const int rt = FAR ? blockIdx.y : 0; // (several row tiles: every one streams the weights again)
 
-    int n0[NT];
-    if constexpr (EPI == EPI_QKV) {
-        const int per_head = a.hd / 32;
-        const int hh = blockIdx.x / per_head;
-        n0[0] = hh * a.hd + (blockIdx.x % per_head) * 16;
-        n0[1] = n0[0] + a.hd / 2;
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        n0[0] = blockIdx.x * 16;
-        n0[1] = a.N + n0[0];
-    } else {
-        n0[0] = blockIdx.x * 16;
-    }
-    const int nrows_w = (EPI == EPI_SWIGLU) ? 2 * a.N : a.N;
-
-    // the tile's 16 x 128 bytes of a step come through LDS by two load-to-LDS instructions, as in gemm_kernel
-    // (lane l: unit (l & 7) xor (row & 7) of row 8i + (l >> 3))
-    const int wucol = ((lane & 7) ^ (lane >> 3)) * 16; // bytes
-    const int bmax = K / 2 - 16;
-    const char *wbase[NT];
-    uint32_t woff[NT][2], soff = 0;
+    // the workgroup's quads; weight rows of a column (of its first half)
+    const int q0 = (int)blockIdx.x * a.quads + min((int)blockIdx.x, a.quads_rest), nq = a.quads + ((int)blockIdx.x < a.quads_rest ? 1 : 0);
+    const int nrows_w = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
+    const int columns = EPI == EPI_QKV ? a.N / 2 : a.N;
+    auto row_of = [&](int p) { // QKV: column p of the first halves is column p mod (hd / 2) of head p / (hd / 2)
+        if constexpr (EPI == EPI_QKV) return p + (p & ~(a.hd / 2 - 1));
+        else return p;
+    };
+    const size_t row_bytes = QB == 4 ? (size_t)K / 2 : QB == 8 ? (size_t)K : (size_t)K * sizeof(T);
+    const int half_rows = EPI == EPI_QKV ? a.hd / 2 : a.N; // from a first half's row to its second half's
+    const int wub = ((lane & 7) ^ (lane >> 3)) * 16;       // this lane's bytes of a step
+    const int row0 = row_of(4 * q0);
+    uint32_t woff[EI];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        wbase[t] = reinterpret_cast<const char *>(a.W) + (size_t)n0[t] * (K / 2);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) woff[t][i] = (uint32_t)(min(n0[t] + 8 * i + (lane >> 3), nrows_w - 1) - n0[t]) * (uint32_t)(K / 2) + wucol; // ragged last tile: a valid row, masked at the store
-        // the step's scales, one load instruction of a word per lane: lane (h * NT + t) * 16 + column has group h, tile t (with one tile
-        // the upper half of the wavefront repeats the lower)
-        if ((lane >> 4) % NT == t) soff = (uint32_t)min(n0[t] + c, nrows_w - 1) * 4u;
+    for (int i = 0; i < EI; ++i) { // instruction i: rows 8i .. 8i + 7; columns that the workgroup or the matrix does not have repeat its last one
+        const int r = min(8 * i + (lane >> 3), 4 * nq - 1);
+        woff[i] = (uint32_t)((row_of(min(4 * q0 + r, columns - 1)) - row0) * (int)row_bytes) + wub;
     }
-    const int sh = (lane >> 4) / NT & 1;
-    // calls of more than 16 rows: one workgroup per (column tile, row tile); every row tile streams the (quarter-size)
-    // weights again
-    const int rt = blockIdx.y;
+    const char *wbase = reinterpret_cast<const char *>(a.W) + (size_t)row0 * row_bytes;
+    uint32_t soff[SW ? SW : 1]; // int4: word 64 i + lane of a step's scales is (group h * NH + half) * 16 CT + column
+    bool sh[SW ? SW : 1];
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {
+        const int w = i * 64 + lane, r = w % (16 * CT), hf = w / (16 * CT) % NH;
+        sh[i] = w / (16 * NT) == 1;
+        soff[i] = (uint32_t)(row_of(min(4 * q0 + min(r, 4 * nq - 1), columns - 1)) + hf * half_rows) * 4u;
+    }
+    // Every workgroup starts at another place of K and wraps around (k_rotation): with all of them walking K in step,
+    // the loads of a moment differ by multiples of the row stride and meet in the same memory channels, and all ask
+    // for the same activation lines (measured on the 7B-shaped layer: 6 % of the 5-row pass, QKV 33.3 -> 29.7 us).
+    const int nst = (K + SK - 1) / SK;
+    const int rot = k_rotation(nst);
+    const bool ragged = K % SK != 0; // the last step ends inside its 128 bytes
+    Stage stage;
+    stage.init(a, rt * 16, K, lane);
+    const uint32_t lds0 = lds_address(lds[wave][0]);
 
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr bool PRE = EPI != EPI_STORE; // the epilogue's own operands, asked for ahead of the K loop
-    EpiPre pre;
-    if (PRE && wave == 0) epi_prefetch<T, EPI>(a, n0, rt, pre);
-    // the row scale of a deferred norm on the activations (1 otherwise): see gemm_kernel
-    float rs = 1.0f;
-    float4 nsq[NSQ4];
-    const bool scaled = a.act_nsq && wave == 0;
-    if (scaled) nsq_prefetch(a, rt, nsq);
-
-    // lane (c, g) reads units g and 4 + g of its weight row: unit 4h + g is entries 128h + 32g .. + 31 of the step, all in
-    // scale group h, i.e. four k-blocks (j = 0..3) of 8 entries whose activations are unit 16h + 4g + j of the row's 32
-    const int ngroups = K / 128;
-    const int nsteps = (ngroups + 1) / 2; // two scale groups (a 128-byte line of a weight row) per step
-    const int rot = k_rotation(nsteps);   // (see gemm_kernel)
-    typedef ActStage<T, 32, RCAP, FAR> Stage;
-    constexpr int SBASE = NT * 2048, WBYTES = SBASE + 256, SBYTES = WBYTES + Stage::BYTES;
-    __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
-    Stage stage;
-    stage.init(a, rt * 16, K, lane);
     int rdw[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) rdw[h] = (c * 8 + ((4 * h + g) ^ (c & 7))) * 16;
+    for (int j = 0; j < 2; ++j) rdw[j] = (c * 8 + ((4 * j + g) ^ (c & 7))) * 16;
+    auto read_act = [&](const unsigned char *cur, int unit, u32x4 (&av)[PV]) {
 #pragma unroll
-    for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
-    const uint32_t lds0 = lds_address(lds[wave][0]);
-    const int n = wave < nsteps ? (nsteps - wave + NW - 1) / NW : 0;
+        for (int pl = 0; pl < PV; ++pl)
+            av[pl] = *reinterpret_cast<const u32x4 *>(cur + WBYTES + (HL ? stage.operand_offset(c & 7, unit, c >> 3) : stage.operand_offset(c, unit, pl)));
+    };
+    auto mul = [&](f32x4 s, u32x4 w, const u32x4 (&av)[PV]) {
+        if constexpr (Traits<T>::PLANES == 2) {
+#pragma unroll
+            for (int pl = 0; pl < PV; ++pl) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, av[pl]), s, 0, 0, 0);
+            return s;
+        } else {
+            Act<T> b;
+            b.p[0] = av[0];
+            return mma(s, w, b);
+        }
+    };
+
+    // The epilogue: thread i of the first EW wavefronts finishes columns 2 (i mod PS) and + 1 of row i / PS; what it needs besides the
+    // sums is asked for behind the first step's request: operands of the epilogue, int8 scales, a deferred norm's sums of squares.
+    constexpr int PS = CT == 1 ? (EI == 1 ? 4 : 8) : 16, EW = ((HL ? 8 : 16) * PS + 63) / 64, NSQ4 = NSQ_MAX_PARTS / 4 / PS;
+    static_assert(EW <= NW && CT <= 2 && NW * NB * SBYTES <= 160 * 1024, "");
+    const int er = (int)threadIdx.x / PS, ep = (int)threadIdx.x % PS; // row, column pair
+    const int m = rt * 16 + er, col = row_of(min(4 * q0 + min(2 * ep, 4 * nq - 2), (columns - 1) & ~1));
+    const bool ends = wave < EW;
+    EpiPre<2> pre;
+    float wsc[NH][2], rs = 1.0f;
+    float4 nsq[NSQ4];
+
+    const int n = wave < nst ? (nst - wave + NW - 1) / NW : 0;
     ring_walk<NB>(
-        n, 2 * NT + 1 + stage.loads(),
+        n,
         [&](int i, int buf) {
-            const int st = rotated(wave + i * NW, rot, nsteps);
-            const bool tail = 2 * st + 1 >= ngroups; // a last step of one group: valid units and scales, not used
+            const int st = rotated(wave + i * NW, rot, nst);
+            const bool tail = ragged && st == nst - 1;
             const uint32_t to = lds0 + buf * SBYTES;
-            const uint32_t over = tail ? (uint32_t)max(st * 128 + wucol - bmax, 0) : 0u;
+            const uint32_t over = tail ? (uint32_t)max(st * 128 + wub - ((int)row_bytes - 16), 0) : 0u; // past a ragged end: the row's last unit, zeroed after the read (int4: a whole group, skipped)
+            const char *b = wbase + (size_t)st * 128;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int h = 0; h < NH; ++h)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) dma16<true>(wbase[t] + (size_t)st * 128, woff[t][j] - over, to + t * 2048 + j * 1024);
-            dma4(a.wscale + (size_t)(2 * st) * nrows_w, soff + (sh && !tail ? (uint32_t)nrows_w * 4u : 0u), to + SBASE);
-            stage.request(to + WBYTES, st * 256, tail);
+                for (int j = 0; j < EI; ++j) dma16<true>(b + (h ? half_rows * row_bytes : 0), woff[j] - over, to + (h * EI + j) * 1024);
+#pragma unroll
+            for (int j = 0; j < SW; ++j) dma4(a.wscale + (size_t)(2 * st) * nrows_w, soff[j] + (sh[j] && !tail ? (uint32_t)nrows_w * 4u : 0u), to + SBASE + j * 256);
+            stage.request(to + WBYTES, st * SK, tail);
         },
         [&](int i, int buf) {
             const unsigned char *cur = lds[wave][buf];
-            const int st = rotated(wave + i * NW, rot, nsteps);
+            const int st = ragged || QB == 4 ? rotated(wave + i * NW, rot, nst) : 0;
+            auto read_w = [&](int t, int j) { return *reinterpret_cast<const u32x4 *>(cur + t / CT * (EI * 1024) + t % CT * 2048 + rdw[j]); };
+            if constexpr (QB == 0) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (2 * st + h < ngroups) { // (the same for the whole wave)
-                    u32x4 w[NT];
-                    f32x4 sc[NT];
-                    Act<T> av[4];
+                for (int j = 0; j < 2; ++j) {
+                    u32x4 w[NT], av[PV];
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        w[t] = *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[h]);
-                        sc[t] = *reinterpret_cast<const f32x4 *>(cur + SBASE + (h * NT + t) * 64 + g * 16);
+                    for (int t = 0; t < NT; ++t) w[t] = read_w(t, j);
+                    read_act(cur, 4 * j + g, av);
+                    if (ragged && (2 * st + j) * KB + g * E >= K) {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) w[t] = zero16();
                     }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
+                    for (int t = 0; t < NT; ++t) acc[t] = mul(acc[t], w[t], av);
+                }
+            } else if constexpr (QB == 8) {
 #pragma unroll
-                        for (int pl = 0; pl < Stage::PL; ++pl)
-                            av[j].p[pl] = *reinterpret_cast<const u32x4 *>(cur + WBYTES + stage.operand_offset(c, 16 * h + 4 * g + j, pl));
-                    // the group's activation sums per row (an all-ones weight tile: every output column gets the sum)
-                    f32x4 asum = f32x4{0.f, 0.f, 0.f, 0.f};
-                    const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+                for (int h = 0; h < 2; ++h) {
+                    u32x4 w[NT], av[2][PV];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) asum = mma(asum, ones, av[j]);
+                    for (int t = 0; t < NT; ++t) w[t] = read_w(t, h);
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int j = 0; j < 2; ++j) read_act(cur, 8 * h + 2 * g + j, av[j]);
+                    if (ragged && st * SK + 64 * h + 16 * g >= K) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) part = mma(part, w4_to_bf16x8_plus136(w[t][j]), av[j]);
+                        for (int t = 0; t < NT; ++t) w[t] = zero16();
+                    }
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[t][v] += sc[t][v] * (part[v] - W4_BIAS * asum[v]);
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) acc[t] = mul(acc[t], w8_to_bf16x8(w[t][2 * j], w[t][2 * j + 1]), av[j]);
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (2 * st + h < K / 128) { // (the same for the whole wave)
+                        u32x4 av[4][PV];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) read_act(cur, 16 * h + 4 * g + j, av[j]);
+                        // the group's activation sums per row (an all-ones weight tile: every output column gets the sum)
+                        f32x4 asum = f32x4{0.f, 0.f, 0.f, 0.f};
+                        const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) asum = mul(asum, ones, av[j]);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            const u32x4 w = read_w(t, h);
+                            const f32x4 sc = *reinterpret_cast<const f32x4 *>(cur + SBASE + ((h * NT + t) * 16 + 4 * g) * 4);
+                            f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) part = mul(part, w4_to_bf16x8_plus136(w[j]), av[j]);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) acc[t][v] += sc[v] * (part[v] - W4_BIAS * asum[v]);
+                        }
                     }
                 }
             }
         },
+        [&] { wait_for_step<NH * EI + SW, Stage::NDMA>(stage.loads()); },
         [&] {
-            if (scaled) rs = deferred_row_scale(a, nsq);
+#pragma unroll
+            for (int s = 0; s < NB; ++s) Stage::clear(lds[wave][s] + WBYTES, lane);
+            if (!ends) return;
+            epi_prefetch<EPI, 2>(a, m, col, pre);
+            if constexpr (QB == 8) {
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) wsc[h][v] = a.wscale[min(col + h * half_rows + v, nrows_w - 1)];
+            }
+            if (a.act_nsq) { // the row's PS threads read its partial sums, 16 bytes at a time in turn
+                const float4 *p = reinterpret_cast<const float4 *>(a.act_nsq + (size_t)min(m, a.R - 1) * a.act_nsq_parts);
+#pragma unroll
+                for (int i = 0; i < NSQ4; ++i) nsq[i] = p[min(ep + i * PS, a.act_nsq_parts / 4 - 1)]; // (surplus slots repeat the last one and are not added)
+            }
+        },
+        [&] {
+            if (!ends) return;
+            epi_prefetch_rope<EPI, 2>(a, m, col, pre);
+            if (a.act_nsq) { // the row scale of a deferred norm on the activations
+                float s = 0.f;
+#pragma unroll
+                for (int i = 0; i < NSQ4; ++i) s += ep + i * PS < a.act_nsq_parts / 4 ? (nsq[i].x + nsq[i].y) + (nsq[i].z + nsq[i].w) : 0.f;
+                rs = 1.0f / sqrtf(row_sum<PS>(s) / (float)K + a.norm_eps);
+            }
         });
 
-    // fixed-order sum of the waves' partial tiles; wave 0 applies the epilogue
-    __shared__ float red[NW][NT][4][64];
+    // the waves' partial tiles, each in the wavefront's own ring (nothing lands there any more), summed in order by the epilogue's threads
+    static_assert(NT * 1024 <= SBYTES, "");
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][t][v][lane] = acc[t][v];
+    for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4 *>(lds[wave][0] + (t * 64 + lane) * 16) = acc[t];
     __syncthreads();
-    if (wave != 0) return;
-    tile_epilogue<T, EPI, NW>(a, red, n0, rt, PRE ? &pre : nullptr, rs);
     move_lengths<EPI>(a);
+    if (!ends) return;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    float x[NH][2];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        // column pair ep: quad ep / 2, i.e. tile ep / 8, lane group (ep / 2) mod 4, accumulator registers 2 (ep mod 2) and + 1
+        const int at = (h * CT + ep / 8) * 1024 + ((ep / 2 & 3) * 16 + (er & 15)) * 16 + (ep & 1) * 8;
+        f32x2 sum = *reinterpret_cast<const f32x2 *>(lds[0][0] + at);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const f32x2 *>(lds[w][0] + at);
+        if constexpr (HL) { // + the sums of the low parts (row + 8)
+            f32x2 low = *reinterpret_cast<const f32x2 *>(lds[0][0] + at + 128);
+#pragma unroll
+            for (int w = 1; w < NW; ++w) low += *reinterpret_cast<const f32x2 *>(lds[w][0] + at + 128);
+            sum += low;
+        }
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            x[h][v] = sum[v];
+            if constexpr (QB == 8) x[h][v] *= wsc[h][v];
+            x[h][v] *= rs; // (1 without a deferred norm: exact)
+        }
+    }
+    float sq = 0.f;
+    if (m < a.R && ep < 2 * nq && 4 * q0 + 2 * ep < columns) sq = epilogue_cols<T, EPI, 2>(a, m, col, x[0], x[NH - 1], pre);
+    if (EPI == EPI_RESID && a.nsq_out) { // deferred norm: the row's sum of squares over the workgroup's columns
+        sq = row_sum<PS>(sq);
+        if (ep == 0 && m < a.R) a.nsq_out[(size_t)m * a.nsq_parts + blockIdx.x] = sq;
+    }
 }
 
 // More than 16 rows of fp32 or quantised models (bf16 matrices: gemm_tile_kernel): the waves of a workgroup split the output columns instead
@@ -1287,7 +1081,7 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
         bc = bc == NBUF - 1 ? 0 : bc + 1;
     }
 
-    auto finish = [&](const float (&out)[NT][4], int r, int p) { // row tile r and column tile (pair) p of the workgroup
+    auto finish = [&](float (&out)[NT][4], int r, int p) { // row tile r and column tile (pair) p of the workgroup
         const int ct = p * NT;
         if ((int)blockIdx.x * (C::CT / NT) + p >= npairs) return;
         int n0[NT];
@@ -1370,7 +1164,7 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(GemmArgs a) {
             x0[0] += lo[z].x; x0[1] += lo[z].y; x0[2] += lo[z].z; x0[3] += lo[z].w;
             x1[0] += hi[z].x; x1[1] += hi[z].y; x1[2] += hi[z].z; x1[3] += hi[z].w;
         }
-    qkv_finish_quad<bf16_t>(a, m, hh / a.H, hh % a.H, j0, x0, x1);
+    epilogue_cols<bf16_t, EPI_QKV, 4>(a, m, hh * a.hd + j0, x0, x1);
 }
 
 // Which tile and which split of K: the least of  rounds * K share * (16 us/MB * activations + 40 us/MB * weights)  over the
@@ -1474,38 +1268,94 @@ extern "C" void ss_dev_gemm_tile(int epi, int R, int N, int K, size_t ws_bytes, 
 
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);
 
-// NW wavefronts per workgroup and NB buffers each, for calls of at most 8 rows and of 9 to 16
-template <typename T, int EPI, int NW, int NB, int NW16 = NW, int NB16 = NB> static void launch_narrow(const GemmArgs &a, int tiles, hipStream_t st) {
-    if (a.R <= 8) hipLaunchKernelGGL((gemm_kernel<T, EPI, NW, NB, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_kernel<T, EPI, NW16, NB16, 16>), dim3(tiles), dim3(NW16 * 64), 0, st, a);
+// Calls of at most 16 rows.  The output columns in quads (of pairs for the fused epilogues) over k workgroups per compute unit of at
+// most eight quads, every one with the same number or one more.  Up to 8 rows k is the one that makes the fewest 16-column tiles of
+// them (a tile costs its LDS reads, MFMAs and conversions whether it is full or not: 2752 quads of pairs, K 4096, three workgroups
+// of four at most against two of six, one tile and a half: 28.8 against 29.2 us bf16, 18.5 / 20.3 int8, 14.5 / 16.6 int4); beyond,
+// where every workgroup's activations weigh as much as its weights, the smallest (12 rows: 31.2 us with two, 32.6 with three).
+struct ColumnSplit {
+    int groups, quads, rest; // workgroups; quads of each, and one more in the first `rest`
+};
+static ColumnSplit split_columns(int epi, int N, int R) {
+    constexpr int UNITS = 256;
+    const int quads = epi == EPI_QKV ? N / 8 : (N + 3) / 4;
+    auto tiles = [&](int k) { return k * (((quads + UNITS * k - 1) / (UNITS * k) + 3) / 4); };
+    const int least = (quads + UNITS * 8 - 1) / (UNITS * 8);
+    int k = least;
+    for (int i = least + 1; R <= 8 && i <= 2 * least; ++i)
+        if (tiles(i) < tiles(k)) k = i;
+    const int groups = std::min(quads, k * UNITS);
+    return ColumnSplit{groups, quads / groups, quads % groups};
+}
+int deferred_norm_parts(int d) {
+    const int groups = split_columns(EPI_RESID, d, 1).groups;
+    return d % 4 == 0 && groups % 16 == 0 && groups <= NSQ_MAX_PARTS ? groups : 0; // (at most 256 workgroups: one k whatever the rows)
+}
+// For the tests, which have to meet every size (not part of the library's interface): workgroups, quads of each, workgroups with one more.
+extern "C" void ss_dev_gemm_share(int epi, int R, int N, int *out3) {
+    const ColumnSplit s = split_columns(epi, N, R);
+    out3[0] = s.groups; out3[1] = s.quads; out3[2] = s.rest;
+}
+template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP, bool FAR = false>
+static void launch_cols_as(const GemmArgs &a0, const ColumnSplit &s, hipStream_t st) {
+    GemmArgs a = a0;
+    a.quads = s.quads; a.quads_rest = s.rest; a.nsq_parts = s.groups;
+    hipLaunchKernelGGL((gemm_cols_kernel<T, QB, EPI, NW, NB, EI, RCAP, FAR>), dim3(s.groups, FAR ? (a.R + 15) / 16 : 1), dim3(NW * 64), 0, st, a);
+}
+// Wavefronts and buffers, from all of (2 .. 16 waves) x (1, 2 buffers) on the matrices of four decoder widths (2048 - 5120) at 1, 5, 12 and 16
+// rows, within 3 % of the best for each: 60 - 90 KB asked for per compute unit (a unit has some 32 KB in flight; more only delays what
+// is needed first), by few waves with two buffers where steps are long and by many with one where they are short.  many: several
+// workgroups per compute unit.
+struct Ring {
+    int waves, buffers;
+};
+constexpr Ring ring_for(int bits, int epi, int ei, int rcap, bool many) {
+    const bool resid = epi == EPI_RESID, store = epi == EPI_STORE;
+    if (bits == 4) {
+        if (rcap == 16) return resid ? (ei <= 3 ? Ring{8, 1} : Ring{6, 1}) : !many && ei <= 2 ? Ring{4, 1} : Ring{6, 1};
+        return resid ? Ring{12, 1} : many ? Ring{4, 1} : Ring{8, 1};
+    }
+    if (bits == 8) {
+        if (rcap == 16) return resid ? Ring{12, 1} : many ? Ring{4, 1} : Ring{8, 1};
+        if (many) return store ? Ring{2, 2} : Ring{4, 1};
+        return resid ? Ring{8, 2} : ei <= 2 ? Ring{8, 1} : ei == 3 ? Ring{12, 1} : Ring{4, 2};
+    }
+    if (many) return store || (rcap == 8 && ei > 2) ? Ring{4, 2} : Ring{4, 1};
+    if (resid || store) return Ring{8, 2};
+    if (ei <= 2) return rcap == 16 ? Ring{12, 1} : Ring{8, 1};
+    return ei == 3 || rcap == 16 ? Ring{6, 2} : Ring{4, 2};
+}
+template <typename T, int QB, int EPI, int EI, bool MANY> static void launch_cols_ei(const GemmArgs &a, const ColumnSplit &s, hipStream_t st) {
+    constexpr int BITS = QB ? QB : 8 * (int)sizeof(T);
+    constexpr Ring R8 = ring_for(BITS, EPI, EI, 8, MANY), R16 = ring_for(BITS, EPI, EI, 16, MANY);
+    if (QB == 4 && a.R <= 5) launch_cols_as<T, QB, EPI, R8.waves, R8.buffers, EI, QB == 4 ? 5 : 8>(a, s, st); // (a step of int4 is mostly activations)
+    else if (a.R <= 8) launch_cols_as<T, QB, EPI, R8.waves, R8.buffers, EI, 8>(a, s, st);
+    else launch_cols_as<T, QB, EPI, R16.waves, R16.buffers, EI, 16>(a, s, st);
+}
+template <typename T, int QB, int EPI> static int launch_cols(const GemmArgs &a, hipStream_t st) {
+    const ColumnSplit s = split_columns(EPI, a.N, a.R);
+    const int ei = (s.quads + (s.rest ? 1 : 0) + 1) / 2;
+    constexpr bool M = EPI != EPI_RESID; // (a residual's columns fill more than one workgroup per unit beyond 8192 only)
+    if (M && s.groups > 256) {
+        if (ei <= 2) launch_cols_ei<T, QB, EPI, 2, M>(a, s, st);
+        else if (ei == 3) launch_cols_ei<T, QB, EPI, 3, M>(a, s, st);
+        else launch_cols_ei<T, QB, EPI, 4, M>(a, s, st);
+    } else if (ei == 1) {
+        launch_cols_ei<T, QB, EPI, 1, false>(a, s, st);
+    } else if (ei == 2) {
+        launch_cols_ei<T, QB, EPI, 2, false>(a, s, st);
+    } else if (ei == 3) {
+        launch_cols_ei<T, QB, EPI, 3, false>(a, s, st);
+    } else {
+        launch_cols_ei<T, QB, EPI, 4, false>(a, s, st);
+    }
+    return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
 }
 
 template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipStream_t st) {
-    int tiles;
-    if (EPI == EPI_QKV) tiles = 3 * a.H * (a.hd / 32);
-    else tiles = (a.N + 15) / 16;
     const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles <= 1) { // the verify pass proper: the waves of a workgroup split K
-        // Measured over (1 - 8 | 10 | 12 | 16 waves) x (1 - 4 buffers) per kind of epilogue on the 7B- and 3B-shaped layers at 5 and 1
-        // rows.  A wave that asks for one step while it multiplies the other (two buffers) is the best where the launch has one or two
-        // workgroups per compute unit; a third buffer makes every launch slower (94 -> 103 us a layer: with more asked for than a
-        // compute unit can have in flight, what is needed first comes later).  Gate/up has several workgroups per compute unit
-        // anyway: up to three, twice the waves with one buffer each are ahead (512 pairs 20.6 -> 18.9 us, 688 31.2 -> 30.0), beyond
-        // (864 pairs, K 5120) two waves with two (49 against 52).
-        constexpr bool BF16 = std::is_same<T, bf16_t>::value;
-        if constexpr (EPI == EPI_QKV) {
-            launch_narrow<T, EPI, 4, 2>(a, tiles, st);
-        } else if constexpr (EPI == EPI_SWIGLU) {
-            if (BF16 && tiles <= 3 * 256) launch_narrow<T, EPI, 4, 1, 2, 2>(a, tiles, st);
-            else launch_narrow<T, EPI, 2, 2>(a, tiles, st);
-        } else if constexpr (EPI == EPI_RESID) {
-            launch_narrow<T, EPI, 8, 2>(a, tiles, st);
-        } else {
-            if (BF16) launch_narrow<T, EPI, 4, 1, 8, 2>(a, tiles, st); // (2000 tiles of 32000 logits: 33.3 -> 32.2 us at K 3072)
-            else launch_narrow<T, EPI, 8, 2>(a, tiles, st);
-        }
-        return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
-    }
+    if (row_tiles <= 1) return launch_cols<T, 0, EPI>(a, st);
+    const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI>(a, tiles, st);
     else return launch_wide_any<T, EPI, 0>(a, tiles, row_tiles, st);
 }
@@ -1537,46 +1387,22 @@ template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs
     }
 }
 
-// waves and buffers per kind of epilogue, measured like those of launch_gemm_t; fewer waves at 9 to 16 rows, whose activations
-// take twice the LDS (O and down on average: 8 waves x 2 buffers 12.1, 16 x 1 11.5, 12 x 1 11.0 us)
-template <int EPI, int NW, int NB, int NW16 = NW> static void launch_w8(const GemmArgs &a, int tiles, hipStream_t st) {
-    if (a.R <= 8) hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW, NB, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_w8_kernel<EPI, NW16, NB, 16>), dim3(tiles), dim3(NW16 * 64), 0, st, a);
-}
-
 template <int EPI> static int launch_gemm_w8(const GemmArgs &a, hipStream_t st) {
-    const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles > 1) return launch_wide_any<bf16_t, EPI, 8>(a, tiles, row_tiles, st);
-    if constexpr (EPI == EPI_QKV) launch_w8<EPI, 4, 2>(a, tiles, st);
-    else if constexpr (EPI == EPI_SWIGLU) launch_w8<EPI, 4, 1>(a, tiles, st);
-    else if constexpr (EPI == EPI_RESID) launch_w8<EPI, 12, 1, 8>(a, tiles, st);
-    else launch_w8<EPI, 8, 1>(a, tiles, st);
-    return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
-}
-
-// one buffer per wave: 8 or 12 waves for the residual projections (12 with the small staging area of at most 5 rows), 4 otherwise
-template <int EPI, int NW, int NW5 = NW> static void launch_w4(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
-    if (a.R <= 5) // the K + 1 = 5 rows of the usual verify pass: the smaller staging area lets a compute unit hold more workgroups
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW5, 1, 5>), dim3(tiles), dim3(NW5 * 64), 0, st, a);
-    else if (a.R <= 8)
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 8>), dim3(tiles), dim3(NW * 64), 0, st, a);
-    else if (row_tiles <= 1)
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16>), dim3(tiles), dim3(NW * 64), 0, st, a);
-    else
-        hipLaunchKernelGGL((gemm_w4_kernel<EPI, NW, 1, 16, true>), dim3(tiles, row_tiles), dim3(NW * 64), 0, st, a);
+    if (row_tiles <= 1) return launch_cols<bf16_t, 8, EPI>(a, st);
+    return launch_wide_any<bf16_t, EPI, 8>(a, EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16, row_tiles, st);
 }
 
 template <int EPI> static int launch_gemm_w4(const GemmArgs &a, hipStream_t st) {
-    const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     const int row_tiles = (a.R + 15) / 16;
+    if (row_tiles <= 1) return launch_cols<bf16_t, 4, EPI>(a, st);
     const int nrows_w = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
-    // more than 16 rows: the wide kernel (it reads a lane's four scales as one 16-byte load); otherwise, or with a
-    // row count that is not a multiple of 4, one workgroup per (column tile, row tile)
-    if (row_tiles > 1 && nrows_w % 4 == 0 && (reinterpret_cast<uintptr_t>(a.wscale) & 15) == 0) return launch_wide_any<bf16_t, EPI, 4>(a, tiles, row_tiles, st);
-    if constexpr (EPI == EPI_RESID) launch_w4<EPI, 8, 12>(a, tiles, row_tiles, st);
-    else launch_w4<EPI, 4>(a, tiles, row_tiles, st);
-    return (EPI == EPI_RESID && a.nsq_out && row_tiles == 1) ? 2 : 0;
+    // more than 16 rows: the wide kernel (it reads a lane's four scales as one 16-byte load); with a weight row count that is not
+    // a multiple of 4 or unaligned scales, one workgroup per (16 columns, row tile)
+    if (nrows_w % 4 == 0 && (reinterpret_cast<uintptr_t>(a.wscale) & 15) == 0) return launch_wide_any<bf16_t, EPI, 4>(a, EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16, row_tiles, st);
+    const int quads = EPI == EPI_QKV ? a.N / 8 : (a.N + 3) / 4, groups = (quads + 3) / 4;
+    launch_cols_as<bf16_t, 4, EPI, EPI == EPI_RESID ? 8 : 4, 1, 2, 16, true>(a, ColumnSplit{groups, quads / groups, quads % groups}, st);
+    return 0;
 }
 
 int launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t st) {

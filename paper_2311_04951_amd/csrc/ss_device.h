@@ -105,31 +105,47 @@ __device__ __forceinline__ void store_act(const ActPlanes<bf16_t> &a, size_t off
 }
 __device__ __forceinline__ void store_act(const ActPlanes<float> &a, size_t off, float x) { a.base[off] = x; }
 
-// four consecutive elements as one store (8 bytes of bf16, 16 of fp32; p aligned accordingly)
-__device__ __forceinline__ void store_quad(bf16_t *p, const float (&x)[4]) {
-    *reinterpret_cast<uint2 *>(p) = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
+// V (2 or 4) consecutive elements as one store (p aligned to it)
+template <int V> __device__ __forceinline__ void store_cols(bf16_t *p, const float (&x)[V]) {
+    typedef uint32_t vec __attribute__((ext_vector_type(V / 2)));
+    vec o;
+#pragma unroll
+    for (int v = 0; v < V / 2; ++v) o[v] = bf16_pair(x[2 * v], x[2 * v + 1]);
+    *reinterpret_cast<vec *>(p) = o;
 }
-__device__ __forceinline__ void store_quad(float *p, const float (&x)[4]) { *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]); }
-// activation values of four consecutive columns, the first `live` of which exist; one store per plane where the planes allow
-__device__ __forceinline__ void store_act_quad(const ActPlanes<bf16_t> &a, size_t off, const float (&x)[4], int live) {
-    if (live >= 4 && a.ld % 4 == 0 && a.plane % 4 == 0 && (reinterpret_cast<uintptr_t>(a.base) & 7) == 0 && off % 4 == 0) {
-        uint2 hi, lo;
-        bf16_split(x[0], x[1], hi.x, lo.x);
-        bf16_split(x[2], x[3], hi.y, lo.y);
-        *reinterpret_cast<uint2 *>(a.base + off) = hi;
-        *reinterpret_cast<uint2 *>(a.base + a.plane + off) = lo;
+template <int V> __device__ __forceinline__ void store_cols(float *p, const float (&x)[V]) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    vec o;
+#pragma unroll
+    for (int v = 0; v < V; ++v) o[v] = x[v];
+    *reinterpret_cast<vec *>(p) = o;
+}
+// activation values of V consecutive columns, the first `live` of which exist; one store per plane where the planes allow
+template <int V> __device__ __forceinline__ void store_act_cols(const ActPlanes<bf16_t> &a, size_t off, const float (&x)[V], int live) {
+    if (live >= V && a.ld % V == 0 && a.plane % V == 0 && (reinterpret_cast<uintptr_t>(a.base) & (2 * V - 1)) == 0 && off % V == 0) {
+        typedef uint32_t vec __attribute__((ext_vector_type(V / 2)));
+        vec hi, lo;
+#pragma unroll
+        for (int v = 0; v < V / 2; ++v) {
+            uint32_t h, l;
+            bf16_split(x[2 * v], x[2 * v + 1], h, l);
+            hi[v] = h;
+            lo[v] = l;
+        }
+        *reinterpret_cast<vec *>(a.base + off) = hi;
+        *reinterpret_cast<vec *>(a.base + a.plane + off) = lo;
     } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < V; ++v)
             if (v < live) store_act(a, off + v, x[v]);
     }
 }
-__device__ __forceinline__ void store_act_quad(const ActPlanes<float> &a, size_t off, const float (&x)[4], int live) {
-    if (live >= 4 && a.ld % 4 == 0 && (reinterpret_cast<uintptr_t>(a.base) & 15) == 0 && off % 4 == 0) {
-        store_quad(a.base + off, x);
+template <int V> __device__ __forceinline__ void store_act_cols(const ActPlanes<float> &a, size_t off, const float (&x)[V], int live) {
+    if (live >= V && a.ld % V == 0 && (reinterpret_cast<uintptr_t>(a.base) & (4 * V - 1)) == 0 && off % V == 0) {
+        store_cols(a.base + off, x);
     } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < V; ++v)
             if (v < live) store_act(a, off + v, x[v]);
     }
 }

@@ -49,13 +49,14 @@ struct GemmArgs {
     int norm_ld;
     float norm_eps;
     // ... a launcher of at most 16 rows defers it instead (returns 2): the planes receive h * gain without the row
-    // scale, and nsq_out[row * nsq_ld + tile] the sum of squares of the 16 columns of each output tile.  The GEMM that
-    // consumes such planes gets act_nsq / act_nsq_tiles / act_nsq_ld (and norm_eps) and multiplies its sums by
-    // 1 / sqrt(sum over the tiles / K + eps) of the row: the norm is linear in the row scale.
+    // scale, and nsq_out[row * parts + i] the sum of squares of the i-th workgroup's columns, parts = deferred_norm_parts(N).
+    // The GEMM that consumes such planes gets act_nsq / act_nsq_parts (and norm_eps) and multiplies its sums by
+    // 1 / sqrt(sum over the parts / K + eps) of the row: the norm is linear in the row scale.
     float *nsq_out;
-    int nsq_ld;
     const float *act_nsq;
-    int act_nsq_tiles, act_nsq_ld;
+    int act_nsq_parts;
+    // set by the launcher of at most 16 rows: quads of columns per workgroup, workgroups with one more, workgroups
+    int quads, quads_rest, nsq_parts;
     // EPI_RESID, optional: the launch also moves the sequences' lengths, len_add[b] += len_delta for b < len_batch (nothing in
     // such a launch reads them; a launch of its own for this costs 4 - 5 us)
     int32_t *len_add;
@@ -68,7 +69,9 @@ struct GemmArgs {
 // 0: no norm written; 1: the RMSNorm asked for through norm_gain has been written as well; 2: written in the deferred
 // form (planes without the row scale + per-tile sums of squares in nsq_out)
 int launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t st);
-constexpr int NSQ_MAX_TILES = 320; // most 16-column tiles of a deferred norm (d_model <= 5120); a multiple of 16
+constexpr int NSQ_MAX_PARTS = 256; // most partial sums of a row of a deferred norm; a multiple of 16
+// partial sums of squares per row that a residual projection of d columns leaves for a deferred norm; 0: it cannot be deferred
+int deferred_norm_parts(int d);
 
 struct AttnArgs {
     const void *q; // activation planes [planes][R16][ldq], rotated queries
