@@ -258,9 +258,15 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
     // are clamped to the row's last unit (the weights there are zero, so any finite value does)
     __device__ __forceinline__ void request(uint32_t to, int k0, bool tail) const {
         const char *b = base + (size_t)k0 * sizeof(T);
+        if (tail) {
+#pragma unroll
+            for (int i = 0; i < NDMA; ++i)
+                if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)), to + i * 1024);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NDMA; ++i)
-            if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, tail ? off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)) : off[i], to + i * 1024);
+            if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, off[i], to + i * 1024);
     }
     // byte offset in a step's region of row c's unit `unit` of plane pl
     __device__ __forceinline__ int operand_offset(int c, int unit, int pl) const {
@@ -310,7 +316,7 @@ template <int PS> __device__ __forceinline__ float row_sum(float x) {
 __device__ __forceinline__ uint32_t w8_pair_to_bf16x2(uint32_t x, int first_byte) {
     const float f0 = (float)((int)(x << (24 - 8 * first_byte)) >> 24); // sign-extended bytes
     const float f1 = (float)((int)(x << (16 - 8 * first_byte)) >> 24);
-    return (f2u(f0) >> 16) | (f2u(f1) & 0xffff0000u); // |q| <= 127: the low 16 bits of the fp32 are zero
+    return __builtin_amdgcn_perm(f2u(f1), f2u(f0), 0x07060302u); // |q| <= 127: the low 16 bits of the fp32 are zero
 }
 __device__ __forceinline__ u32x4 w8_to_bf16x8(uint32_t a, uint32_t b) {
     return u32x4{w8_pair_to_bf16x2(a, 0), w8_pair_to_bf16x2(a, 2), w8_pair_to_bf16x2(b, 0), w8_pair_to_bf16x2(b, 2)};
@@ -328,22 +334,20 @@ __device__ __forceinline__ u32x4 w4_to_bf16x8(uint32_t x) {
     return u32x4{r[0], r[1], r[2], r[3]};
 }
 
-// The same eight entries as bf16 values q + 136 (0x4300 | (q + 8): 128 + n is exact in bf16 for n < 128), without a
-// conversion instruction: flip the sign bits (two's complement -> q + 8), split the even and the odd nibbles into bytes,
-// and let four byte permutes place a pair of them into the low mantissa bits of 0x4300 4300.  About half the vector
-// instructions of w4_to_bf16x8, which bound the kernel for at most 16 rows (its gate/up launch took longer than the
-// int8 one for half the bytes); the caller takes 136 * (sum of the activations of the k-block) off the product.
-// Measured on the 7B-shaped model: 5-row int4 pass -9 %.
-__device__ __forceinline__ u32x4 w4_to_bf16x8_plus136(uint32_t x) {
-    x ^= 0x88888888u;
-    const uint32_t even = x & 0x0F0F0F0Fu, odd = (x >> 4) & 0x0F0F0F0Fu; // byte i: entry 2i / entry 2i + 1
+// The same eight entries as bf16 values q + 136 (even entries: 0x4300 | n is 128 + n) and q + 24 (odd ones: 0x4180 | n << 3 is 16 + n; n the
+// entry with its sign bit flipped, q + 8), without a conversion instruction: a byte permute places a byte in both halves of a register,
+// for the upper half shifted right by one, so that its upper nibble lies where bf16 has a step of one there, and one three-operand
+// logical instruction masks the nibbles, flips their signs and sets the exponents.  Nine vector instructions per eight entries (22 by
+// conversions, 12 with both nibbles in the same place); the caller starts its sums at -(136, 24) * the activations (W4_BIAS).
+__device__ __forceinline__ u32x4 w4_to_bf16x8_biased(uint32_t x) {
+    const uint32_t y = x >> 1;
     uint32_t r[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) // bytes [even.i, 0, odd.i, 0] (selector bytes 0-3: second operand, 4-7: first, 0x0c: zero)
-        r[i] = __builtin_amdgcn_perm(odd, even, 0x0c000c00u | ((4u + i) << 16) | (uint32_t)i) | 0x43004300u;
+    for (int i = 0; i < 4; ++i) // bytes [x.i, 0, y.i, 0] (selector bytes 0-3: second operand, 4-7: first, 0x0c: zero)
+        r[i] = (__builtin_amdgcn_perm(y, x, 0x0c000c00u | ((4u + i) << 16) | (uint32_t)i) & 0x0078000Fu) ^ 0x41C04308u;
     return u32x4{r[0], r[1], r[2], r[3]};
 }
-constexpr float W4_BIAS = 136.0f;
+constexpr uint32_t W4_BIAS = 0xC1C0C308u; // -136 and -24 as a pair of bf16
 
 // The kernel for at most 16 rows, for every kind of matrix (QB: 0 storage type, 8 int8 with one scale per weight row, 4 int4 with one
 // scale per 128 K entries).  blockIdx.x owns a share of the output columns, in quads of four (a quad of pairs for the fused epilogues:
@@ -351,7 +355,8 @@ constexpr float W4_BIAS = 136.0f;
 // fetch - with 16 columns to a workgroup the compute units with one workgroup more than the others were what a launch took (a 13B-shaped
 // down projection, 320 workgroups on 256 units: 21 us the median workgroup, 37 the launch) - and stages the activations once for all
 // its columns.  The NW wavefronts interleave over K in steps of 128 bytes of every row, each through a ring of NB buffers of its own;
-// EI load instructions of eight weight rows (per half) make a step, in CT 16-column tiles.
+// EI load instructions of eight weight rows (per half) make a step.  The 16-column tiles are cut from the first halves' rows and the second
+// ones' behind them, so that an odd EI wastes at most one half tile, not one a half (a 7B-shaped QKV share is 24 + 24 rows: three tiles).
 //   Up to 8 rows (RCAP), two planes: operand columns 0 .. 7 hold the rows' high parts and 8 .. 15 the low ones, one MFMA and one LDS read
 // per k-block instead of two; the two halves of the sums are added in front of the epilogue.
 //   int8: a lane's 16-byte unit holds 16 entries of its weight row, two k-blocks: lane (c, g) supplies k = 64h + 16g + 8j .. + 7 of the
@@ -366,10 +371,13 @@ constexpr float W4_BIAS = 136.0f;
 // 17.7, 7.9, 28.8, 16.5 (6.2 TB/s in gate/up); 13B 28.8, 16.0, 49.0, 35.4 -> 26.9, 11.3, 45.7, 24.3; 3B 15.6, 7.2, 17.9, 12.1 -> 11.8, 6.3, 17.7, 10.9;
 // 7B int8 15.7, 7.8, 20.0, 14.3 -> 12.0, 6.3, 18.5, 11.7; int4 13.0, 7.2, 16.3, 11.2 -> 10.7, 5.9, 14.5, 9.7.  Heads of 32000 columns, K 4096: bf16
 // 42.0 -> 40.6, int8 35.3 -> 24.0, int4 24.6 -> 17.2; 12 rows: gate/up 32.6 -> 31.2, 13B 59.0 -> 49.0, bf16 head 65.4 -> 43.3.
+//   int4 and int8 launches were bound by vector instructions as much as by bytes (7B int4 gate/up: 387 a wavefront and step, 7.7 of its 14.5 us):
+// the nine-instruction unpacking, sums that start at the biases' share, the packed tiles and a uniform branch for the ragged last step, five
+// rows, 7B shape: 8 int4 layers 400 -> 380 us, 4 int8 layers 235 -> 228; 13B int4 at 8 rows, 3 layers 230 -> 222.
 template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP, bool FAR = false>
 __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
-    constexpr int E = Traits<T>::E, KB = 4 * E, CT = (EI + 1) / 2;
-    constexpr int NH = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1, NT = NH * CT; // halves; 16-column tiles
+    constexpr int E = Traits<T>::E, KB = 4 * E;
+    constexpr int NH = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1, NT = (NH * EI + 1) / 2; // halves; 16-column tiles: the first halves' columns, then the second ones'
     constexpr bool HL = Traits<T>::PLANES == 2 && RCAP <= 8; // high and low rows side by side in one operand
     constexpr int SK = QB == 4 ? 256 : QB == 8 ? 128 : 128 / (int)sizeof(T); // K entries of a step
     constexpr int PV = HL ? 1 : Traits<T>::PLANES;
@@ -401,11 +409,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
         woff[i] = (uint32_t)((row_of(min(4 * q0 + r, columns - 1)) - row0) * (int)row_bytes) + wub;
     }
     const char *wbase = reinterpret_cast<const char *>(a.W) + (size_t)row0 * row_bytes;
-    uint32_t soff[SW ? SW : 1]; // int4: word 64 i + lane of a step's scales is (group h * NH + half) * 16 CT + column
+    uint32_t soff[SW ? SW : 1]; // int4: word 64 i + lane of a step's scales is group h * 16 NT + column of the tiles
     bool sh[SW ? SW : 1];
 #pragma unroll
     for (int i = 0; i < SW; ++i) {
-        const int w = i * 64 + lane, r = w % (16 * CT), hf = w / (16 * CT) % NH;
+        const int w = i * 64 + lane, hf = w % (16 * NT) / (8 * EI) % NH, r = w % (16 * NT) - hf * 8 * EI;
         sh[i] = w / (16 * NT) == 1;
         soff[i] = (uint32_t)(row_of(min(4 * q0 + min(r, 4 * nq - 1), columns - 1)) + hf * half_rows) * 4u;
     }
@@ -444,8 +452,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
 
     // The epilogue: thread i of the first EW wavefronts finishes columns 2 (i mod PS) and + 1 of row i / PS; what it needs besides the
     // sums is asked for behind the first step's request: operands of the epilogue, int8 scales, a deferred norm's sums of squares.
-    constexpr int PS = CT == 1 ? (EI == 1 ? 4 : 8) : 16, EW = ((HL ? 8 : 16) * PS + 63) / 64, NSQ4 = NSQ_MAX_PARTS / 4 / PS;
-    static_assert(EW <= NW && CT <= 2 && NW * NB * SBYTES <= 160 * 1024, "");
+    constexpr int PS = EI == 1 ? 4 : EI == 2 ? 8 : 16, EW = ((HL ? 8 : 16) * PS + 63) / 64, NSQ4 = NSQ_MAX_PARTS / 4 / PS;
+    static_assert(EW <= NW && EI <= 4 && NW * NB * SBYTES <= 160 * 1024, "");
     const int er = (int)threadIdx.x / PS, ep = (int)threadIdx.x % PS; // row, column pair
     const int m = rt * 16 + er, col = row_of(min(4 * q0 + min(2 * ep, 4 * nq - 2), (columns - 1) & ~1));
     const bool ends = wave < EW;
@@ -473,7 +481,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
         [&](int i, int buf) {
             const unsigned char *cur = lds[wave][buf];
             const int st = ragged || QB == 4 ? rotated(wave + i * NW, rot, nst) : 0;
-            auto read_w = [&](int t, int j) { return *reinterpret_cast<const u32x4 *>(cur + t / CT * (EI * 1024) + t % CT * 2048 + rdw[j]); };
+            auto read_w = [&](int t, int j) { return *reinterpret_cast<const u32x4 *>(cur + t * 2048 + rdw[j]); };
             if constexpr (QB == 0) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
@@ -512,20 +520,20 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
                         u32x4 av[4][PV];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) read_act(cur, 16 * h + 4 * g + j, av[j]);
-                        // the group's activation sums per row (an all-ones weight tile: every output column gets the sum)
-                        f32x4 asum = f32x4{0.f, 0.f, 0.f, 0.f};
-                        const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+                        // what the biases of the entries add to the group's sums, off them (the same for every output column)
+                        f32x4 start = f32x4{0.f, 0.f, 0.f, 0.f};
+                        const u32x4 bias = u32x4{W4_BIAS, W4_BIAS, W4_BIAS, W4_BIAS};
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) asum = mul(asum, ones, av[j]);
+                        for (int j = 0; j < 4; ++j) start = mul(start, bias, av[j]);
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
                             const u32x4 w = read_w(t, h);
                             const f32x4 sc = *reinterpret_cast<const f32x4 *>(cur + SBASE + ((h * NT + t) * 16 + 4 * g) * 4);
-                            f32x4 part = f32x4{0.f, 0.f, 0.f, 0.f};
+                            f32x4 part = start;
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) part = mul(part, w4_to_bf16x8_plus136(w[j]), av[j]);
+                            for (int j = 0; j < 4; ++j) part = mul(part, w4_to_bf16x8_biased(w[j]), av[j]);
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) acc[t][v] += sc[v] * (part[v] - W4_BIAS * asum[v]);
+                            for (int v = 0; v < 4; ++v) acc[t][v] += sc[v] * part[v];
                         }
                     }
                 }
@@ -571,8 +579,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     float x[NH][2];
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        // column pair ep: quad ep / 2, i.e. tile ep / 8, lane group (ep / 2) mod 4, accumulator registers 2 (ep mod 2) and + 1
-        const int at = (h * CT + ep / 8) * 1024 + ((ep / 2 & 3) * 16 + (er & 15)) * 16 + (ep & 1) * 8;
+        // column 2 ep of half h, row r of the tiles: tile r / 16, lane group (r / 4) mod 4, accumulator registers r mod 4 and + 1
+        const int r = h * 8 * EI + 2 * ep, at = r / 16 * 1024 + ((r / 4 & 3) * 16 + (er & 15)) * 16 + (r & 3) * 4;
         f32x2 sum = *reinterpret_cast<const f32x2 *>(lds[0][0] + at);
 #pragma unroll
         for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const f32x2 *>(lds[w][0] + at);
