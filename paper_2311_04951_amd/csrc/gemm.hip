@@ -244,10 +244,11 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
         base = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + (size_t)row0 * a.ld_act);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
-            const int p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
-            const int plane = PL == 2 && p >= rows * UPS, rem = p - plane * rows * UPS, row = rem / UPS, pos = rem % UPS; // (UPS is a power of two)
+            const unsigned p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
+            const bool low = PL == 2 && p >= (unsigned)(rows * UPS);
+            const unsigned rem = low ? p - rows * UPS : p, row = rem / UPS, pos = rem % UPS; // (UPS is a power of two)
             ucol[i] = (pos ^ (row & (UPS - 1))) * EPU;
-            off[i] = (uint32_t)(((FAR ? 0 : plane * a.act_plane) + (size_t)min(row, live - 1) * a.ld_act + ucol[i]) * sizeof(T));
+            off[i] = ((!FAR && low ? (uint32_t)a.act_plane : 0u) + (FAR ? min(row, live - 1u) : row) * (uint32_t)a.ld_act + ucol[i]) * (uint32_t)sizeof(T);
         }
     }
     __device__ __forceinline__ static void clear(unsigned char *region, int lane) {
@@ -424,7 +425,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     const int rot = k_rotation(nst);
     const bool ragged = K % SK != 0; // the last step ends inside its 128 bytes
     Stage stage;
-    stage.init(a, rt * 16, K, lane);
     const uint32_t lds0 = lds_address(lds[wave][0]);
 
     f32x4 acc[NT];
@@ -476,6 +476,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
                 for (int j = 0; j < EI; ++j) dma16<true>(b + (h ? half_rows * row_bytes : 0), woff[j] - over, to + (h * EI + j) * 1024);
 #pragma unroll
             for (int j = 0; j < SW; ++j) dma4(a.wscale + (size_t)(2 * st) * nrows_w, soff[j] + (sh[j] && !tail ? (uint32_t)nrows_w * 4u : 0u), to + SBASE + j * 256);
+            if (i == 0) { // (nothing of it stands in front of the first weights' request)
+                int l = lane;
+                asm volatile("" : "+v"(l));
+                stage.init(a, rt * 16, K, l);
+            }
             stage.request(to + WBYTES, st * SK, tail);
         },
         [&](int i, int buf) {
