@@ -182,3 +182,32 @@ def test_rows_of_equal_weights_take_no_multiple_of_the_time_of_others(V):
     for f in (lambda x, o: sv.ss_top_k_filter(x, 200, o), lambda x, o: sv.ss_top_p_filter(x, 0.9, o)):
         times = [us(x, f) for x in (usual, flat, mixed)]
         assert max(times) < 4.5 * times[0], times
+
+
+@pytest.mark.parametrize("V", [8192, 8193, 32000, 32768, 32771, 50260])
+def test_rows_with_few_candidates_equal_oracle_bit_for_bit(V):
+    """Rows whose kept tokens are looked for among candidates (from 8193 entries on): as many tokens with a weight as the candidates' list
+    holds, one fewer and one more, few and none; the heaviest token in the row's last entries; ties at the boundary; more tokens above the
+    bound than the list holds (all in the first units of a few threads); aligned rows and others, in place and not."""
+    n = si.normal(12, f"f{V}", (8, V), 2.0).numpy()
+    rows = oracle.softmax(n, 1.0)
+    for r, nnz in enumerate((1535, 1536, 1537, 60)):
+        rows[r, np.argsort(rows[r])[: V - nnz]] = 0.0
+    rows[4, V - 3:] = (0.3, 0.2, 0.1)
+    rows[5, np.argsort(rows[5])[-200:-20]] = rows[5].max() / 2          # 180 ties below the twenty heaviest
+    rows[6] = 2.0 ** -33                                                # nothing has a weight but one token
+    rows[6, V // 2] = 0.5
+    rows[7].reshape(-1)[: V // 4096 * 4096].reshape(-1, 4096)[:, :1600] += 0.01
+    arena = torch.zeros(8 * V + 8, device=dev())
+    for at in (0, 1):
+        g = arena[at:at + 8 * V].view(8, V)
+        for k in (1, 30, 100, 511, 512, 513, 1536, 1537):
+            want = oracle.top_k_filter(rows, k)
+            g.copy_(torch.from_numpy(rows))
+            assert np.array_equal(_bits(sv.ss_top_k_filter(g, k, torch.empty_like(arena)[at:at + 8 * V].view(8, V)).cpu().numpy()), _bits(want)), (V, k, at)
+            assert np.array_equal(_bits(sv.ss_top_k_filter(g, k, g).cpu().numpy()), _bits(want)), (V, k, at)
+        for top_p in (0.01, 0.7, 0.999):
+            want = oracle.top_p_filter(rows, top_p)
+            g.copy_(torch.from_numpy(rows))
+            assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p, torch.empty_like(arena)[at:at + 8 * V].view(8, V)).cpu().numpy()), _bits(want)), (V, top_p, at)
+            assert np.array_equal(_bits(sv.ss_top_p_filter(g, top_p, g).cpu().numpy()), _bits(want)), (V, top_p, at)
