@@ -33,14 +33,6 @@ __device__ __forceinline__ float prob_from_logit(float l, float inv_t, float mx,
 
 // ------------------------------------------------------------------ row statistics
 
-__device__ __forceinline__ void online_add(float &m, float &s, float x) {
-    if (x > m) {
-        s = s * fast_exp(m - x) + 1.0f;
-        m = x;
-    } else {
-        s += fast_exp(x - m);
-    }
-}
 __device__ __forceinline__ void online_merge(float &m, float &s, float m2, float s2) {
     const float mm = fmaxf(m, m2);
     s = s * fast_exp(m - mm) + s2 * fast_exp(m2 - mm);
@@ -88,7 +80,33 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
             s += add;
         }
     } else {
-        for (int i = threadIdx.x; i < V; i += 256) online_add(m, s, scaled_logit(x[i], inv_t));
+        // rows without 16-byte alignment: the same with words, in whole lines (one load at a time, each with an exponential behind a
+        // branch: 32 x K 10 x 50257 117.5 us a call of the logits entry, 58.6 now).  Which thread adds an entry depends on the row's
+        // length alone, as above.
+        auto words = [&](auto u_) {
+            constexpr int U = decltype(u_)::value;
+            for (int i0 = threadIdx.x; i0 < V; i0 += 256 * U) {
+                float t[U], mx = -INFINITY;
+#pragma unroll
+                for (int j = 0; j < U; ++j) t[j] = __builtin_nontemporal_load(x + min(i0 + 256 * j, V - 1));
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    t[j] = i0 + 256 * j < V ? scaled_logit(t[j], inv_t) : -INFINITY;
+                    mx = fmaxf(mx, t[j]);
+                }
+                if (mx == -INFINITY) continue;
+                if (mx > m) {
+                    s *= fast_exp(m - mx);
+                    m = mx;
+                }
+                float add = 0.f;
+#pragma unroll
+                for (int j = 0; j < U; j += 4) add += (fast_exp(t[j] - m) + fast_exp(t[j + 1] - m)) + (fast_exp(t[j + 2] - m) + fast_exp(t[j + 3] - m));
+                s += add;
+            }
+        };
+        if (V <= 256 * STATS_UNROLL) words(std::integral_constant<int, STATS_UNROLL>{});
+        else words(std::integral_constant<int, 4 * STATS_UNROLL>{});
     }
     if (m == -INFINITY) s = 0.f; // a thread that saw nothing: exp(-inf - -inf) must not appear
 #pragma unroll
@@ -281,11 +299,57 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
     seg = (seg + 255) & ~255;
     const int v_begin = min(r0 + wave * seg, r1), v_end = min(v_begin + seg, r1);
 
-    unsigned long long sum = 0;
-    for (int v = v_begin + 4 * lane; v < v_end; v += 256) {
-        unsigned long long w[4];
-        weights4<RESID>(P, Q, v, V, vec, w);
-        sum += (w[0] + w[1]) + (w[2] + w[3]);
+    // A range of up to four entries per lane and round stays in registers between the passes, all of it asked for at once (a round's loads
+    // behind the one before, and again in pass B, were most of the finishing launch: logits entry of 64 x K 8 x 128256 101.4 -> 99.1 us,
+    // 8 x 4 x 32000 22.1 -> 20.9)
+    constexpr int KEEP = 4;
+    const bool keep = seg <= 256 * KEEP && r1 - r0 >= 4;
+    unsigned long long sum = 0, kw[KEEP][4];
+    if (keep) {
+        const int own = v_begin + 4 * lane;
+        auto fetch = [&](auto rounds_, auto vec_) { // (no branch between the loads: they are all in flight together)
+            constexpr int ROUNDS = decltype(rounds_)::value;
+            float kp[ROUNDS][4], kq[ROUNDS][4];
+#pragma unroll
+            for (int j = 0; j < ROUNDS; ++j) {
+                if constexpr (decltype(vec_)::value) { // (r0 and r1 are multiples of 4)
+                    const int v = min(own + 256 * j, r1 - 4);
+                    const float4 a = *reinterpret_cast<const float4 *>(P.row + v), b = RESID ? *reinterpret_cast<const float4 *>(Q.row + v) : a;
+                    kp[j][0] = a.x; kp[j][1] = a.y; kp[j][2] = a.z; kp[j][3] = a.w;
+                    kq[j][0] = b.x; kq[j][1] = b.y; kq[j][2] = b.z; kq[j][3] = b.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int v = min(own + 256 * j + e, r1 - 1);
+                        kp[j][e] = P.row[v];
+                        kq[j][e] = RESID ? Q.row[v] : 0.f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < KEEP; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    kw[j][e] = 0;
+                    if (j < ROUNDS) {
+                        const float w = RESID ? fmaxf(__fsub_rn(P.conv(kp[j][e]), Q.conv(kq[j][e])), 0.f) : P.conv(kp[j][e]);
+                        kw[j][e] = own + 256 * j + e < v_end ? fx_weight(w) : 0ull;
+                        sum += kw[j][e];
+                    }
+                }
+        };
+        auto fetch_rounds = [&](auto vec_) {
+            if (seg <= 256) fetch(std::integral_constant<int, 1>{}, vec_);
+            else fetch(std::integral_constant<int, KEEP>{}, vec_);
+        };
+        if (vec) fetch_rounds(std::true_type{});
+        else fetch_rounds(std::false_type{});
+    } else {
+        for (int v = v_begin + 4 * lane; v < v_end; v += 256) {
+            unsigned long long w[4];
+            weights4<RESID>(P, Q, v, V, vec, w);
+            sum += (w[0] + w[1]) + (w[2] + w[3]);
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += shfl_xor_u64(sum, o);
@@ -302,10 +366,8 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
     unsigned long long C = 0; // weight of the segments before mine
     for (int w = 0; w < wave; ++w) C += sm_wave[w];
     if (C <= T && T < C + sm_wave[wave]) { // wave-uniform: exactly one wave rescans its segment
-        for (int v0 = v_begin; v0 < v_end; v0 += 256) {
-            const int v = v0 + 4 * lane;
-            unsigned long long w[4] = {0, 0, 0, 0};
-            if (v < v_end) weights4<RESID>(P, Q, v, V, vec, w);
+        // true: the threshold is among these 256 entries
+        auto find = [&](int v, const unsigned long long (&w)[4]) {
             const unsigned long long mine = (w[0] + w[1]) + (w[2] + w[3]);
             unsigned long long incl = mine;
 #pragma unroll
@@ -328,9 +390,23 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
                     }
                     *sm_tok = tok;
                 }
-                break;
+                return true;
             }
             C += total;
+            return false;
+        };
+        if (keep) {
+            bool found = false;
+#pragma unroll
+            for (int j = 0; j < KEEP; ++j)
+                if (!found) found = find(v_begin + 256 * j + 4 * lane, kw[j]);
+        } else {
+            for (int v0 = v_begin; v0 < v_end; v0 += 256) {
+                const int v = v0 + 4 * lane;
+                unsigned long long w[4] = {0, 0, 0, 0};
+                if (v < v_end) weights4<RESID>(P, Q, v, V, vec, w);
+                if (find(v, w)) break;
+            }
         }
     }
     __syncthreads();
@@ -491,11 +567,20 @@ __global__ __launch_bounds__(PART_THREADS) void accept_partial_kernel(AcceptArgs
                 }
         }
     } else {
-        for (int v = r0 + 4 * threadIdx.x; v < r1; v += 4 * PART_THREADS) {
-            unsigned long long w[4];
-            if (resid) weights4<true>(P, Q, v, a.V, false, w);
-            else weights4<false>(P, P, v, a.V, false, w);
-            sum += (w[0] + w[1]) + (w[2] + w[3]);
+        constexpr int U = 2 * PART_UNROLL; // (words, in whole lines)
+        for (int v0 = r0 + threadIdx.x; v0 < r1; v0 += PART_THREADS * U) {
+            float p[U], q[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) p[j] = P.row[min(v0 + PART_THREADS * j, r1 - 1)];
+#pragma unroll
+            for (int j = 0; j < U; ++j) q[j] = p[j];
+            if (resid) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) q[j] = Q.row[min(v0 + PART_THREADS * j, r1 - 1)];
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if (v0 + PART_THREADS * j < r1) sum += fx_weight(resid ? fmaxf(__fsub_rn(P.conv(p[j]), Q.conv(q[j])), 0.f) : P.conv(p[j]));
         }
     }
 #pragma unroll
@@ -523,18 +608,21 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void accept_finish_kernel(AcceptArg
     const RowSrc P = make_row(a.p, a.p_stats, (size_t)b * (a.K + 1) + n, a.V, a.from_logits, a.inv_t);
     const bool resid = n < a.K;
     const RowSrc Q = resid ? make_row(a.q, a.q_stats, (size_t)b * a.K + n, a.V, a.from_logits, a.inv_t) : P;
-    unsigned long long S = 0;
-    for (int sgi = 0; sgi < nseg; ++sgi) S += partial[(size_t)b * nseg + sgi];
+    // the segments' sums, one per lane (at most 16), and what is up to each of them
+    const int lane = threadIdx.x & 63;
+    const unsigned long long ps = lane < nseg ? partial[(size_t)b * nseg + lane] : 0ull;
+    unsigned long long incl = ps;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const unsigned long long x = shfl_up_u64(incl, o);
+        if (lane >= o) incl += x;
+    }
+    const unsigned long long S = shfl_u64(incl, 15);
     int tok = -1;
     if (S != 0) {
-        const unsigned long long T = inv_cdf_threshold(u, S);
-        unsigned long long C = 0;
-        int sgi = 0;
-        for (; sgi < nseg - 1; ++sgi) { // the segment with C <= T < C + partial
-            const unsigned long long ps = partial[(size_t)b * nseg + sgi];
-            if (T < C + ps) break;
-            C += ps;
-        }
+        const unsigned long long T = inv_cdf_threshold(u, S); // (below S)
+        const int sgi = min((int)__ffsll((long long)__ballot(lane < nseg && T < incl)) - 1, nseg - 1); // the segment with C <= T < C + its sum
+        const unsigned long long C = shfl_u64(incl - ps, sgi);
         const int r0 = min(sgi * seg_len, a.V), r1 = min(r0 + seg_len, a.V);
         tok = resid ? block_inv_cdf<true>(P, Q, a.V, r0, r1, true, T - C, u, sm_wave, &sm_tok)
                     : block_inv_cdf<false>(P, P, a.V, r0, r1, true, T - C, u, sm_wave, &sm_tok);

@@ -76,6 +76,21 @@ def test_softmax_close_to_oracle(rows, V, T):
     assert np.allclose(got.astype(np.float64).sum(-1), 1.0, atol=1e-5)
 
 
+@pytest.mark.parametrize("V", [5, 1023, 2047, 2049, 8195, 16387, 50257])
+def test_statistics_of_rows_without_alignment(V):
+    """Rows whose length is no multiple of 4 (read word by word): whole and with masked entries (minus infinity in front, in between, nearly
+    everywhere) against 64 bits, and the same row at another place gives the same bits, whatever its alignment is there."""
+    l = si.normal(13, f"o{V}", (5, V), 2.0)
+    l[1, : V // 2] = -float("inf")
+    l[2, ::2] = -float("inf")
+    l[3, 1:] = -float("inf")
+    l[4] = l[0]
+    got = sv.ss_softmax(l.to(dev()), 0.7)
+    ref = oracle.softmax(l.numpy(), 0.7)
+    assert np.all(np.abs(got.cpu().numpy() - ref) <= 1e-6 + 1e-5 * ref)
+    assert torch.equal(got[0], got[4])
+
+
 @pytest.mark.parametrize("B,K,V,T", [(4, 4, 1024, 1.0), (6, 8, 5000, 0.8), (3, 2, 333, 1.3)])
 def test_fused_logits_path_equals_materialised_path_and_oracle(B, K, V, T):
     pl, ql, u, ud = si.accept_workload(21, B, K, V)
