@@ -594,6 +594,12 @@ __global__ __launch_bounds__(PART_THREADS) void accept_partial_kernel(AcceptArgs
     }
 }
 
+// The segment that holds the threshold: the first of the nseg whose running sum passes it (bit i of `passed`).  None does where the
+// threshold is not below the total (a uniform of 1 or more): the last one, in which nothing is found.
+__host__ __device__ __forceinline__ int segment_of(unsigned long long passed, int nseg) { return passed ? __builtin_ctzll(passed) : nseg - 1; }
+// For the tests (not part of the library's interface).
+extern "C" int ss_dev_accept_segment(unsigned long long passed, int nseg) { return segment_of(passed, nseg); }
+
 // one workgroup per sequence: locate the segment that holds the threshold and rescan it.  All residual
 // weights zero (possible only through rounding): sample from p with the same uniform; all of those
 // zero too: argmax.
@@ -620,8 +626,8 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void accept_finish_kernel(AcceptArg
     const unsigned long long S = shfl_u64(incl, 15);
     int tok = -1;
     if (S != 0) {
-        const unsigned long long T = inv_cdf_threshold(u, S); // (below S)
-        const int sgi = min((int)__ffsll((long long)__ballot(lane < nseg && T < incl)) - 1, nseg - 1); // the segment with C <= T < C + its sum
+        const unsigned long long T = inv_cdf_threshold(u, S); // (below S for a uniform in [0, 1))
+        const int sgi = segment_of(__ballot(lane < nseg && T < incl), nseg); // the segment with C <= T < C + its sum
         const unsigned long long C = shfl_u64(incl - ps, sgi);
         const int r0 = min(sgi * seg_len, a.V), r1 = min(r0 + seg_len, a.V);
         tok = resid ? block_inv_cdf<true>(P, Q, a.V, r0, r1, true, T - C, u, sm_wave, &sm_tok)

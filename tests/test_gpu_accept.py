@@ -47,6 +47,22 @@ def test_speculative_accept_bit_exact(B, K, V):
         assert len(set(ona.tolist())) > 1          # the case really mixes accept counts
 
 
+@pytest.mark.parametrize("B,K,V", [(1, 0, 333), (3, 2, 5000), (1, 4, 32000), (70, 1, 4099), (2, 3, 50257)])
+def test_a_last_uniform_of_one_or_more_takes_the_target_rows_argmax(B, K, V):
+    """Outside the contract (what rounding a 64-bit uniform to 32 bits leaves): the threshold is not below the total of the weights, no segment
+    holds it, and the token is the argmax of the target's row, from inside the rows: q's first row rejects at once in every other sequence."""
+    p, q = _dists(V, B, K, V)
+    u = torch.full((B, K + 1), 1.0)
+    u[1::2, -1] = 1.5
+    d = q.argmax(-1).to(torch.int32) if K else torch.zeros(1, dtype=torch.int32)
+    if K:
+        p[::2, 0].scatter_(-1, d[::2, :1].long(), 0.0)      # p_0(d_0) = 0 < q_0(d_0)
+    na, nx = sv.ss_speculative_accept(p.to(dev()), q.to(dev()) if K else torch.zeros(1, device=dev()), d.to(dev()), u.to(dev()))
+    na, nx = na.cpu().tolist(), nx.cpu().tolist()
+    assert K == 0 or na[::2] == [0] * len(na[::2])
+    assert nx == [int(np.argmax(p[b, na[b]].numpy())) for b in range(B)]
+
+
 def test_accept_special_cases_match_oracle():
     B, K, V = 4, 3, 257
     p, q = _dists(7, B, K, V)
