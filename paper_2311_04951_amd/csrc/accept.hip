@@ -80,33 +80,49 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
             s += add;
         }
     } else {
-        // rows without 16-byte alignment: the same with words, in whole lines (one load at a time, each with an exponential behind a
-        // branch: 32 x K 10 x 50257 117.5 us a call of the logits entry, 58.6 now).  Which thread adds an entry depends on the row's
+        // rows without 16-byte alignment: the same with words, in whole lines, U of a thread's entries in flight (one load at a time, each
+        // with an exponential behind a branch: 32 x K 10 x 50257 117.5 us a call of the logits entry, 50.6 now).  U by the length, and
+        // exponentials four at a time only where one of a wavefront's lanes has an entry: short rows of a batch are bound by them (softmax
+        // of 1800 rows of 4099, us, one load at a time | always 32 | now: 22.5 | 27.6 | 21.2).  Ordinary loads: what writes the probabilities
+        // or draws the token reads the row again (the call of 32 x K 10 57.8 us with non-temporal ones; only a softmax of more
+        // than the last-level cache holds gains by those, 1000 rows of 100001 259 us against 272).  Which thread adds an entry depends on the row's
         // length alone, as above.
-        auto words = [&](auto u_) {
+        auto words = [&](int w0, auto u_, auto full_) { // entries w0 .. of a wavefront; FULL: all of the workgroup's 256 * U exist
             constexpr int U = decltype(u_)::value;
-            for (int i0 = threadIdx.x; i0 < V; i0 += 256 * U) {
-                float t[U], mx = -INFINITY;
+            constexpr bool FULL = decltype(full_)::value;
+            const int lane = threadIdx.x & 63;
+            float t[U], mx = -INFINITY;
 #pragma unroll
-                for (int j = 0; j < U; ++j) t[j] = __builtin_nontemporal_load(x + min(i0 + 256 * j, V - 1));
+            for (int j = 0; j < U; ++j) t[j] = x[FULL ? w0 + 256 * j + lane : min(w0 + 256 * j + lane, V - 1)];
 #pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    t[j] = i0 + 256 * j < V ? scaled_logit(t[j], inv_t) : -INFINITY;
-                    mx = fmaxf(mx, t[j]);
-                }
-                if (mx == -INFINITY) continue;
-                if (mx > m) {
-                    s *= fast_exp(m - mx);
-                    m = mx;
-                }
-                float add = 0.f;
-#pragma unroll
-                for (int j = 0; j < U; j += 4) add += (fast_exp(t[j] - m) + fast_exp(t[j + 1] - m)) + (fast_exp(t[j + 2] - m) + fast_exp(t[j + 3] - m));
-                s += add;
+            for (int j = 0; j < U; ++j) {
+                t[j] = FULL || w0 + 256 * j + lane < V ? scaled_logit(t[j], inv_t) : -INFINITY;
+                mx = fmaxf(mx, t[j]);
             }
+            if (mx == -INFINITY) return;
+            if (mx > m) {
+                s *= fast_exp(m - mx);
+                m = mx;
+            }
+            float add = 0.f;
+#pragma unroll
+            for (int j = 0; j < U; j += 4)
+                if (FULL || w0 + 256 * j < V) add += (fast_exp(t[j] - m) + fast_exp(t[j + 1] - m)) + (fast_exp(t[j + 2] - m) + fast_exp(t[j + 3] - m));
+            s += add;
         };
-        if (V <= 256 * STATS_UNROLL) words(std::integral_constant<int, STATS_UNROLL>{});
-        else words(std::integral_constant<int, 4 * STATS_UNROLL>{});
+        constexpr std::integral_constant<int, STATS_UNROLL / 2> few{};
+        constexpr std::integral_constant<int, STATS_UNROLL> some{};
+        constexpr std::integral_constant<int, 4 * STATS_UNROLL> many{};
+        const int own = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+        if (V <= 256 * few) {
+            words(own, few, std::false_type{});
+        } else if (V <= 256 * some) {
+            words(own, some, std::false_type{});
+        } else {
+            int v = 0;
+            for (; v + 256 * many <= V; v += 256 * many) words(v + own, many, std::true_type{});
+            if (v < V) words(v + own, many, std::false_type{});
+        }
     }
     if (m == -INFINITY) s = 0.f; // a thread that saw nothing: exp(-inf - -inf) must not appear
 #pragma unroll
