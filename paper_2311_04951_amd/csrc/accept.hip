@@ -316,8 +316,9 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
     const int v_begin = min(r0 + wave * seg, r1), v_end = min(v_begin + seg, r1);
 
     // A range of up to four entries per lane and round stays in registers between the passes, all of it asked for at once (a round's loads
-    // behind the one before, and again in pass B, were most of the finishing launch: logits entry of 64 x K 8 x 128256 101.4 -> 99.1 us,
-    // 8 x 4 x 32000 22.1 -> 20.9)
+    // behind the one before, and again in pass B, were most of the finishing launch: logits entry of 64 x K 8 x 128256 104.7 -> 102.7 us,
+    // 8 x 4 x 32000 22.1 -> 21.0).  As many rounds as the range has, and none for wavefronts behind its end (four for everyone, each with a
+    // conversion to 64 bits: 1 x 8 x 5000 13.8 us one at a time, 15.0 with four, 13.4 now; probabilities 1 x 1 x 1000 6.8, 7.3, 7.0)
     constexpr int KEEP = 4;
     const bool keep = seg <= 256 * KEEP && r1 - r0 >= 4;
     unsigned long long sum = 0, kw[KEEP][4];
@@ -356,10 +357,13 @@ __device__ int block_inv_cdf(const RowSrc &P, const RowSrc &Q, int V, int r0, in
         };
         auto fetch_rounds = [&](auto vec_) {
             if (seg <= 256) fetch(std::integral_constant<int, 1>{}, vec_);
+            else if (seg <= 512) fetch(std::integral_constant<int, 2>{}, vec_);
             else fetch(std::integral_constant<int, KEEP>{}, vec_);
         };
-        if (vec) fetch_rounds(std::true_type{});
-        else fetch_rounds(std::false_type{});
+        if (v_begin < v_end) { // (the same for the whole wavefront)
+            if (vec) fetch_rounds(std::true_type{});
+            else fetch_rounds(std::false_type{});
+        }
     } else {
         for (int v = v_begin + 4 * lane; v < v_end; v += 256) {
             unsigned long long w[4];

@@ -107,7 +107,8 @@ def test_statistics_of_rows_without_alignment(V):
     assert torch.equal(got[0], got[4])
 
 
-@pytest.mark.parametrize("B,K,V,T", [(4, 4, 1024, 1.0), (6, 8, 5000, 0.8), (3, 2, 333, 1.3)])
+@pytest.mark.parametrize("B,K,V,T", [(4, 4, 1024, 1.0), (6, 8, 5000, 0.8), (3, 2, 333, 1.3),
+                                     (5, 3, 3, 1.0), (5, 3, 4096, 1.0), (5, 3, 4097, 1.0), (5, 3, 8192, 0.9), (5, 3, 8193, 1.0), (5, 2, 16383, 1.0)])
 def test_fused_logits_path_equals_materialised_path_and_oracle(B, K, V, T):
     pl, ql, u, ud = si.accept_workload(21, B, K, V)
     qp = oracle.softmax(ql.numpy(), T)
