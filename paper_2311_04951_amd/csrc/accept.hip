@@ -99,7 +99,11 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
                 t[j] = FULL || w0 + 256 * j + lane < V ? scaled_logit(t[j], inv_t) : -INFINITY;
                 mx = fmaxf(mx, t[j]);
             }
-            if (mx == -INFINITY) return;
+            if (mx == -INFINITY) { // nothing but masked entries - or a NaN (which a maximum passes over): the sum of a thread that has others becomes one
+#pragma unroll
+                for (int j = 0; j < U; ++j) s += t[j] != t[j] ? t[j] : 0.f;
+                return;
+            }
             if (mx > m) {
                 s *= fast_exp(m - mx);
                 m = mx;

@@ -107,6 +107,18 @@ def test_statistics_of_rows_without_alignment(V):
     assert torch.equal(got[0], got[4])
 
 
+@pytest.mark.parametrize("V,at", [(333, 300), (2049, 2048), (8195, 8194), (8195, 8000), (24583, 24580)])
+def test_a_nan_among_the_logits_of_an_unaligned_row_reaches_its_sum(V, at):
+    """Also where it is all that a thread reads in its last round (a maximum passes over it): every probability of the row is a NaN, none of
+    another row's changes."""
+    l = si.normal(14, f"nan{V}", (3, V), 2.0)
+    l[1, at] = float("nan")
+    got = sv.ss_softmax(l.to(dev()), 0.7)
+    assert bool(torch.isnan(got[1]).all())
+    l[1] = l[0]
+    assert torch.equal(got[::2], sv.ss_softmax(l.to(dev()), 0.7)[::2]) and not bool(torch.isnan(got[::2]).any())
+
+
 @pytest.mark.parametrize("B,K,V,T", [(4, 4, 1024, 1.0), (6, 8, 5000, 0.8), (3, 2, 333, 1.3),
                                      (5, 3, 3, 1.0), (5, 3, 4096, 1.0), (5, 3, 4097, 1.0), (5, 3, 8192, 0.9), (5, 3, 8193, 1.0), (5, 2, 16383, 1.0)])
 def test_fused_logits_path_equals_materialised_path_and_oracle(B, K, V, T):
