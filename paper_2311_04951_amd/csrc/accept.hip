@@ -85,8 +85,8 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
         // exponentials four at a time only where one of a wavefront's lanes has an entry: short rows of a batch are bound by them (softmax
         // of 1800 rows of 4099, us, one load at a time | always 32 | now: 22.5 | 27.6 | 21.2).  Ordinary loads: what writes the probabilities
         // or draws the token reads the row again (the call of 32 x K 10 57.8 us with non-temporal ones; only a softmax of more
-        // than the last-level cache holds gains by those, 1000 rows of 100001 259 us against 272).  Which thread adds an entry depends on the row's
-        // length alone, as above.
+        // than the last-level cache holds gains by those, 1000 rows of 100001 259 us against 272).  Which thread adds an entry depends on
+        // the row's length - and, where that is a multiple of 4, on the alignment of the rows, which leads here or to the 16 bytes above.
         auto words = [&](int w0, auto u_, auto full_) { // entries w0 .. of a wavefront; FULL: all of the workgroup's 256 * U exist
             constexpr int U = decltype(u_)::value;
             constexpr bool FULL = decltype(full_)::value;

@@ -95,16 +95,32 @@ def test_softmax_close_to_oracle(rows, V, T):
 @pytest.mark.parametrize("V", [5, 257, 1023, 1025, 2047, 2049, 4099, 8193, 8195, 16383, 16387, 50257])
 def test_statistics_of_rows_without_alignment(V):
     """Rows whose length is no multiple of 4 (read word by word): whole and with masked entries (minus infinity in front, in between, nearly
-    everywhere) against 64 bits, and the same row at another place gives the same bits, whatever its alignment is there."""
-    l = si.normal(13, f"o{V}", (5, V), 2.0)
-    l[1, : V // 2] = -float("inf")
-    l[2, ::2] = -float("inf")
-    l[3, 1:] = -float("inf")
-    l[4] = l[0]
+    everywhere) against 64 bits, and the same row at other places, of every alignment that a row of this length has, gives the same bits."""
+    l = si.normal(13, f"o{V}", (7, V), 2.0)
+    l[1] = l[2] = l[3] = l[0]
+    l[4, : V // 2] = -float("inf")
+    l[5, ::2] = -float("inf")
+    l[6, 1:] = -float("inf")
+    assert len({i * V % 4 for i in range(4)}) == (4 if V % 2 else 2)
     got = sv.ss_softmax(l.to(dev()), 0.7)
     ref = oracle.softmax(l.numpy(), 0.7)
     assert np.all(np.abs(got.cpu().numpy() - ref) <= 1e-6 + 1e-5 * ref)
-    assert torch.equal(got[0], got[4])
+    assert torch.equal(got[:1].expand(3, V), got[1:4])
+
+
+@pytest.mark.parametrize("V", [4, 1024, 8192, 16388, 32000])
+def test_statistics_of_aligned_lengths_at_unaligned_places(V):
+    """Rows of a multiple of 4 that start 4, 8 or 12 bytes behind a 16-byte boundary (word by word too) against 64 bits.  Their sums are in
+    another order than at the boundary: the same to 32-bit rounding, not to the bit."""
+    l = si.normal(13, f"a{V}", (3, V), 2.0)
+    l[1, : V // 2] = -float("inf")
+    ref = oracle.softmax(l.numpy(), 0.7)
+    arena = torch.empty(3 * V + 4, device=dev())
+    for at in range(4):
+        x = arena[at:at + 3 * V].view(3, V)
+        x.copy_(l)
+        assert x.data_ptr() % 16 == 4 * at
+        assert np.all(np.abs(sv.ss_softmax(x, 0.7).cpu().numpy() - ref) <= 1e-6 + 1e-5 * ref)
 
 
 @pytest.mark.parametrize("V,at", [(333, 300), (2049, 2048), (8195, 8194), (8195, 8000), (24583, 24580)])
