@@ -1091,48 +1091,60 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
         n_keep = P24 - S;
     }
     int cut = V; // ties are kept up to and including this index
-    if (n_keep < n_ties) {
+    if (__builtin_expect(n_keep < n_ties, 0)) {
         // the n_keep-th token of weight tau in index order: every wavefront counts a contiguous part of the row, and the one whose part holds it
-        // looks for it there (a part per thread read a line per entry: 1 row of 128256 equal weights 159 us, now 110)
-        const int lane = t & 63, wave = t >> 6;
-        constexpr int TU = 16; // loads in flight
-        const int part = ((V + TP_WAVES - 1) / TP_WAVES + 63) & ~63, v0 = wave * part, v1 = min(v0 + part, V);
-        auto ties = [&](int v, unsigned long long (&m)[TU]) { // of v .. v + 64 TU - 1
-            float x[TU];
-#pragma unroll
-            for (int j = 0; j < TU; ++j) {
-                const int at = min(v + 64 * j + lane, V - 1);
-                if constexpr (FITS) x[j] = reinterpret_cast<const float *>(row)[VEC ? at : ((at >> 12) * TP_THREADS + (at & (TP_THREADS - 1))) * 4 + ((at >> 10) & 3)]; // (see tp_entry)
-                else x[j] = p[at];
-            }
-#pragma unroll
-            for (int j = 0; j < TU; ++j) m[j] = __ballot(v + 64 * j + lane < v1 && tp_key(x[j]) == tau);
-        };
-        unsigned long long m[TU], cnt = 0, before = 0;
-        for (int v = v0; v < v1; v += 64 * TU) {
-            ties(v, m);
-#pragma unroll
-            for (int j = 0; j < TU; ++j) cnt += __popcll(m[j]);
-        }
-        __syncthreads(); // (sm_wave may still be read)
-        if (lane == 0) sm_wave[wave] = cnt;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) before += sm_wave[w];
-        if (before < n_keep && n_keep <= before + cnt) { // (one wavefront)
-            bool found = false;
-            for (int v = v0; v < v1 && !found; v += 64 * TU) {
-                ties(v, m);
+        // looks for it there (a part per thread read a line per entry: 1 row of 128256 equal weights 159 us, now 110).  A part that one look
+        // covers is looked at once, with as many loads as it has, and the sums in front of it are asked for together (5 rows of equal weights,
+        // top-k 40, us, a part per thread | two looks of 16 loads and one sum after another | now: 1000 entries 11.3 | 12.7 | 11.0, 3001 17.4 |
+        // 19.4 | 17.2, 6000 18.0 | 18.6 | 17.4).
+        auto find_cut = [&](auto tu_, auto once_) {
+            constexpr int TU = decltype(tu_)::value; // loads in flight
+            constexpr bool ONCE = decltype(once_)::value; // a look covers the part
+            const int lane = t & 63, wave = t >> 6;
+            const int part = ((V + TP_WAVES - 1) / TP_WAVES + 63) & ~63, v0 = wave * part, v1 = min(v0 + part, V);
+            auto ties = [&](int v, unsigned long long (&m)[TU]) { // of v .. v + 64 TU - 1
+                float x[TU];
 #pragma unroll
                 for (int j = 0; j < TU; ++j) {
-                    const unsigned long long c = __popcll(m[j]);
-                    if (!found && before + c >= n_keep) {
-                        found = true;
-                        if ((m[j] >> lane & 1) && before + __popcll(m[j] & ((1ull << lane) - 1)) + 1 == n_keep) sm_cut = v + 64 * j + lane;
+                    const int at = min(v + 64 * j + lane, V - 1);
+                    if constexpr (FITS) x[j] = reinterpret_cast<const float *>(row)[VEC ? at : ((at >> 12) * TP_THREADS + (at & (TP_THREADS - 1))) * 4 + ((at >> 10) & 3)]; // (see tp_entry)
+                    else x[j] = p[at];
+                }
+#pragma unroll
+                for (int j = 0; j < TU; ++j) m[j] = __ballot(v + 64 * j + lane < v1 && tp_key(x[j]) == tau);
+            };
+            unsigned long long m[TU], cnt = 0, before = 0;
+            for (int v = v0; ONCE || v < v1; v += 64 * TU) {
+                ties(v, m);
+#pragma unroll
+                for (int j = 0; j < TU; ++j) cnt += __popcll(m[j]);
+                if (ONCE) break;
+            }
+            __syncthreads(); // (sm_wave may still be read)
+            if (lane == 0) sm_wave[wave] = cnt;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < TP_WAVES; ++w) before += w < wave ? sm_wave[w] : 0ull;
+            if (before < n_keep && n_keep <= before + cnt) { // (one wavefront)
+                bool found = false;
+                for (int v = v0; v < v1 && !found; v += 64 * TU) {
+                    if (!ONCE) ties(v, m);
+#pragma unroll
+                    for (int j = 0; j < TU; ++j) {
+                        const unsigned long long c = __popcll(m[j]);
+                        if (!found && before + c >= n_keep) {
+                            found = true;
+                            if ((m[j] >> lane & 1) && before + __popcll(m[j] & ((1ull << lane) - 1)) + 1 == n_keep) sm_cut = v + 64 * j + lane;
+                        }
+                        before += found ? 0 : c;
                     }
-                    before += found ? 0 : c;
                 }
             }
-        }
+        };
+        if (FITS && V <= 64 * 4 * TP_WAVES) find_cut(std::integral_constant<int, 4>{}, std::true_type{});
+        else if (FITS && V <= 64 * 8 * TP_WAVES) find_cut(std::integral_constant<int, 8>{}, std::true_type{});
+        else if (FITS && V <= 64 * 16 * TP_WAVES) find_cut(std::integral_constant<int, 16>{}, std::true_type{});
+        else find_cut(std::integral_constant<int, 16>{}, std::false_type{});
         __syncthreads();
         cut = sm_cut;
     }

@@ -18,6 +18,25 @@ def _bits(a):
     return np.ascontiguousarray(a, dtype=np.float32).view(np.uint32)
 
 
+@pytest.mark.parametrize("V", [2, 64, 1000, 4095, 4096, 4097, 8191, 8192, 8193, 16384, 16385, 32769])
+def test_the_cut_among_ties_is_the_oracles(V):
+    """Equal weights in every place, in every other and in none but the ends of the wavefronts' parts: the last kept one found in the first
+    part, at the ends of parts and in the last, whatever number of looks a part takes (up to 4096, 8192, 16384 entries and beyond)."""
+    rows = np.full((3, V), 1.0 / V, dtype=np.float32)
+    rows[1, 1::2] = 0.25 / V
+    part = ((V + 15) // 16 + 63) // 64 * 64
+    rows[2] = 0.25 / V
+    for v in range(0, V, part):
+        rows[2, v] = rows[2, min(v + part, V) - 1] = 1.0 / V
+    g = torch.from_numpy(rows).to(dev())
+    for k in sorted({k for k in (1, 2, 3, part - 1, part, part + 1, V // 2, V // 2 + 1, V - 2, V - 1) if 1 <= k < V}):
+        got = sv.ss_top_k_filter(g, k)
+        assert np.array_equal(_bits(got.cpu().numpy()), _bits(oracle.top_k_filter(rows, k))), (V, k)
+    for top_p in (1e-6, 0.5, 0.9999):
+        got = sv.ss_top_p_filter(g, top_p)
+        assert np.array_equal(_bits(got.cpu().numpy()), _bits(oracle.top_p_filter(rows, top_p))), (V, top_p)
+
+
 @pytest.mark.parametrize("V", [7, 1000, 32000, 50257, 128256])
 def test_filter_equals_oracle_bit_for_bit(V):
     rows = oracle.softmax(si.normal(5, f"tk{V}", (7, V), 2.0).numpy(), 0.8)
