@@ -736,8 +736,12 @@ constexpr int TP_LIST = 2048, TP_RANK = 192;
 // Candidates: few enough tokens that hold every one that can be kept, found before the histogram, which then is theirs and not the row's
 constexpr int TP_CAND = 1536;
 // Most k for which the bound from the threads' largest tokens is looked for (more than that and the tokens above it are too many), and
-// shortest row (its units are up to two per thread: nothing to save)
+// shortest row: of shorter ones a pass takes less than the bound (5 rows, top-k 40 | 200 | 512, us without and with it: 9001 entries 12.2 | 12.7 |
+// 12.8 and 12.2 | 12.9 | 13.2, one aligned row of them 10.2 | 10.4 | 11.0 and 11.7 | 12.1 | 12.7; 64 rows of 16384 12.4 | 13.1 | 13.7 and 12.8 |
+// 13.6 | 14.3, of 20000 14.2 | 15.2 | 23.6 and 13.3 | 14.2 | 19.6)
 constexpr unsigned TP_FEW = 512;
+constexpr int TP_FRONT_K = 18433;
+// shortest row in which a top-p looks whether few tokens have a weight (its units are up to two per thread: nothing to save)
 constexpr int TP_FRONT = 8193;
 constexpr float TP_LEAST = 2.3283064365386963e-10f; // 2^-32, the smallest probability with a weight
 
@@ -1198,7 +1202,7 @@ static void launch_filter(const float *probs, long long ld_in, int rows, int V, 
     if (rows <= 0) return;
     const bool vec = ((reinterpret_cast<uintptr_t>(probs) | reinterpret_cast<uintptr_t>(out)) & 15) == 0 && (rows == 1 || (ld_in % 4 == 0 && ld_out % 4 == 0));
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(rows), dim3(TP_THREADS), 0, st, probs, ld_in, V, arg, out, ld_out); };
-    const bool front = V >= TP_FRONT && (!BY_COUNT || arg <= TP_FEW);
+    const bool front = BY_COUNT ? V >= TP_FRONT_K && arg <= TP_FEW : V >= TP_FRONT;
     auto pick = [&](auto v) {
         constexpr bool VEC = decltype(v)::value;
         if (V <= TP_FITS) {

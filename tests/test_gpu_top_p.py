@@ -184,9 +184,9 @@ def test_rows_of_equal_weights_take_no_multiple_of_the_time_of_others(V):
         assert max(times) < 4.5 * times[0], times
 
 
-@pytest.mark.parametrize("V", [8192, 8193, 32000, 32768, 32771, 50260])
+@pytest.mark.parametrize("V", [8192, 8193, 18432, 18433, 32000, 32768, 32771, 50260])
 def test_rows_with_few_candidates_equal_oracle_bit_for_bit(V):
-    """Rows whose kept tokens are looked for among candidates (from 8193 entries on): as many tokens with a weight as the candidates' list
+    """Rows whose kept tokens are looked for among candidates (top-p from 8193 entries on, top-k from 18433): as many tokens with a weight as the candidates' list
     holds, one fewer and one more, few and none; the heaviest token in the row's last entries; ties at the boundary; more tokens above the
     bound than the list holds (all in the first units of a few threads); aligned rows and others, in place and not."""
     n = si.normal(12, f"f{V}", (8, V), 2.0).numpy()
