@@ -789,7 +789,8 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     __shared__ unsigned long long sm_wave[TP_WAVES];
     __shared__ unsigned long long sm_above, sm_binw;
     __shared__ uint32_t list[TP_LIST];
-    __shared__ int sm_bin, sm_cut, sm_n, sm_nc, sm_nz[TP_WAVES];
+    __shared__ int sm_bin, sm_cut, sm_n, sm_nc;
+    __shared__ __align__(16) uint8_t sm_nz[TP_WAVES]; // (16 of them)
     __shared__ f32x4 row[FITS ? TP_FITS / 4 : TP_CAND / 4]; // (a longer row: the candidates' probabilities)
     __shared__ int cand[TP_CAND];                            // 4 * unit + entry
     const float *p = probs + (size_t)blockIdx.x * (size_t)ld_in;
@@ -812,12 +813,18 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
                 for (int e = 0; e < 4; ++e) f(tp_key(x[j][e]));
         }
     };
-    // The row is fetched (one that fits LDS: once), and on the way one entry of every fourth unit of a thread is looked at for a weight, and
-    // top-k finds each thread's largest entry.  In a longer row a top-p looks at one entry per thread instead, which the histogram needs anyway.
+    // The row is fetched (one that fits LDS: once); a top-k that looks for candidates finds each thread's largest entry on the way and looks at
+    // one entry of every fourth unit of a thread for a weight.
     uint32_t sample = 0; // the key of one entry, the lanes' spread over the row: the first of one of the thread's own units
     auto take_sample = [&]() {
         const int own = t + TP_THREADS * ((t & 63) * ((n4 - t + TP_THREADS - 1) / TP_THREADS) >> 6);
-        if (own < n4 && tp_entry<VEC>(own, 0) < V) sample = tp_key(FITS ? row[own].x : p[tp_entry<VEC>(own, 0)]);
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if (own < n4) {
+            if constexpr (FITS || VEC) x = FITS ? row[own] : tp_load4<VEC>(p, own, V);
+            else if (tp_entry<VEC>(own, 0) < V) x[0] = p[tp_entry<VEC>(own, 0)];
+        }
+        sample = tp_key(x[0]);
+        return x;
     };
     float most = 0.f;
     int nz = 0; // of the wavefront's looks, those that found a weight
@@ -830,16 +837,12 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
             for (int j = 0; j < 8; ++j) {
                 const int i = i0 + (t & 63) + TP_THREADS * j;
                 if (FITS && i < n4) row[i] = x[j]; // (read back by the same thread; clear() below has the barrier for others)
-                if (FRONT && j % 4 == 0) nz += __popcll(__ballot(i < n4 && x[j][j / 4] >= TP_LEAST));
+                if (FRONT && BY_COUNT && j % 4 == 0) nz += __popcll(__ballot(i < n4 && x[j][j / 4] >= TP_LEAST));
                 if (FRONT && BY_COUNT && i < n4) most = fmaxf(fmaxf(most, fmaxf(x[j][0], x[j][1])), fmaxf(x[j][2], x[j][3])); // (the same token at one thread only)
             }
         }
     }
-    if constexpr (FRONT && !FITS && !BY_COUNT) {
-        take_sample();
-        nz = __popcll(__ballot(sample != 0));
-    }
-    if (FRONT && (t & 63) == 0) sm_nz[t >> 6] = nz;
+    if (FRONT && BY_COUNT && (t & 63) == 0) sm_nz[t >> 6] = (uint8_t)min(nz, 255);
     auto unchanged = [&]() {
         for (int v = t; v < V; v += TP_THREADS) o[v] = p[v];
     };
@@ -927,60 +930,83 @@ __global__ __launch_bounds__(TP_THREADS) void top_p_filter_kernel(const float *p
     // where they turn out to be too many, everything below works on the row.  us, before -> now: 5 rows of 32000, top-k 40 15.3 -> 13.0, 200 16.2 ->
     // 14.5, top-p behind top-40 12.6 -> 9.2; of 50257 28.7 -> 19.4, 29.7 -> 21.2, 26.5 -> 12.0; 9 of 128256 41 -> 25, 42 -> 27.5, 38 -> 17.
     int nc = 0; // candidates (0: the row)
-    if constexpr (FRONT) {
-        __syncthreads();
-        nz = 0;
+    auto gather = [&](float least) { // those of at least this probability
+        for (int i0 = t; i0 < n4 && __hip_atomic_load(&sm_nc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= TP_CAND; i0 += TP_THREADS * 2) {
+            f32x4 x[2];
 #pragma unroll
-        for (int w = 0; w < TP_WAVES; ++w) nz += sm_nz[w];
-        const int seen = FITS || BY_COUNT ? n4 / (4 * TP_THREADS) * TP_THREADS + min(n4 % (4 * TP_THREADS), TP_THREADS) : TP_THREADS; // looks
+            for (int j = 0; j < 2; ++j) x[j] = FITS ? row[min(i0 + TP_THREADS * j, n4 - 1)] : tp_load4<VEC>(p, min(i0 + TP_THREADS * j, n4 - 1), V);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (i0 + TP_THREADS * j < n4 && fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])) >= least) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (x[j][e] >= least) {
+                            const int at = atomicAdd(&sm_nc, 1);
+                            if (at < TP_CAND) {
+                                cand[at] = 4 * (i0 + TP_THREADS * j) + e;
+                                if (!FITS) reinterpret_cast<float *>(row)[at] = x[j][e];
+                            }
+                        }
+                }
+        }
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(sm_nc);
+        nc = n <= TP_CAND && (!BY_COUNT || P24 <= (unsigned)n) ? n : 0;
+    };
+    auto candidate = [&](int i) { return reinterpret_cast<const float *>(row)[FITS ? cand[i] : i]; };
+    auto each_candidate = [&](auto f) {
+        for (int i = t; i < nc; i += TP_THREADS) f(tp_key(candidate(i)));
+    };
+    auto few_have_a_weight = [&](unsigned limit) { // by the wavefronts' counts, up to 255 each (more than the limit wherever a wavefront looks more often)
+        const u32x4 c = *reinterpret_cast<const u32x4 *>(sm_nz);
+        uint32_t n = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) n = __builtin_amdgcn_sad_u8(c[w], 0u, n); // + its four bytes
+        return n <= limit;
+    };
+    const auto live = [](uint32_t key) { return key != 0; };
+    const auto bin = [](uint32_t key) { return tp_bin(key); };
+    int hot = -1;
+    if constexpr (FRONT && BY_COUNT) {
+        __syncthreads();
         float least = 0.f;
-        if ((long long)nz * V <= (long long)TP_CAND * seen) {
+        const unsigned looks = n4 / (4 * TP_THREADS) * TP_THREADS + min(n4 % (4 * TP_THREADS), TP_THREADS);
+        if (few_have_a_weight((unsigned)((unsigned long long)TP_CAND * looks / (unsigned)V))) {
             least = TP_LEAST;
-        } else if (BY_COUNT) {
+        } else {
             clear();
             if (most >= TP_LEAST) atomicAdd(&hist[tp_bin(tp_key(most))], (Bin)1);
             const int b = choose(true);
             // (of threads with one above the bound; where they are most of them, so are the tokens above it - all those of a flat row)
             if (b >= 0 && P24 - need + binw <= TP_CAND / 2) least = u2f(tp_bin_prefix(b) << 17) * TP_LEAST;
         }
-        if (least > 0.f) {
-            for (int i0 = t; i0 < n4 && __hip_atomic_load(&sm_nc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= TP_CAND; i0 += TP_THREADS * 2) {
-                f32x4 x[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) x[j] = FITS ? row[min(i0 + TP_THREADS * j, n4 - 1)] : tp_load4<VEC>(p, min(i0 + TP_THREADS * j, n4 - 1), V);
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (i0 + TP_THREADS * j < n4 && fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])) >= least) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x[j][e] >= least) {
-                                const int at = atomicAdd(&sm_nc, 1);
-                                if (at < TP_CAND) {
-                                    cand[at] = 4 * (i0 + TP_THREADS * j) + e;
-                                    if (!FITS) reinterpret_cast<float *>(row)[at] = x[j][e];
-                                }
-                            }
-                    }
-            }
-            __syncthreads();
-            nc = sm_nc <= TP_CAND && (!BY_COUNT || P24 <= (unsigned)sm_nc) ? sm_nc : 0;
+        if (least > 0.f) gather(least);
+        if (!nc) {
+            take_sample();
+            hot = crowded_bin(live, bin);
         }
-    }
-    auto candidate = [&](int i) { return reinterpret_cast<const float *>(row)[FITS ? cand[i] : i]; };
-    auto each_candidate = [&](auto f) {
-        for (int i = t; i < nc; i += TP_THREADS) f(tp_key(candidate(i)));
-    };
-    if (nc) {
         clear();
-        each_candidate([&](uint32_t key) { atomicAdd(&hist[tp_bin(key)], add_of(key)); });
     } else {
-        if constexpr (!FRONT || FITS || BY_COUNT) take_sample();
-        const auto live = [](uint32_t key) { return key != 0; };
-        const auto bin = [](uint32_t key) { return tp_bin(key); };
-        const int hot = crowded_bin(live, bin);
+        // A top-p takes the histogram's samples for the look (of a longer row with 16-byte loads all four entries of their units: the limit is small
+        // there) and adds the wavefronts' counts up behind the barrier that there is anyway.  Where nothing comes of it - every call that sets
+        // top-p alone - it costs 0.1 - 0.2 us (5 rows, top-p 0.9, us, no look | a look of its own with a barrier of its own | now: 9001 entries 11.5 |
+        // 11.9 | 11.7, 32000 18.8 | 19.2 | 18.9; top-p 0.3 of 128256 46.2 | 47.2 | 46.3, of 262144 87.2 | 88.9 | 87.2).
+        const f32x4 x = take_sample();
+        unsigned limit = 0;
+        if constexpr (FRONT) {
+            constexpr int LOOKS = !FITS && VEC ? 4 : 1;
+            limit = TP_CAND * LOOKS * TP_THREADS / (unsigned)V;
+            int n = 0;
+#pragma unroll
+            for (int e = 0; e < LOOKS; ++e) n += __popcll(__ballot(x[e] >= TP_LEAST));
+            if ((t & 63) == 0) sm_nz[t >> 6] = (uint8_t)min(n, 255);
+        }
+        hot = crowded_bin(live, bin);
         clear();
-        histogram(hot, live, bin);
+        if (FRONT && __builtin_expect(few_have_a_weight(limit), 0)) gather(TP_LEAST);
     }
+    if (nc) each_candidate([&](uint32_t key) { atomicAdd(&hist[bin(key)], add_of(key)); });
+    else histogram(hot, live, bin);
     const int bin0 = choose(true);
     if (S == 0) { // nothing has a weight: the row is returned as it is
         unchanged();
