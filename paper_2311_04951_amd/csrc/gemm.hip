@@ -1338,29 +1338,35 @@ constexpr Ring ring_for(int bits, int epi, int ei, int rcap, bool many) {
     if (ei <= 2) return rcap == 16 ? Ring{12, 1} : Ring{8, 1};
     return ei == 3 || rcap == 16 ? Ring{6, 2} : Ring{4, 2};
 }
-template <typename T, int QB, int EPI, int EI, bool MANY> static void launch_cols_ei(const GemmArgs &a, const ColumnSplit &s, hipStream_t st) {
-    constexpr int BITS = QB ? QB : 8 * (int)sizeof(T);
-    constexpr Ring R8 = ring_for(BITS, EPI, EI, 8, MANY), R16 = ring_for(BITS, EPI, EI, 16, MANY);
-    if (QB == 4 && a.R <= 5) launch_cols_as<T, QB, EPI, R8.waves, R8.buffers, EI, QB == 4 ? 5 : 8>(a, s, st); // (a step of int4 is mostly activations)
-    else if (a.R <= 8) launch_cols_as<T, QB, EPI, R8.waves, R8.buffers, EI, 8>(a, s, st);
-    else launch_cols_as<T, QB, EPI, R16.waves, R16.buffers, EI, 16>(a, s, st);
+template <typename T, int QB, int EPI, int EI, bool MANY, int RCAP> static void launch_cols_rows(const GemmArgs &a, const ColumnSplit &s, hipStream_t st) {
+    constexpr Ring RING = ring_for(QB ? QB : 8 * (int)sizeof(T), EPI, EI, RCAP, MANY);
+    if (QB == 4 && RCAP == 8 && a.R <= 5) launch_cols_as<T, QB, EPI, RING.waves, RING.buffers, EI, QB == 4 && RCAP == 8 ? 5 : RCAP>(a, s, st); // (a step of int4 is mostly activations)
+    else launch_cols_as<T, QB, EPI, RING.waves, RING.buffers, EI, RCAP>(a, s, st);
+}
+template <typename T, int QB, int EPI, int EI> static void launch_cols_ei(const GemmArgs &a, const ColumnSplit &s, hipStream_t st) {
+    if (a.R <= 8) launch_cols_rows<T, QB, EPI, EI, false, 8>(a, s, st);
+    else launch_cols_rows<T, QB, EPI, EI, false, 16>(a, s, st);
 }
 template <typename T, int QB, int EPI> static int launch_cols(const GemmArgs &a, hipStream_t st) {
     const ColumnSplit s = split_columns(EPI, a.N, a.R);
     const int ei = (s.quads + (s.rest ? 1 : 0) + 1) / 2;
     constexpr bool M = EPI != EPI_RESID; // (a residual's columns fill more than one workgroup per unit beyond 8192 only)
-    if (M && s.groups > 256) {
-        if (ei <= 2) launch_cols_ei<T, QB, EPI, 2, M>(a, s, st);
-        else if (ei == 3) launch_cols_ei<T, QB, EPI, 3, M>(a, s, st);
-        else launch_cols_ei<T, QB, EPI, 4, M>(a, s, st);
+    if (M && s.groups > 256) { // shares of up to 4 and of 7 or 8 quads up to 8 rows, of 5 or 6 and of 7 or 8 beyond: split_columns makes no others
+        if (a.R <= 8) {
+            if (ei <= 2) launch_cols_rows<T, QB, EPI, 2, M, 8>(a, s, st);
+            else launch_cols_rows<T, QB, EPI, 4, M, 8>(a, s, st);
+        } else {
+            if (ei <= 3) launch_cols_rows<T, QB, EPI, 3, M, 16>(a, s, st);
+            else launch_cols_rows<T, QB, EPI, 4, M, 16>(a, s, st);
+        }
     } else if (ei == 1) {
-        launch_cols_ei<T, QB, EPI, 1, false>(a, s, st);
+        launch_cols_ei<T, QB, EPI, 1>(a, s, st);
     } else if (ei == 2) {
-        launch_cols_ei<T, QB, EPI, 2, false>(a, s, st);
+        launch_cols_ei<T, QB, EPI, 2>(a, s, st);
     } else if (ei == 3) {
-        launch_cols_ei<T, QB, EPI, 3, false>(a, s, st);
+        launch_cols_ei<T, QB, EPI, 3>(a, s, st);
     } else {
-        launch_cols_ei<T, QB, EPI, 4, false>(a, s, st);
+        launch_cols_ei<T, QB, EPI, 4>(a, s, st);
     }
     return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
 }

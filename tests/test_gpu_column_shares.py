@@ -39,8 +39,19 @@ def test_shares_cover_the_columns_and_every_size_is_met():
     for more in (False, True):
         for epi in (STORE, SWIGLU, QKV):
             assert {ei for e, m, many, ei in met if (e, m, many) == (epi, more, False)} == {1, 2, 3, 4}, (epi, more)
-            assert {ei for e, m, many, ei in met if (e, m, many) == (epi, more, True)} >= {2, 4} - ({2} if more else set()), (epi, more)
+            # several workgroups per unit: shares of up to 4 quads and of 7 or 8 up to 8 rows, of 5 or 6 and of 7 or 8 beyond - no others, of any matrix
+            assert {ei for e, m, many, ei in met if (e, m, many) == (epi, more, True)} == ({3, 4} if more else {2, 4}), (epi, more)
         assert {ei for e, m, many, ei in met if (e, m) == (RESID, more)} == {1, 2, 3, 4}
+
+
+@pytest.mark.parametrize("R", [1, 8, 9, 16])
+def test_no_matrix_has_a_share_that_no_kernel_is_built_for(R):
+    """No GPU: of all sizes up to 300000 columns, those with more than one workgroup per compute unit."""
+    for epi in range(4):
+        for N in range(96 if epi == 3 else 8193, 300000, 96 if epi == 3 else 7):
+            groups, quads, rest = _share(epi, R, N)
+            ei = (quads + (rest > 0) + 1) // 2
+            assert ei <= 4 and (groups <= 256 or ei in ((2, 4) if R <= 8 else (3, 4))), (epi, N)
 
 
 def _rms(x, eps=1e-5):
