@@ -1282,10 +1282,12 @@ extern "C" void ss_dev_gemm_tile(int epi, int R, int N, int K, size_t ws_bytes, 
 template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);
 
 // Calls of at most 16 rows.  The output columns in quads (of pairs for the fused epilogues) over k workgroups per compute unit of at
-// most eight quads, every one with the same number or one more.  Up to 8 rows k is the one that makes the fewest 16-column tiles of
-// them (a tile costs its LDS reads, MFMAs and conversions whether it is full or not: 2752 quads of pairs, K 4096, three workgroups
-// of four at most against two of six, one tile and a half: 28.8 against 29.2 us bf16, 18.5 / 20.3 int8, 14.5 / 16.6 int4); beyond,
-// where every workgroup's activations weigh as much as its weights, the smallest (12 rows: 31.2 us with two, 32.6 with three).
+// most eight quads, every one with the same number or one more: the smallest k - except that up to 8 rows a k that makes a tenth fewer
+// 16-column tiles of them is taken (a tile costs its LDS reads, MFMAs and conversions whether it is full or not: 2752 quads of pairs, K 4096,
+// three workgroups of four at most against two of six, one tile and a half: 28.8 against 29.2 us bf16, 18.5 / 20.3 int8, 14.5 / 16.6 int4).
+// Fewer tiles than that don't pay for the workgroups (heads of 50257 columns, 13 tiles against 14 but 13 workgroups against 7, 5 rows, us:
+// K 256 bf16 16.6 / 15.6, K 4096 73.8 / 71.4, int8 52.6 / 48.0, int4 42.6 / 36.4; K 256 fp32 18.4 / 19.4), nor beyond 8 rows, where
+// every workgroup's activations weigh as much as its weights (12 rows: 31.2 us with two, 32.6 with three).
 struct ColumnSplit {
     int groups, quads, rest; // workgroups; quads of each, and one more in the first `rest`
 };
@@ -1296,7 +1298,7 @@ static ColumnSplit split_columns(int epi, int N, int R) {
     const int least = (quads + UNITS * 8 - 1) / (UNITS * 8);
     int k = least;
     for (int i = least + 1; R <= 8 && i <= 2 * least; ++i)
-        if (tiles(i) < tiles(k)) k = i;
+        if (10 * tiles(i) < 9 * tiles(k)) k = i;
     const int groups = std::min(quads, k * UNITS);
     return ColumnSplit{groups, quads / groups, quads % groups};
 }
