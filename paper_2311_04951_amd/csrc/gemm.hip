@@ -276,7 +276,9 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
 };
 // A wavefront's n steps of K through a ring of NB (one or two) buffers of its own.  request(i, buffer) asks for its i-th step, use(i, buffer)
 // multiplies it; between them the step's loads are waited for - with two buffers by wait_ahead(), which leaves the next step's in
-// flight.  behind_first() runs behind the first request, what it asks for has arrived when the first step has; with_first() runs then.
+// flight.  behind_first() runs behind the first request; what it asks for is older than the second step and has arrived when the first
+// has.  with_first() runs then, and uses it.  (The compiler does not count the requests, which are assembly, and puts a vmcnt(0) of its own in
+// front of the first such use: with two buffers the wavefronts that finish the launch wait for their second step there.)
 template <int NB, class Request, class Use, class Wait, class Behind, class With>
 __device__ __forceinline__ void ring_walk(int n, Request request, Use use, Wait wait_ahead, Behind behind_first, With with_first) {
     static_assert(NB == 1 || NB == 2, "a third buffer made every launch slower: no counted wait for two steps");
@@ -670,7 +672,7 @@ __device__ __forceinline__ size_t splitk_index(int z, int ntiles, int tile, int 
 // multiple of 4 weight rows).  A slab is exactly one scale group and a lane's single 16-byte load holds 32 K entries =
 // its four k-blocks (dword j = entries 32g + 8j .., activations in LDS unit 4g + j): a step multiplies into fresh tiles
 // and adds them, times the group's scales of the lane's four columns (one 16-byte load, requested with the weights), to
-// the running sums - the arithmetic of gemm_w4_kernel.
+// the running sums.  The entries themselves are the operands (w4_to_bf16x8, by conversions): no biases to take off as in gemm_cols_kernel.
 // QB = 8 (W8): the matrix is int8 with row scales (bf16 activation planes only).  A lane's 16-byte load then holds 16 K entries,
 // two MFMA k-blocks: per slab and tile two loads instead of four, and quarter q = 2h + j of the slab multiplies bytes
 // 8j..8j+7 of load h with the activations of k = 64h + 16g + 8j .., which sit in LDS unit 8h + 2g + j of the row.
@@ -719,7 +721,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     const int s_lo = a.ksplit > 1 ? blockIdx.z * a.kslabs : 0;
     const int s_hi = a.ksplit > 1 ? min(s_lo + a.kslabs, nslab_all) : nslab_all;
     const int nslab = s_hi - s_lo;
-    // the workgroup's slabs in rotated order (see gemm_kernel: workgroups that walk K in step meet in the same memory
+    // the workgroup's slabs in rotated order (see gemm_cols_kernel: workgroups that walk K in step meet in the same memory
     // channels and activation lines); a request past the end repeats the last slab of the rotated order
     const int rot = k_rotation(nslab);
     auto slab_at = [&](int sl) { return s_lo + rotated(min(sl, nslab - 1), rot, nslab); };

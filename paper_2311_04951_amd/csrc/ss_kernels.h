@@ -64,10 +64,10 @@ struct GemmArgs {
     // weight-only int8: W is int8 [N][K] and output column n is scaled by wscale[n] (NULL: W is in the storage type).
     // bf16 activation planes only; K a multiple of 16.
     const float *wscale;
-    int wbits; // with wscale: 8 = int8, one scale per output column; 4 = int4, two entries per byte, scales [K/128][columns] (at most 16 rows, K % 128 == 0)
+    int wbits; // with wscale: 8 = int8, one scale per output column; 4 = int4, two entries per byte, scales [K/128][columns] (K % 128 == 0)
 };
 // 0: no norm written; 1: the RMSNorm asked for through norm_gain has been written as well; 2: written in the deferred
-// form (planes without the row scale + per-tile sums of squares in nsq_out)
+// form (planes without the row scale + partial sums of squares in nsq_out, one per row and workgroup of the launch)
 int launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t st);
 constexpr int NSQ_MAX_PARTS = 256; // most partial sums of a row of a deferred norm; a multiple of 16
 // partial sums of squares per row that a residual projection of d columns leaves for a deferred norm; 0: it cannot be deferred

@@ -110,9 +110,9 @@ def test_two_layers_against_64_bits(d, heads, ff, kind):
 @pytest.mark.parametrize("V", VOCABS)
 def test_a_head_against_64_bits(V, kind):
     """No layers: the norm of the embedded row times the head, the columns of the last share in part.  Sums of up to 1152 products in 32 bits:
-    1e-5 of the outputs' rms, 0.02 sqrt(1152).  int4 entries are multiplied as q + 136 and 136 times the group's activations taken off: sums
-    of 136 sqrt(128) = 1540 whose roundings (2^-24 of it, some four to a group) the scale, 0.01, and nine groups leave at 1540 * 2^-24 * 0.01
-    * 2 * 3 = 6e-6, 1e-5 of that rms: four times that."""
+    1e-5 of the outputs' rms, 0.02 sqrt(1152).  int4 entries are multiplied as q + 136 (even ones) and q + 24 (odd ones), and a group's
+    sum starts at what these biases add to it: 136 sqrt(64) and 24 sqrt(64), 1105 together, whose roundings (2^-24 of it, some four to a group)
+    the scale, 0.01, and nine groups leave at 1105 * 2^-24 * 0.01 * 2 * 3 = 4e-6, 6e-6 of that rms: six times that."""
     d = 1152 + RAGGED[kind]
     g = torch.Generator(device=dev()).manual_seed(V)
     n = lambda *s: (torch.randn(s, generator=g, device=dev()) * 0.02).to(torch.float32 if kind == "f32" else torch.bfloat16)
