@@ -26,14 +26,14 @@ HBM_PEAK = 8.0e12  # B/s, MI355X published peak
 # HBM bytes per launch of the persistent kernel on the default workload: a stored measurement (two rocprofv3 --pmc runs,
 # FETCH_SIZE then WRITE_SIZE, each scaled by what the counter reads for a plain 1 GiB device copy), valid for the kernel
 # source it was taken on; bench.py reports it only on that workload and names the file it comes from
-PERSISTENT_7B_TRAFFIC_BYTES = 13.601e9  # 13.465 GB fetched + 0.136 GB written
+PERSISTENT_7B_TRAFFIC_BYTES = 13.610e9  # 13.474 GB fetched + 0.136 GB written
 PERSISTENT_7B_TRAFFIC_SOURCE = "profiles/verify_pass_7b_persistent_hbm_traffic.txt"
 # the same kind of stored measurement for the stand-alone accept workload (the kernels stop reading a sequence's rows at
 # its first rejection, so they fetch less than "every logit once") and for the batched long-context pass
-ACCEPT_TRAFFIC_BYTES, ACCEPT_TRAFFIC_SOURCE = 365.8e6, "profiles/standalone_accept_hbm_traffic.txt"
+ACCEPT_TRAFFIC_BYTES, ACCEPT_TRAFFIC_SOURCE = 366.0e6, "profiles/standalone_accept_hbm_traffic.txt"
 GATEUP_TRAFFIC_BYTES, GATEUP_TRAFFIC_SOURCE = 181.2e6, "profiles/verify_pass_7b_per_phase_hbm_traffic.txt"
-PER_PHASE_PASS_TRAFFIC_BYTES = 13.459e9  # 13.429 GB fetched + 0.029 GB written over the launches of one pass (same file)
-BATCHED_TRAFFIC_BYTES, BATCHED_TRAFFIC_SOURCE = 36.209e9, "profiles/batched_long_context_pass_hbm_traffic.txt"
+PER_PHASE_PASS_TRAFFIC_BYTES = 13.458e9  # 13.425 GB fetched + 0.032 GB written over the launches of one pass (same file)
+BATCHED_TRAFFIC_BYTES, BATCHED_TRAFFIC_SOURCE = 35.120e9, "profiles/batched_long_context_pass_hbm_traffic.txt"
 STORED = " (stored counter measurement of this workload, not taken in this run)"
 
 
@@ -607,7 +607,7 @@ def main():
     else:
         gu = classes["gateup_gemm"]
         k_bytes = 2 * shape.d_ff * shape.d_model * 2          # W_gate | W_up streamed once per launch
-        k_name = "gemm_kernel<bf16, SWIGLU> (gate/up projection, 42.8% of the pass's bytes)"
+        k_name = "gemm_cols_kernel<bf16, SWIGLU> (gate/up projection, 42.8% of the pass's bytes)"
         k_us = gu["avg_us"]
     achieved = k_bytes / (k_us * 1e-6) / 1e9
     # HBM bytes per launch from the FETCH_SIZE and WRITE_SIZE counters of two rocprofv3 --pmc runs, each scaled by
