@@ -81,12 +81,13 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
         }
     } else {
         // rows without 16-byte alignment: the same with words, in whole lines, U of a thread's entries in flight (one load at a time, each
-        // with an exponential behind a branch: 32 x K 10 x 50257 117.5 us a call of the logits entry, 50.6 now).  U by the length, and
-        // exponentials four at a time only where one of a wavefront's lanes has an entry: short rows of a batch are bound by them (softmax
-        // of 1800 rows of 4099, us, one load at a time | always 32 | now: 22.5 | 27.6 | 21.2).  Ordinary loads: what writes the probabilities
-        // or draws the token reads the row again (the call of 32 x K 10 57.8 us with non-temporal ones; only a softmax of more
-        // than the last-level cache holds gains by those, 1000 rows of 100001 259 us against 272).  Which thread adds an entry depends on
-        // the row's length - and, where that is a multiple of 4, on the alignment of the rows, which leads here or to the 16 bytes above.
+        // with an exponential behind a branch: 32 x K 10 x 50257 117.5 us a call of the logits entry, 50.6 now).  32 of them as long as there
+        // are as many, then what the rest takes, and exponentials four at a time only where one of a wavefront's lanes has an entry: short rows
+        // of a batch are bound by them (softmax of 1800 rows of 2051 | 4099, us, one load at a time 14.9 | 22.6, always 32 20.4 | 27.7, now
+        // 14.3 | 21.5).  Ordinary loads: what writes the probabilities or draws the token reads the row again (the call of 32 x K 10 57.8 us with
+        // non-temporal ones; only a softmax of more than the last-level cache holds gains by those, 1000 rows of 100001 259 us against
+        // 272).  Which thread adds an entry depends on the row's length - and, where that is a multiple of 4, on the alignment of the
+        // rows, which leads here or to the 16 bytes above.
         auto words = [&](int w0, auto u_, auto full_) { // entries w0 .. of a wavefront; FULL: all of the workgroup's 256 * U exist
             constexpr int U = decltype(u_)::value;
             constexpr bool FULL = decltype(full_)::value;
@@ -111,22 +112,25 @@ __device__ __forceinline__ float2 segment_stats(const float *x, int V, float inv
             float add = 0.f;
 #pragma unroll
             for (int j = 0; j < U; j += 4)
-                if (FULL || w0 + 256 * j < V) add += (fast_exp(t[j] - m) + fast_exp(t[j + 1] - m)) + (fast_exp(t[j + 2] - m) + fast_exp(t[j + 3] - m));
+                if (FULL || U <= 4 || w0 + 256 * j < V) {
+                    float e[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < (U < 4 ? U : 4); ++i) e[i] = fast_exp(t[j + i] - m);
+                    add += (e[0] + e[1]) + (e[2] + e[3]);
+                }
             s += add;
         };
-        constexpr std::integral_constant<int, STATS_UNROLL / 2> few{};
-        constexpr std::integral_constant<int, STATS_UNROLL> some{};
-        constexpr std::integral_constant<int, 4 * STATS_UNROLL> many{};
+        constexpr int MANY = 4 * STATS_UNROLL;
         const int own = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
-        if (V <= 256 * few) {
-            words(own, few, std::false_type{});
-        } else if (V <= 256 * some) {
-            words(own, some, std::false_type{});
-        } else {
-            int v = 0;
-            for (; v + 256 * many <= V; v += 256 * many) words(v + own, many, std::true_type{});
-            if (v < V) words(v + own, many, std::false_type{});
-        }
+        int v = 0;
+        for (; v + 256 * MANY <= V; v += 256 * MANY) words(v + own, std::integral_constant<int, MANY>{}, std::true_type{});
+        const int rest = V - v;
+        if (rest > 256 * 16) words(v + own, std::integral_constant<int, MANY>{}, std::false_type{});
+        else if (rest > 256 * 8) words(v + own, std::integral_constant<int, 16>{}, std::false_type{});
+        else if (rest > 256 * 4) words(v + own, std::integral_constant<int, 8>{}, std::false_type{});
+        else if (rest > 256 * 2) words(v + own, std::integral_constant<int, 4>{}, std::false_type{});
+        else if (rest > 256) words(v + own, std::integral_constant<int, 2>{}, std::false_type{});
+        else if (rest > 0) words(v + own, std::integral_constant<int, 1>{}, std::false_type{});
     }
     if (m == -INFINITY) s = 0.f; // a thread that saw nothing: exp(-inf - -inf) must not appear
 #pragma unroll

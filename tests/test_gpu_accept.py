@@ -92,7 +92,7 @@ def test_softmax_close_to_oracle(rows, V, T):
     assert np.allclose(got.astype(np.float64).sum(-1), 1.0, atol=1e-5)
 
 
-@pytest.mark.parametrize("V", [5, 257, 1023, 1025, 2047, 2049, 4099, 8193, 8195, 16383, 16387, 50257])
+@pytest.mark.parametrize("V", [5, 255, 257, 511, 513, 1023, 1025, 2047, 2049, 4095, 4099, 8193, 8195, 16383, 16387, 50257])
 def test_statistics_of_rows_without_alignment(V):
     """Rows whose length is no multiple of 4 (read word by word): whole and with masked entries (minus infinity in front, in between, nearly
     everywhere) against 64 bits, and the same row at other places, of every alignment that a row of this length has, gives the same bits."""
