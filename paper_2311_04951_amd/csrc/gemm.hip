@@ -944,25 +944,34 @@ template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wid
 // row, and are read back as operands (16-byte units of a row at position unit xor row: no bank conflicts).  The wavefronts split
 // the rows WR ways, the columns WC ways and the k-blocks of a stage WK ways (their sums meet in LDS at the end), each keeps
 // RTW x CTW tiles in registers: with one column tile per wavefront, as in the kernel below, every 10 - 20 MFMAs cost 10 KB of LDS reads.
-//   What bounds it: a compute unit has about 32 KB of loads in flight whatever the ring in LDS holds (a loads-only build
-// takes 85 - 95 % of the time, deeper rings change nothing), so a launch costs about 16 us per MB of activations and 40 us per MB of
-// weights that one workgroup fetches - 32 KB per round trip to the L2 and to memory.  Hence tiles that are as square as LDS and
-// registers allow, and the choice of tile and split by exactly that sum (launch_tile).
-//   Measured against the column-per-wavefront kernel (7B shape, us): 256 rows gate/up 180 -> 103, QKV 112 -> 71, O 40 -> 21,
-// down 115 -> 48; 72 rows 61 -> 52, 49 -> 45, 22 -> 12 (+ 6 for the second launch), 41 -> 30 (+ 6).
-template <int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int NBUF_> struct TileCfg {
-    static constexpr int RTW = RTW_, CTW = CTW_, WR = WR_, WC = WC_, WK = WK_, KBS = KBS_, NBUF = NBUF_;
+//   What bounds it: up to about 100 rows the loads.  The weights have one trip through memory, the activations come from the L2 at 116 GB/s
+// per compute unit (80 rows of K 4096: 14 us) and both share one path, so loads alone take their sum: 80 rows x 96 columns 35 us a launch
+// of 22016 columns, the kernel 48.  They got there by
+//   - a ring of ABUF stages of activations and WBUF of the matrix, the matrix's one stage deeper where LDS does not hold three of both (loads
+//     alone, one | two stages ahead: 45 | 37 us), asked for in that order, so that the counted wait leaves the younger ones in flight;
+//   - 256 bytes of a row at a time where LDS allows (128: 40 us) and the non-temporal bit on those matrix requests (37.4 -> 34.7; not for
+//     the residual projections, whose short splits lose by it: 4096 x 4096, 72 rows, 16.3 -> 17.5);
+//   - a start in K that depends on the XCD: its workgroups walk K together and find each other's activations in their L2, the eight XCDs
+//     ask different memory channels (no rotation 38 us, every workgroup its own 35.4; 256 rows, where the activations fill an L2: 71, 99, 67);
+//   - row blocks of the same columns on one XCD, next to one another in time (tile_place): weights of two blocks from memory once (52 -> 37 us).
+// With 128 rows and more to a block a launch is bound by the power of the card: 256 rows of 4096 x 22016 take 100 us, the same launch on zeros 79,
+// its loads alone 76, its MFMAs and LDS reads alone 64.  (MFMAs of 32 x 32: 113 us; requests between the MFMAs: 100; the two wavefronts
+// of a SIMD half a step apart: 107.)  More wavefronts of smaller tiles pay where a wavefront's MFMAs, requests and LDS reads stand behind
+// one another (4 -> 8 waves, 128 x 64: 34 -> 29 us; 4 -> 12, 80 x 96: 52 -> 48), not where they read the LDS twice as often.
+//   Measured (7B shape, us, before this form of it -> now; R rows, QKV and O / down with their second launches): gate/up 256 rows 109 -> 100,
+// 192 112 -> 74, 72 53.6 -> 48, 40 47.8 -> 34, 24 47 -> 31; QKV 256 rows 68 -> 58, 192 68 -> 50, 40 28 -> 27; down 192 rows 57 -> 43.
+template <int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int ABUF_, int WBUF_> struct TileCfg {
+    static constexpr int RTW = RTW_, CTW = CTW_, WR = WR_, WC = WC_, WK = WK_, KBS = KBS_, ABUF = ABUF_, WBUF = WBUF_;
     static constexpr int NW = WR * WC * WK;         // wavefronts
     static constexpr int BM = 16 * RTW * WR;        // rows
     static constexpr int CT = CTW * WC;             // 16-column tiles
     static constexpr int ROWB = 64 * KBS;           // bytes of a row in a stage (KBS k-blocks of 32 entries)
     static constexpr int UPR = 4 * KBS;             // ... in 16-byte units
     static constexpr int RPI = 64 / UPR;            // rows per load instruction
-    static constexpr int LROWS = 2 * BM + 16 * CT;  // rows of a stage: two activation planes, then the matrix
-    static constexpr int STAGE = LROWS * ROWB;
-    static constexpr int GROUPS = LROWS / RPI;      // load instructions per stage
-    static constexpr int GMAX = (GROUPS + NW - 1) / NW, GMIN = GROUPS / NW;
-    static_assert(NBUF * STAGE <= 160 * 1024, "LDS");
+    static constexpr int ASTAGE = 2 * BM * ROWB, WSTAGE = 16 * CT * ROWB; // a stage's two activation planes, its piece of the matrix
+    static constexpr int AG = 2 * BM / RPI, WG = 16 * CT / RPI, AL = (AG + NW - 1) / NW, WL = (WG + NW - 1) / NW; // load instructions of a wavefront and stage
+    static constexpr int LDS = ABUF * ASTAGE + WBUF * WSTAGE;
+    static_assert(LDS <= 160 * 1024 && WBUF >= ABUF && ABUF >= 2 && WBUF <= 3, "");
 };
 
 __device__ __forceinline__ void stage_barrier() { // ... which no LDS access may cross
@@ -971,24 +980,41 @@ __device__ __forceinline__ void stage_barrier() { // ... which no LDS access may
     asm volatile("" ::: "memory");
 }
 
+// The workgroup's place: the row blocks of a column share lie on one XCD (workgroups go round the eight of them), next to one another in time,
+// so that the second reads the weights of the first from their L2.
+struct TilePlace {
+    int x, y, id; // column share, row block, number in launch order (of a split)
+};
+__device__ __forceinline__ TilePlace tile_place() {
+    const int gx = gridDim.x, gy = gridDim.y, id = blockIdx.x + gx * blockIdx.y, whole = (gx & ~7) * gy;
+    if (id >= whole) {
+        const int rest = id - whole, w = gx & 7;
+        return TilePlace{(gx & ~7) + rest % w, rest / w, id};
+    }
+    const int slot = id >> 3;
+    return TilePlace{slot / gy * 8 + (id & 7), slot % gy, id};
+}
+
 template <int EPI, class C>
 __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, NBUF = C::NBUF, NW = C::NW;
-    static_assert(CTW % NT == 0 && KBS % WK == 0 && NBUF <= 3, "");
-    __shared__ __align__(16) unsigned char lds[NBUF * C::STAGE];
+    constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, ABUF = C::ABUF, WBUF = C::WBUF, NW = C::NW;
+    static_assert(CTW % NT == 0 && KBS % WK == 0, "");
+    constexpr bool STREAM = KBS == 4 && EPI != EPI_RESID; // (see TileCfg)
+    __shared__ __align__(16) unsigned char lds[C::LDS];
     const uint32_t lds0 = lds_address(lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int wk = wave % WK, wc = (wave / WK) % C::WC, wr = wave / (WK * C::WC);
+    const int wk = wave / (NW / WK), wc = wave % C::WC, wr = wave % (NW / WK) / C::WC;
     const int K = a.K;
-    const int row0 = blockIdx.y * C::BM;
+    const TilePlace place = tile_place();
+    const int row0 = place.y * C::BM;
     // first column of output tile `ct` of the workgroup (fused epilogues: tiles 2p and 2p + 1 are the two halves of pair p)
     const int npairs = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     const int nrows_w = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
     auto tile_col = [&](int ct) {
-        const int p = min((int)blockIdx.x * (C::CT / NT) + ct / NT, npairs - 1), half = ct % NT;
+        const int p = min(place.x * (C::CT / NT) + ct / NT, npairs - 1), half = ct % NT;
         if constexpr (EPI == EPI_QKV) {
             const int per_head = a.hd / 32, hh = p / per_head;
             return hh * a.hd + (p % per_head) * 16 + half * (a.hd / 2);
@@ -1001,47 +1027,51 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     const int nst_all = (K + 32 * KBS - 1) / (32 * KBS);
     const int s_lo = a.ksplit > 1 ? blockIdx.z * a.kslabs : 0;
     const int nst = (a.ksplit > 1 ? min(s_lo + a.kslabs, nst_all) : nst_all) - s_lo;
-    const int rot = a.rotate ? k_rotation(nst) : 0; // (see the launcher)
+    const int rot = (place.id & 7) * nst / 8; // (see TileCfg)
     auto stage_at = [&](int s) { return s_lo + rotated(s, rot, nst); };
 
     // this wave's load instructions of a stage: group wave + i * NW; lane l brings unit (l % UPR) xor row of row l / UPR
-    const char *base[C::GMAX];
-    uint32_t voff[C::GMAX];
+    const char *abase[C::AL], *wbase[C::WL];
+    uint32_t aoff[C::AL], woff[C::WL];
     const int lr = lane / C::UPR, lu = lane % C::UPR;
 #pragma unroll
-    for (int i = 0; i < C::GMAX; ++i) {
-        const int grp = min(wave + i * NW, C::GROUPS - 1);
-        const int r0 = grp * C::RPI, row = r0 + lr;
-        if (r0 < 2 * C::BM) {
-            const int pl = r0 / C::BM, r = row - pl * C::BM;
-            base[i] = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + pl * a.act_plane + (size_t)min(row0, a.R - 1) * a.ld_act);
-            voff[i] = (uint32_t)(min(row0 + r, a.R - 1) - min(row0, a.R - 1)) * (uint32_t)a.ld_act * 2u;
-        } else {
-            const int wrow0 = r0 - 2 * C::BM, ct = wrow0 / 16, n0 = tile_col(ct);
-            const int n = min(n0 + (wrow0 & 15) + lr, nrows_w - 1);
-            base[i] = reinterpret_cast<const char *>(a.W) + (size_t)n0 * K * 2;
-            voff[i] = (uint32_t)(n - n0) * (uint32_t)K * 2u;
-        }
-        voff[i] += (uint32_t)(lu ^ (row & (C::UPR - 1))) * 16u;
+    for (int i = 0; i < C::AL; ++i) {
+        const int r0 = min(wave + i * NW, C::AG - 1) * C::RPI, row = r0 + lr, pl = r0 / C::BM, r = row - pl * C::BM;
+        abase[i] = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + pl * a.act_plane + (size_t)min(row0, a.R - 1) * a.ld_act);
+        aoff[i] = (uint32_t)(min(row0 + r, a.R - 1) - min(row0, a.R - 1)) * (uint32_t)a.ld_act * 2u + (uint32_t)(lu ^ (row & (C::UPR - 1))) * 16u;
+    }
+#pragma unroll
+    for (int i = 0; i < C::WL; ++i) {
+        const int row = min(wave + i * NW, C::WG - 1) * C::RPI, n0 = tile_col(row / 16), n = min(n0 + (row & 15) + lr, nrows_w - 1);
+        wbase[i] = reinterpret_cast<const char *>(a.W) + (size_t)n0 * K * 2;
+        woff[i] = (uint32_t)(n - n0) * (uint32_t)K * 2u + (uint32_t)(lu ^ ((row + lr) & (C::UPR - 1))) * 16u;
     }
     const bool ragged = K % (32 * KBS) != 0;
-    auto issue = [&](int s, int buf) {
+    // past a ragged end: units past K repeat the row's last one (their weights are zeroed when used)
+    auto beyond = [&](int st, int grp) {
+        const int row = grp * C::RPI + lr, u = lu ^ (row & (C::UPR - 1));
+        return 2u * (uint32_t)max(st * 32 * KBS + u * 8 - (K - 8), 0);
+    };
+    auto issue_act = [&](int s, int buf) {
         const int st = stage_at(s);
-        const uint32_t to = lds0 + buf * C::STAGE + wave * 1024;
+        const uint32_t to = lds0 + buf * C::ASTAGE;
         const size_t kb = (size_t)st * C::ROWB;
-        if (ragged && st == nst_all - 1) { // units past K repeat the row's last one (their weights are zeroed when used)
 #pragma unroll
-            for (int i = 0; i < C::GMAX; ++i)
-                if (i < C::GMIN || wave + i * NW < C::GROUPS) {
-                    const int row = (wave + i * NW) * C::RPI + lr, u = lu ^ (row & (C::UPR - 1));
-                    dma16(base[i] + kb, voff[i] - 2u * (uint32_t)max(st * 32 * KBS + u * 8 - (K - 8), 0), to + i * NW * 1024);
-                }
-        } else {
+        for (int i = 0; i < C::AL; ++i) {
+            const int grp = min(wave + i * NW, C::AG - 1);
+            if (ragged && st == nst_all - 1) dma16(abase[i] + kb, aoff[i] - beyond(st, grp), to + grp * 1024);
+            else dma16(abase[i] + kb, aoff[i], to + grp * 1024);
+        }
+    };
+    auto issue_w = [&](int s, int buf) {
+        const int st = stage_at(s);
+        const uint32_t to = lds0 + ABUF * C::ASTAGE + buf * C::WSTAGE;
+        const size_t kb = (size_t)st * C::ROWB;
 #pragma unroll
-            for (int i = 0; i < C::GMAX; ++i)
-                if (i < C::GMIN || wave + i * NW < C::GROUPS) {
-                    dma16(base[i] + kb, voff[i], to + i * NW * 1024);
-                }
+        for (int i = 0; i < C::WL; ++i) {
+            const int grp = min(wave + i * NW, C::WG - 1);
+            if (ragged && st == nst_all - 1) dma16<STREAM>(wbase[i] + kb, woff[i] - beyond(st, grp), to + grp * 1024);
+            else dma16<STREAM>(wbase[i] + kb, woff[i], to + grp * 1024);
         }
     };
     f32x4 acc[RTW][CTW];
@@ -1050,55 +1080,60 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
 #pragma unroll
         for (int t = 0; t < CTW; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // operand offsets in a stage (the xor only touches the low bits of the row, which is c's for every tile)
-    auto step = [&](int s, int bcur, int bfill) {
-        const unsigned char *cur = lds + bcur * C::STAGE;
-        // stages s + 1 .. of what was issued may still be in flight
-        const int ahead = min(NBUF - 2, nst - 1 - s);
-        if (C::GMAX == C::GMIN || wave < C::GROUPS % NW) {
-            if (NBUF > 2 && ahead) wait_vmcnt_at_most<C::GMAX>();
-            else wait_vmcnt_at_most<0>();
-        } else {
-            if (NBUF > 2 && ahead) wait_vmcnt_at_most<C::GMIN>();
-            else wait_vmcnt_at_most<0>();
+    // waits for stage s: younger are only the stages requested ahead of it
+    auto wait_stage = [&](int s) {
+        const int wa = min(WBUF - 2, nst - 1 - s), aa = min(ABUF - 2, nst - 1 - s);
+        if (ABUF > 2 && aa > 0) wait_vmcnt_at_most<(ABUF - 2) * C::AL + (WBUF - 2) * C::WL>();
+        else if (WBUF > 2 && wa > 0) wait_vmcnt_at_most<(WBUF - 2) * C::WL>();
+        else wait_vmcnt_at_most<0>();
+    };
+    u32x4 w[CTW], b[RTW][2];
+    auto read_operands = [&](int s, int ab, int wb, int kk) { // of k-block kk of this wavefront's share of a stage
+        const int kb = wk * (KBS / WK) + kk;
+        const int un = ((4 * kb + g) ^ (c & (C::UPR - 1))) * 16; // (the xor only touches the low bits of the row, which is c's for every tile)
+        const unsigned char *ap = lds + ab * C::ASTAGE, *wp = lds + ABUF * C::ASTAGE + wb * C::WSTAGE;
+#pragma unroll
+        for (int t = 0; t < CTW; ++t) w[t] = *reinterpret_cast<const u32x4 *>(wp + ((wc * CTW + t) * 16 + c) * C::ROWB + un);
+#pragma unroll
+        for (int r = 0; r < RTW; ++r)
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl) b[r][pl] = *reinterpret_cast<const u32x4 *>(ap + (pl * C::BM + (wr * RTW + r) * 16 + c) * C::ROWB + un);
+        if (ragged && stage_at(s) == nst_all - 1 && (nst_all - 1) * 32 * KBS + kb * 32 + g * 8 >= K) {
+#pragma unroll
+            for (int t = 0; t < CTW; ++t) w[t] = zero16();
         }
-        stage_barrier(); // everybody's part of the stage has landed, and everybody is done reading the one that is filled next
-        if (s + NBUF - 1 < nst) issue(s + NBUF - 1, bfill);
-        const int st = stage_at(s);
+    };
+    auto multiply = [&] {
 #pragma unroll
-        for (int kk = 0; kk < KBS / WK; ++kk) {
-            const int kb = wk * (KBS / WK) + kk;
-            const int un = ((4 * kb + g) ^ (c & (C::UPR - 1))) * 16;
-            u32x4 w[CTW], b[RTW][2];
-#pragma unroll
-            for (int t = 0; t < CTW; ++t) w[t] = *reinterpret_cast<const u32x4 *>(cur + (2 * C::BM + (wc * CTW + t) * 16 + c) * C::ROWB + un);
+        for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
             for (int r = 0; r < RTW; ++r)
 #pragma unroll
-                for (int pl = 0; pl < 2; ++pl) b[r][pl] = *reinterpret_cast<const u32x4 *>(cur + (pl * C::BM + (wr * RTW + r) * 16 + c) * C::ROWB + un);
-            if (ragged && st == nst_all - 1 && st * 32 * KBS + kb * 32 + g * 8 >= K) {
-#pragma unroll
-                for (int t = 0; t < CTW; ++t) w[t] = zero16();
-            }
-#pragma unroll
-            for (int pl = 0; pl < 2; ++pl)
-#pragma unroll
-                for (int r = 0; r < RTW; ++r)
-#pragma unroll
-                    for (int t = 0; t < CTW; ++t)
-                        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, b[r][pl]), acc[r][t], 0, 0, 0);
-        }
+                for (int t = 0; t < CTW; ++t)
+                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, b[r][pl]), acc[r][t], 0, 0, 0);
     };
-    issue(0, 0);
-    if (NBUF > 2 && nst > 1) issue(1, 1);
-    for (int s = 0, bc = 0; s < nst; ++s) {
-        step(s, bc, bc == 0 ? NBUF - 1 : bc - 1);
-        bc = bc == NBUF - 1 ? 0 : bc + 1;
+#pragma unroll
+    for (int s = 0; s < WBUF - 1; ++s) {
+        if (s < ABUF - 1 && s < nst) issue_act(s, s);
+        if (s < nst) issue_w(s, s);
+    }
+    for (int s = 0, ab = 0, wb = 0; s < nst; ++s) {
+        wait_stage(s);
+        stage_barrier(); // everybody's part of the stage has landed, and everybody is done reading the ones that are filled next
+        if (s + ABUF - 1 < nst) issue_act(s + ABUF - 1, ab == 0 ? ABUF - 1 : ab - 1);
+        if (s + WBUF - 1 < nst) issue_w(s + WBUF - 1, wb == 0 ? WBUF - 1 : wb - 1);
+#pragma unroll
+        for (int kk = 0; kk < KBS / WK; ++kk) {
+            read_operands(s, ab, wb, kk);
+            multiply();
+        }
+        ab = ab == ABUF - 1 ? 0 : ab + 1;
+        wb = wb == WBUF - 1 ? 0 : wb + 1;
     }
 
     auto finish = [&](float (&out)[NT][4], int r, int p) { // row tile r and column tile (pair) p of the workgroup
         const int ct = p * NT;
-        if ((int)blockIdx.x * (C::CT / NT) + p >= npairs) return;
+        if (place.x * (C::CT / NT) + p >= npairs) return;
         int n0[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) n0[t] = tile_col(ct + t);
@@ -1127,10 +1162,10 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
             }
     } else {
         // the K shares of a tile are summed in order through LDS, a row tile at a time in alternating buffers
-        static_assert(NW * CTW * 1024 <= C::STAGE, "");
+        static_assert(2 * NW * CTW * 1024 <= C::LDS, "");
 #pragma unroll
         for (int r = 0; r < RTW; ++r) {
-            float *red = reinterpret_cast<float *>(lds + (r & 1) * C::STAGE);
+            float *red = reinterpret_cast<float *>(lds + (r & 1) * (NW * CTW * 1024));
             if (r == 0) stage_barrier(); // nobody reads the stages any more
 #pragma unroll
             for (int t = 0; t < CTW; ++t) *reinterpret_cast<f32x4 *>(red + ((size_t)(wave * CTW + t) * 64 + lane) * 4) = acc[r][t];
@@ -1144,7 +1179,7 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
                         f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int k2 = 0; k2 < WK; ++k2)
-                            sum += *reinterpret_cast<const f32x4 *>(red + ((size_t)((wave - wk + k2) * CTW + p * NT + t) * 64 + lane) * 4);
+                            sum += *reinterpret_cast<const f32x4 *>(red + ((size_t)((wave % (NW / WK) + k2 * (NW / WK)) * CTW + p * NT + t) * 64 + lane) * 4);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) out[t][v] = sum[v];
                     }
@@ -1182,19 +1217,26 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(GemmArgs a) {
     epilogue_cols<bf16_t, EPI_QKV, 4>(a, m, hh * a.hd + j0, x0, x1);
 }
 
-// Which tile and which split of K: the least of  rounds * K share * (16 us/MB * activations + 40 us/MB * weights)  over the
-// shapes there are (see gemm_tile_kernel; within 15 % of what every 7B-shaped matrix takes at 72 and 256 rows), where a second
-// row block on the chip reads the same weights from the L2 (34 on average).  A split adds its partial rows, written and read
-// once (8 MB/us), and for QKV a launch (4.5 us; a residual projection's is the RMSNorm that follows anyway).
+// Which tile and which split of K: the least of  rounds * (1.1 us + K share * (A us/MB * activations + W us/MB * weights)) + 3 ns a workgroup
+// over the shapes there are; A and W were fitted to 40 launches of 2048- to 5120-wide models at 17 to 256 rows (they are within 8 % of
+// what those take on average, and the choice within 2 % of the best one; 5 - 7 % for QKV of up to 48 rows, where 192 columns are taken and
+// 96 would be 1.2 us faster).  A: 9 in stages of 128 bytes a row, 13.5 in stages of 256 with three of them in LDS, 15 with two.  W: 31 in
+// stages of 256 bytes, 26 in blocks of 128 rows with up to 96 columns, 29 for 128 columns, 32.5 for 192, 34.5 with several row blocks.  A
+// split adds its partial rows, written and read once (8 MB/us), 0.16 us of the second launch and for QKV that launch (4.5 us; a residual
+// projection's is the RMSNorm that follows anyway).
 struct TileChoice {
     int rows, cols, ksplit;
     double us;
 };
 static TileChoice tile_cost(int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
-    const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols;
-    const int rounds = (gx * gy * ksplit + 255) / 256;
-    const double per = bm * 4 * 16e-6 + cols * 2 * (gy > 1 ? 34e-6 : 40e-6);
-    return TileChoice{bm, cols, ksplit, rounds * (double)((K + ksplit - 1) / ksplit) * per + (ksplit > 1 ? launch_us + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
+    const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols, wgs = gx * gy * ksplit;
+    const int rounds = (wgs + 255) / 256;
+    const bool long_stage = cols <= 96 && bm <= 96; // 256 bytes of a row
+    const double act = !long_stage ? 9e-6 : bm <= 48 ? 13.5e-6 : 15e-6;
+    const double mat = long_stage ? 31e-6 : cols <= 96 ? 26e-6 : cols == 128 ? 29e-6 : gy > 1 ? 34.5e-6 : 32.5e-6;
+    const double per = bm * 4 * act + cols * 2 * mat;
+    return TileChoice{bm, cols, ksplit, rounds * (1.1 + (double)((K + ksplit - 1) / ksplit) * per) + 0.003 * wgs +
+                                            (ksplit > 1 ? launch_us + 0.16 * ksplit + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
 }
 
 template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int columns, int ksplit, hipStream_t st) {
@@ -1202,11 +1244,6 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     const int nst = (a.K + 32 * C::KBS - 1) / (32 * C::KBS);
     a.kslabs = (nst + ksplit - 1) / ksplit;
     a.ksplit = (nst + a.kslabs - 1) / a.kslabs; // no empty split
-    // Workgroups that start at different places of K (k_rotation) do not meet in one memory channel where the rows of the matrix
-    // lie a multiple of 4 KB apart (72 rows, gate/up 54 us against 59), but share no activations in the L2 at a time: not where
-    // those of a pass over K are too many to stay there (256 rows of K 11008: 69 us with, 48 without), and for nothing where the
-    // rows lie otherwise (72 rows of K 11008: 33 with, 31 without)
-    a.rotate = a.K % 2048 == 0 && (size_t)a.R * a.K * 4 / a.ksplit <= (size_t)3 << 19;
     hipLaunchKernelGGL((gemm_tile_kernel<EPI, C>), dim3((columns + 16 * C::CT - 1) / (16 * C::CT), (a.R + C::BM - 1) / C::BM, a.ksplit), dim3(C::NW * 64), 0, st, a);
     if (a.ksplit == 1) return 0;
     if constexpr (EPI == EPI_QKV) {
@@ -1217,22 +1254,37 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     return a.norm_gain != nullptr ? 1 : 0;
 }
 
-template <int EPI, int RT> static int launch_tile_rows(const GemmArgs &a, int columns, const TileChoice &c, hipStream_t st) {
-    if constexpr (RT == 8) {
-        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-            if (c.cols == 192) return launch_tile_as<EPI, TileCfg<4, 6, 2, 2, 2, 2, 2>>(a, columns, c.ksplit, st);
-            return launch_tile_as<EPI, TileCfg<4, 6, 2, 1, 2, 2, 3>>(a, columns, c.ksplit, st);
-        } else {
-            if (c.cols == 128) return launch_tile_as<EPI, TileCfg<4, 4, 2, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
-            return launch_tile_as<EPI, TileCfg<4, 4, 2, 1, 2, 2, 3>>(a, columns, c.ksplit, st);
+template <int EPI> static int launch_tile_rows(const GemmArgs &a, int columns, const TileChoice &c, hipStream_t st) {
+    auto go = [&](auto cfg) { return launch_tile_as<EPI, decltype(cfg)>(a, columns, c.ksplit, st); };
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+        switch (c.rows * 1000 + c.cols) {
+        case 32064: return go(TileCfg<2, 4, 1, 1, 4, 4, 3, 3>{});
+        case 32096: return go(TileCfg<2, 6, 1, 1, 4, 4, 3, 3>{});
+        case 32192: return go(TileCfg<2, 6, 1, 2, 2, 2, 3, 3>{});
+        case 48064: return go(TileCfg<3, 4, 1, 1, 4, 4, 3, 3>{});
+        case 48096: return go(TileCfg<3, 6, 1, 1, 4, 4, 3, 3>{});
+        case 48192: return go(TileCfg<3, 6, 1, 2, 2, 2, 3, 3>{});
+        case 80064: return go(TileCfg<5, 2, 1, 2, 4, 4, 2, 3>{});
+        case 80096: return go(TileCfg<5, 2, 1, 3, 4, 4, 2, 3>{});
+        case 80192: return go(TileCfg<5, 6, 1, 2, 2, 2, 3, 3>{});
+        case 96096: return go(TileCfg<3, 6, 2, 1, 4, 4, 2, 2>{});
+        case 96192: return go(TileCfg<3, 6, 2, 2, 2, 2, 3, 3>{});
+        case 128096: return go(TileCfg<2, 6, 4, 1, 2, 2, 3, 3>{});
+        default: return go(TileCfg<4, 6, 2, 2, 2, 2, 2, 3>{}); // 128 x 192
         }
-    } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-        if (c.cols == 192) return launch_tile_as<EPI, TileCfg<RT, 6, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
-        if (c.cols == 96) return launch_tile_as<EPI, TileCfg<RT, 6, 1, 1, 4, 4, 2>>(a, columns, c.ksplit, st);
-        return launch_tile_as<EPI, TileCfg<RT, 4, 1, 1, 4, 4, 2>>(a, columns, c.ksplit, st);
     } else {
-        if (c.cols == 128) return launch_tile_as<EPI, TileCfg<RT, 4, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
-        return launch_tile_as<EPI, TileCfg<RT, 2, 1, 2, 2, 2, 3>>(a, columns, c.ksplit, st);
+        switch (c.rows * 1000 + c.cols) {
+        case 32064: return go(TileCfg<2, 2, 1, 2, 4, 4, 3, 3>{});
+        case 32128: return go(TileCfg<2, 2, 1, 4, 2, 2, 3, 3>{});
+        case 48064: return go(TileCfg<3, 2, 1, 2, 4, 4, 3, 3>{});
+        case 48128: return go(TileCfg<3, 2, 1, 4, 2, 2, 3, 3>{});
+        case 80064: return go(TileCfg<5, 2, 1, 2, 4, 4, 2, 3>{});
+        case 80128: return go(TileCfg<5, 2, 1, 4, 2, 2, 3, 3>{});
+        case 96064: return go(TileCfg<3, 2, 2, 2, 2, 4, 2, 3>{});
+        case 96128: return go(TileCfg<3, 4, 2, 2, 2, 2, 3, 3>{});
+        case 128064: return go(TileCfg<2, 4, 4, 1, 2, 2, 3, 3>{});
+        default: return go(TileCfg<4, 4, 2, 2, 2, 2, 3, 3>{}); // 128 x 128
+        }
     }
 }
 
@@ -1240,21 +1292,22 @@ template <int EPI, int RT> static int launch_tile_rows(const GemmArgs &a, int co
 static TileChoice choose_tile(int epi, int tiles, int R, int N, int K, size_t ws_bytes) {
     const bool fused = epi == EPI_SWIGLU || epi == EPI_QKV;
     const int columns = 16 * tiles * (fused ? 2 : 1);
-    // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80, where that pads less
-    const int p80 = (R + 79) / 80 * 80, p128 = (R + 127) / 128 * 128;
-    const int bm0 = R <= 32 ? 32 : R <= 48 ? 48 : (R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
+    // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80 or, beyond 160 rows, 96, where that pads less
+    // (192 rows, us, blocks of 128 | 96: gate/up 93 | 75, QKV 59 | 50, O 25.8 | 22.7, down 51 | 43)
+    const int p80 = (R + 79) / 80 * 80, p96 = (R + 95) / 96 * 96, p128 = (R + 127) / 128 * 128;
+    const int bm0 = R <= 32 ? 32 : R <= 48 ? 48 : (R > 160 && p96 * 1.1 < std::min(p80, p128)) ? 96 : (R <= 80 || p80 * 1.1 < p128) ? 80 : 128;
     // Many rows of a short K: few such blocks leave most of the chip idle and splitting K cannot fill it (a share of less than 256 entries
     // is over before the ring is full, and the partial rows come on top), so the cost chooses the block as well.  1024 rows, a pass of
     // 2 layers, us: d_model 128 133 -> 81, 256 161 -> 115, 512 205 -> 188, 1024 428 both (the column-per-wavefront kernel 127, 147, 250, 603)
     const bool short_k = R > 512 && K <= 1024;
-    const int rows[4] = {32, 48, 80, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
+    const int rows[5] = {32, 48, 80, 96, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
     const int splits = epi == EPI_QKV ? 4 : epi == EPI_RESID ? 8 : 1;
     TileChoice best{0, 0, 1, 1e30};
     for (int bm : rows) {
-        if (bm != bm0 && !(short_k && bm < bm0)) continue;
+        if (bm != bm0 && !(short_k && bm < bm0 && bm != 96)) continue;
         for (int i = 0; i < (fused ? 3 : 2); ++i) {
             const int cols = fused ? narrow[i] : plain[i];
-            if (bm == 128 && cols == 64 && fused) continue;
+            if (bm >= 96 && cols == 64 && fused) continue;
             for (int ks = 1; ks <= splits; ++ks) {
                 if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
                 const TileChoice c = tile_cost(bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
@@ -1269,10 +1322,7 @@ template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStrea
     // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
     const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
     const TileChoice best = choose_tile(EPI, tiles, a.R, a.N, a.K, split_ok ? a.splitk_ws_bytes : 0);
-    if (best.rows == 32) return launch_tile_rows<EPI, 2>(a, columns, best, st);
-    if (best.rows == 48) return launch_tile_rows<EPI, 3>(a, columns, best, st);
-    if (best.rows == 80) return launch_tile_rows<EPI, 5>(a, columns, best, st);
-    return launch_tile_rows<EPI, 8>(a, columns, best, st);
+    return launch_tile_rows<EPI>(a, columns, best, st);
 }
 // For the tests, which have to meet every tile (not part of the library's interface): what a launch of R rows, N columns (3 * heads *
 // head_dim for EPI_QKV) and K entries takes: rows and columns of a workgroup, splits of K.
