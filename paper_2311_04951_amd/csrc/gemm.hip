@@ -204,6 +204,13 @@ template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_wai
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Waits until at most n loads are in flight, LO <= n <= HI (n is the same for the wavefront).
+template <int LO, int HI> __device__ __forceinline__ void wait_vmcnt(int n) {
+    if constexpr (LO < HI) {
+        if (n < HI) return wait_vmcnt<LO, HI - 1>(n);
+    }
+    wait_vmcnt_at_most<HI>();
+}
 // Waits until at most `loads` + FIXED loads are in flight (1 <= loads <= MOST).
 template <int FIXED, int MOST> __device__ __forceinline__ void wait_for_step(int loads) {
     if constexpr (MOST > 1) {
@@ -219,10 +226,8 @@ template <int FIXED, int MOST> __device__ __forceinline__ void wait_for_step(int
 // 16 bytes each) and the operands are read back from LDS.  Piece (plane * R + row) * UPS + (unit xor row) holds unit
 // `unit` of the row, so that the 16 rows a wave reads together fall into different banks.  Lanes of rows that do not
 // exist read a slot that holds zeros.  Measured on the 7B-shaped layer: 5-row pass 3.62 -> 3.37 ms, 1 row 3.29 -> 3.18.
-// FAR: the planes may lie more than 2^32 bytes apart (calls of more than 16 rows: max_rows apart).  A step then always brings RCAP
-// rows of each plane, the last one again past the end, so that an instruction's pieces are of one plane, whose base is uniform and
-// has 64 bits; without it the plane is part of a piece's 32-bit offset (calls of at most 16 rows pack their planes 16 rows apart).
-template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage { // RCAP: most rows (5, 8 or 16)
+// (The plane is part of a piece's 32-bit offset: calls of at most 16 rows pack their planes 16 rows apart.)
+template <typename T, int UPS, int RCAP = 16> struct ActStage { // RCAP: most rows (5, 8 or 16)
     static constexpr int PL = Traits<T>::PLANES, EPU = 16 / (int)sizeof(T);
     static constexpr int NDMA = (PL * RCAP * UPS + 63) / 64; // instructions that bring a step at RCAP rows
     static constexpr int SLOTS = NDMA * 64;                   // ... and the slots they fill
@@ -230,25 +235,21 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
     uint32_t off[NDMA]; // byte offset in the planes of this lane's piece of instruction i in the step at K = 0
     int ucol[NDMA];     // its first K element inside the step
     const char *base;
-    size_t plane_bytes;
     int rows, npiece, kmax;
-    static_assert(!FAR || RCAP * UPS % 64 == 0, "an instruction's pieces are of one plane");
 
-    // row0: first row of the tile; K: reduction length (a multiple of EPU)
-    __device__ __forceinline__ void init(const GemmArgs &a, int row0, int K, int lane) {
-        const int live = min(a.R - row0, RCAP);
-        rows = FAR ? RCAP : live;
+    // K: reduction length (a multiple of EPU)
+    __device__ __forceinline__ void init(const GemmArgs &a, int K, int lane) {
+        rows = min(a.R, RCAP);
         npiece = PL * rows * UPS;
         kmax = K - EPU;
-        plane_bytes = a.act_plane * sizeof(T);
-        base = reinterpret_cast<const char *>(reinterpret_cast<const T *>(a.act) + (size_t)row0 * a.ld_act);
+        base = reinterpret_cast<const char *>(a.act);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
             const unsigned p = min(i * 64 + lane, npiece - 1); // surplus lanes repeat the last piece into slots nobody reads
             const bool low = PL == 2 && p >= (unsigned)(rows * UPS);
             const unsigned rem = low ? p - rows * UPS : p, row = rem / UPS, pos = rem % UPS; // (UPS is a power of two)
             ucol[i] = (pos ^ (row & (UPS - 1))) * EPU;
-            off[i] = ((!FAR && low ? (uint32_t)a.act_plane : 0u) + (FAR ? min(row, live - 1u) : row) * (uint32_t)a.ld_act + ucol[i]) * (uint32_t)sizeof(T);
+            off[i] = ((low ? (uint32_t)a.act_plane : 0u) + row * (uint32_t)a.ld_act + ucol[i]) * (uint32_t)sizeof(T);
         }
     }
     __device__ __forceinline__ static void clear(unsigned char *region, int lane) {
@@ -262,12 +263,12 @@ template <typename T, int UPS, int RCAP = 16, bool FAR = false> struct ActStage 
         if (tail) {
 #pragma unroll
             for (int i = 0; i < NDMA; ++i)
-                if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)), to + i * 1024);
+                if (i * 64 < npiece) dma16(b, off[i] - (uint32_t)(max(k0 + ucol[i] - kmax, 0) * (int)sizeof(T)), to + i * 1024);
             return;
         }
 #pragma unroll
         for (int i = 0; i < NDMA; ++i)
-            if (i * 64 < npiece) dma16(FAR ? b + (i * 64 / (RCAP * UPS)) * plane_bytes : b, off[i], to + i * 1024);
+            if (i * 64 < npiece) dma16(b, off[i], to + i * 1024);
     }
     // byte offset in a step's region of row c's unit `unit` of plane pl
     __device__ __forceinline__ int operand_offset(int c, int unit, int pl) const {
@@ -325,14 +326,17 @@ __device__ __forceinline__ u32x4 w8_to_bf16x8(uint32_t a, uint32_t b) {
     return u32x4{w8_pair_to_bf16x2(a, 0), w8_pair_to_bf16x2(a, 2), w8_pair_to_bf16x2(b, 0), w8_pair_to_bf16x2(b, 2)};
 }
 
-// int4 entries as bf16: dword j of a unit holds entries 8j .. 8j + 7, entry e in bits 4e .. 4e + 3, two's complement
-__device__ __forceinline__ u32x4 w4_to_bf16x8(uint32_t x) {
+// int4 entries as bf16 values q / 16 (exact): dword j of a unit holds entries 8j .. 8j + 7, entry e in bits 4e .. 4e + 3, two's complement.  The
+// conversion instruction takes the low four bits of a byte that it selects itself and makes a sixteenth of them: 13 instructions a
+// dword (22 by shifts and integer conversions).
+__device__ __forceinline__ u32x4 w4_to_bf16x8_sixteenths(uint32_t x) {
+    uint32_t y = x >> 4;
+    asm("" : "+v"(y)); // (one shift for all odd entries, not one each)
     uint32_t r[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float f0 = (float)((int)(x << (28 - 8 * i)) >> 28); // sign-extended nibbles 2i and 2i + 1
-        const float f1 = (float)((int)(x << (24 - 8 * i)) >> 28);
-        r[i] = (f2u(f0) >> 16) | (f2u(f1) & 0xffff0000u); // |q| <= 7: exact in bf16
+        const float f0 = __builtin_amdgcn_cvt_off_f32_i4((int)(x >> (8 * i) & 0xff)), f1 = __builtin_amdgcn_cvt_off_f32_i4((int)(y >> (8 * i) & 0xff));
+        r[i] = __builtin_amdgcn_perm(f2u(f1), f2u(f0), 0x07060302u); // the low 16 bits of the fp32 are zero
     }
     return u32x4{r[0], r[1], r[2], r[3]};
 }
@@ -377,7 +381,7 @@ constexpr uint32_t W4_BIAS = 0xC1C0C308u; // -136 and -24 as a pair of bf16
 //   int4 and int8 launches were bound by vector instructions as much as by bytes (7B int4 gate/up: 387 a wavefront and step, 7.7 of its 14.5 us):
 // the nine-instruction unpacking, sums that start at the biases' share, the packed tiles and a uniform branch for the ragged last step, five
 // rows, 7B shape: 8 int4 layers 400 -> 380 us, 4 int8 layers 235 -> 228; 13B int4 at 8 rows, 3 layers 230 -> 222.
-template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP, bool FAR = false>
+template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP>
 __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     constexpr int E = Traits<T>::E, KB = 4 * E;
     constexpr int NH = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1, NT = (NH * EI + 1) / 2; // halves; 16-column tiles: the first halves' columns, then the second ones'
@@ -385,13 +389,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     constexpr int SK = QB == 4 ? 256 : QB == 8 ? 128 : 128 / (int)sizeof(T); // K entries of a step
     constexpr int PV = HL ? 1 : Traits<T>::PLANES;
     constexpr int SW = QB == 4 ? (2 * NT * 16 + 63) / 64 : 0; // int4: load instructions for a step's scales
-    typedef ActStage<T, SK * (int)sizeof(T) / 16, RCAP, FAR> Stage;
+    typedef ActStage<T, SK * (int)sizeof(T) / 16, RCAP> Stage;
     constexpr int SBASE = NH * EI * 1024, WBYTES = SBASE + SW * 256, SBYTES = WBYTES + Stage::BYTES; // (the rows that an odd EI's last tile does not have read what follows)
     __shared__ __align__(16) unsigned char lds[NW][NB][SBYTES];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int K = a.K;
-    const int rt = FAR ? blockIdx.y : 0; // (several row tiles: every one streams the weights again)
 
     // the workgroup's quads; weight rows of a column (of its first half)
     const int q0 = (int)blockIdx.x * a.quads + min((int)blockIdx.x, a.quads_rest), nq = a.quads + ((int)blockIdx.x < a.quads_rest ? 1 : 0);
@@ -457,7 +460,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     constexpr int PS = EI == 1 ? 4 : EI == 2 ? 8 : 16, EW = ((HL ? 8 : 16) * PS + 63) / 64, NSQ4 = NSQ_MAX_PARTS / 4 / PS;
     static_assert(EW <= NW && EI <= 4 && NW * NB * SBYTES <= 160 * 1024, "");
     const int er = (int)threadIdx.x / PS, ep = (int)threadIdx.x % PS; // row, column pair
-    const int m = rt * 16 + er, col = row_of(min(4 * q0 + min(2 * ep, 4 * nq - 2), (columns - 1) & ~1));
+    const int m = er, col = row_of(min(4 * q0 + min(2 * ep, 4 * nq - 2), (columns - 1) & ~1));
     const bool ends = wave < EW;
     EpiPre<2> pre;
     float wsc[NH][2], rs = 1.0f;
@@ -481,7 +484,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
             if (i == 0) { // (nothing of it stands in front of the first weights' request)
                 int l = lane;
                 asm volatile("" : "+v"(l));
-                stage.init(a, rt * 16, K, l);
+                stage.init(a, K, l);
             }
             stage.request(to + WBYTES, st * SK, tail);
         },
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
     }
 }
 
-// More than 16 rows of fp32 or quantised models (bf16 matrices: gemm_tile_kernel): the waves of a workgroup split the output columns instead
+// More than 16 rows of fp32 models (bf16 and quantised matrices: gemm_tile_kernel): the waves of a workgroup split the output columns instead
 // of K, so that all of them walk K together and share the activation rows through LDS - with R rows
 // the activations a wave needs are R*4/32 times its weight bytes, too much to fetch per wave from L2.
 //   * wave w owns the 16 (or, fused epilogues, 2 x 16) weight rows of tile blockIdx.x*NW + w and the
@@ -628,11 +631,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
 constexpr int WIDE_SLAB_BYTES = 256; // bytes of K per row, plane and slab
 
 // acc0 / acc1 += one weight chunk x one activation k-block, into two independent accumulators
-__device__ __forceinline__ void mma_split(f32x4 &acc0, f32x4 &acc1, u32x4 w, const Act<bf16_t> &b, int) {
-    const bf16x8 av = __builtin_bit_cast(bf16x8, w);
-    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b.p[0]), acc0, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b.p[1]), acc1, 0, 0, 0);
-}
 __device__ __forceinline__ void mma_split(f32x4 &acc0, f32x4 &acc1, u32x4 w, const Act<float> &b, int kb) {
     if (kb & 1) acc1 = mma(acc1, w, b);
     else acc0 = mma(acc0, w, b);
@@ -668,18 +666,8 @@ __device__ __forceinline__ size_t splitk_index(int z, int ntiles, int tile, int 
     return (((((size_t)z * ntiles + tile) * row_tiles + rt) * NT + t) * 4 + v) * 64 + lane;
 }
 
-// QB = 4: the matrix is int4 with one scale per 128 K entries and output column (bf16 planes, K a multiple of 128, a
-// multiple of 4 weight rows).  A slab is exactly one scale group and a lane's single 16-byte load holds 32 K entries =
-// its four k-blocks (dword j = entries 32g + 8j .., activations in LDS unit 4g + j): a step multiplies into fresh tiles
-// and adds them, times the group's scales of the lane's four columns (one 16-byte load, requested with the weights), to
-// the running sums.  The entries themselves are the operands (w4_to_bf16x8, by conversions): no biases to take off as in gemm_cols_kernel.
-// QB = 8 (W8): the matrix is int8 with row scales (bf16 activation planes only).  A lane's 16-byte load then holds 16 K entries,
-// two MFMA k-blocks: per slab and tile two loads instead of four, and quarter q = 2h + j of the slab multiplies bytes
-// 8j..8j+7 of load h with the activations of k = 64h + 16g + 8j .., which sit in LDS unit 8h + 2g + j of the row.
-template <typename T, int EPI, int NW, int RT, int QB = 0>
+template <typename T, int EPI, int NW, int RT>
 __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
-    constexpr bool W8 = QB == 8, W4 = QB == 4;
-    static_assert(QB == 0 || Traits<T>::E == 8, "quantised matrices go with bf16 activation planes");
     constexpr int E = Traits<T>::E, KB = 4 * E, PL = Traits<T>::PLANES;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     constexpr int WIDE_KS = WIDE_SLAB_BYTES / (int)sizeof(T); // elements of K per slab
@@ -689,9 +677,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     constexpr int BUF = PL * ROWS * WIDE_SLAB_BYTES;          // bytes of one slab buffer
     constexpr int GROUPS = PL * ROWS / 4;                     // 1 KB load instructions per slab (4 rows each)
     constexpr int DPW = (GROUPS + NW - 1) / NW;               // ... per wave
-    constexpr int WLD = W4 ? 1 : (W8 ? KBS / 2 : KBS);        // weight loads per tile and step
-    constexpr int WN = NT * WLD + (W4 ? NT : 0);              // weight (and int4 scale) loads per wave and step
-    constexpr int WE = W4 ? 32 : (W8 ? 16 : E);               // K entries per weight load
+    constexpr int WN = NT * KBS;                              // weight loads per wave and step
     __shared__ __align__(16) unsigned char slab0[BUF], slab1[BUF], slab2[BUF];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 15, g = lane >> 4;
@@ -704,16 +690,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     const bool tile_live = tile < ntiles; // a dead wave still helps with the slab copies and barriers
     const int nrows_w = (EPI == EPI_SWIGLU) ? 2 * a.N : a.N;
 
-    constexpr size_t WB2 = W4 ? 1 : (W8 ? 2 : 2 * sizeof(T)); // twice the bytes of a matrix entry (an int4 entry is half a byte)
     const char *W = reinterpret_cast<const char *>(a.W);
     const char *wrow[NT]; // byte pointers: this lane's row at its lane group's offset
-    const float *srow[NT]; // int4: the scales of the lane's four output columns in group 0
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         int n = n0[t] + c;
         if (n > nrows_w - 1) n = nrows_w - 1; // ragged last tile: load a valid row, masked at the store
-        wrow[t] = W + ((size_t)n * K + g * WE) * WB2 / 2;
-        srow[t] = W4 ? a.wscale + min(n0[t] + 4 * g, nrows_w - 4) : nullptr; // (nrows_w % 4 == 0: either all four columns exist or none)
+        wrow[t] = W + ((size_t)n * K + g * E) * sizeof(T);
     }
     const T *act = reinterpret_cast<const T *>(a.act);
     // split-K (a.ksplit > 1): workgroup z multiplies K slabs [s_lo, s_hi) only and leaves raw partial tiles
@@ -743,23 +726,19 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
         }
         asm volatile("" ::: "memory");
     };
-    auto w_load = [&](int sl, u32x4 (&w)[NT][WLD], u32x4 (&sc)[W4 ? NT : 1]) {
+    auto w_load = [&](int sl, u32x4 (&w)[NT][KBS]) {
         const int k0 = slab_at(sl) * WIDE_KS; // past the end: the last slab again (a cache hit; never multiplied)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int kb = 0; kb < WLD; ++kb) {
-                const int k = k0 + kb * 4 * WE;
-                w[t][kb] = ld16_global(wrow[t] + (size_t)min(k, K - (g + 1) * WE) * WB2 / 2); // zeroed past K when it is used
+            for (int kb = 0; kb < KBS; ++kb) {
+                const int k = k0 + kb * 4 * E;
+                w[t][kb] = ld16_global(wrow[t] + (size_t)min(k, K - (g + 1) * E) * sizeof(T)); // zeroed past K when it is used
             }
-        if constexpr (W4) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) sc[t] = ld16_global(srow[t] + (size_t)(k0 / WIDE_KS) * nrows_w);
-        }
         asm volatile("" ::: "memory");
     };
 
-    // two accumulator sets per output tile (bf16: hi and lo plane; f32: alternate k-blocks) so that
+    // two accumulator sets per output tile (alternate k-blocks) so that
     // consecutive MFMAs never wait on each other
     f32x4 acc[2][RT][NT];
 #pragma unroll
@@ -774,20 +753,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     // weights sl+2 -> registers]; buffers and register sets are compile-time choices, so the loop below is
     // unrolled over three steps and the last one or two steps of a slab count that is not a multiple of
     // three are written out after it (no idle step: the projections with K split four ways have 8 steps).
-    u32x4 wring[3][NT][WLD];
-    u32x4 sring[3][W4 ? NT : 1]; // int4: the slab's scales (four floats per tile), travelling with its weights
+    u32x4 wring[3][NT][KBS];
     slab_dma(0, slab0);
-    w_load(0, wring[0], sring[0]);
+    w_load(0, wring[0]);
     slab_dma(1, slab1);
-    w_load(1, wring[1], sring[1]);
-    auto step = [&](int sl, const unsigned char *cur, unsigned char *fill, u32x4 (&wcur)[NT][WLD], u32x4 (&wfill)[NT][WLD],
-                    u32x4 (&scur)[W4 ? NT : 1], u32x4 (&sfill)[W4 ? NT : 1]) {
+    w_load(1, wring[1]);
+    auto step = [&](int sl, const unsigned char *cur, unsigned char *fill, u32x4 (&wcur)[NT][KBS], u32x4 (&wfill)[NT][KBS]) {
         // this wave's part of slab sl and its weight slab sl have landed: the only younger loads are
         // those of the previous step (slab sl+1, weights sl+1)
         wait_vmcnt_at_most<DPW + WN>();
         wide_barrier(); // everybody's part has landed, and everybody is done reading `fill` (slab sl - 1)
         slab_dma(sl + 2, fill);
-        w_load(sl + 2, wfill, sfill);
+        w_load(sl + 2, wfill);
         const unsigned char *base = cur + (size_t)c * WIDE_SLAB_BYTES;
         // the LDS reads of k-block kb+1 are issued before the MFMAs of k-block kb (the scheduling
         // barriers keep the compiler from sinking them next to their uses, which serialises every
@@ -798,59 +775,32 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl)
                     av[r].p[pl] = *reinterpret_cast<const u32x4 *>(base + (size_t)(pl * ROWS + r * 16) * WIDE_SLAB_BYTES +
-                                                                   (((W4 ? 4 * g + kb : (W8 ? 8 * (kb >> 1) + 2 * g + (kb & 1) : kb * 4 + g)) ^ c) * 16));
+                                                                   (((kb * 4 + g) ^ c) * 16));
             __builtin_amdgcn_sched_barrier(0);
         };
         Act<T> av[2][RT];
         read_av(0, av[0]);
-        if constexpr (W4) {
-            f32x4 part[RT][NT]; // this scale group's sums
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
+        for (int kb = 0; kb < KBS; ++kb) {
+            if (kb + 1 < KBS) read_av(kb + 1, av[(kb + 1) & 1]);
+            const bool in_k = slab_at(sl) * WIDE_KS + kb * KB + g * E < k_end;
 #pragma unroll
-                for (int t = 0; t < NT; ++t) part[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < NT; ++t) {
+                const u32x4 wm = in_k ? wcur[t][kb] : zero16();
 #pragma unroll
-            for (int kb = 0; kb < KBS; ++kb) {
-                if (kb + 1 < KBS) read_av(kb + 1, av[(kb + 1) & 1]);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const u32x4 wm = w4_to_bf16x8(wcur[t][0][kb]); // a slab of a K that is a multiple of 128 lies inside K
-#pragma unroll
-                    for (int r = 0; r < RT; ++r) part[r][t] = mma(part[r][t], wm, av[kb & 1][r]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                for (int r = 0; r < RT; ++r) mma_split(acc[0][r][t], acc[1][r][t], wm, av[kb & 1][r], kb);
             }
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[0][r][t][v] += u2f(scur[t][v]) * part[r][t][v];
-        } else {
-#pragma unroll
-            for (int kb = 0; kb < KBS; ++kb) {
-                if (kb + 1 < KBS) read_av(kb + 1, av[(kb + 1) & 1]);
-                const bool in_k = slab_at(sl) * WIDE_KS + (W8 ? (kb >> 1) * 64 + g * 16 : kb * KB + g * E) < k_end;
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    u32x4 wm;
-                    if constexpr (W8) wm = in_k ? w8_to_bf16x8(wcur[t][kb >> 1][2 * (kb & 1)], wcur[t][kb >> 1][2 * (kb & 1) + 1]) : zero16();
-                    else wm = in_k ? wcur[t][kb] : zero16();
-#pragma unroll
-                    for (int r = 0; r < RT; ++r) mma_split(acc[0][r][t], acc[1][r][t], wm, av[kb & 1][r], kb);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     int s0 = 0;
     for (; s0 + 3 <= nslab; s0 += 3) {
-        step(s0, slab0, slab2, wring[0], wring[2], sring[0], sring[2]);
-        step(s0 + 1, slab1, slab0, wring[1], wring[0], sring[1], sring[0]);
-        step(s0 + 2, slab2, slab1, wring[2], wring[1], sring[2], sring[1]);
+        step(s0, slab0, slab2, wring[0], wring[2]);
+        step(s0 + 1, slab1, slab0, wring[1], wring[0]);
+        step(s0 + 2, slab2, slab1, wring[2], wring[1]);
     }
-    if (s0 < nslab) step(s0, slab0, slab2, wring[0], wring[2], sring[0], sring[2]);
-    if (s0 + 1 < nslab) step(s0 + 1, slab1, slab0, wring[1], wring[0], sring[1], sring[0]);
+    if (s0 < nslab) step(s0, slab0, slab2, wring[0], wring[2]);
+    if (s0 + 1 < nslab) step(s0 + 1, slab1, slab0, wring[1], wring[0]);
     wait_vmcnt_at_most<0>(); // nothing may still be landing in LDS when the workgroup ends
     move_lengths<EPI>(a);
     if (!tile_live) return;
@@ -863,7 +813,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 out[t][v] = acc[0][r][t][v] + acc[1][r][t][v];
-                if constexpr (W8) out[t][v] *= a.wscale[min(n0[t] + 4 * g + v, nrows_w - 1)]; // linear: also right for split-K partials
             }
         if (a.ksplit > 1) {
             if (EPI == EPI_RESID && a.splitk_rows) { // plain rows [split][R][N]: the launch that follows works row by row
@@ -910,7 +859,7 @@ __global__ __launch_bounds__(64) void gemm_splitk_finish_kernel(GemmArgs a) {
 // A residual projection (whole 16-column tiles, dense output rows) leaves its partials as plain rows, and the
 // second launch is the RMSNorm kernel with the sum over the splits in front: it completes h and, when the caller
 // named the norm that follows, writes that too (returns true then).
-template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wide(const GemmArgs &a0, int tiles, int row_tiles, hipStream_t st) {
+template <typename T, int EPI, int NW, int RT> static int launch_wide(const GemmArgs &a0, int tiles, int row_tiles, hipStream_t st) {
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     constexpr int WIDE_KS = WIDE_SLAB_BYTES / (int)sizeof(T);
     GemmArgs a = a0;
@@ -929,7 +878,7 @@ template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wid
         }
     }
     a.splitk_rows = EPI == EPI_RESID && a.ksplit > 1 && a.ksplit <= 4 && a.N % 16 == 0 && a.ldo == a.N && a.out == a.resid;
-    hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, NW, RT, QB>), dim3(gx, gy, a.ksplit), dim3(NW * 64), 0, st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, NW, RT>), dim3(gx, gy, a.ksplit), dim3(NW * 64), 0, st, a);
     if (a.splitk_rows) {
         launch_splitk_resid_norm(std::is_same<T, bf16_t>::value ? 1 : 0, a.out, a.splitk_ws, a.ksplit, a.norm_gain, a.R, a.N, a.norm_eps,
                                  a.norm_act, a.norm_act_plane, a.norm_ld, st);
@@ -939,7 +888,7 @@ template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wid
     return 0;
 }
 
-// More than 16 rows, bf16 matrices.  A workgroup multiplies BM = 16 * RTW * WR rows (two planes of activations) with 16 * CT columns;
+// More than 16 rows, bf16, int8 and int4 matrices.  A workgroup multiplies BM = 16 * RTW * WR rows (two planes of activations) with 16 * CT columns;
 // both operands of a stage (KBS k-blocks of 32 K entries) come by load-to-LDS instructions, whole 128- or 256-byte pieces of a
 // row, and are read back as operands (16-byte units of a row at position unit xor row: no bank conflicts).  The wavefronts split
 // the rows WR ways, the columns WC ways and the k-blocks of a stage WK ways (their sums meet in LDS at the end), each keeps
@@ -960,16 +909,32 @@ template <typename T, int EPI, int NW, int RT, int QB = 0> static int launch_wid
 // one another (4 -> 8 waves, 128 x 64: 34 -> 29 us; 4 -> 12, 80 x 96: 52 -> 48), not where they read the LDS twice as often.
 //   Measured (7B shape, us, before this form of it -> now; R rows, QKV and O / down with their second launches): gate/up 256 rows 109 -> 100,
 // 192 112 -> 74, 72 53.6 -> 48, 40 47.8 -> 34, 24 47 -> 31; QKV 256 rows 68 -> 58, 192 68 -> 50, 40 28 -> 27; down 192 rows 57 -> 43.
-template <int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int ABUF_, int WBUF_> struct TileCfg {
+//   A wavefront's load instructions are its share and no more (surplus ones that repeat the last: 3 - 6 % of every launch).
+//   Quantised matrices are staged as they are and converted where they are read as operands, eight entries a lane and k-block: the loads shrink
+// by what the entries do, conversions take their place.  int8: the row's scale on the finished sums.  int4: a stage is one scale
+// group; its sums start at zero, a column tile at a time, and are added times the group's scales, which come with the stage.  Against the
+// column-per-wavefront kernel, 2 layers of 7B shape, us: int8 24 rows 204 -> 165, 72 314 -> 234, 128 503 -> 324, 256 857 -> 505; int4 198 -> 181, 327 ->
+// 263, 539 -> 334, 922 -> 525 (bf16: 212, 275, 328, 485).  int4 rows are 64 bytes a stage, half a line: without the non-temporal bit (72
+// rows, gate/up, 47.0 with, 45.3 without).
+template <int QB_, int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int ABUF_, int WBUF_> struct TileCfg {
+    static constexpr int QB = QB_; // bits of a quantised matrix, 0: bf16
     static constexpr int RTW = RTW_, CTW = CTW_, WR = WR_, WC = WC_, WK = WK_, KBS = KBS_, ABUF = ABUF_, WBUF = WBUF_;
     static constexpr int NW = WR * WC * WK;         // wavefronts
     static constexpr int BM = 16 * RTW * WR;        // rows
     static constexpr int CT = CTW * WC;             // 16-column tiles
-    static constexpr int ROWB = 64 * KBS;           // bytes of a row in a stage (KBS k-blocks of 32 entries)
-    static constexpr int UPR = 4 * KBS;             // ... in 16-byte units
-    static constexpr int RPI = 64 / UPR;            // rows per load instruction
-    static constexpr int ASTAGE = 2 * BM * ROWB, WSTAGE = 16 * CT * ROWB; // a stage's two activation planes, its piece of the matrix
-    static constexpr int AG = 2 * BM / RPI, WG = 16 * CT / RPI, AL = (AG + NW - 1) / NW, WL = (WG + NW - 1) / NW; // load instructions of a wavefront and stage
+    static constexpr int ROWB = 64 * KBS, WROWB = QB ? ROWB * QB / 16 : ROWB; // bytes of a row in a stage (KBS k-blocks of 32 entries): activations, matrix
+    static constexpr int UPR = ROWB / 16, WUPR = WROWB / 16;                   // ... in 16-byte units
+    static constexpr int RPI = 64 / UPR, WRPI = 64 / WUPR;                     // rows per load instruction
+    static constexpr int SCALES = QB == 4 ? (16 * CT + 63) / 64 : 0;           // int4: load instructions (of a word per lane) for the stage's scales
+    static constexpr int ASTAGE = 2 * BM * ROWB, WBYTES = 16 * CT * WROWB, WSTAGE = WBYTES + 256 * SCALES; // a stage's two activation planes, its piece of the matrix
+    // load instructions of a stage: activations, matrix (and scales), dealt out to the wavefronts in turn; most and fewest of a wavefront
+    static constexpr int AG = 2 * BM / RPI, WG = 16 * CT / WRPI, WS = WG + SCALES;
+    static constexpr int AL = (AG + NW - 1) / NW, AMIN = AG / NW, WL = (WS + NW - 1) / NW, WMIN = WS / NW;
+    // 16-byte unit u of row r of the matrix lies at position u xor (r mod 8 or 16), with four units a row u xor (r / 2 mod 4): sixteen rows'
+    // units are in different banks
+    static __device__ __forceinline__ int swizzle(int row) { return WUPR == 4 ? (row >> 1) & 3 : row & (WUPR - 1); }
+    static_assert(QB != 4 || KBS == 4, "an int4 stage is a scale group");
+    static_assert(WUPR >= 4, "");
     static constexpr int LDS = ABUF * ASTAGE + WBUF * WSTAGE;
     static_assert(LDS <= 160 * 1024 && WBUF >= ABUF && ABUF >= 2 && WBUF <= 3, "");
 };
@@ -1000,8 +965,9 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, ABUF = C::ABUF, WBUF = C::WBUF, NW = C::NW;
+    constexpr int QB = C::QB;
     static_assert(CTW % NT == 0 && KBS % WK == 0, "");
-    constexpr bool STREAM = KBS == 4 && EPI != EPI_RESID; // (see TileCfg)
+    constexpr bool STREAM = EPI != EPI_RESID && C::WROWB >= 128; // (see TileCfg)
     __shared__ __align__(16) unsigned char lds[C::LDS];
     const uint32_t lds0 = lds_address(lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1030,10 +996,14 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     const int rot = (place.id & 7) * nst / 8; // (see TileCfg)
     auto stage_at = [&](int s) { return s_lo + rotated(s, rot, nst); };
 
-    // this wave's load instructions of a stage: group wave + i * NW; lane l brings unit (l % UPR) xor row of row l / UPR
+    // this wave's load instructions of a stage: of the activations wave + i * NW, of the matrix (int4: the scales behind it) wwave + i * NW; lane l
+    // brings unit (l % UPR) xor row of row l / UPR
+    const int wwave = wave < C::AG % NW ? wave - C::AG % NW + NW : wave - C::AG % NW; // the first ones go to those with fewer of the activations
+    const int na = C::AMIN + (wave < C::AG % NW), nw = C::WMIN + (wwave < C::WS % NW);
+    const size_t row_bytes = QB ? (size_t)K * QB / 8 : (size_t)K * 2;
     const char *abase[C::AL], *wbase[C::WL];
     uint32_t aoff[C::AL], woff[C::WL];
-    const int lr = lane / C::UPR, lu = lane % C::UPR;
+    const int lr = lane / C::UPR, lu = lane % C::UPR, wlr = lane / C::WUPR, wlu = lane % C::WUPR;
 #pragma unroll
     for (int i = 0; i < C::AL; ++i) {
         const int r0 = min(wave + i * NW, C::AG - 1) * C::RPI, row = r0 + lr, pl = r0 / C::BM, r = row - pl * C::BM;
@@ -1042,37 +1012,46 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < C::WL; ++i) {
-        const int row = min(wave + i * NW, C::WG - 1) * C::RPI, n0 = tile_col(row / 16), n = min(n0 + (row & 15) + lr, nrows_w - 1);
-        wbase[i] = reinterpret_cast<const char *>(a.W) + (size_t)n0 * K * 2;
-        woff[i] = (uint32_t)(n - n0) * (uint32_t)K * 2u + (uint32_t)(lu ^ ((row + lr) & (C::UPR - 1))) * 16u;
+        const int grp = wwave + i * NW;
+        if (QB == 4 && grp >= C::WG) {
+            const int w = min((grp - C::WG) * 64 + lane, 16 * C::CT - 1);
+            wbase[i] = reinterpret_cast<const char *>(a.wscale);
+            woff[i] = (uint32_t)min(tile_col(w / 16) + (w & 15), nrows_w - 1) * 4u;
+        } else {
+            const int row = min(grp, C::WG - 1) * C::WRPI, n0 = tile_col(row / 16), n = min(n0 + (row & 15) + wlr, nrows_w - 1);
+            wbase[i] = reinterpret_cast<const char *>(a.W) + (size_t)n0 * row_bytes;
+            woff[i] = (uint32_t)(n - n0) * (uint32_t)row_bytes + (uint32_t)(wlu ^ C::swizzle(row + wlr)) * 16u;
+        }
     }
-    const bool ragged = K % (32 * KBS) != 0;
-    // past a ragged end: units past K repeat the row's last one (their weights are zeroed when used)
-    auto beyond = [&](int st, int grp) {
-        const int row = grp * C::RPI + lr, u = lu ^ (row & (C::UPR - 1));
-        return 2u * (uint32_t)max(st * 32 * KBS + u * 8 - (K - 8), 0);
-    };
+    const bool ragged = K % (32 * KBS) != 0; // (never with int4)
     auto issue_act = [&](int s, int buf) {
         const int st = stage_at(s);
-        const uint32_t to = lds0 + buf * C::ASTAGE;
+        const uint32_t to = lds0 + buf * C::ASTAGE + wave * 1024;
         const size_t kb = (size_t)st * C::ROWB;
 #pragma unroll
-        for (int i = 0; i < C::AL; ++i) {
-            const int grp = min(wave + i * NW, C::AG - 1);
-            if (ragged && st == nst_all - 1) dma16(abase[i] + kb, aoff[i] - beyond(st, grp), to + grp * 1024);
-            else dma16(abase[i] + kb, aoff[i], to + grp * 1024);
-        }
+        for (int i = 0; i < C::AL; ++i)
+            if (i < C::AMIN || i < na) {
+                // past a ragged end: units past K repeat the row's last one (their weights are zeroed when used)
+                const int row = (wave + i * NW) * C::RPI + lr;
+                const uint32_t over = ragged && st == nst_all - 1 ? (uint32_t)max(st * C::ROWB + (lu ^ (row & (C::UPR - 1))) * 16 - (2 * K - 16), 0) : 0u;
+                dma16(abase[i] + kb, aoff[i] - over, to + i * NW * 1024);
+            }
     };
     auto issue_w = [&](int s, int buf) {
         const int st = stage_at(s);
         const uint32_t to = lds0 + ABUF * C::ASTAGE + buf * C::WSTAGE;
-        const size_t kb = (size_t)st * C::ROWB;
+        const size_t kb = (size_t)st * C::WROWB;
 #pragma unroll
-        for (int i = 0; i < C::WL; ++i) {
-            const int grp = min(wave + i * NW, C::WG - 1);
-            if (ragged && st == nst_all - 1) dma16<STREAM>(wbase[i] + kb, woff[i] - beyond(st, grp), to + grp * 1024);
-            else dma16<STREAM>(wbase[i] + kb, woff[i], to + grp * 1024);
-        }
+        for (int i = 0; i < C::WL; ++i)
+            if (i < C::WMIN || i < nw) {
+                const int grp = wwave + i * NW;
+                if (QB == 4 && grp >= C::WG) {
+                    dma4(wbase[i] + (size_t)st * nrows_w * 4, woff[i], to + C::WBYTES + (grp - C::WG) * 256);
+                } else {
+                    const uint32_t over = ragged && st == nst_all - 1 ? (uint32_t)max(st * C::WROWB + (wlu ^ C::swizzle(grp * C::WRPI + wlr)) * 16 - ((int)row_bytes - 16), 0) : 0u;
+                    dma16<STREAM>(wbase[i] + kb, woff[i] - over, to + grp * 1024);
+                }
+            }
     };
     f32x4 acc[RTW][CTW];
 #pragma unroll
@@ -1083,34 +1062,86 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     // waits for stage s: younger are only the stages requested ahead of it
     auto wait_stage = [&](int s) {
         const int wa = min(WBUF - 2, nst - 1 - s), aa = min(ABUF - 2, nst - 1 - s);
-        if (ABUF > 2 && aa > 0) wait_vmcnt_at_most<(ABUF - 2) * C::AL + (WBUF - 2) * C::WL>();
-        else if (WBUF > 2 && wa > 0) wait_vmcnt_at_most<(WBUF - 2) * C::WL>();
+        constexpr int AF = ABUF - 2, WF = WBUF - 2;
+        if (AF && aa > 0) wait_vmcnt<AF * C::AMIN + WF * C::WMIN, AF * C::AL + WF * C::WL>(AF * na + WF * nw);
+        else if (WF && wa > 0) wait_vmcnt<WF * C::WMIN, WF * C::WL>(WF * nw);
         else wait_vmcnt_at_most<0>();
     };
-    u32x4 w[CTW], b[RTW][2];
-    auto read_operands = [&](int s, int ab, int wb, int kk) { // of k-block kk of this wavefront's share of a stage
-        const int kb = wk * (KBS / WK) + kk;
-        const int un = ((4 * kb + g) ^ (c & (C::UPR - 1))) * 16; // (the xor only touches the low bits of the row, which is c's for every tile)
-        const unsigned char *ap = lds + ab * C::ASTAGE, *wp = lds + ABUF * C::ASTAGE + wb * C::WSTAGE;
-#pragma unroll
-        for (int t = 0; t < CTW; ++t) w[t] = *reinterpret_cast<const u32x4 *>(wp + ((wc * CTW + t) * 16 + c) * C::ROWB + un);
+    // Which K entries lane (c, g) supplies to k-block kb of a stage is free as long as both operands agree.  bf16: unit 4 kb + g of a row.  int8:
+    // half kb % 2 of unit 4 (kb / 2) + g of the matrix, 8 entries, unit 8 (kb / 2) + 2g + kb % 2 of the activations.  int4: dword kb of
+    // unit g, 8 entries, unit 4g + kb.
+    auto act_unit = [&](int kb) { return QB == 4 ? 4 * g + kb : QB == 8 ? 8 * (kb >> 1) + 2 * g + (kb & 1) : 4 * kb + g; };
+    auto read_act = [&](int ab, int kb, u32x4 (&b)[RTW][2]) {
+        const int un = (act_unit(kb) ^ (c & (C::UPR - 1))) * 16; // (the xor only touches the low bits of the row, which is c's for every tile)
+        const unsigned char *ap = lds + ab * C::ASTAGE;
 #pragma unroll
         for (int r = 0; r < RTW; ++r)
 #pragma unroll
             for (int pl = 0; pl < 2; ++pl) b[r][pl] = *reinterpret_cast<const u32x4 *>(ap + (pl * C::BM + (wr * RTW + r) * 16 + c) * C::ROWB + un);
-        if (ragged && stage_at(s) == nst_all - 1 && (nst_all - 1) * 32 * KBS + kb * 32 + g * 8 >= K) {
-#pragma unroll
-            for (int t = 0; t < CTW; ++t) w[t] = zero16();
-        }
     };
-    auto multiply = [&] {
+    auto mma1 = [&](f32x4 s, u32x4 w, u32x4 b) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, b), s, 0, 0, 0); };
+    auto compute = [&](int s, int ab, int wb) {
+        constexpr int KK = KBS / WK; // k-blocks of this wavefront
+        const unsigned char *wp = lds + ABUF * C::ASTAGE + wb * C::WSTAGE;
+        if constexpr (QB == 4) {
+            // the stage is one scale group: its sums, a column tile at a time, times the scales of the lane's four columns
+            typedef uint32_t dwords __attribute__((ext_vector_type(KK)));
+            u32x4 b[KK][RTW][2];
 #pragma unroll
-        for (int pl = 0; pl < 2; ++pl)
+            for (int kk = 0; kk < KK; ++kk) read_act(ab, wk * KK + kk, b[kk]);
 #pragma unroll
-            for (int r = 0; r < RTW; ++r)
+            for (int t = 0; t < CTW; ++t) {
+                const int tile = wc * CTW + t;
+                const dwords q = *reinterpret_cast<const dwords *>(wp + (tile * 16 + c) * C::WROWB + (g ^ C::swizzle(c)) * 16 + 4 * wk * KK);
+                const f32x4 sc = *reinterpret_cast<const f32x4 *>(wp + C::WBYTES + (tile * 16 + 4 * g) * 4);
+                f32x4 part[RTW];
 #pragma unroll
-                for (int t = 0; t < CTW; ++t)
-                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]), __builtin_bit_cast(bf16x8, b[r][pl]), acc[r][t], 0, 0, 0);
+                for (int r = 0; r < RTW; ++r) part[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    const u32x4 w = w4_to_bf16x8_sixteenths(q[kk]);
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                        for (int r = 0; r < RTW; ++r) part[r] = mma1(part[r], w, b[kk][r][pl]);
+                }
+#pragma unroll
+                for (int r = 0; r < RTW; ++r)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[r][t][v] += sc[v] * part[r][v];
+            }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const int kb = wk * KK + kk;
+                u32x4 w[CTW], b[RTW][2];
+                uint2 q[CTW];
+#pragma unroll
+                for (int t = 0; t < CTW; ++t) {
+                    const unsigned char *row = wp + ((wc * CTW + t) * 16 + c) * C::WROWB;
+                    if constexpr (QB == 8) q[t] = *reinterpret_cast<const uint2 *>(row + ((4 * (kb >> 1) + g) ^ C::swizzle(c)) * 16 + 8 * (kb & 1));
+                    else w[t] = *reinterpret_cast<const u32x4 *>(row + ((4 * kb + g) ^ C::swizzle(c)) * 16);
+                }
+                read_act(ab, kb, b);
+                if (ragged && stage_at(s) == nst_all - 1 && (nst_all - 1) * 32 * KBS + act_unit(kb) * 8 >= K) {
+#pragma unroll
+                    for (int t = 0; t < CTW; ++t) {
+                        if constexpr (QB == 8) q[t] = make_uint2(0u, 0u);
+                        else w[t] = zero16();
+                    }
+                }
+                if constexpr (QB == 8) {
+#pragma unroll
+                    for (int t = 0; t < CTW; ++t) w[t] = w8_to_bf16x8(q[t].x, q[t].y);
+                }
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+                        for (int t = 0; t < CTW; ++t) acc[r][t] = mma1(acc[r][t], w[t], b[r][pl]);
+            }
+        }
     };
 #pragma unroll
     for (int s = 0; s < WBUF - 1; ++s) {
@@ -1122,22 +1153,30 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
         stage_barrier(); // everybody's part of the stage has landed, and everybody is done reading the ones that are filled next
         if (s + ABUF - 1 < nst) issue_act(s + ABUF - 1, ab == 0 ? ABUF - 1 : ab - 1);
         if (s + WBUF - 1 < nst) issue_w(s + WBUF - 1, wb == 0 ? WBUF - 1 : wb - 1);
-#pragma unroll
-        for (int kk = 0; kk < KBS / WK; ++kk) {
-            read_operands(s, ab, wb, kk);
-            multiply();
-        }
+        compute(s, ab, wb);
         ab = ab == ABUF - 1 ? 0 : ab + 1;
         wb = wb == WBUF - 1 ? 0 : wb + 1;
     }
 
     auto finish = [&](float (&out)[NT][4], int r, int p) { // row tile r and column tile (pair) p of the workgroup
+        if constexpr (QB == 4) { // (the entries were sixteenths)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[t][v] *= 16.0f;
+        }
         const int ct = p * NT;
         if (place.x * (C::CT / NT) + p >= npairs) return;
         int n0[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) n0[t] = tile_col(ct + t);
         const int m = row0 + r * 16 + c;
+        if constexpr (QB == 8) { // (linear: also right for partial sums)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[t][v] *= a.wscale[min(n0[t] + 4 * g + v, nrows_w - 1)];
+        }
         if ((EPI == EPI_RESID || EPI == EPI_QKV) && a.ksplit > 1) { // plain rows [split][R][N]: the launch that follows works row by row
             if (m < a.R) {
 #pragma unroll
@@ -1223,18 +1262,19 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(GemmArgs a) {
 // 96 would be 1.2 us faster).  A: 9 in stages of 128 bytes a row, 13.5 in stages of 256 with three of them in LDS, 15 with two.  W: 31 in
 // stages of 256 bytes, 26 in blocks of 128 rows with up to 96 columns, 29 for 128 columns, 32.5 for 192, 34.5 with several row blocks.  A
 // split adds its partial rows, written and read once (8 MB/us), 0.16 us of the second launch and for QKV that launch (4.5 us; a residual
-// projection's is the RMSNorm that follows anyway).
+// projection's is the RMSNorm that follows anyway).  Quantised matrices (bits < 16), where conversions and MFMAs weigh more than the bytes, take
+// 2 ns (int4: 3) and 0.81 ps (0.875) an output for every K entry: seven tiles of a 4096 x 22016 matrix within 10 %.
 struct TileChoice {
     int rows, cols, ksplit;
     double us;
 };
-static TileChoice tile_cost(int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
+static TileChoice tile_cost(int bits, int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
     const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols, wgs = gx * gy * ksplit;
     const int rounds = (wgs + 255) / 256;
     const bool long_stage = cols <= 96 && bm <= 96; // 256 bytes of a row
     const double act = !long_stage ? 9e-6 : bm <= 48 ? 13.5e-6 : 15e-6;
     const double mat = long_stage ? 31e-6 : cols <= 96 ? 26e-6 : cols == 128 ? 29e-6 : gy > 1 ? 34.5e-6 : 32.5e-6;
-    const double per = bm * 4 * act + cols * 2 * mat;
+    const double per = bits == 16 ? bm * 4 * act + cols * 2 * mat : bits == 8 ? 2.0e-3 + 8.1e-7 * bm * cols : 3.0e-3 + 8.75e-7 * bm * cols;
     return TileChoice{bm, cols, ksplit, rounds * (1.1 + (double)((K + ksplit - 1) / ksplit) * per) + 0.003 * wgs +
                                             (ksplit > 1 ? launch_us + 0.16 * ksplit + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
 }
@@ -1254,42 +1294,75 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     return a.norm_gain != nullptr ? 1 : 0;
 }
 
-template <int EPI> static int launch_tile_rows(const GemmArgs &a, int columns, const TileChoice &c, hipStream_t st) {
+template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, int columns, const TileChoice &c, hipStream_t st) {
     auto go = [&](auto cfg) { return launch_tile_as<EPI, decltype(cfg)>(a, columns, c.ksplit, st); };
-    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-        switch (c.rows * 1000 + c.cols) {
-        case 32064: return go(TileCfg<2, 4, 1, 1, 4, 4, 3, 3>{});
-        case 32096: return go(TileCfg<2, 6, 1, 1, 4, 4, 3, 3>{});
-        case 32192: return go(TileCfg<2, 6, 1, 2, 2, 2, 3, 3>{});
-        case 48064: return go(TileCfg<3, 4, 1, 1, 4, 4, 3, 3>{});
-        case 48096: return go(TileCfg<3, 6, 1, 1, 4, 4, 3, 3>{});
-        case 48192: return go(TileCfg<3, 6, 1, 2, 2, 2, 3, 3>{});
-        case 80064: return go(TileCfg<5, 2, 1, 2, 4, 4, 2, 3>{});
-        case 80096: return go(TileCfg<5, 2, 1, 3, 4, 4, 2, 3>{});
-        case 80192: return go(TileCfg<5, 6, 1, 2, 2, 2, 3, 3>{});
-        case 96096: return go(TileCfg<3, 6, 2, 1, 4, 4, 2, 2>{});
-        case 96192: return go(TileCfg<3, 6, 2, 2, 2, 2, 3, 3>{});
-        case 128096: return go(TileCfg<2, 6, 4, 1, 2, 2, 3, 3>{});
-        default: return go(TileCfg<4, 6, 2, 2, 2, 2, 2, 3>{}); // 128 x 192
+    constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV;
+    const int tile = c.rows * 1000 + c.cols;
+    if constexpr (QB != 0 && FUSED) {
+        switch (tile) {
+        case 32096: return go(TileCfg<QB, 2, 2, 1, 3, 4, 4, 3, 3>{});
+        case 48096: return go(TileCfg<QB, 3, 2, 1, 3, 4, 4, 3, 3>{});
+        case 80096: return go(TileCfg<QB, 5, 2, 1, 3, 4, 4, 3, 3>{});
+        case 96096:
+            if constexpr (QB == 4) return go(TileCfg<4, 3, 2, 2, 3, 2, 4, 2, 3>{});
+            else return go(TileCfg<8, 3, 6, 2, 1, 4, 4, 2, 3>{});
+        case 96192: return go(TileCfg<QB, 3, 6, 2, 2, 2, 4, 2, QB == 4 ? 3 : 2>{});
+        case 128096: return go(TileCfg<QB, 4, 2, 2, 3, 2, 4, 2, QB == 4 ? 3 : 2>{});
+        default: // 128 x 192
+            if constexpr (QB == 4) return go(TileCfg<4, 4, 6, 2, 2, 2, 4, 2, 2>{});
+            else return go(TileCfg<8, 4, 6, 2, 2, 2, 2, 2, 3>{});
+        }
+    } else if constexpr (QB != 0) {
+        switch (tile) {
+        case 32064: return go(TileCfg<QB, 2, 2, 1, 2, 4, 4, 3, 3>{});
+        case 32128: return go(TileCfg<QB, 2, 2, 1, 4, 2, 4, 3, 3>{});
+        case 48064: return go(TileCfg<QB, 3, 2, 1, 2, 4, 4, 3, 3>{});
+        case 48128: return go(TileCfg<QB, 3, 2, 1, 4, 2, 4, 3, 3>{});
+        case 80064: return go(TileCfg<QB, 5, 2, 1, 2, 4, 4, 3, 3>{});
+        case 80128: return go(TileCfg<QB, 5, 2, 1, 4, 2, 4, 2, 3>{});
+        case 96128: return go(TileCfg<QB, 3, 4, 2, 2, 2, 4, 2, QB == 4 ? 3 : 2>{});
+        default: // 128 x 128
+            if constexpr (QB == 4) return go(TileCfg<4, 4, 4, 2, 2, 2, 4, 2, 2>{});
+            else return go(TileCfg<8, 4, 4, 2, 2, 2, 2, 3, 3>{});
+        }
+    } else if constexpr (FUSED) {
+        switch (tile) {
+        case 32064: return go(TileCfg<0, 2, 4, 1, 1, 4, 4, 3, 3>{});
+        case 32096: return go(TileCfg<0, 2, 6, 1, 1, 4, 4, 3, 3>{});
+        case 32192: return go(TileCfg<0, 2, 6, 1, 2, 2, 2, 3, 3>{});
+        case 48064: return go(TileCfg<0, 3, 4, 1, 1, 4, 4, 3, 3>{});
+        case 48096: return go(TileCfg<0, 3, 6, 1, 1, 4, 4, 3, 3>{});
+        case 48192: return go(TileCfg<0, 3, 6, 1, 2, 2, 2, 3, 3>{});
+        case 80064: return go(TileCfg<0, 5, 2, 1, 2, 4, 4, 2, 3>{});
+        case 80096: return go(TileCfg<0, 5, 2, 1, 3, 4, 4, 2, 3>{});
+        case 80192: return go(TileCfg<0, 5, 6, 1, 2, 2, 2, 3, 3>{});
+        case 96096: return go(TileCfg<0, 3, 6, 2, 1, 4, 4, 2, 2>{});
+        case 96192: return go(TileCfg<0, 3, 6, 2, 2, 2, 2, 3, 3>{});
+        case 128096: return go(TileCfg<0, 2, 6, 4, 1, 2, 2, 3, 3>{});
+        default: return go(TileCfg<0, 4, 6, 2, 2, 2, 2, 2, 3>{}); // 128 x 192
         }
     } else {
-        switch (c.rows * 1000 + c.cols) {
-        case 32064: return go(TileCfg<2, 2, 1, 2, 4, 4, 3, 3>{});
-        case 32128: return go(TileCfg<2, 2, 1, 4, 2, 2, 3, 3>{});
-        case 48064: return go(TileCfg<3, 2, 1, 2, 4, 4, 3, 3>{});
-        case 48128: return go(TileCfg<3, 2, 1, 4, 2, 2, 3, 3>{});
-        case 80064: return go(TileCfg<5, 2, 1, 2, 4, 4, 2, 3>{});
-        case 80128: return go(TileCfg<5, 2, 1, 4, 2, 2, 3, 3>{});
-        case 96064: return go(TileCfg<3, 2, 2, 2, 2, 4, 2, 3>{});
-        case 96128: return go(TileCfg<3, 4, 2, 2, 2, 2, 3, 3>{});
-        case 128064: return go(TileCfg<2, 4, 4, 1, 2, 2, 3, 3>{});
-        default: return go(TileCfg<4, 4, 2, 2, 2, 2, 3, 3>{}); // 128 x 128
+        switch (tile) {
+        case 32064: return go(TileCfg<0, 2, 2, 1, 2, 4, 4, 3, 3>{});
+        case 32128: // (heads: 24 rows x 32000 columns 55 us in stages of 128 bytes, 48 of 256; K split eight ways: 22.2 both)
+            if constexpr (EPI == EPI_STORE) return go(TileCfg<0, 2, 2, 1, 4, 2, 4, 2, 3>{});
+            else return go(TileCfg<0, 2, 2, 1, 4, 2, 2, 3, 3>{});
+        case 48064: return go(TileCfg<0, 3, 2, 1, 2, 4, 4, 3, 3>{});
+        case 48128:
+            if constexpr (EPI == EPI_STORE) return go(TileCfg<0, 3, 2, 1, 4, 2, 4, 2, 3>{});
+            else return go(TileCfg<0, 3, 2, 1, 4, 2, 2, 3, 3>{});
+        case 80064: return go(TileCfg<0, 5, 2, 1, 2, 4, 4, 2, 3>{});
+        case 80128: return go(TileCfg<0, 5, 2, 1, 4, 2, 2, 3, 3>{});
+        case 96064: return go(TileCfg<0, 3, 2, 2, 2, 2, 4, 2, 3>{});
+        case 96128: return go(TileCfg<0, 3, 4, 2, 2, 2, 2, 3, 3>{});
+        case 128064: return go(TileCfg<0, 2, 4, 4, 1, 2, 2, 3, 3>{});
+        default: return go(TileCfg<0, 4, 4, 2, 2, 2, 2, 3, 3>{}); // 128 x 128
         }
     }
 }
 
 // tiles: 16-column tiles (pairs of them for the fused epilogues); ws_bytes: room for partial rows (0: K is not split)
-static TileChoice choose_tile(int epi, int tiles, int R, int N, int K, size_t ws_bytes) {
+static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K, size_t ws_bytes) {
     const bool fused = epi == EPI_SWIGLU || epi == EPI_QKV;
     const int columns = 16 * tiles * (fused ? 2 : 1);
     // rows per workgroup: 32, 48, 80 where that is all of them, else blocks of 128 - or of 80 or, beyond 160 rows, 96, where that pads less
@@ -1300,38 +1373,40 @@ static TileChoice choose_tile(int epi, int tiles, int R, int N, int K, size_t ws
     // is over before the ring is full, and the partial rows come on top), so the cost chooses the block as well.  1024 rows, a pass of
     // 2 layers, us: d_model 128 133 -> 81, 256 161 -> 115, 512 205 -> 188, 1024 428 both (the column-per-wavefront kernel 127, 147, 250, 603)
     const bool short_k = R > 512 && K <= 1024;
+    // Quantised matrices: 96 where that is all of them, beyond it the cost chooses among blocks of 80, 96 and 128
+    const int q0 = R <= 32 ? 32 : R <= 48 ? 48 : R <= 80 ? 80 : 96, q1 = R <= 96 ? q0 : 128;
     const int rows[5] = {32, 48, 80, 96, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
     const int splits = epi == EPI_QKV ? 4 : epi == EPI_RESID ? 8 : 1;
     TileChoice best{0, 0, 1, 1e30};
     for (int bm : rows) {
-        if (bm != bm0 && !(short_k && bm < bm0 && bm != 96)) continue;
+        if (bits == 16 ? bm != bm0 && !(short_k && bm < bm0 && bm != 96) : bm > q1 || (bm < std::min(q0, 80) && !short_k)) continue;
         for (int i = 0; i < (fused ? 3 : 2); ++i) {
             const int cols = fused ? narrow[i] : plain[i];
-            if (bm >= 96 && cols == 64 && fused) continue;
+            if (bm >= 96 && cols == 64 && (fused || bits < 16)) continue;
+            if (bits < 16 && fused && bm <= 80 && cols != 96) continue;
             for (int ks = 1; ks <= splits; ++ks) {
                 if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
-                const TileChoice c = tile_cost(bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
+                const TileChoice c = tile_cost(bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
                 if (c.us < best.us) best = c;
             }
         }
     }
     return best;
 }
-template <int EPI> static int launch_tile(const GemmArgs &a, int tiles, hipStream_t st) {
+template <int EPI, int QB> static int launch_tile(const GemmArgs &a, int tiles, hipStream_t st) {
     const int columns = 16 * tiles * (EPI == EPI_SWIGLU || EPI == EPI_QKV ? 2 : 1);
     // partial rows need whole 16-column tiles, room in the workspace and, for a residual, dense output rows
     const bool split_ok = a.splitk_ws && a.N % 16 == 0 && (EPI == EPI_QKV || (EPI == EPI_RESID && a.ldo == a.N && a.out == a.resid));
-    const TileChoice best = choose_tile(EPI, tiles, a.R, a.N, a.K, split_ok ? a.splitk_ws_bytes : 0);
-    return launch_tile_rows<EPI>(a, columns, best, st);
+    const TileChoice best = choose_tile(EPI, QB ? QB : 16, tiles, a.R, a.N, a.K, split_ok ? a.splitk_ws_bytes : 0);
+    return launch_tile_as_chosen<EPI, QB>(a, columns, best, st);
 }
 // For the tests, which have to meet every tile (not part of the library's interface): what a launch of R rows, N columns (3 * heads *
 // head_dim for EPI_QKV) and K entries takes: rows and columns of a workgroup, splits of K.
-extern "C" void ss_dev_gemm_tile(int epi, int R, int N, int K, size_t ws_bytes, int *out3) {
-    const TileChoice c = choose_tile(epi, epi == EPI_QKV ? N / 32 : (N + 15) / 16, R, N, K, N % 16 == 0 ? ws_bytes : 0);
+extern "C" void ss_dev_gemm_tile_bits(int bits, int epi, int R, int N, int K, size_t ws_bytes, int *out3) { // bits 16, 8 or 4
+    const TileChoice c = choose_tile(epi, bits, epi == EPI_QKV ? N / 32 : (N + 15) / 16, R, N, K, N % 16 == 0 ? ws_bytes : 0);
     out3[0] = c.rows; out3[1] = c.cols; out3[2] = c.ksplit;
 }
-
-template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st);
+extern "C" void ss_dev_gemm_tile(int epi, int R, int N, int K, size_t ws_bytes, int *out3) { ss_dev_gemm_tile_bits(16, epi, R, N, K, ws_bytes, out3); }
 
 // Calls of at most 16 rows.  The output columns in quads (of pairs for the fused epilogues) over k workgroups per compute unit of at
 // most eight quads, every one with the same number or one more: the smallest k - except that up to 8 rows a k that makes a tenth fewer
@@ -1363,11 +1438,11 @@ extern "C" void ss_dev_gemm_share(int epi, int R, int N, int *out3) {
     const ColumnSplit s = split_columns(epi, N, R);
     out3[0] = s.groups; out3[1] = s.quads; out3[2] = s.rest;
 }
-template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP, bool FAR = false>
+template <typename T, int QB, int EPI, int NW, int NB, int EI, int RCAP>
 static void launch_cols_as(const GemmArgs &a0, const ColumnSplit &s, hipStream_t st) {
     GemmArgs a = a0;
     a.quads = s.quads; a.quads_rest = s.rest; a.nsq_parts = s.groups;
-    hipLaunchKernelGGL((gemm_cols_kernel<T, QB, EPI, NW, NB, EI, RCAP, FAR>), dim3(s.groups, FAR ? (a.R + 15) / 16 : 1), dim3(NW * 64), 0, st, a);
+    hipLaunchKernelGGL((gemm_cols_kernel<T, QB, EPI, NW, NB, EI, RCAP>), dim3(s.groups), dim3(NW * 64), 0, st, a);
 }
 // Wavefronts and buffers, from all of (2 .. 16 waves) x (1, 2 buffers) on the matrices of four decoder widths (2048 - 5120) at 1, 5, 12 and 16
 // rows, within 3 % of the best for each: 60 - 90 KB asked for per compute unit (a unit has some 32 KB in flight; more only delays what
@@ -1425,25 +1500,17 @@ template <typename T, int QB, int EPI> static int launch_cols(const GemmArgs &a,
     return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
 }
 
-template <typename T, int EPI> static int launch_gemm_t(const GemmArgs &a, hipStream_t st) {
-    const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles <= 1) return launch_cols<T, 0, EPI>(a, st);
-    const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
-    if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI>(a, tiles, st);
-    else return launch_wide_any<T, EPI, 0>(a, tiles, row_tiles, st);
-}
-
-template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
+template <typename T, int EPI> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
     // larger batches and prefill chunks: waves split the columns; fewer waves per workgroup when the
     // matrix has few tiles, so that the launch still covers the chip
     constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV; // two weight tiles per wave: more registers
     const bool small = tiles < 8 * 128;
     if (row_tiles <= 2) {
-        if (small) return launch_wide<T, EPI, 4, 2, QB>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 8, 2, QB>(a, tiles, row_tiles, st);
+        if (small) return launch_wide<T, EPI, 4, 2>(a, tiles, row_tiles, st);
+        return launch_wide<T, EPI, 8, 2>(a, tiles, row_tiles, st);
     } else if (row_tiles <= 3) {
-        if (small) return launch_wide<T, EPI, 4, 3, QB>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 8, 3, QB>(a, tiles, row_tiles, st);
+        if (small) return launch_wide<T, EPI, 4, 3>(a, tiles, row_tiles, st);
+        return launch_wide<T, EPI, 8, 3>(a, tiles, row_tiles, st);
     } else {
         // one workgroup per compute unit fits: 3 waves per workgroup when that fills more of a 256-unit chip
         // in whole rounds than 4 (688 gate/up tiles: 230 workgroups instead of 172; 384 QKV tiles: 128, split in two)
@@ -1453,53 +1520,30 @@ template <typename T, int EPI, int QB> static int launch_wide_any(const GemmArgs
             return (double)(wgs * ks) / (double)((wgs * ks + 255) / 256 * 256);
         };
         if constexpr (!FUSED) {
-            if (!small) return launch_wide<T, EPI, 8, 5, QB>(a, tiles, row_tiles, st);
+            if (!small) return launch_wide<T, EPI, 8, 5>(a, tiles, row_tiles, st);
         }
-        if (fill(3) > fill(4) + 0.1) return launch_wide<T, EPI, 3, 5, QB>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 4, 5, QB>(a, tiles, row_tiles, st);
+        if (fill(3) > fill(4) + 0.1) return launch_wide<T, EPI, 3, 5>(a, tiles, row_tiles, st);
+        return launch_wide<T, EPI, 4, 5>(a, tiles, row_tiles, st);
     }
 }
 
-template <int EPI> static int launch_gemm_w8(const GemmArgs &a, hipStream_t st) {
+template <typename T, int QB, int EPI> static int launch_gemm_t(const GemmArgs &a, hipStream_t st) {
     const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles <= 1) return launch_cols<bf16_t, 8, EPI>(a, st);
-    return launch_wide_any<bf16_t, EPI, 8>(a, EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16, row_tiles, st);
-}
-
-template <int EPI> static int launch_gemm_w4(const GemmArgs &a, hipStream_t st) {
-    const int row_tiles = (a.R + 15) / 16;
-    if (row_tiles <= 1) return launch_cols<bf16_t, 4, EPI>(a, st);
-    const int nrows_w = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
-    // more than 16 rows: the wide kernel (it reads a lane's four scales as one 16-byte load); with a weight row count that is not
-    // a multiple of 4 or unaligned scales, one workgroup per (16 columns, row tile)
-    if (nrows_w % 4 == 0 && (reinterpret_cast<uintptr_t>(a.wscale) & 15) == 0) return launch_wide_any<bf16_t, EPI, 4>(a, EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16, row_tiles, st);
-    const int quads = EPI == EPI_QKV ? a.N / 8 : (a.N + 3) / 4, groups = (quads + 3) / 4;
-    launch_cols_as<bf16_t, 4, EPI, EPI == EPI_RESID ? 8 : 4, 1, 2, 16, true>(a, ColumnSplit{groups, quads / groups, quads % groups}, st);
-    return 0;
+    if (row_tiles <= 1) return launch_cols<T, QB, EPI>(a, st);
+    const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
+    if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI, QB>(a, tiles, st);
+    else return launch_wide_any<T, EPI>(a, tiles, row_tiles, st);
 }
 
 int launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t st) {
-    if (a.wscale && a.wbits == 4) { // int4 weights: the caller has checked bf16 planes and K % 128 == 0
-        switch (epi) {
-        case EPI_STORE: return launch_gemm_w4<EPI_STORE>(a, st);
-        case EPI_RESID: return launch_gemm_w4<EPI_RESID>(a, st);
-        case EPI_SWIGLU: return launch_gemm_w4<EPI_SWIGLU>(a, st);
-        case EPI_QKV: return launch_gemm_w4<EPI_QKV>(a, st);
-        }
-        return 0;
-    }
-    if (a.wscale) { // int8 weights: the caller has checked bf16 planes and K % 16 == 0
-        switch (epi) {
-        case EPI_STORE: return launch_gemm_w8<EPI_STORE>(a, st);
-        case EPI_RESID: return launch_gemm_w8<EPI_RESID>(a, st);
-        case EPI_SWIGLU: return launch_gemm_w8<EPI_SWIGLU>(a, st);
-        case EPI_QKV: return launch_gemm_w8<EPI_QKV>(a, st);
-        }
-        return 0;
-    }
-#define SS_CASE(EP)                                                  \
-    case EP:                                                         \
-        return dtype ? launch_gemm_t<bf16_t, EP>(a, st) : launch_gemm_t<float, EP>(a, st);
+    // quantised weights: the caller has checked bf16 planes and K % 128 == 0 (int4) or K % 16 == 0 (int8)
+    const int kind = a.wscale ? a.wbits : dtype ? 16 : 32;
+#define SS_CASE(EP)                                              \
+    case EP:                                                     \
+        return kind == 4   ? launch_gemm_t<bf16_t, 4, EP>(a, st)   \
+               : kind == 8  ? launch_gemm_t<bf16_t, 8, EP>(a, st)  \
+               : kind == 16 ? launch_gemm_t<bf16_t, 0, EP>(a, st)  \
+                            : launch_gemm_t<float, 0, EP>(a, st);
     switch (epi) {
         SS_CASE(EPI_STORE)
         SS_CASE(EPI_RESID)
