@@ -898,8 +898,7 @@ template <typename T, int EPI, int NW, int RT> static int launch_wide(const Gemm
 // of 22016 columns, the kernel 48.  They got there by
 //   - a ring of ABUF stages of activations and WBUF of the matrix, the matrix's one stage deeper where LDS does not hold three of both (loads
 //     alone, one | two stages ahead: 45 | 37 us), asked for in that order, so that the counted wait leaves the younger ones in flight;
-//   - 256 bytes of a row at a time where LDS allows (128: 40 us) and the non-temporal bit on those matrix requests (37.4 -> 34.7; not for
-//     the residual projections, whose short splits lose by it: 4096 x 4096, 72 rows, 16.3 -> 17.5);
+//   - 256 bytes of a row at a time where LDS allows (128: 40 us) and the non-temporal bit on requests of large matrices (37.4 -> 34.7);
 //   - a start in K that depends on the XCD: its workgroups walk K together and find each other's activations in their L2, the eight XCDs
 //     ask different memory channels (no rotation 38 us, every workgroup its own 35.4; 256 rows, where the activations fill an L2: 71, 99, 67);
 //   - row blocks of the same columns on one XCD, next to one another in time (tile_place): weights of two blocks from memory once (52 -> 37 us).
@@ -914,8 +913,7 @@ template <typename T, int EPI, int NW, int RT> static int launch_wide(const Gemm
 // by what the entries do, conversions take their place.  int8: the row's scale on the finished sums.  int4: a stage is one scale
 // group; its sums start at zero, a column tile at a time, and are added times the group's scales, which come with the stage.  Against the
 // column-per-wavefront kernel, 2 layers of 7B shape, us: int8 24 rows 204 -> 165, 72 314 -> 234, 128 503 -> 324, 256 857 -> 505; int4 198 -> 181, 327 ->
-// 263, 539 -> 334, 922 -> 525 (bf16: 212, 275, 328, 485).  int4 rows are 64 bytes a stage, half a line: without the non-temporal bit (72
-// rows, gate/up, 47.0 with, 45.3 without).
+// 263, 539 -> 334, 922 -> 525 (bf16: 212, 275, 328, 485).
 template <int QB_, int RTW_, int CTW_, int WR_, int WC_, int WK_, int KBS_, int ABUF_, int WBUF_> struct TileCfg {
     static constexpr int QB = QB_; // bits of a quantised matrix, 0: bf16
     static constexpr int RTW = RTW_, CTW = CTW_, WR = WR_, WC = WC_, WK = WK_, KBS = KBS_, ABUF = ABUF_, WBUF = WBUF_;
@@ -951,6 +949,7 @@ struct TilePlace {
     int x, y, id; // column share, row block, number in launch order (of a split)
 };
 __device__ __forceinline__ TilePlace tile_place() {
+    if (gridDim.y == 1) return TilePlace{(int)blockIdx.x, 0, (int)blockIdx.x}; // (no divisions in front of the first load)
     const int gx = gridDim.x, gy = gridDim.y, id = blockIdx.x + gx * blockIdx.y, whole = (gx & ~7) * gy;
     if (id >= whole) {
         const int rest = id - whole, w = gx & 7;
@@ -967,7 +966,6 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
     constexpr int RTW = C::RTW, CTW = C::CTW, WK = C::WK, KBS = C::KBS, ABUF = C::ABUF, WBUF = C::WBUF, NW = C::NW;
     constexpr int QB = C::QB;
     static_assert(CTW % NT == 0 && KBS % WK == 0, "");
-    constexpr bool STREAM = EPI != EPI_RESID && C::WROWB >= 128; // (see TileCfg)
     __shared__ __align__(16) unsigned char lds[C::LDS];
     const uint32_t lds0 = lds_address(lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1049,7 +1047,8 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
                     dma4(wbase[i] + (size_t)st * nrows_w * 4, woff[i], to + C::WBYTES + (grp - C::WG) * 256);
                 } else {
                     const uint32_t over = ragged && st == nst_all - 1 ? (uint32_t)max(st * C::WROWB + (wlu ^ C::swizzle(grp * C::WRPI + wlr)) * 16 - ((int)row_bytes - 16), 0) : 0u;
-                    dma16<STREAM>(wbase[i] + kb, woff[i] - over, to + grp * 1024);
+                    if (a.stream) dma16<true>(wbase[i] + kb, woff[i] - over, to + grp * 1024);
+                    else dma16(wbase[i] + kb, woff[i] - over, to + grp * 1024);
                 }
             }
     };
@@ -1284,6 +1283,11 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     const int nst = (a.K + 32 * C::KBS - 1) / (32 * C::KBS);
     a.kslabs = (nst + ksplit - 1) / ksplit;
     a.ksplit = (nst + a.kslabs - 1) / a.kslabs; // no empty split
+    // The non-temporal bit on the matrix's requests: for one that fills most of the 256 MB memory-side cache by itself and is gone from it
+    // before it is used again (7B shape, gate/up 24 | 40 | 72 rows 33.9 -> 30.9 | 36.2 -> 34.2 | 49.3 -> 47.8 us).  A smaller one may still be
+    // there, where the requests with the bit take longer (one layer of 3B shape, 40 rows, every matrix with | without 89.1 | 85.3 us, of 1B shape
+    // 68.4 | 66.0).  Not for a residual projection, whose short splits lose by it (4096 x 4096, 72 rows, 16.3 -> 17.5).
+    a.stream = EPI != EPI_RESID && C::QB == 0 && (size_t)a.K * columns * 2 >= (size_t)160 << 20;
     hipLaunchKernelGGL((gemm_tile_kernel<EPI, C>), dim3((columns + 16 * C::CT - 1) / (16 * C::CT), (a.R + C::BM - 1) / C::BM, a.ksplit), dim3(C::NW * 64), 0, st, a);
     if (a.ksplit == 1) return 0;
     if constexpr (EPI == EPI_QKV) {

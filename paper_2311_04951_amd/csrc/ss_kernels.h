@@ -39,6 +39,7 @@ struct GemmArgs {
     float *splitk_ws;
     size_t splitk_ws_bytes;
     int ksplit, kslabs; // set by the launcher: K splits, K slabs (stages) per split
+    int stream;         // set by the launcher of the tile kernel: the non-temporal bit on the matrix's requests
     int splitk_rows;    // set by the launcher: partials are plain rows [split][R][N] (EPI_RESID), not accumulator tiles
     // EPI_RESID, optional: the RMSNorm that follows the projection (gain over the N output columns; planes
     // [planes][R16][norm_ld]).  A launcher that can fold it into its last launch does and returns true.
