@@ -591,6 +591,17 @@ static int check_pair(const ss_model *m, const ss_kv_cache *kv, int batch, int M
 // a buffer descriptor of 2 GiB.
 static size_t plane_rows(const ss_model *m, int R) { return R <= 16 ? 16 : (size_t)m->R16; }
 
+// Whether what every pass reads, the matrices of the layers and `more` bytes, is more than the 256 MB memory-side cache holds: then nothing of it is
+// still there when the next pass wants it, and large calls ask for it with the non-temporal bit.  (Keys and values count on top of the
+// matrices; with the bit they leave the matrices of a shallow model in the cache, so those don't count the other way round: one layer of
+// 1B shape, 103 MB, 16 x 2000 positions, 116.6 us with the bit on both, 111.3 on keys and values alone.)
+static bool streams_through(const ss_model *m, size_t more) {
+    const ss_model_cfg &c = m->cfg;
+    const size_t bits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : c.weight_quant ? 8 : c.dtype ? 16 : 32;
+    const size_t W = m->W, d = c.d_model;
+    return (4 * W * d + 3 * d * c.d_ff) * bits / 8 * c.n_layers + more >= (size_t)256 << 20;
+}
+
 // All layers over the R = batch*M rows in h.  normed: whether act_a already holds the first layer's normalised rows (the
 // embedding writes them).  final_gain: the norm that follows the last layer when it covers all rows in order (NULL: none, or
 // the head gathers rows).  Returns what the last projection did about that norm (launch_gemm).
@@ -610,6 +621,9 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
     const int chunk = round_up((Lmax + nsplit - 1) / nsplit, 64);
     nsplit = (Lmax + chunk - 1) / chunk;
 
+    size_t kv_bytes = 0;
+    for (int b = 0; b < batch; ++b) kv_bytes += (size_t)kv->len_ub[b] * 2 * W * kv->esz * c.n_layers;
+    const int stream = streams_through(m, 0), stream_kv = streams_through(m, kv_bytes);
     const int wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
     // The two residual projections name the RMSNorm that follows them.  A launcher that has a row-wise last launch
     // anyway (split K, more than 16 rows) writes the normalised planes there (1); the kernels of at most 16 rows write
@@ -635,6 +649,7 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
         g.splitk_ws = m->splitk_ws; g.splitk_ws_bytes = m->splitk_ws_bytes;
         g.W = L.wqkv; g.N = 3 * W; g.K = d; g.wscale = c.weight_quant ? L.sqkv : nullptr; g.wbits = wbits;
         g.act = m->act_a; g.act_plane = pl * d; g.ld_act = d; g.R = R;
+        g.stream = stream;
         g.act_out = m->act_q; g.act_out_plane = pl * W; g.ld_act_out = W;
         g.H = c.n_heads; g.hd = c.head_dim; g.M = M; g.S = kv->S; g.max_pos = c.max_pos;
         g.len = kv->len_dev; g.rope = m->rope; g.kcache = kc; g.vcache = vc;
@@ -648,7 +663,7 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
         a.q = m->act_q; a.q_plane = pl * W; a.ldq = W;
         a.kcache = kc; a.vcache = vc; a.len = kv->len_dev;
         a.B = batch; a.M = M; a.H = c.n_heads; a.hd = c.head_dim; a.S = kv->S; a.R = R;
-        a.nsplit = nsplit; a.chunk = chunk;
+        a.nsplit = nsplit; a.chunk = chunk; a.stream = stream_kv;
         a.part_o = m->part_o; a.part_m = m->part_m; a.part_l = m->part_l;
         a.act_out = m->act_o; a.act_out_plane = pl * W; a.ld_out = W;
         a.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
@@ -672,6 +687,7 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
             launch_rmsnorm_pack(c.dtype, h, L.g2, R, d, c.rms_eps, m->act_a, pl * d, d, st);
         }
         GemmArgs u{};
+        u.stream = stream;
         u.splitk_ws = m->splitk_ws; u.splitk_ws_bytes = m->splitk_ws_bytes;
         u.W = L.wgu; u.N = F; u.K = d; u.wscale = c.weight_quant ? L.sgu : nullptr; u.wbits = wbits;
         u.act = m->act_a; u.act_plane = pl * d; u.ld_act = d; u.R = R;
@@ -722,6 +738,7 @@ static void run_head(ss_model *m, int normed, int nrows, int row0, int stride, f
     g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.wscale = m->s_head; g.wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
     g.act = m->act_a; g.act_plane = pl * c.d_model; g.ld_act = c.d_model; g.R = nrows;
     g.out = logits; g.ldo = c.vocab;
+    g.stream = streams_through(m, (size_t)c.vocab * c.d_model * (g.wscale ? g.wbits : c.dtype ? 16 : 32) / 8);
     if (normed == 2) { g.act_nsq = m->nsq_ws; g.act_nsq_parts = deferred_norm_parts(c.d_model); g.norm_eps = c.rms_eps; }
     launch_gemm(c.dtype, EPI_STORE, g, st);
 }

@@ -17,6 +17,7 @@
 // Online softmax in the log2 domain per wave; waves, then splits, are merged by log-sum-exp in a
 // fixed order.  The second kernel merges the splits, normalises and writes the result as the
 // activation planes the O projection consumes.
+#include <type_traits>
 #include "attention_core.h"
 
 namespace ss {
@@ -35,6 +36,114 @@ __global__ __launch_bounds__(NWX * 64) void attn_direct_kernel(AttnArgs a) {
     attn_unit<T, HD, NWX, false, true>(a, 0, blockIdx.y, blockIdx.z, a.len[blockIdx.z], sm);
 }
 
+// A single split of many positions, bf16: blocks of 64 positions go round the wavefronts, each block's keys, then its values, through the
+// wavefront's own 16 KB of LDS.  What bounds it is the cache's bytes: keys and values of a block are 16 KB in one piece each, so every
+// load-to-LDS instruction brings a contiguous kilobyte, where loads in operand layout take half lines of 16 rows.  The other wavefronts' requests
+// fill the time in which one multiplies (a compute unit has some 32 KB of loads in flight; 64 or 128 KB are asked for).
+//   A layer, us, loads in operand layout -> blocks -> and the non-temporal bit: 7B shape 8 x 9 rows at up to 4080 positions 234 -> 232 -> 212, at
+// 1200 167.6 with blocks, 158.3 with the bit; 1B shape, 100 MB and 16 x 1000 positions, all in the memory-side cache, 89.0 and 92.9: the bit
+// goes by the bytes of the pass.
+template <int HD, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
+    typedef bf16_t T;
+    constexpr int NKC = HD / 32, NDT = HD / 16, BLOCK = 64 * HD * 2, UPR = HD / 8, RPI = 64 / UPR; // (16-byte units of a key, keys per load instruction)
+    static_assert(sizeof(AttnSmem<HD, NW>) <= NW * BLOCK, "");
+    __shared__ __align__(16) unsigned char lds[NW * BLOCK];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int h = blockIdx.y, b = blockIdx.z, L = a.len[b], ntot = L + a.M;
+    unsigned char *buf = lds + wave * BLOCK;
+    const uint32_t to = lds_address(buf);
+
+    ActPlanes<T> qp{const_cast<T *>(reinterpret_cast<const T *>(a.q)), a.q_plane, a.ldq};
+    const int qrow = min(b * a.M + c, a.R - 1);
+    Act<T> q[NKC];
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) q[kc] = load_act(qp, (size_t)qrow * a.ldq + h * HD + kc * 32 + g * 8);
+    const char *Kb = reinterpret_cast<const char *>(a.kcache) + ((size_t)b * a.H + h) * a.S * HD * 2;
+    const char *Vb = reinterpret_cast<const char *>(a.vcache) + ((size_t)b * a.H + h) * a.S * HD * 2;
+
+    // Unit u of key r sits at position u xor (r mod 4 + 4 (r / 8 mod 4 or 2)): the sixteen keys of a tile (below) in different banks.  Values:
+    // unit u of head element e at u xor (e mod 8).
+    const uint32_t voff = (uint32_t)(lane / 8) * 128u + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
+    auto request = [&](const char *p, auto offset) {
+        if (a.stream) {
+#pragma unroll
+            for (int i = 0; i < BLOCK / 1024; ++i) dma16<true>(p + i * 1024, offset(i), to + i * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < BLOCK / 1024; ++i) dma16(p + i * 1024, offset(i), to + i * 1024);
+        }
+    };
+    auto request_keys = [&](int blk) {
+        request(Kb + (size_t)blk * BLOCK, [&](int i) {
+            const int r = i * RPI + lane / UPR, f = (r & 3) + 4 * ((r >> 3) & (UPR / 4 - 1)); // key of the block
+            return (uint32_t)(lane / UPR) * HD * 2u + (uint32_t)((lane % UPR) ^ f) * 16u;
+        });
+    };
+    auto request_values = [&](int blk) { request(Vb + (size_t)blk * BLOCK, [&](int) { return voff; }); };
+    const bool row_ok = c < a.M;
+    const int row_limit = L + c; // last position row c may attend
+    float m_run = NEG_BIG, l_run = 0.f;
+    f32x4 o[NDT];
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave * 64 < ntot) request_keys(wave);
+    for (int blk = wave; blk * 64 < ntot; blk += NW) {
+        wait_vmcnt_at_most<0>();
+        asm volatile("" ::: "memory");
+        // keys of a half block's tile t: row i is position 8 (i / 4) + 4t + i mod 4, so that lane (c, g) receives 8g + 4t + v
+        f32x4 s[2][2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                s[hh][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                const int r = 32 * hh + (c >> 2) * 8 + 4 * t + (c & 3), f = (c & 3) + 4 * ((c >> 2) & (UPR / 4 - 1));
+#pragma unroll
+                for (int kc = 0; kc < NKC; ++kc) s[hh][t] = mma(s[hh][t], *reinterpret_cast<const u32x4 *>(buf + r * HD * 2 + ((kc * 4 + g) ^ f) * 16), q[kc]);
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the keys have been read
+        request_values(blk);
+        float pv[2][8], bm = NEG_BIG;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int pos = blk * 64 + 32 * hh + g * 8 + e;
+                const float x = row_ok && pos <= row_limit ? s[hh][e >> 2][e & 3] * a.scale_log2e : NEG_BIG;
+                pv[hh][e] = x;
+                bm = fmaxf(bm, x);
+            }
+        bm = fmaxf(bm, __shfl_xor(bm, 16));
+        bm = fmaxf(bm, __shfl_xor(bm, 32));
+        const float m_new = fmaxf(m_run, bm), alpha = exp2f(m_run - m_new);
+        l_run *= alpha;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float p = pv[hh][e] > 0.5f * NEG_BIG ? exp2f(pv[hh][e] - m_new) : 0.f;
+                l_run += p;
+                pv[hh][e] = p;
+            }
+        m_run = m_new;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) o[dt] *= alpha;
+        const Act<T> P[2] = {pack_act(pv[0], T{}), pack_act(pv[1], T{})};
+        wait_vmcnt_at_most<0>();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+                o[dt] = mma(o[dt], *reinterpret_cast<const u32x4 *>(buf + (dt * 16 + c) * 128 + ((hh * 4 + g) ^ (c & 7)) * 16), P[hh]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // ... and the values
+        if ((blk + NW) * 64 < ntot) request_keys(blk + NW);
+    }
+    attn_finish<T, HD, NW, false, true>(a, 0, h, b, m_run, l_run, o, *reinterpret_cast<AttnSmem<HD, NW> *>(lds));
+}
+
 template <typename T>
 __global__ void attn_merge_kernel(AttnArgs a) {
     const int row = blockIdx.x, h = blockIdx.y, e = threadIdx.x;
@@ -45,6 +154,15 @@ __global__ void attn_merge_kernel(AttnArgs a) {
 template <typename T> static void launch_attention_t(const AttnArgs &a, hipStream_t st) {
     dim3 grid(a.nsplit, a.H, a.B);
     if (a.nsplit == 1) {
+        if constexpr (std::is_same<T, bf16_t>::value) {
+            // from 256 positions on (four blocks)
+            if (a.chunk >= 256 && a.hd >= 64) {
+                if (a.hd == 128 && a.B * a.H <= 256) hipLaunchKernelGGL((attn_blocks_kernel<128, 8>), grid, dim3(512), 0, st, a);
+                else if (a.hd == 128) hipLaunchKernelGGL((attn_blocks_kernel<128, 4>), grid, dim3(256), 0, st, a);
+                else hipLaunchKernelGGL((attn_blocks_kernel<64, 8>), grid, dim3(512), 0, st, a);
+                return;
+            }
+        }
         // few units with a short context (one split by the host's choice): 8 waves, so that a wave has one step up to 256 positions
         if (a.hd == 128 && a.B * a.H < 256) {
             hipLaunchKernelGGL((attn_direct_kernel<T, 128, 8>), grid, dim3(512), 0, st, a);

@@ -185,25 +185,6 @@ __device__ __forceinline__ int rotated(int i, int rot, int nst) {
     return i >= nst ? i - nst : i;
 }
 
-typedef const unsigned char __attribute__((address_space(3))) *lds_ptr;
-__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(lds_ptr)p; }
-// A load-to-LDS instruction (16 bytes per lane, from base + off to lds + 16 * lane) that the compiler does not see as one: it
-// would wait for every such load in flight in front of the next LDS read.  It has no register result; whoever reads the data
-// waits for it with counted waits (such loads return in order with the wavefront's other loads).
-// STREAM: the non-temporal bit, for weight lines, which are used once (the activation lines by every workgroup): 7B-shaped bf16 pass
-// 3.04 -> 2.85 ms at 5 rows, 2.97 -> 2.75 at 1 row (int8 -3.6 %, int4 -2.5 %); the scope bits on top of it change nothing.
-template <bool STREAM = false> __device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
-    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
-}
-
-__device__ __forceinline__ void dma4(const void *base, uint32_t off, uint32_t lds) { // the same, a word per lane
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_waitcnt vmcnt(N), N < 64
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
 // Waits until at most n loads are in flight, LO <= n <= HI (n is the same for the wavefront).
 template <int LO, int HI> __device__ __forceinline__ void wait_vmcnt(int n) {
     if constexpr (LO < HI) {
@@ -898,7 +879,7 @@ template <typename T, int EPI, int NW, int RT> static int launch_wide(const Gemm
 // of 22016 columns, the kernel 48.  They got there by
 //   - a ring of ABUF stages of activations and WBUF of the matrix, the matrix's one stage deeper where LDS does not hold three of both (loads
 //     alone, one | two stages ahead: 45 | 37 us), asked for in that order, so that the counted wait leaves the younger ones in flight;
-//   - 256 bytes of a row at a time where LDS allows (128: 40 us) and the non-temporal bit on requests of large matrices (37.4 -> 34.7);
+//   - 256 bytes of a row at a time where LDS allows (128: 40 us) and the non-temporal bit on the matrix's (37.4 -> 34.7; launch_tile_as says when);
 //   - a start in K that depends on the XCD: its workgroups walk K together and find each other's activations in their L2, the eight XCDs
 //     ask different memory channels (no rotation 38 us, every workgroup its own 35.4; 256 rows, where the activations fill an L2: 71, 99, 67);
 //   - row blocks of the same columns on one XCD, next to one another in time (tile_place): weights of two blocks from memory once (52 -> 37 us).
@@ -1283,11 +1264,11 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     const int nst = (a.K + 32 * C::KBS - 1) / (32 * C::KBS);
     a.kslabs = (nst + ksplit - 1) / ksplit;
     a.ksplit = (nst + a.kslabs - 1) / a.kslabs; // no empty split
-    // The non-temporal bit on the matrix's requests: for one that fills most of the 256 MB memory-side cache by itself and is gone from it
-    // before it is used again (7B shape, gate/up 24 | 40 | 72 rows 33.9 -> 30.9 | 36.2 -> 34.2 | 49.3 -> 47.8 us).  A smaller one may still be
-    // there, where the requests with the bit take longer (one layer of 3B shape, 40 rows, every matrix with | without 89.1 | 85.3 us, of 1B shape
-    // 68.4 | 66.0).  Not for a residual projection, whose short splits lose by it (4096 x 4096, 72 rows, 16.3 -> 17.5).
-    a.stream = EPI != EPI_RESID && C::QB == 0 && (size_t)a.K * columns * 2 >= (size_t)160 << 20;
+    // The non-temporal bit on the matrix's requests: where the pass leaves nothing of the matrix in the memory-side cache (7B shape, gate/up
+    // 24 | 40 | 72 rows 33.9 -> 30.9 | 36.2 -> 34.2 | 49.3 -> 47.8 us); what is still there comes later with the bit (one layer of 3B shape, 40
+    // rows, 89.1 us with, 85.3 without; of 1B shape 68.4, 66.0).  Not for a residual projection, whose short splits lose by it (4096 x
+    // 4096, 72 rows, 16.3 -> 17.5), nor for int4 (half a line a request: gate/up of 72 rows 45.3 -> 47.0; int8 was not measured by itself).
+    a.stream = a0.stream && EPI != EPI_RESID && C::QB == 0;
     hipLaunchKernelGGL((gemm_tile_kernel<EPI, C>), dim3((columns + 16 * C::CT - 1) / (16 * C::CT), (a.R + C::BM - 1) / C::BM, a.ksplit), dim3(C::NW * 64), 0, st, a);
     if (a.ksplit == 1) return 0;
     if constexpr (EPI == EPI_QKV) {

@@ -182,6 +182,26 @@ __device__ __forceinline__ f32x4 mma(f32x4 acc, u32x4 a, const Act<float> &b) {
     return acc;
 }
 
+// ---- loads that go to LDS ----------------------------------------------------------------------
+typedef const unsigned char __attribute__((address_space(3))) *lds_ptr;
+__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(lds_ptr)p; }
+// A load-to-LDS instruction (16 bytes per lane, from base + off to lds + 16 * lane) that the compiler does not see as one: it
+// would wait for every such load in flight in front of the next LDS read.  It has no register result; whoever reads the data
+// waits for it with counted waits (such loads return in order with the wavefront's other loads).
+// STREAM: the non-temporal bit, for weight lines, which are used once (the activation lines by every workgroup): 7B-shaped bf16 pass
+// 3.04 -> 2.85 ms at 5 rows, 2.97 -> 2.75 at 1 row (int8 -3.6 %, int4 -2.5 %); the scope bits on top of it change nothing.
+template <bool STREAM = false> __device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t lds) {
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
+}
+
+__device__ __forceinline__ void dma4(const void *base, uint32_t off, uint32_t lds) { // the same, a word per lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(off), "s"(base) : "m0", "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vmcnt_at_most() { // s_waitcnt vmcnt(N), N < 64
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 // ---- agent-coherent accesses ------------------------------------------------------------------
 // Data that one workgroup writes and another reads INSIDE one kernel (persistent verify kernel) is
 // moved with relaxed agent-scope atomics: they are performed at the memory side, so no cache

@@ -39,7 +39,7 @@ struct GemmArgs {
     float *splitk_ws;
     size_t splitk_ws_bytes;
     int ksplit, kslabs; // set by the launcher: K splits, K slabs (stages) per split
-    int stream;         // set by the launcher of the tile kernel: the non-temporal bit on the matrix's requests
+    int stream;         // the matrices of a pass are more than the memory-side cache holds (the tile kernel: non-temporal requests)
     int splitk_rows;    // set by the launcher: partials are plain rows [split][R][N] (EPI_RESID), not accumulator tiles
     // EPI_RESID, optional: the RMSNorm that follows the projection (gain over the N output columns; planes
     // [planes][R16][norm_ld]).  A launcher that can fold it into its last launch does and returns true.
@@ -81,6 +81,7 @@ struct AttnArgs {
     const int32_t *len;          // [batch] lengths before this call's append
     int B, M, H, hd, S, R;
     int nsplit, chunk;  // positions per split (multiple of 64)
+    int stream;         // matrices, keys and values of a pass are more than the memory-side cache holds (large calls: non-temporal requests)
     float *part_o;      // [nsplit][R][H][hd] unnormalised
     float *part_m;      // [nsplit][R][H] running max (log2 domain)
     float *part_l;      // [nsplit][R][H] sum of weights

@@ -1,0 +1,62 @@
+"""The attention of one split in blocks of 64 positions (bf16, heads of 64 and 128, calls of 256 and more (sequence, head) units at 256 and
+more positions): lengths at the edges of blocks and of the round over the wavefronts, sequences of very different lengths."""
+import math
+
+import pytest
+import torch
+
+import paper_2311_04951_amd as sv
+import seeded_inputs as si
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _want(q, k, v, lens, M):
+    """64-bit attention; q [B, M, H, hd], k / v per sequence [n + M, H, hd]."""
+    out = torch.empty_like(q, dtype=torch.float64)
+    for b, n in enumerate(lens):
+        s = torch.einsum("mhe,phe->hmp", q[b].double(), k[b].double()) / math.sqrt(q.shape[-1])
+        seen = torch.arange(n + M, device=q.device)[None, :] <= n + torch.arange(M, device=q.device)[:, None]
+        out[b] = torch.einsum("hmp,phe->mhe", s.masked_fill(~seen, -math.inf).softmax(-1), v[b].double())
+    return out
+
+
+# heads x sequences: 256 units and fewer take 8 wavefronts, more take 4; layers: the second one's matrices push a pass beyond 256 MB
+@pytest.mark.parametrize("hd,heads,lens,M,ff", [
+    (128, 32, [252, 0, 63, 64, 65, 191, 192, 193], 4, 256), (128, 32, [511, 510, 512, 448, 449, 447, 1, 250], 1, 256), (128, 40, [300, 255, 256, 257, 319, 320, 17, 128], 9, 256),
+    (128, 32, [1000, 40, 575, 576, 577, 300, 2, 900], 16, 11008), (64, 32, [252, 0, 63, 64, 65, 511, 512, 513], 3, 256), (64, 64, [700, 255, 256, 639, 640], 16, 256)])
+def test_layer_attention_against_64_bits(hd, heads, lens, M, ff):
+    """A layer whose d_ff part is nearly nothing and whose O projection is the identity: h grows by the attention's result.  Queries, weights and
+    results carry 16 bits (two planes), sums 32: 2^-16 of values around 1, and of the sum of the weights, which is 1."""
+    B, W, d = len(lens), heads * hd, heads * hd
+    g = torch.Generator(device=dev()).manual_seed(hd + heads)
+    r = lambda *s: torch.randn(s, generator=g, device=dev())
+    eye = torch.eye(d, device=dev(), dtype=torch.bfloat16)
+    L = {"wqkv": (r(3 * W, d) * 0.02).to(torch.bfloat16), "wo": eye, "wgu": torch.zeros(2 * ff, d, device=dev(), dtype=torch.bfloat16),
+         "wd": torch.zeros(d, ff, device=dev(), dtype=torch.bfloat16), "g1": torch.ones(d, device=dev()), "g2": torch.ones(d, device=dev())}
+    gm = sv.Model(si.DecoderShape(1, d, heads, hd, ff, 64, dtype="bf16"), None, max_rows=B * M, max_pos=max(lens) + 64, packed_layers=[L])
+    kv = sv.KVCache(gm, B, max(lens) + 40)
+    S = (max(lens) + 40 + 63) // 64 * 64
+    for b, n in enumerate(lens):
+        if n:
+            sv.ss_kv_cache_append(kv, 0, b, 0, r(n, W).to(torch.bfloat16), r(n, W).to(torch.bfloat16))
+    sv.ss_kv_cache_set_len(kv, lens)
+    h = r(B * M, d)
+    out = sv.ss_decoder_layers_forward(gm, kv, h.clone(), B, M)
+    cache = kv.buf.view(torch.bfloat16)[:2 * B * heads * S * hd].view(2, B, heads, S, hd)
+    k = [cache[0, b, :, :n + M].permute(1, 0, 2).float() for b, n in enumerate(lens)]
+    v = [cache[1, b].reshape(heads, S // 64, hd, 64).permute(0, 1, 3, 2).reshape(heads, S, hd)[:, :n + M].permute(1, 0, 2).float() for b, n in enumerate(lens)]
+    x = h.double()
+    q = (x * torch.rsqrt(x.square().mean(-1, keepdim=True) + 1e-5)) @ L["wqkv"][:W].double().t()
+    q = q.view(B, M, heads, hd)
+    pos = torch.tensor(lens, device=dev(), dtype=torch.float64)[:, None] + torch.arange(M, device=dev(), dtype=torch.float64)
+    ang = pos[..., None] * 10000.0 ** (-2.0 * torch.arange(hd // 2, device=dev(), dtype=torch.float64) / hd)
+    cs, sn = ang.cos()[:, :, None], ang.sin()[:, :, None]
+    lo, hi = q[..., :hd // 2], q[..., hd // 2:]
+    q = torch.cat([lo * cs - hi * sn, lo * sn + hi * cs], -1)
+    want = _want(q, k, v, lens, M).reshape(B * M, W)
+    got = out.double() - x
+    # a score's error: 2^-17 of each of hd products of about 1 x 1.3, over sqrt(hd), and the fp32 rotation; results of up to 4: 1e-4 is ten of them
+    assert float((got - want).norm() / want.norm()) < 3e-5
+    assert float((got - want).abs().max()) < 3e-4
