@@ -1267,8 +1267,9 @@ template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int co
     // The non-temporal bit on the matrix's requests: where the pass leaves nothing of the matrix in the memory-side cache (7B shape, gate/up
     // 24 | 40 | 72 rows 33.9 -> 30.9 | 36.2 -> 34.2 | 49.3 -> 47.8 us); what is still there comes later with the bit (one layer of 3B shape, 40
     // rows, 89.1 us with, 85.3 without; of 1B shape 68.4, 66.0).  Not for a residual projection, whose short splits lose by it (4096 x
-    // 4096, 72 rows, 16.3 -> 17.5), nor for int4 (half a line a request: gate/up of 72 rows 45.3 -> 47.0; int8 was not measured by itself).
-    a.stream = a0.stream && EPI != EPI_RESID && C::QB == 0;
+    // 4096, 72 rows, 16.3 -> 17.5), nor where a stage takes half a line of a row (int4 gate/up of 72 rows 45.3 -> 47.0; int8 with whole lines, 2 layers of
+    // 7B shape, 40 | 72 rows 208 -> 194 | 258 -> 245).
+    a.stream = a0.stream && EPI != EPI_RESID && C::WROWB >= 128;
     hipLaunchKernelGGL((gemm_tile_kernel<EPI, C>), dim3((columns + 16 * C::CT - 1) / (16 * C::CT), (a.R + C::BM - 1) / C::BM, a.ksplit), dim3(C::NW * 64), 0, st, a);
     if (a.ksplit == 1) return 0;
     if constexpr (EPI == EPI_QKV) {
@@ -1288,6 +1289,9 @@ template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, i
         case 32096: return go(TileCfg<QB, 2, 2, 1, 3, 4, 4, 3, 3>{});
         case 48096: return go(TileCfg<QB, 3, 2, 1, 3, 4, 4, 3, 3>{});
         case 80096: return go(TileCfg<QB, 5, 2, 1, 3, 4, 4, 3, 3>{});
+        case 32192: return go(TileCfg<QB, 2, 2, 1, 6, 2, 4, 3, 3>{}); // (13B shape, 27648 columns: one round instead of two of 96)
+        case 48192: return go(TileCfg<QB, 3, 2, 1, 6, 2, 4, 3, 3>{});
+        case 80192: return go(TileCfg<QB, 5, 2, 1, 6, 2, 4, 2, 3>{});
         case 96096:
             if constexpr (QB == 4) return go(TileCfg<4, 3, 2, 2, 3, 2, 4, 2, 3>{});
             else return go(TileCfg<8, 3, 6, 2, 1, 4, 4, 2, 3>{});
@@ -1368,7 +1372,7 @@ static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K,
         for (int i = 0; i < (fused ? 3 : 2); ++i) {
             const int cols = fused ? narrow[i] : plain[i];
             if (bm >= 96 && cols == 64 && (fused || bits < 16)) continue;
-            if (bits < 16 && fused && bm <= 80 && cols != 96) continue;
+            if (bits < 16 && fused && cols == 64) continue;
             for (int ks = 1; ks <= splits; ++ks) {
                 if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
                 const TileChoice c = tile_cost(bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
