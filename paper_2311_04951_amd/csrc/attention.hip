@@ -51,7 +51,7 @@ __global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
     __shared__ __align__(16) unsigned char lds[NW * BLOCK];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int h = blockIdx.y, b = blockIdx.z, L = a.len[b], ntot = L + a.M;
+    const int h = blockIdx.y, b = blockIdx.z, L = a.len[b], ntot = min(L + a.M, a.chunk); // (the host's bound on the lengths, which fits the cache)
     unsigned char *buf = lds + wave * BLOCK;
     const uint32_t to = lds_address(buf);
 
@@ -134,10 +134,12 @@ __global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
         wait_vmcnt_at_most<0>();
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+        for (int hh = 0; hh < 2; ++hh) {
+            if (hh && blk * 64 + 32 >= ntot) break; // (what lies there may be no numbers, which a weight of zero would not undo)
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
                 o[dt] = mma(o[dt], *reinterpret_cast<const u32x4 *>(buf + (dt * 16 + c) * 128 + ((hh * 4 + g) ^ (c & 7)) * 16), P[hh]);
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // ... and the values
         if ((blk + NW) * 64 < ntot) request_keys(blk + NW);
     }

@@ -60,3 +60,26 @@ def test_layer_attention_against_64_bits(hd, heads, lens, M, ff):
     # a score's error: 2^-17 of each of hd products of about 1 x 1.3, over sqrt(hd), and the fp32 rotation; results of up to 4: 1e-4 is ten of them
     assert float((got - want).norm() / want.norm()) < 3e-5
     assert float((got - want).abs().max()) < 3e-4
+
+
+@pytest.mark.parametrize("hd,heads", [(128, 32), (64, 32), (128, 40)])
+def test_positions_behind_the_end_need_not_be_numbers(hd, heads):
+    """What a longer sequence left behind in the second half of the last block, 32 positions that nothing reads as a position: the same bits as with zeros."""
+    lens, M, d, S = [257, 270, 284, 320, 14, 383, 321, 510], 4, heads * hd, 640
+    g = torch.Generator(device=dev()).manual_seed(hd + heads)
+    r = lambda *s: torch.randn(s, generator=g, device=dev())
+    L = {"wqkv": (r(3 * d, d) * 0.02).to(torch.bfloat16), "wo": torch.eye(d, device=dev(), dtype=torch.bfloat16), "wgu": torch.zeros(512, d, device=dev(), dtype=torch.bfloat16),
+         "wd": torch.zeros(d, 256, device=dev(), dtype=torch.bfloat16), "g1": torch.ones(d, device=dev()), "g2": torch.ones(d, device=dev())}
+    gm = sv.Model(si.DecoderShape(1, d, heads, hd, 256, 64, dtype="bf16"), None, max_rows=len(lens) * M, max_pos=S, packed_layers=[L])
+    h, k, v = r(len(lens) * M, d), [r(n, d) for n in lens], [r(n, d) for n in lens]
+    out = []
+    for behind in (0.0, math.nan, math.inf):
+        kv = sv.KVCache(gm, len(lens), S)
+        for b, n in enumerate(lens):
+            full = torch.full((2, S, d), behind, device=dev())
+            full[:, :(n + M + 31) // 32 * 32] = 0
+            full[0, :n], full[1, :n] = k[b], v[b]
+            sv.ss_kv_cache_append(kv, 0, b, 0, full[0].to(torch.bfloat16), full[1].to(torch.bfloat16))
+        sv.ss_kv_cache_set_len(kv, lens)
+        out.append(sv.ss_decoder_layers_forward(gm, kv, h.clone(), len(lens), M))
+    assert bool(out[0].isfinite().all()) and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
