@@ -1248,10 +1248,11 @@ struct TileChoice {
     int rows, cols, ksplit;
     double us;
 };
-static TileChoice tile_cost(int bits, int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
+static TileChoice tile_cost(int epi, int bits, int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
     const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols, wgs = gx * gy * ksplit;
     const int rounds = (wgs + 255) / 256;
-    const bool long_stage = cols <= 96 && bm <= 96; // 256 bytes of a row
+    const bool fused = epi == EPI_SWIGLU || epi == EPI_QKV;
+    const bool long_stage = cols <= 96 ? bm <= 96 : fused && cols == 128 && bm <= 48; // 256 bytes of a row
     const double act = !long_stage ? 9e-6 : bm <= 48 ? 13.5e-6 : 15e-6;
     const double mat = long_stage ? 31e-6 : cols <= 96 ? 26e-6 : cols == 128 ? 29e-6 : gy > 1 ? 34.5e-6 : 32.5e-6;
     const double per = bits == 16 ? bm * 4 * act + cols * 2 * mat : bits == 8 ? 2.0e-3 + 8.1e-7 * bm * cols : 3.0e-3 + 8.75e-7 * bm * cols;
@@ -1285,11 +1286,16 @@ template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, i
     constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV;
     const int tile = c.rows * 1000 + c.cols;
     if constexpr (QB != 0 && FUSED) {
+        if constexpr (EPI == EPI_SWIGLU) {
+            if (tile == 32128) return go(TileCfg<QB, 2, 2, 1, 4, 2, 4, 3, 3>{});
+            if (tile == 48128) return go(TileCfg<QB, 3, 2, 1, 4, 2, 4, 3, 3>{});
+            if (tile == 80128) return go(TileCfg<QB, 5, 2, 1, 4, 2, 4, 2, 3>{});
+        }
         switch (tile) {
         case 32096: return go(TileCfg<QB, 2, 2, 1, 3, 4, 4, 3, 3>{});
         case 48096: return go(TileCfg<QB, 3, 2, 1, 3, 4, 4, 3, 3>{});
         case 80096: return go(TileCfg<QB, 5, 2, 1, 3, 4, 4, 3, 3>{});
-        case 32192: return go(TileCfg<QB, 2, 2, 1, 6, 2, 4, 3, 3>{}); // (13B shape, 27648 columns: one round instead of two of 96)
+        case 32192: return go(TileCfg<QB, 2, 2, 1, 6, 2, 4, 3, 3>{}); // (one round where 128 columns would make two)
         case 48192: return go(TileCfg<QB, 3, 2, 1, 6, 2, 4, 3, 3>{});
         case 80192: return go(TileCfg<QB, 5, 2, 1, 6, 2, 4, 2, 3>{});
         case 96096:
@@ -1315,6 +1321,11 @@ template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, i
             else return go(TileCfg<8, 4, 4, 2, 2, 2, 2, 3, 3>{});
         }
     } else if constexpr (FUSED) {
+        if constexpr (EPI == EPI_SWIGLU) {
+            if (tile == 32128) return go(TileCfg<0, 2, 2, 1, 4, 2, 4, 3, 3>{});
+            if (tile == 48128) return go(TileCfg<0, 3, 2, 1, 4, 2, 4, 2, 3>{});
+            if (tile == 80128) return go(TileCfg<0, 5, 2, 1, 4, 2, 2, 3, 3>{});
+        }
         switch (tile) {
         case 32064: return go(TileCfg<0, 2, 4, 1, 1, 4, 4, 3, 3>{});
         case 32096: return go(TileCfg<0, 2, 6, 1, 1, 4, 4, 3, 3>{});
@@ -1364,18 +1375,23 @@ static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K,
     const bool short_k = R > 512 && K <= 1024;
     // Quantised matrices: 96 where that is all of them, beyond it the cost chooses among blocks of 80, 96 and 128
     const int q0 = R <= 32 ? 32 : R <= 48 ? 48 : R <= 80 ? 80 : 96, q1 = R <= 96 ? q0 : 128;
-    const int rows[5] = {32, 48, 80, 96, 128}, narrow[3] = {64, 96, 192}, plain[2] = {64, 128};
+    const int rows[5] = {32, 48, 80, 96, 128}, narrow[4] = {64, 96, 128, 192}, plain[2] = {64, 128};
     const int splits = epi == EPI_QKV ? 4 : epi == EPI_RESID ? 8 : 1;
     TileChoice best{0, 0, 1, 1e30};
     for (int bm : rows) {
         if (bits == 16 ? bm != bm0 && !(short_k && bm < bm0 && bm != 96) : bm > q1 || (bm < std::min(q0, 80) && !short_k)) continue;
-        for (int i = 0; i < (fused ? 3 : 2); ++i) {
+        for (int i = 0; i < (fused ? 4 : 2); ++i) {
             const int cols = fused ? narrow[i] : plain[i];
             if (bm >= 96 && cols == 64 && (fused || bits < 16)) continue;
             if (bits < 16 && fused && cols == 64) continue;
+            // Gate and up in 128 columns: one row block, where 96 columns make more workgroups than there are compute units and 128 do not.  192, the other
+            // way to one round, leave up to half of the units idle: 13B shape, 27648 columns, 144 workgroups of 192 -> 216 of 128, a layer, us: bf16
+            // 18 | 40 | 80 rows 156.3 -> 147.9 | 180.5 -> 167.7 | 218.4 -> 205.0; two of int8 240.6 -> 224.7 | 289.8 -> 274.5 | 391.6 -> 372.2; three of
+            // int4 404.0 -> 375.0 | 478.4 -> 449.9 | 646.6 -> 603.3.  (QKV splits K instead: level with 192 columns by the cost.)
+            if (fused && cols == 128 && (epi == EPI_QKV || bm > 80 || R > bm || (columns + 95) / 96 <= 256 || (columns + 127) / 128 > 256)) continue;
             for (int ks = 1; ks <= splits; ++ks) {
                 if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
-                const TileChoice c = tile_cost(bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
+                const TileChoice c = tile_cost(epi, bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
                 if (c.us < best.us) best = c;
             }
         }
