@@ -143,7 +143,39 @@ __global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // ... and the values
         if ((blk + NW) * 64 < ntot) request_keys(blk + NW);
     }
-    attn_finish<T, HD, NW, false, true>(a, 0, h, b, m_run, l_run, o, *reinterpret_cast<AttnSmem<HD, NW> *>(lds));
+    // The wavefronts' results, merged in order as attn_unit does.  (Code of its own: as a function that both call it changed the registers and the first
+    // loads of every kernel that attn_unit is in, 0.2 - 0.35 us a layer of few rows.)
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    auto &sm = *reinterpret_cast<AttnSmem<HD, NW> *>(lds);
+    __syncthreads(); // nobody reads keys or values any more
+    if (g == 0) {
+        sm.m[wave][c] = m_run;
+        sm.l[wave][c] = l_run;
+    }
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sm.o[wave][dt][v][lane] = o[dt][v];
+    __syncthreads();
+    if (!row_ok) return;
+    float mstar = sm.m[0][c], wt[NW], l = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mstar = fmaxf(mstar, sm.m[w][c]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wt[w] = exp2f(sm.m[w][c] - mstar);
+        l += sm.l[w][c] * wt[w];
+    }
+    ActPlanes<T> out{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_out};
+    for (int dt = wave; dt < NDT; dt += NW)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float acc = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) acc += sm.o[w][dt][v][lane] * wt[w];
+            store_act(out, (size_t)(b * a.M + c) * a.ld_out + h * HD + dt * 16 + 4 * g + v, acc / l);
+        }
 }
 
 template <typename T>

@@ -14,82 +14,6 @@ template <int HD, int NW> struct AttnSmem {
     float o[NW][HD / 16][4][64];
 };
 
-// The end of a unit: the wavefronts' sums o (column group dt, register v: head element dt * 16 + 4g + v of row c), row maxima and sums of
-// weights (this lane's share of them) merged in order, and written: the split's unnormalised partial, or (DIRECT) the result.
-template <typename T, int HD, int NW, bool COH, bool DIRECT>
-__device__ __forceinline__ void attn_finish(const AttnArgs &a, int split, int h, int b, float m_run, float l_run, const f32x4 (&o)[HD / 16], AttnSmem<HD, NW> &sm) {
-    constexpr int NDT = HD / 16;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    const bool row_ok = c < a.M;
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-
-    // merge the waves (fixed order) and write this split's partial
-    auto &sm_m = sm.m;
-    auto &sm_l = sm.l;
-    auto &sm_o = sm.o;
-    __syncthreads(); // the previous unit's readers are done with the buffers
-    if (g == 0) {
-        sm_m[wave][c] = m_run;
-        sm_l[wave][c] = l_run;
-    }
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sm_o[wave][dt][v][lane] = o[dt][v];
-    __syncthreads();
-    float mstar = sm_m[0][c];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) mstar = fmaxf(mstar, sm_m[w][c]);
-    float wt[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) wt[w] = exp2f(sm_m[w][c] - mstar);
-    if (!row_ok) return;
-    const int row = b * a.M + c;
-    if (DIRECT) {
-        float l = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) l += sm_l[w][c] * wt[w];
-        ActPlanes<T> out{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_out};
-        for (int dt = wave; dt < NDT; dt += NW) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float acc = 0.f;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) acc += sm_o[w][dt][v][lane] * wt[w];
-                const size_t o = (size_t)row * a.ld_out + h * HD + dt * 16 + 4 * g + v;
-                if (COH) store_act_coh(out, o, acc / l);
-                else store_act(out, o, acc / l);
-            }
-        }
-        return;
-    }
-    const size_t pidx = ((size_t)split * a.R + row) * a.H + h;
-    if (wave == 0 && g == 0) {
-        float l = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) l += sm_l[w][c] * wt[w];
-        if (COH) {
-            st_coh(&a.part_m[pidx], mstar);
-            st_coh(&a.part_l[pidx], l);
-        } else {
-            a.part_m[pidx] = mstar;
-            a.part_l[pidx] = l;
-        }
-    }
-    for (int dt = wave; dt < NDT; dt += NW) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float acc = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) acc += sm_o[w][dt][v][lane] * wt[w];
-            if (COH) st_coh(&a.part_o[pidx * HD + dt * 16 + 4 * g + v], acc);
-            else a.part_o[pidx * HD + dt * 16 + 4 * g + v] = acc;
-        }
-    }
-}
-
 // One (sequence b, head h, KV split) unit by a workgroup of NW wavefronts; L = cached length of
 // sequence b before this pass.  Writes the split's unnormalised partial (part_o, part_m, part_l).  Every thread of the workgroup must call it.
 // COH: queries are read and partials written with agent-coherent accesses (persistent kernel).
@@ -190,8 +114,74 @@ __device__ __forceinline__ void attn_unit(const AttnArgs &a, int split, int h, i
         for (int dt = 0; dt < NDT; ++dt) o[dt] = mma(o[dt], cur.v[dt], P);
         if (more) cur = nxt;
     }
-    attn_finish<T, HD, NW, COH, DIRECT>(a, split, h, b, m_run, l_run, o, sm);
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+
+    // merge the waves (fixed order) and write this split's partial
+    auto &sm_m = sm.m;
+    auto &sm_l = sm.l;
+    auto &sm_o = sm.o;
+    __syncthreads(); // the previous unit's readers are done with the buffers
+    if (g == 0) {
+        sm_m[wave][c] = m_run;
+        sm_l[wave][c] = l_run;
+    }
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sm_o[wave][dt][v][lane] = o[dt][v];
+    __syncthreads();
+    float mstar = sm_m[0][c];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mstar = fmaxf(mstar, sm_m[w][c]);
+    float wt[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) wt[w] = exp2f(sm_m[w][c] - mstar);
+    if (!row_ok) return;
+    const int row = b * a.M + c;
+    if (DIRECT) {
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l += sm_l[w][c] * wt[w];
+        ActPlanes<T> out{reinterpret_cast<T *>(a.act_out), a.act_out_plane, a.ld_out};
+        for (int dt = wave; dt < NDT; dt += NW) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float acc = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) acc += sm_o[w][dt][v][lane] * wt[w];
+                const size_t o = (size_t)row * a.ld_out + h * HD + dt * 16 + 4 * g + v;
+                if (COH) store_act_coh(out, o, acc / l);
+                else store_act(out, o, acc / l);
+            }
+        }
+        return;
+    }
+    const size_t pidx = ((size_t)split * a.R + row) * a.H + h;
+    if (wave == 0 && g == 0) {
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l += sm_l[w][c] * wt[w];
+        if (COH) {
+            st_coh(&a.part_m[pidx], mstar);
+            st_coh(&a.part_l[pidx], l);
+        } else {
+            a.part_m[pidx] = mstar;
+            a.part_l[pidx] = l;
+        }
+    }
+    for (int dt = wave; dt < NDT; dt += NW) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float acc = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) acc += sm_o[w][dt][v][lane] * wt[w];
+            if (COH) st_coh(&a.part_o[pidx * HD + dt * 16 + 4 * g + v], acc);
+            else a.part_o[pidx * HD + dt * 16 + 4 * g + v] = acc;
+        }
+    }
 }
+
 
 constexpr int ATTN_MAX_SPLITS = 16;
 

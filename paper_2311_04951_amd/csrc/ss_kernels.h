@@ -77,11 +77,11 @@ struct AttnArgs {
     const void *q; // activation planes [planes][R16][ldq], rotated queries
     size_t q_plane;
     int ldq;
+    int stream;         // matrices, keys and values of a pass are more than the memory-side cache holds (large calls: non-temporal requests)
     const void *kcache, *vcache; // this layer
     const int32_t *len;          // [batch] lengths before this call's append
     int B, M, H, hd, S, R;
     int nsplit, chunk;  // positions per split (multiple of 64)
-    int stream;         // matrices, keys and values of a pass are more than the memory-side cache holds (large calls: non-temporal requests)
     float *part_o;      // [nsplit][R][H][hd] unnormalised
     float *part_m;      // [nsplit][R][H] running max (log2 domain)
     float *part_l;      // [nsplit][R][H] sum of weights
