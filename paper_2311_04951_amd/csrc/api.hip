@@ -591,16 +591,34 @@ static int check_pair(const ss_model *m, const ss_kv_cache *kv, int batch, int M
 // a buffer descriptor of 2 GiB.
 static size_t plane_rows(const ss_model *m, int R) { return R <= 16 ? 16 : (size_t)m->R16; }
 
-// Whether what every pass reads, the matrices of the layers and `more` bytes, is more than the 256 MB memory-side cache holds: then nothing of it is
-// still there when the next pass wants it, and large calls ask for it with the non-temporal bit.  (Keys and values count on top of the
-// matrices; with the bit they leave the matrices of a shallow model in the cache, so those don't count the other way round: one layer of
-// 1B shape, 103 MB, 16 x 2000 positions, 116.6 us with the bit on both, 111.3 on keys and values alone.)
-static bool streams_through(const ss_model *m, size_t more) {
+// The memory-side cache holds 256 MB.  What a pass asks for with the non-temporal bit leaves it to the rest.
+constexpr size_t SIDE_CACHE = (size_t)256 << 20;
+
+// Bytes of the layers' matrices: all of them, or the two residual projections'.
+static size_t matrix_bytes(const ss_model *m, bool residual_only) {
     const ss_model_cfg &c = m->cfg;
     const size_t bits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : c.weight_quant ? 8 : c.dtype ? 16 : 32;
-    const size_t W = m->W, d = c.d_model;
-    return (4 * W * d + 3 * d * c.d_ff) * bits / 8 * c.n_layers + more >= (size_t)256 << 20;
+    const size_t W = m->W, d = c.d_model, F = c.d_ff;
+    return (residual_only ? W * d + d * F : 4 * W * d + 3 * d * F) * bits / 8 * c.n_layers;
 }
+
+// Whether what every pass reads, the matrices of the layers and `more` bytes, is more than the cache holds: then nothing of it is
+// still there when the next pass wants it, and calls of more than 16 rows ask for matrices with the non-temporal bit.
+static bool streams_through(const ss_model *m, size_t more) { return matrix_bytes(m, false) + more >= SIDE_CACHE; }
+
+// Whether the attention in blocks asks for keys and values (kv_bytes in all layers) with the bit: where they and the matrices that come without it (plain_bytes)
+// are more than stays in the cache.  Calls of at most 16 rows always ask for matrices with the bit, so their keys and values have the cache to
+// themselves, and some of the lines are still there when they are a little more than it holds; 17 rows and more ask for the residual
+// projections (and, where all of them fit the cache or an int4 stage takes half a line, for every matrix) without it.
+//   A layer, us, without | with the bit.  One row a sequence, 16 sequences of 7B shape (405 MB of matrices): 66 MB of keys and values 108.3 | 110.3, 136 MB
+// 120.2 | 124.5, 262 MB 136.7 | 141.6, 524 MB 189.6 | 181.5; 10 of 13B shape: 328 MB (four layers) 144.5 | 144.7, 410 MB (one) 206.7 | 200.2.
+// 16 rows a sequence, 16 of 7B shape (124 MB plain): 66 MB 260.1 | 267.7, 105 MB 273.5 | 274.1, 136 MB 282.0 | 279.9, 262 MB 302.7 | 294.9; 7 of 13B
+// shape (194 MB plain), 36 MB 259.2 | 255.6; 16 of 1B shape (103 MB, all plain), 131 MB 130.6 | 131.4, 262 MB 162.1 | 150.5.
+static bool streams_kv(size_t plain_bytes, size_t kv_bytes, int R) {
+    return R <= 16 ? kv_bytes >= SIDE_CACHE / 4 * 5 : plain_bytes + kv_bytes >= SIDE_CACHE / 8 * 7;
+}
+// For the tests (not part of the library's interface)
+extern "C" int ss_dev_streams_kv(size_t plain_bytes, size_t kv_bytes, int R) { return streams_kv(plain_bytes, kv_bytes, R); }
 
 // All layers over the R = batch*M rows in h.  normed: whether act_a already holds the first layer's normalised rows (the
 // embedding writes them).  final_gain: the norm that follows the last layer when it covers all rows in order (NULL: none, or
@@ -623,8 +641,9 @@ static int run_layers(ss_model *m, ss_kv_cache *kv, float *h, int normed, const 
 
     size_t kv_bytes = 0;
     for (int b = 0; b < batch; ++b) kv_bytes += (size_t)kv->len_ub[b] * 2 * W * kv->esz * c.n_layers;
-    const int stream = streams_through(m, 0), stream_kv = streams_through(m, kv_bytes);
     const int wbits = c.weight_quant == SS_QUANT_INT4_G128 ? 4 : 8;
+    const int stream = streams_through(m, 0);
+    const int stream_kv = streams_kv(matrix_bytes(m, stream && !(c.weight_quant && wbits == 4)), kv_bytes, R);
     // The two residual projections name the RMSNorm that follows them.  A launcher that has a row-wise last launch
     // anyway (split K, more than 16 rows) writes the normalised planes there (1); the kernels of at most 16 rows write
     // h * gain as planes and partial sums of squares, and the GEMM that consumes the planes multiplies its sums by the

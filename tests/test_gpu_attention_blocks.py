@@ -1,5 +1,6 @@
 """The attention of one split in blocks of 64 positions (bf16, heads of 64 and 128, calls of 256 and more (sequence, head) units at 256 and
 more positions): lengths at the edges of blocks and of the round over the wavefronts, sequences of very different lengths."""
+import ctypes
 import math
 
 import pytest
@@ -8,8 +9,6 @@ import torch
 import paper_2311_04951_amd as sv
 import seeded_inputs as si
 from gpu_util import dev
-
-pytestmark = pytest.mark.gpu
 
 
 def _want(q, k, v, lens, M):
@@ -22,10 +21,39 @@ def _want(q, k, v, lens, M):
     return out
 
 
-# heads x sequences: 256 units and fewer take 8 wavefronts, more take 4; layers: the second one's matrices push a pass beyond 256 MB
-@pytest.mark.parametrize("hd,heads,lens,M,ff", [
+# head size, heads, cached positions, rows per sequence, d_ff
+LAYERS = [
     (128, 32, [252, 0, 63, 64, 65, 191, 192, 193], 4, 256), (128, 32, [511, 510, 512, 448, 449, 447, 1, 250], 1, 256), (128, 40, [300, 255, 256, 257, 319, 320, 17, 128], 9, 256),
-    (128, 32, [1000, 40, 575, 576, 577, 300, 2, 900], 16, 11008), (64, 32, [252, 0, 63, 64, 65, 511, 512, 513], 3, 256), (64, 64, [700, 255, 256, 639, 640], 16, 256)])
+    (128, 32, [1000, 40, 575, 576, 577, 300, 2, 900], 16, 11008), (64, 32, [252, 0, 63, 64, 65, 511, 512, 513], 3, 256), (64, 64, [700, 255, 256, 639, 640], 16, 256)]
+# ... of which these, by the bytes of a pass, ask for keys and values with the non-temporal bit (a wide d_ff, or many positions in a call of at most 16 rows)
+STREAMED = [(128, 32, [1000, 40, 575, 576, 577, 300, 2, 900], 16, 4608), (64, 64, [700, 255, 256, 639, 640], 16, 4096), (128, 32, [1280 + 9 * i for i in range(16)], 1, 256)]
+
+
+def _streams(hd, heads, lens, M, ff):
+    """The library's own choice for a bf16 model of one layer whose matrices are few enough to be asked for without the bit."""
+    W = hd * heads
+    matrices = 2 * (4 * W * W + 3 * W * ff)
+    rows = len(lens) * M
+    assert rows <= 16 or matrices < 256 << 20
+    f = sv.lib().ss_dev_streams_kv
+    f.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int]
+    return bool(f(matrices, 4 * W * sum(lens), rows))
+
+
+def test_keys_and_values_are_streamed_where_the_cache_does_not_hold_them():
+    f = sv.lib().ss_dev_streams_kv
+    f.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int]
+    MB = 1 << 20
+    # up to 16 rows ask for every matrix with the bit: keys and values have the cache of 256 MB to themselves
+    assert [f(400 * MB, kv * MB, 16) for kv in (0, 136, 262, 319, 320, 500)] == [0, 0, 0, 0, 1, 1]
+    # more rows: with the matrices that come without it
+    assert [f(118 * MB, kv * MB, 17) for kv in (0, 64, 105, 106, 500)] == [0, 0, 0, 1, 1]
+    assert [f(plain * MB, 0, 256) for plain in (0, 223, 224)] == [0, 0, 1]
+    assert not any(_streams(*c) for c in LAYERS if c[4] == 256 and c[1] == 32) and all(_streams(*c) for c in STREAMED)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hd,heads,lens,M,ff", LAYERS + STREAMED)
 def test_layer_attention_against_64_bits(hd, heads, lens, M, ff):
     """A layer whose d_ff part is nearly nothing and whose O projection is the identity: h grows by the attention's result.  Queries, weights and
     results carry 16 bits (two planes), sums 32: 2^-16 of values around 1, and of the sum of the weights, which is 1."""
@@ -62,6 +90,7 @@ def test_layer_attention_against_64_bits(hd, heads, lens, M, ff):
     assert float((got - want).abs().max()) < 3e-4
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("hd,heads", [(128, 32), (64, 32), (128, 40)])
 def test_positions_behind_the_end_need_not_be_numbers(hd, heads):
     """What a longer sequence left behind in the second half of the last block, 32 positions that nothing reads as a position: the same bits as with zeros."""
