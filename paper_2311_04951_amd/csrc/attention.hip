@@ -39,10 +39,9 @@ __global__ __launch_bounds__(NWX * 64) void attn_direct_kernel(AttnArgs a) {
 // A single split of many positions, bf16: blocks of 64 positions go round the wavefronts, each block's keys, then its values, through the
 // wavefront's own 16 KB of LDS.  What bounds it is the cache's bytes: keys and values of a block are 16 KB in one piece each, so every
 // load-to-LDS instruction brings a contiguous kilobyte, where loads in operand layout take half lines of 16 rows.  The other wavefronts' requests
-// fill the time in which one multiplies (a compute unit has some 32 KB of loads in flight; 64 or 128 KB are asked for).
-//   A layer, us, loads in operand layout -> blocks -> and the non-temporal bit: 7B shape 8 x 9 rows at up to 4080 positions 234 -> 232 -> 212, at
-// 1200 167.6 with blocks, 158.3 with the bit; 1B shape, 100 MB and 16 x 1000 positions, all in the memory-side cache, 89.0 and 92.9: the bit
-// goes by the bytes of the pass.
+// fill the time in which one multiplies (a compute unit has some 32 KB of loads in flight; 64 KB or more are asked for).
+//   A layer, us, loads in operand layout -> blocks -> and the non-temporal bit (when: streams_kv in api.hip): 7B shape 8 x 9 rows at 2000 | 4000 positions
+// 189.6 -> 188.4 -> 178.0 | 235.6 -> 233.9 -> 215.1; 9 sequences (288 units, 32 compute units with two) 321 -> 298 -> 278 at 4000.
 template <int HD, int NW>
 __global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
     typedef bf16_t T;
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(NW * 64) void attn_blocks_kernel(AttnArgs a) {
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            if (hh && blk * 64 + 32 >= ntot) break; // (what lies there may be no numbers, which a weight of zero would not undo)
+            if (hh && blk * 64 + 32 >= ntot) break; // (what lies there may be no numbers, which a weight of zero would not undo; up to 31 positions of the half before it are multiplied, as in attn_unit)
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
                 o[dt] = mma(o[dt], *reinterpret_cast<const u32x4 *>(buf + (dt * 16 + c) * 128 + ((hh * 4 + g) ^ (c & 7)) * 16), P[hh]);
@@ -189,10 +188,13 @@ template <typename T> static void launch_attention_t(const AttnArgs &a, hipStrea
     dim3 grid(a.nsplit, a.H, a.B);
     if (a.nsplit == 1) {
         if constexpr (std::is_same<T, bf16_t>::value) {
-            // from 256 positions on (four blocks)
+            // From 256 positions on (four blocks); a call has one split of so many from 256 units on.  A layer at 250 | 400 positions, us, attn_direct_kernel ->
+            // blocks: 7B shape, 16 sequences of one row 107.9 -> 108.3 | 113.6 -> 115.7, 8 x 9 rows 142.6 -> 142.7 | 144.6 -> 144.1, 16 x 16
+            // 259.5 -> 260.1 | 271.5 -> 273.5; 13B shape, 10 x 9 260 -> 250 | 262 -> 255.  Heads of 128: eight wavefronts, 128 KB of LDS, are no faster than four
+            // where a compute unit has one unit (8 x 9 rows at 520 | 4000 positions 147.0 | 218.7 with eight, 147.7 | 215.1 with four; at lengths from
+            // 3188 to 4080 218.1, 214.5) and keep a second one out where it has two (16 x 16 at 400 276, 273).
             if (a.chunk >= 256 && a.hd >= 64) {
-                if (a.hd == 128 && a.B * a.H <= 256) hipLaunchKernelGGL((attn_blocks_kernel<128, 8>), grid, dim3(512), 0, st, a);
-                else if (a.hd == 128) hipLaunchKernelGGL((attn_blocks_kernel<128, 4>), grid, dim3(256), 0, st, a);
+                if (a.hd == 128) hipLaunchKernelGGL((attn_blocks_kernel<128, 4>), grid, dim3(256), 0, st, a);
                 else hipLaunchKernelGGL((attn_blocks_kernel<64, 8>), grid, dim3(512), 0, st, a);
                 return;
             }

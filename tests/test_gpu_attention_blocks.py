@@ -93,7 +93,8 @@ def test_layer_attention_against_64_bits(hd, heads, lens, M, ff):
 @pytest.mark.gpu
 @pytest.mark.parametrize("hd,heads", [(128, 32), (64, 32), (128, 40)])
 def test_positions_behind_the_end_need_not_be_numbers(hd, heads):
-    """What a longer sequence left behind in the second half of the last block, 32 positions that nothing reads as a position: the same bits as with zeros."""
+    """What a longer sequence left behind the half block (32 positions) that holds the end: the same bits as with zeros.  Positions between the end and the
+    next multiple of 32 are multiplied with weights of zero, here and in every other attention kernel: they have to be finite and are zeros here."""
     lens, M, d, S = [257, 270, 284, 320, 14, 383, 321, 510], 4, heads * hd, 640
     g = torch.Generator(device=dev()).manual_seed(hd + heads)
     r = lambda *s: torch.randn(s, generator=g, device=dev())
