@@ -1002,7 +1002,10 @@ __global__ __launch_bounds__(C::NW * 64) void gemm_tile_kernel(GemmArgs a) {
             woff[i] = (uint32_t)(n - n0) * (uint32_t)row_bytes + (uint32_t)(wlu ^ C::swizzle(row + wlr)) * 16u;
         }
     }
-    const bool ragged = K % (32 * KBS) != 0; // (never with int4)
+    // (Never with int4.  A constant there: the rows and units that only a ragged end needs took the registers of two addresses in the 80 x 192 tile of QKV, and the
+    // wait behind each of their spills emptied the ring: three layers of 7B | 13B shape,
+    // 72 rows, us: 398.0 -> 386.1 | 554.5 -> 531.8, and 18 rows, which spilled nothing, 272.0 -> 262.9 | 357.4 -> 345.9.)
+    const bool ragged = QB != 4 && K % (32 * KBS) != 0;
     auto issue_act = [&](int s, int buf) {
         const int st = stage_at(s);
         const uint32_t to = lds0 + buf * C::ASTAGE + wave * 1024;
