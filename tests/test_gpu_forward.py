@@ -213,8 +213,8 @@ def test_7b_width_data_synchronisation_equals_barriers_over_many_launches():
 @pytest.mark.parametrize("quant", [None, "int8", "int4"])
 def test_batched_7b_layer_72_rows_matches_per_sequence_oracle(quant):
     """The batched workload's launch shapes at full width: one 7B-shaped bf16 layer, 8 sequences with
-    ragged contexts, K = 8 -> 72 rows in one call (wide GEMMs with split-K, split-KV attention), with bf16
-    matrices and with the int8 and int4 matrices the library quantises from them (the wide kernel's two
+    ragged contexts, K = 8 -> 72 rows in one call (tile GEMMs with split-K, attention in blocks), with bf16
+    matrices and with the int8 and int4 matrices the library quantises from them (the tile kernel's two
     quantised modes at K = 4096 and 11008).  Each sequence's hidden rows against the oracle's model of the
     same kind run on that sequence alone (reduced depth and context: the full 32-layer, 4096-position pass
     is out of the oracle's reach)."""
@@ -249,7 +249,7 @@ def test_batched_long_context_layer_at_its_real_shape_matches_per_sequence_oracl
     of it): one 7B-shaped bf16 layer, 8 sequences whose caches hold 4096 - jitter(0..63) positions (Section 2: the
     cache of a long context is a large object), K = 8 -> 72 rows in one call against a cache of 4608 positions per
     sequence: block indices far past the first cache blocks, the transposed value blocks of a long sequence,
-    one workgroup per (sequence, head) walking the whole context, split-K wide GEMMs.  With 2 sequences (18 rows:
+    one workgroup per (sequence, head) walking the whole context, split-K tile GEMMs.  With 2 sequences (18 rows:
     two row tiles) the same contexts go through 8-way split-KV attention with a partly empty tail split and the
     merge launch.  Every sequence's hidden rows against the oracle run on that sequence alone; then a ragged
     roll-back (Section 4.4: sequences accept different numbers of tokens) and a second pass over the shortened

@@ -96,9 +96,9 @@ def test_greedy_speculative_equals_greedy_autoregressive_with_int8_models():
 
 
 @pytest.mark.parametrize("B,M,vocab", [(3, 8, 1000), (3, 16, 1000), (8, 9, 1000),      # 24, 48 and 72 rows per call: 2, 3 and 5 row tiles
-                                       (3, 8, 20000), (3, 16, 20000), (8, 9, 20000)])  # an LM head of 1250 tiles: 8-wave workgroups
+                                       (3, 8, 20000), (3, 16, 20000), (8, 9, 20000)])  # an LM head of 1250 tiles
 def test_int8_model_in_launches_of_more_than_16_rows(B, M, vocab):
-    """Batched calls of an int8 model go through the wide GEMMs (LDS-shared activation slabs, split-K): whole
+    """Batched calls of an int8 model go through the tile GEMMs (both operands staged in LDS, split-K): whole
     forward with ragged contexts, every sequence against the oracle's int8 model run on that sequence alone.
     d_ff = 688 gives the down projection a ragged last K slab."""
     shape = si.DecoderShape(2, 256, 4, 64, 688, vocab, dtype="bf16")

@@ -11,7 +11,7 @@ from gpu_util import dev, maxabs, weights_to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("batch,rows", [(1, 1), (3, 5), (3, 8), (5, 16)])      # 1, 15 rows; 24 and 80 rows take the wide kernels
+@pytest.mark.parametrize("batch,rows", [(1, 1), (3, 5), (3, 8), (5, 16)])      # 1, 15 rows; 24 and 80 rows take the GEMMs of more than 16
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rows_that_the_caller_holds_unaligned(dtype, batch, rows):
     """ss_decoder_layers_forward on rows at an address that is only 4-byte aligned: the same numbers as on aligned ones (the norm

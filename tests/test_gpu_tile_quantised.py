@@ -14,7 +14,13 @@ LAYERS = {8: [(17, 1040, 8, 1744), (18, 1040, 8, 13824), (40, 1040, 8, 13824), (
               (128, 2048, 32, 8192), (129, 1040, 12, 1744), (161, 144, 40, 11008), (192, 1040, 32, 5632), (256, 4096, 32, 2064), (250, 144, 16, 11008), (272, 1040, 8, 1744)],
           4: [(17, 1024, 8, 1792), (18, 1024, 8, 13824), (40, 1024, 8, 13824), (72, 1024, 8, 13824), (40, 1024, 8, 16512), (33, 1024, 8, 1792), (49, 1152, 12, 1792), (80, 4096, 32, 1152), (81, 1024, 9, 1792), (96, 2048, 64, 11008), (128, 1024, 8, 2048), (18, 4096, 32, 128),
               (128, 2048, 32, 8192), (129, 1152, 12, 1792), (161, 128, 40, 11008), (192, 1024, 32, 5632), (256, 4096, 32, 2048), (250, 128, 16, 11008), (272, 1024, 8, 1792)]}
+# what those leave out of each product's own tiles; the last of int8 has matrices of more than 256 MB, which are asked for with the non-temporal bit
+LAYERS[8] += [(40, 4096, 32, 2064), (100, 3088, 40, 1744), (120, 4096, 32, 1040), (144, 4112, 24, 4096), (192, 4096, 32, 2064), (288, 144, 40, 4096), (24, 128, 2, 11008), (161, 4112, 12, 272),
+              (288, 4112, 2, 272), (40, 144, 1, 272), (40, 5120, 40, 13824)]
+LAYERS[4] += [(40, 4096, 32, 2048), (100, 3072, 24, 1792), (120, 4096, 32, 1024), (144, 4096, 24, 4096), (192, 4096, 32, 2048), (288, 128, 40, 4096), (24, 128, 2, 11008), (256, 3072, 12, 1024),
+              (288, 256, 2, 128), (40, 512, 1, 128)]
 HEADS = [(17, 333), (24, 32000), (40, 50257), (72, 32000), (72, 5003), (90, 32000), (200, 32000)]      # rows, columns; K 256
+HEADS += [(40, 1000), (40, 32000), (32, 50257), (48, 33000)]                                           # one round of workgroups and more
 
 
 def _met(bits):
@@ -44,6 +50,18 @@ def test_the_shapes_below_meet_every_tile(bits):
     assert {m[3] for m in met if m[0] == QKV} == {m[3] for m in met if m[0] == RESID} == {False, True}
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+def test_the_shapes_below_meet_every_tile_of_every_product(bits):
+    """Every epilogue is a kernel of its own, with its own registers, columns and ends."""
+    met = _met(bits)
+    rows, plain = (32, 48, 80, 96, 128), {(32, 64), (32, 128), (48, 64), (48, 128), (80, 64), (80, 128), (96, 128), (128, 128)}
+    built = {(QKV, r, c) for r in rows for c in (96, 192)} | {(SWIGLU, r, c) for r in rows for c in (96, 192)} | {(SWIGLU, r, 128) for r in (32, 48, 80)}
+    assert {m[:3] for m in met} == built | {(e, r, c) for e in (STORE, RESID) for r, c in plain}
+    # with K split and not, wherever the choice comes to it
+    for r in rows:
+        assert {s for e, rr, c, s in met if (e, rr) == (RESID, r)} >= ({True} if r > 80 else {False, True}), r
+
+
 def _dequantised(w, bits):
     """The matrix that a quantised model stands for, in 64 bits: scales of 32 bits, entries of q."""
     top = 127.0 if bits == 8 else 7.0
@@ -60,7 +78,7 @@ def _rms(x, g):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("bits,i", [(b, i) for b in (8, 4) for i in range(len(LAYERS[8]))])
+@pytest.mark.parametrize("bits,i", [(b, i) for b in (8, 4) for i in range(len(LAYERS[b]))])
 def test_one_layer_against_64_bits(bits, i):
     """A layer without cached positions, one row per sequence, whose attention is the row's own value: four products.  Activations carry 16
     bits (two planes), sums and scales 32: 1e-5 relative, the bound of the bf16 matrices."""
