@@ -1313,9 +1313,15 @@ template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, i
     } else if constexpr (QB != 0) {
         switch (tile) {
         case 32064: return go(TileCfg<QB, 2, 2, 1, 2, 4, 4, 3, 3>{});
-        case 32128: return go(TileCfg<QB, 2, 2, 1, 4, 2, 4, 3, 3>{});
+        case 32128: // (heads: see below; int8, K 4096, 18 rows, 32000 | 40960 | 128256 columns 37.5 -> 36.7 | 59.4 -> 47.8 | 123.9 -> 105.8 us)
+            if constexpr (EPI == EPI_STORE) return go(TileCfg<QB, 2, 2, 1, 4, 2, 4, 2, 2>{});
+            else return go(TileCfg<QB, 2, 2, 1, 4, 2, 4, 3, 3>{});
         case 48064: return go(TileCfg<QB, 3, 2, 1, 2, 4, 4, 3, 3>{});
-        case 48128: return go(TileCfg<QB, 3, 2, 1, 4, 2, 4, 3, 3>{});
+        case 48128: // (48 rows, one round of workgroups: 41.7 us with the deep rings, 45.0 with these; 40960 | 128256 columns 68.6 -> 55.3 | 149.8 -> 134.1)
+            if constexpr (EPI == EPI_STORE) {
+                if (columns > 128 * 256) return go(TileCfg<QB, 3, 2, 1, 4, 2, 4, 2, 2>{});
+            }
+            return go(TileCfg<QB, 3, 2, 1, 4, 2, 4, 3, 3>{});
         case 80064: return go(TileCfg<QB, 5, 2, 1, 2, 4, 4, 3, 3>{});
         case 80128: return go(TileCfg<QB, 5, 2, 1, 4, 2, 4, 2, 3>{});
         case 96128: return go(TileCfg<QB, 3, 4, 2, 2, 2, 4, 2, QB == 4 ? 3 : 2>{});
@@ -1347,13 +1353,21 @@ template <int EPI, int QB> static int launch_tile_as_chosen(const GemmArgs &a, i
     } else {
         switch (tile) {
         case 32064: return go(TileCfg<0, 2, 2, 1, 2, 4, 4, 3, 3>{});
-        case 32128: // (heads: 24 rows x 32000 columns 55 us in stages of 128 bytes, 48 of 256; K split eight ways: 22.2 both)
-            if constexpr (EPI == EPI_STORE) return go(TileCfg<0, 2, 2, 1, 4, 2, 4, 2, 3>{});
+        // Heads are several rounds of workgroups as a rule: rings of 64 to 80 KB, so that a compute unit holds two of them and one starts or ends while
+        // the other streams.  K 4096, 18 rows, 32000 | 40960 | 128256 columns, one workgroup a unit (stages of 256 bytes a row, 128 KB) -> two:
+        // 49.8 -> 49.6 | 83.1 -> 77.9 | 201.6 -> 185.3 us.  Of 48 rows only beyond one round: K 2048 31.2 -> 32.7 | 47.6 -> 42.7 | 115.3 -> 110.4,
+        // K 4096 52.6 -> 54.8 | 86.3 -> 87.5 | 206.0 -> 200.6.
+        case 32128:
+            if constexpr (EPI == EPI_STORE) return go(TileCfg<0, 2, 2, 1, 4, 2, 2, 2, 3>{});
             else return go(TileCfg<0, 2, 2, 1, 4, 2, 2, 3, 3>{});
         case 48064: return go(TileCfg<0, 3, 2, 1, 2, 4, 4, 3, 3>{});
         case 48128:
-            if constexpr (EPI == EPI_STORE) return go(TileCfg<0, 3, 2, 1, 4, 2, 4, 2, 3>{});
-            else return go(TileCfg<0, 3, 2, 1, 4, 2, 2, 3, 3>{});
+            if constexpr (EPI == EPI_STORE) {
+                if (columns > 128 * 256) return go(TileCfg<0, 3, 2, 1, 4, 2, 2, 2, 3>{});
+                return go(TileCfg<0, 3, 2, 1, 4, 2, 4, 2, 3>{});
+            } else {
+                return go(TileCfg<0, 3, 2, 1, 4, 2, 2, 3, 3>{});
+            }
         case 80064: return go(TileCfg<0, 5, 2, 1, 2, 4, 4, 2, 3>{});
         case 80128: return go(TileCfg<0, 5, 2, 1, 4, 2, 2, 3, 3>{});
         case 96064: return go(TileCfg<0, 3, 2, 2, 2, 2, 4, 2, 3>{});
