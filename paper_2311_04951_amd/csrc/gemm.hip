@@ -1251,16 +1251,23 @@ struct TileChoice {
     int rows, cols, ksplit;
     double us;
 };
-static TileChoice tile_cost(int epi, int bits, int bm, int cols, int columns, int R, int K, int ksplit, double launch_us) {
+//   Two tiles are priced otherwise than they are built: gate and up in 48 rows x 128 columns with two stages of activations at 13.5, a head of one round in 48 x 128
+// with stages of 256 bytes at 9 and 29.  With 15, and with 15 and 31, they would be taken at the same sizes (10.8 ns for every entry of K against
+// 14.2 in 192 columns and two rounds of 8.5 in 96; against two rounds of 6.6 in 64).
+//   Many rows of a short K (bf16) have an older form of the sum, 16 us/MB of activations and 40 (several row blocks: 34) of the matrix and no start:
+// launches of one to sixteen stages are bound by their ends, and the terms above, fitted to long ones, chose blocks of 128 rows and splits there.  1024 rows, a
+// layer of d_model 128 | 256 | 512, us: 39.3 -> 36.9 | 57.4 -> 52.1 | 71.2 -> 69.8.
+static TileChoice tile_cost(int epi, int bits, int bm, int cols, int columns, int R, int K, int ksplit, double launch_us, bool short_k) {
     const int gy = (R + bm - 1) / bm, gx = (columns + cols - 1) / cols, wgs = gx * gy * ksplit;
     const int rounds = (wgs + 255) / 256;
+    const double second = ksplit > 1 ? launch_us + 8.0 * ksplit * R * columns / 8e6 : 0.0;
+    if (short_k && bits == 16) return TileChoice{bm, cols, ksplit, rounds * (double)((K + ksplit - 1) / ksplit) * (bm * 4 * 16e-6 + cols * 2 * (gy > 1 ? 34e-6 : 40e-6)) + second};
     const bool fused = epi == EPI_SWIGLU || epi == EPI_QKV;
     const bool long_stage = cols <= 96 ? bm <= 96 : fused && cols == 128 && bm <= 48; // 256 bytes of a row
     const double act = !long_stage ? 9e-6 : bm <= 48 ? 13.5e-6 : 15e-6;
     const double mat = long_stage ? 31e-6 : cols <= 96 ? 26e-6 : cols == 128 ? 29e-6 : gy > 1 ? 34.5e-6 : 32.5e-6;
     const double per = bits == 16 ? bm * 4 * act + cols * 2 * mat : bits == 8 ? 2.0e-3 + 8.1e-7 * bm * cols : 3.0e-3 + 8.75e-7 * bm * cols;
-    return TileChoice{bm, cols, ksplit, rounds * (1.1 + (double)((K + ksplit - 1) / ksplit) * per) + 0.003 * wgs +
-                                            (ksplit > 1 ? launch_us + 0.16 * ksplit + 8.0 * ksplit * R * columns / 8e6 : 0.0)};
+    return TileChoice{bm, cols, ksplit, rounds * (1.1 + (double)((K + ksplit - 1) / ksplit) * per) + 0.003 * wgs + second + (ksplit > 1 ? 0.16 * ksplit : 0.0)};
 }
 
 template <int EPI, class C> static int launch_tile_as(const GemmArgs &a0, int columns, int ksplit, hipStream_t st) {
@@ -1408,7 +1415,7 @@ static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K,
             if (fused && cols == 128 && (epi == EPI_QKV || bm > 80 || R > bm || (columns + 95) / 96 <= 256 || (columns + 127) / 128 > 256)) continue;
             for (int ks = 1; ks <= splits; ++ks) {
                 if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
-                const TileChoice c = tile_cost(epi, bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0);
+                const TileChoice c = tile_cost(epi, bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0, short_k);
                 if (c.us < best.us) best = c;
             }
         }

@@ -34,3 +34,13 @@ def test_every_tile_is_met():
         for rows in (32, 48, 80, 128):
             assert {s for e, r, c, s in met if (e, r) == (epi, rows)} == {False, True}, (epi, rows)
     assert not any(s for e, r, c, s in met if e in (STORE, SWIGLU))
+
+
+def test_many_rows_of_a_short_k_take_small_blocks():
+    """1024 rows of models of 128 to 512: a launch of a few stages is bound by its ends; blocks of 128 rows, or K split, where small blocks fill the chip are slower."""
+    for d, heads, ff, want in ((128, 2, 384, [(32, 64, 1), (32, 64, 1), (32, 96, 1), (32, 64, 1)]), (256, 4, 768, [(32, 96, 1), (32, 64, 1), (80, 96, 1), (32, 64, 2)]),
+                               (512, 8, 1536, [(80, 96, 1), (32, 64, 1), (128, 96, 1)])):
+        W = 64 * heads
+        ws = 4 * max(3 * W, 2 * ff, d) * 1024
+        got = [_tile(epi, 1024, N, K, ws) for epi, N, K in ((QKV, 3 * W, d), (RESID, d, W), (SWIGLU, ff, d), (RESID, d, ff))]
+        assert got[:len(want)] == want, d
