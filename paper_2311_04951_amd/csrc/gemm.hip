@@ -1398,12 +1398,15 @@ static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K,
     // 2 layers, us: d_model 128 133 -> 81, 256 161 -> 115, 512 205 -> 188, 1024 428 both (the column-per-wavefront kernel 127, 147, 250, 603)
     const bool short_k = R > 512 && K <= 1024;
     // Quantised matrices: 96 where that is all of them, beyond it the cost chooses among blocks of 80, 96 and 128
-    const int q0 = R <= 32 ? 32 : R <= 48 ? 48 : R <= 80 ? 80 : 96, q1 = R <= 96 ? q0 : 128;
+    // (int4 of a few groups: 96 beyond 48 rows as well, where the wavefronts share K two ways, not four.  80 rows, a layer of d_model 128 | 256 | 512, us: QKV in
+    // 80 -> 96 rows 42.8 -> 41.2 | 45.2 -> 43.5 | 51.1 -> 49.9, gate and up another 0.6 | 0.6 | 0.1 less)
+    const bool few_groups = bits == 4 && fused && K <= 512 && R > 48;
+    const int q0 = R <= 32 ? 32 : R <= 48 ? 48 : R <= 80 && !few_groups ? 80 : 96, q1 = R <= 96 ? q0 : 128;
     const int rows[5] = {32, 48, 80, 96, 128}, narrow[4] = {64, 96, 128, 192}, plain[2] = {64, 128};
     const int splits = epi == EPI_QKV ? 4 : epi == EPI_RESID ? 8 : 1;
     TileChoice best{0, 0, 1, 1e30};
     for (int bm : rows) {
-        if (bits == 16 ? bm != bm0 && !(short_k && bm < bm0 && bm != 96) : bm > q1 || (bm < std::min(q0, 80) && !short_k)) continue;
+        if (bits == 16 ? bm != bm0 && !(short_k && bm < bm0 && bm != 96) : bm > q1 || (bm < (few_groups ? 96 : std::min(q0, 80)) && !short_k)) continue;
         for (int i = 0; i < (fused ? 4 : 2); ++i) {
             const int cols = fused ? narrow[i] : plain[i];
             if (bm >= 96 && cols == 64 && (fused || bits < 16)) continue;
@@ -1414,7 +1417,9 @@ static TileChoice choose_tile(int epi, int bits, int tiles, int R, int N, int K,
             // int4 404.0 -> 375.0 | 478.4 -> 449.9 | 646.6 -> 603.3.  (QKV splits K instead: level with 192 columns by the cost.)
             if (fused && cols == 128 && (epi == EPI_QKV || bm > 80 || R > bm || (columns + 95) / 96 <= 256 || (columns + 127) / 128 > 256)) continue;
             for (int ks = 1; ks <= splits; ++ks) {
-                if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks))) break;
+                // (Quantised, K between 256 and 512: shares of a stage or two cost more than they save.  A layer of d_model 128, d_ff 384, 18 rows, three
+                // shares -> one: int4 32.2 -> 30.7 us, int8 32.1 -> 30.4.)
+                if (ks > 1 && (sizeof(float) * (size_t)ks * R * N > ws_bytes || (short_k && K < 256 * ks) || (bits < 16 && K > 256 && K < 512))) break;
                 const TileChoice c = tile_cost(epi, bits, bm, cols, columns, R, K, ks, epi == EPI_QKV ? 4.5 : 0.0, short_k);
                 if (c.us < best.us) best = c;
             }

@@ -18,7 +18,7 @@ LAYERS = {8: [(17, 1040, 8, 1744), (18, 1040, 8, 13824), (40, 1040, 8, 13824), (
 LAYERS[8] += [(40, 4096, 32, 2064), (100, 3088, 40, 1744), (120, 4096, 32, 1040), (144, 4112, 24, 4096), (192, 4096, 32, 2064), (288, 144, 40, 4096), (24, 128, 2, 11008), (161, 4112, 12, 272),
               (288, 4112, 2, 272), (40, 144, 1, 272), (40, 5120, 40, 13824)]
 LAYERS[4] += [(40, 4096, 32, 2048), (100, 3072, 24, 1792), (120, 4096, 32, 1024), (144, 4096, 24, 4096), (192, 4096, 32, 2048), (288, 128, 40, 4096), (24, 128, 2, 11008), (256, 3072, 12, 1024),
-              (288, 256, 2, 128), (40, 512, 1, 128)]
+              (288, 256, 2, 128), (40, 512, 1, 128), (320, 640, 1, 4096)]
 HEADS = [(17, 333), (24, 32000), (40, 50257), (72, 32000), (72, 5003), (90, 32000), (200, 32000)]      # rows, columns; K 256
 HEADS += [(40, 1000), (40, 32000), (32, 50257), (48, 33000)]                                           # one round of workgroups and more
 
@@ -60,6 +60,25 @@ def test_the_shapes_below_meet_every_tile_of_every_product(bits):
     # with K split and not, wherever the choice comes to it
     for r in rows:
         assert {s for e, rr, c, s in met if (e, rr) == (RESID, r)} >= ({True} if r > 80 else {False, True}), r
+
+
+def test_a_few_groups_of_k():
+    """int4, K of up to 512, more than 48 rows of QKV or gate/up: blocks of 96 rows.  A residual projection of 256 < K < 512, both widths: K in one piece."""
+    L = sv.lib()
+    L.ss_dev_gemm_tile_bits.argtypes = [ctypes.c_int] * 5 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+    out = (ctypes.c_int * 3)()
+
+    def tile(bits, epi, R, N, K):
+        L.ss_dev_gemm_tile_bits(bits, epi, R, N, K, 1 << 30, out)
+        return tuple(out)
+
+    for epi in (QKV, SWIGLU):
+        for K in (128, 256, 512):
+            assert [tile(4, epi, R, 384, K)[0] for R in (32, 48, 49, 80, 96, 128)] == [32, 48, 96, 96, 96, 96]
+            assert tile(8, epi, 80, 384, K)[0] == 80
+        assert tile(4, epi, 80, 384, 640)[0] == 80
+    for bits in (8, 4):
+        assert [tile(bits, RESID, R, 128, 384)[2] for R in (18, 80, 256)] == [1, 1, 1] and tile(bits, RESID, 80, 256, 256)[2] > 1 and tile(bits, RESID, 18, 128, 768)[2] > 1
 
 
 def _dequantised(w, bits):

@@ -17,7 +17,7 @@ SHAPES = {16: [(17, 136, 2), (17, 2056, 2), (17, 2048, 16), (18, 3080, 24), (33,
           8: [(17, 144, 2), (17, 2064, 2), (18, 3088, 24), (33, 144, 2), (33, 2048, 2), (33, 2048, 24), (49, 144, 2), (49, 1040, 2), (288, 144, 24), (72, 4096, 32), (129, 3072, 12), (81, 144, 16),
               (81, 1168, 8), (256, 144, 40), (161, 4112, 12), (200, 144, 24), (200, 2064, 8), (100, 3088, 40)],
           4: [(17, 128, 2), (17, 2048, 2), (18, 2176, 24), (33, 128, 2), (33, 1024, 2), (40, 2048, 24), (49, 128, 2), (49, 1152, 2), (288, 128, 24), (72, 4096, 32), (129, 2176, 12), (81, 128, 16),
-              (81, 1152, 8), (256, 128, 40), (161, 3072, 12), (200, 128, 24), (200, 2176, 8), (100, 3072, 24)]}
+              (81, 1152, 8), (256, 128, 40), (161, 3072, 12), (200, 128, 24), (200, 2176, 8), (100, 3072, 24), (288, 640, 24), (64, 640, 2), (96, 1024, 8), (320, 128, 40)]}
 QKV, D_FF = 3, 128
 
 
