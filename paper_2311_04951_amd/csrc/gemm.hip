@@ -609,7 +609,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_cols_kernel(GemmArgs a) {
 // Every step issues the same number of memory instructions (addresses are clamped into the operands; weights
 // past K are zeroed after the load, so whatever finite activation sits there contributes nothing): the
 // waits on "the loads issued two steps ago" are exact counts.
-constexpr int WIDE_SLAB_BYTES = 256; // bytes of K per row, plane and slab
+constexpr int WIDE_SLAB_BYTES = 256; // bytes of K per row and slab
 
 // acc0 / acc1 += one weight chunk x one activation k-block, into two independent accumulators
 __device__ __forceinline__ void mma_split(f32x4 &acc0, f32x4 &acc1, u32x4 w, const Act<float> &b, int kb) {
@@ -647,16 +647,17 @@ __device__ __forceinline__ size_t splitk_index(int z, int ntiles, int tile, int 
     return (((((size_t)z * ntiles + tile) * row_tiles + rt) * NT + t) * 4 + v) * 64 + lane;
 }
 
-template <typename T, int EPI, int NW, int RT>
+template <int EPI, int NW, int RT>
 __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
-    constexpr int E = Traits<T>::E, KB = 4 * E, PL = Traits<T>::PLANES;
+    typedef float T;
+    constexpr int E = Traits<T>::E, KB = 4 * E;
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     constexpr int WIDE_KS = WIDE_SLAB_BYTES / (int)sizeof(T); // elements of K per slab
     constexpr int KBS = WIDE_KS / KB;                         // k-blocks per slab (4)
     constexpr int EPU = 16 / (int)sizeof(T);                  // elements per 16-byte unit
     constexpr int ROWS = RT * 16;
-    constexpr int BUF = PL * ROWS * WIDE_SLAB_BYTES;          // bytes of one slab buffer
-    constexpr int GROUPS = PL * ROWS / 4;                     // 1 KB load instructions per slab (4 rows each)
+    constexpr int BUF = ROWS * WIDE_SLAB_BYTES;               // bytes of one slab buffer
+    constexpr int GROUPS = ROWS / 4;                          // 1 KB load instructions per slab (4 rows each)
     constexpr int DPW = (GROUPS + NW - 1) / NW;               // ... per wave
     constexpr int WN = NT * KBS;                              // weight loads per wave and step
     __shared__ __align__(16) unsigned char slab0[BUF], slab1[BUF], slab2[BUF];
@@ -700,9 +701,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
         for (int i = 0; i < DPW; ++i) {
             const int grp = min(wave * DPW + i, GROUPS - 1); // a surplus instruction repeats the last group
-            const int pr = 4 * grp + r4, pl = pr / ROWS, row = pr % ROWS;
+            const int row = 4 * grp + r4;
             const int k = min(k0 + (q ^ (row & 15)) * EPU, a.ld_act - EPU);
-            const T *src = act + pl * a.act_plane + (size_t)min(rt0 * 16 + row, a.R - 1) * a.ld_act + k;
+            const T *src = act + (size_t)min(rt0 * 16 + row, a.R - 1) * a.ld_act + k;
             __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(buf + grp * 1024), 16, 0, 0);
         }
         asm volatile("" ::: "memory");
@@ -752,11 +753,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
         // MFMA behind an LDS round trip)
         auto read_av = [&](int kb, Act<T> (&av)[RT]) {
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int pl = 0; pl < PL; ++pl)
-                    av[r].p[pl] = *reinterpret_cast<const u32x4 *>(base + (size_t)(pl * ROWS + r * 16) * WIDE_SLAB_BYTES +
-                                                                   (((kb * 4 + g) ^ c) * 16));
+            for (int r = 0; r < RT; ++r) av[r].p[0] = *reinterpret_cast<const u32x4 *>(base + (size_t)r * 16 * WIDE_SLAB_BYTES + (((kb * 4 + g) ^ c) * 16));
             __builtin_amdgcn_sched_barrier(0);
         };
         Act<T> av[2][RT];
@@ -792,9 +789,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                out[t][v] = acc[0][r][t][v] + acc[1][r][t][v];
-            }
+            for (int v = 0; v < 4; ++v) out[t][v] = acc[0][r][t][v] + acc[1][r][t][v];
         if (a.ksplit > 1) {
             if (EPI == EPI_RESID && a.splitk_rows) { // plain rows [split][R][N]: the launch that follows works row by row
                 const int row = (rt0 + r) * 16 + c;
@@ -815,7 +810,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 
 // Second pass of a split-K launch: one wave per (wave tile, row tile) sums the splits' partial tiles in
 // split order and runs the epilogue.  grid (wave tiles, row tiles).
-template <typename T, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(64) void gemm_splitk_finish_kernel(GemmArgs a) {
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
     const int lane = threadIdx.x, tile = blockIdx.x, rt = blockIdx.y, row_tiles = gridDim.y;
@@ -830,7 +825,7 @@ __global__ __launch_bounds__(64) void gemm_splitk_finish_kernel(GemmArgs a) {
             for (int z = 0; z < a.ksplit; ++z) s += a.splitk_ws[splitk_index(z, ntiles, tile, row_tiles, rt, NT, t, v, lane)];
             out[t][v] = s;
         }
-    apply_epilogue<T, EPI>(a, out, n0, rt);
+    apply_epilogue<float, EPI>(a, out, n0, rt);
 }
 
 // Matrices with few column tiles would leave most of the chip idle (one workgroup per compute unit fits:
@@ -840,9 +835,9 @@ __global__ __launch_bounds__(64) void gemm_splitk_finish_kernel(GemmArgs a) {
 // A residual projection (whole 16-column tiles, dense output rows) leaves its partials as plain rows, and the
 // second launch is the RMSNorm kernel with the sum over the splits in front: it completes h and, when the caller
 // named the norm that follows, writes that too (returns true then).
-template <typename T, int EPI, int NW, int RT> static int launch_wide(const GemmArgs &a0, int tiles, int row_tiles, hipStream_t st) {
+template <int EPI, int NW, int RT> static int launch_wide(const GemmArgs &a0, int tiles, int row_tiles, hipStream_t st) {
     constexpr int NT = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? 2 : 1;
-    constexpr int WIDE_KS = WIDE_SLAB_BYTES / (int)sizeof(T);
+    constexpr int WIDE_KS = WIDE_SLAB_BYTES / (int)sizeof(float);
     GemmArgs a = a0;
     const int gx = (tiles + NW - 1) / NW, gy = (row_tiles + RT - 1) / RT;
     const int nslab = (a.K + WIDE_KS - 1) / WIDE_KS;
@@ -859,13 +854,13 @@ template <typename T, int EPI, int NW, int RT> static int launch_wide(const Gemm
         }
     }
     a.splitk_rows = EPI == EPI_RESID && a.ksplit > 1 && a.ksplit <= 4 && a.N % 16 == 0 && a.ldo == a.N && a.out == a.resid;
-    hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, NW, RT>), dim3(gx, gy, a.ksplit), dim3(NW * 64), 0, st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<EPI, NW, RT>), dim3(gx, gy, a.ksplit), dim3(NW * 64), 0, st, a);
     if (a.splitk_rows) {
-        launch_splitk_resid_norm(std::is_same<T, bf16_t>::value ? 1 : 0, a.out, a.splitk_ws, a.ksplit, a.norm_gain, a.R, a.N, a.norm_eps,
+        launch_splitk_resid_norm(0, a.out, a.splitk_ws, a.ksplit, a.norm_gain, a.R, a.N, a.norm_eps,
                                  a.norm_act, a.norm_act_plane, a.norm_ld, st);
         return a.norm_gain != nullptr ? 1 : 0;
     }
-    if (a.ksplit > 1) hipLaunchKernelGGL((gemm_splitk_finish_kernel<T, EPI>), dim3(tiles, row_tiles), dim3(64), 0, st, a);
+    if (a.ksplit > 1) hipLaunchKernelGGL((gemm_splitk_finish_kernel<EPI>), dim3(tiles, row_tiles), dim3(64), 0, st, a);
     return 0;
 }
 
@@ -1534,17 +1529,17 @@ template <typename T, int QB, int EPI> static int launch_cols(const GemmArgs &a,
     return (EPI == EPI_RESID && a.nsq_out) ? 2 : 0;
 }
 
-template <typename T, int EPI> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
+template <int EPI> static int launch_wide_any(const GemmArgs &a, int tiles, int row_tiles, hipStream_t st) {
     // larger batches and prefill chunks: waves split the columns; fewer waves per workgroup when the
     // matrix has few tiles, so that the launch still covers the chip
     constexpr bool FUSED = EPI == EPI_SWIGLU || EPI == EPI_QKV; // two weight tiles per wave: more registers
     const bool small = tiles < 8 * 128;
     if (row_tiles <= 2) {
-        if (small) return launch_wide<T, EPI, 4, 2>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 8, 2>(a, tiles, row_tiles, st);
+        if (small) return launch_wide<EPI, 4, 2>(a, tiles, row_tiles, st);
+        return launch_wide<EPI, 8, 2>(a, tiles, row_tiles, st);
     } else if (row_tiles <= 3) {
-        if (small) return launch_wide<T, EPI, 4, 3>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 8, 3>(a, tiles, row_tiles, st);
+        if (small) return launch_wide<EPI, 4, 3>(a, tiles, row_tiles, st);
+        return launch_wide<EPI, 8, 3>(a, tiles, row_tiles, st);
     } else {
         // one workgroup per compute unit fits: 3 waves per workgroup when that fills more of a 256-unit chip
         // in whole rounds than 4 (688 gate/up tiles: 230 workgroups instead of 172; 384 QKV tiles: 128, split in two)
@@ -1554,10 +1549,10 @@ template <typename T, int EPI> static int launch_wide_any(const GemmArgs &a, int
             return (double)(wgs * ks) / (double)((wgs * ks + 255) / 256 * 256);
         };
         if constexpr (!FUSED) {
-            if (!small) return launch_wide<T, EPI, 8, 5>(a, tiles, row_tiles, st);
+            if (!small) return launch_wide<EPI, 8, 5>(a, tiles, row_tiles, st);
         }
-        if (fill(3) > fill(4) + 0.1) return launch_wide<T, EPI, 3, 5>(a, tiles, row_tiles, st);
-        return launch_wide<T, EPI, 4, 5>(a, tiles, row_tiles, st);
+        if (fill(3) > fill(4) + 0.1) return launch_wide<EPI, 3, 5>(a, tiles, row_tiles, st);
+        return launch_wide<EPI, 4, 5>(a, tiles, row_tiles, st);
     }
 }
 
@@ -1566,7 +1561,7 @@ template <typename T, int QB, int EPI> static int launch_gemm_t(const GemmArgs &
     if (row_tiles <= 1) return launch_cols<T, QB, EPI>(a, st);
     const int tiles = EPI == EPI_QKV ? 3 * a.H * (a.hd / 32) : (a.N + 15) / 16;
     if constexpr (std::is_same<T, bf16_t>::value) return launch_tile<EPI, QB>(a, tiles, st);
-    else return launch_wide_any<T, EPI>(a, tiles, row_tiles, st);
+    else return launch_wide_any<EPI>(a, tiles, row_tiles, st);
 }
 
 int launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t st) {
